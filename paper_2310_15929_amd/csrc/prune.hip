@@ -7,8 +7,8 @@
 //   - sums of squares and column sums of |w| are accumulated EXACTLY: every term is split by its
 //     binary exponent into one of a few 64-bit integer accumulators (16 exponents per accumulator),
 //     and the host adds the accumulators exactly and rounds once;
-//   - the retained metric of a candidate group is summed over the output rows in a FIXED order (16
-//     interleaved sub-sums, see ROW_LANES) in float64 without contraction, so repeated runs make the
+//   - the retained metric of a candidate group is summed over the output rows in a FIXED order (interleaved
+//     sub-sums, see k_lbs_eval) in float64 without contraction, so repeated runs make the
 //     same exchanges; eq. (5) fixes no order for that sum, and the exchanges Algorithm 1 makes do not
 //     hinge on it where candidates are not tied to the last bit (the tests compare them with a plain
 //     ascending-row sum);
@@ -433,15 +433,19 @@ int esp_stats_device(esparse_ctx* ctx, const void* calib, long long T, long long
 // ------------------------------------------------------------------------------------------------
 // local block shuffle
 // ------------------------------------------------------------------------------------------------
-// Panel: P[j][p] = |W[j, theta0[p]]| as raw 16-bit magnitudes, p in GNS order (so the B channels of a
-// block are contiguous in every row).
-template <int DT>
+// Panel: P[blk][j][c] = |W[j, theta0[blk B + c]]| as raw 16-bit magnitudes: the N x B values of a block are
+// contiguous, so that a block's share (512 KiB for N = 4096, B = 64) stays in the L2 of the XCD that works on it.
+// Npad >= N rows per block; the rows past N are read but never used and stay as they are.
 __global__ void __launch_bounds__(256) k_build_panel(const uint16_t* __restrict__ W, const int32_t* __restrict__ theta0,
-                                                      long long N, long long K, uint16_t* __restrict__ P) {
+                                                      long long N, long long Npad, long long K, int B, unsigned int inf_bits,
+                                                      uint16_t* __restrict__ P, int* __restrict__ not_finite) {
   long long e = (long long)blockIdx.x * 256 + threadIdx.x;
   if (e >= N * K) return;
   long long j = e / K, p = e % K;
-  P[e] = W[j * K + theta0[p]] & 0x7fffu;
+  long long blk = p / B, c = p - blk * B;
+  const unsigned int v = W[j * K + theta0[p]] & 0x7fffu;
+  if (v >= inf_bits) atomicOr(not_finite, 1);
+  P[(blk * Npad + j) * B + c] = (uint16_t)v;
 }
 
 template <int NKEEP, int MG>
@@ -477,30 +481,60 @@ __device__ __forceinline__ double lanes_total(double part) {
   return acc;
 }
 
+// ------------------------------------------------------------------------------------------------
+// The exchanges are found with a table of its own that is cheaper to evaluate and proven close enough.
+//
+// What a candidate x adds to a row depends on the group's other members only through the NKEEP largest of them,
+// o_0 >= o_1 >= ...: the row keeps o_0 + .. + o_(NKEEP-2) + max(o_(NKEEP-1), x).  Summed over the rows, the first part is
+// one number per (group, member) and the second takes a maximum and an addition per row and candidate - two float64
+// operations instead of 5 (2:4) or about 60 (4:8).  The sum is that of the exact table in another order: with no negative
+// value both are within (N + 4) 2^-53 of the real one, relatively, and a group's value with a member replaced is at
+// most twice the largest v(g) (a channel's column is nowhere larger than its own group's largest).  So two deltas of
+// this table that differ by more than LBS_TOL (N + 64) 2^-53 max v(g) are in the same order in the exact table (four
+// values of both deltas, in both tables: 32 (N + 4) 2^-53 max v(g) and roundings; LBS_TOL is twice that), and a delta is
+// above or below zero in both if it is farther than that from it.  A round whose best exchange is not proven that way - a
+// tie, an exchange that moves the total by rounding only, weights or scores that are not finite or scores below zero -
+// leaves the block to the exact table from there on, so the exchanges made are those of the exact table in every case.
+//
+// Replacing the member that the last exchange brought into a group leaves the same other members as before it, so those
+// entries stay valid: NM = MG - 1 members per touched group are re-evaluated.
+//
+// A workgroup (8 waves) takes NG groups, LPR * 4 columns and every nsplit-th set of rows.  A lane owns four columns and
+// every S-th row (S = row lanes of all workgroups of the block), so the panel value and its product with the score are
+// formed once for NG * NM combinations, and an operand that comes out of LDS serves four candidates.  A wave forms the
+// operands of its next 32 rows itself (one lane per row and group: the NKEEP + 1 largest members) and needs no barrier.
+#define LBS_WAVES 8
+#define LBS_ROWS 32  // rows whose operands a wave keeps in LDS
+#define LBS_ROUNDS_QUEUED 12
+#define LBS_REC 12  // ints per touched group: exchanged position (-1: none), columns of the members
+#define LBS_TOL 64.0
+enum { LBS_FAST = 0, LBS_DONE = 1, LBS_EXACT = 2 };  // state of a block
+
+// ---- the exact table
 // V[blk][g][i][x] = retained metric of group g of block blk with its i-th member replaced by panel
 // column x of the block (x == the member itself gives v(g)).  grid (entries / 64, blocks), block 1024 =
-// 64 entries x 16 row lanes.  `groups` = list of 2 group numbers per block to refresh (or NULL = all
+// 64 entries x 16 row lanes.  `rec` = the exchanged positions, whose groups are refreshed (or NULL = all
 // groups).  Entries whose x sits in group g (other than the member itself) are skipped.
 // The block's metric values go through LDS in chunks of rows_chunk rows (a multiple of 16; rows are
 // padded by one value so that the 16 row lanes of an entry read different banks); the panel values of
 // the next chunk are loaded into registers before the current chunk is evaluated.
 template <int DT, int NKEEP, int MG>
-__global__ void __launch_bounds__(1024) k_lbs_eval(const uint16_t* __restrict__ P, const double* __restrict__ sp /*[K] score in panel order*/,
+__global__ void __launch_bounds__(1024) k_lbs_exact(const uint16_t* __restrict__ P, const double* __restrict__ sp /*[K] score in panel order*/,
                                                     const int* __restrict__ lp /*[nblk][B] position -> panel column*/,
-                                                    const int* __restrict__ groups /*[nblk][2] or null*/,
-                                                    const int* __restrict__ done /*[nblk]*/, long long N, long long K, int B,
+                                                    const int* __restrict__ rec /*[nblk][2][LBS_REC] or null*/,
+                                                    const int* __restrict__ state /*[nblk]*/, long long N, long long Npad, int B,
                                                     int rows_chunk, double* __restrict__ V /*[nblk][G][MG][B]*/) {
   extern __shared__ unsigned char smem_raw[];
   double* s_xi = reinterpret_cast<double*>(smem_raw);  // [rows_chunk][B + 1]
   __shared__ int s_lp[1024];
   const int blk = blockIdx.y;
-  if (done[blk]) return;
+  if (state[blk] != LBS_EXACT) return;
   const int G = B / MG;
   const int tid = threadIdx.x;
   const int rl = tid & (ROW_LANES - 1);                  // row lane
   const int eid = blockIdx.x * 64 + (tid >> 4);          // entry within this block's refresh list
   const int per_group = MG * B;
-  const int ngroups = groups ? 2 : G;
+  const int ngroups = rec ? 2 : G;
   const int stride = B + 1;
   for (int i = tid; i < B; i += 1024) s_lp[i] = lp[blk * B + i];
   __syncthreads();
@@ -511,7 +545,7 @@ __global__ void __launch_bounds__(1024) k_lbs_eval(const uint16_t* __restrict__ 
   for (int k = 0; k < MG; k++) cols[k] = 0;
   if (active) {
     int gsel = eid / per_group;
-    g = groups ? groups[blk * 2 + gsel] : gsel;
+    g = rec ? rec[(blk * 2 + gsel) * LBS_REC] / MG : gsel;
     i = (eid / B) % MG;
     x = eid % B;
     if (g < 0) active = false;
@@ -526,7 +560,7 @@ __global__ void __launch_bounds__(1024) k_lbs_eval(const uint16_t* __restrict__ 
     }
     if (in_group) active = false;
   }
-  const uint16_t* Pb = P + (long long)blk * B;
+  const uint16_t* Pb = P + (long long)blk * Npad * B;
   const double* spb = sp + (long long)blk * B;
   // this thread's share of a chunk: values tid, tid + 1024, ... of the rows_chunk x B values (the same
   // places in every chunk)
@@ -545,7 +579,7 @@ __global__ void __launch_bounds__(1024) k_lbs_eval(const uint16_t* __restrict__ 
   auto fetch = [&](long long r0) {
     const int nr = (int)((N - r0) < rows_chunk ? (N - r0) : rows_chunk);
 #pragma unroll
-    for (int q = 0; q < EPT; q++) nextv[q] = (rq[q] < nr) ? Pb[(r0 + rq[q]) * K + cq[q]] : (uint16_t)0;
+    for (int q = 0; q < EPT; q++) nextv[q] = (rq[q] < nr) ? Pb[(r0 + rq[q]) * B + cq[q]] : (uint16_t)0;
   };
   double acc = 0.0;  // this lane's sub-sum
   fetch(0);
@@ -580,21 +614,21 @@ __global__ void __launch_bounds__(1024) k_lbs_eval(const uint16_t* __restrict__ 
 // block's metric values once per chunk and evaluates NC units with them; a unit is a combination and
 // a slice of XL = min(B, 64) candidates.  grid (ceil(units / NC), blocks); B % 64 == 0 or B < 64.
 template <int DT, int NC>
-__global__ void __launch_bounds__(1024) k_lbs_eval_2_4(const uint16_t* __restrict__ P, const double* __restrict__ sp,
-                                                        const int* __restrict__ lp, const int* __restrict__ groups,
-                                                        const int* __restrict__ done, long long N, long long K, int B, int rows_chunk,
+__global__ void __launch_bounds__(1024) k_lbs_exact_2_4(const uint16_t* __restrict__ P, const double* __restrict__ sp,
+                                                        const int* __restrict__ lp, const int* __restrict__ rec,
+                                                        const int* __restrict__ state, long long N, long long Npad, int B, int rows_chunk,
                                                         double* __restrict__ V) {
   constexpr int MG = 4;
   extern __shared__ unsigned char smem_raw[];
   double* s_xi = reinterpret_cast<double*>(smem_raw);  // [rows_chunk][B + 1]
   __shared__ int s_lp[256];
   const int blk = blockIdx.y;
-  if (done[blk]) return;
+  if (state[blk] != LBS_EXACT) return;
   const int G = B / MG;
   const int tid = threadIdx.x;
   const int rl = tid & (ROW_LANES - 1), xl = tid >> 4;
   const int XL = B < 64 ? B : 64, xslices = B / XL;
-  const int ngroups = groups ? 2 : G;
+  const int ngroups = rec ? 2 : G;
   const int nunits = ngroups * MG * xslices;
   const int stride = B + 1;
   double* s_pair = s_xi + (size_t)rows_chunk * stride;  // [NC][rows_chunk][2]: the 16 row lanes read 256 contiguous bytes
@@ -611,7 +645,7 @@ __global__ void __launch_bounds__(1024) k_lbs_eval_2_4(const uint16_t* __restric
     ui[c] = cmb % MG;
     const int gsel = cmb / MG;
     ug[c] = -1;
-    if (u < nunits) ug[c] = groups ? groups[blk * 2 + gsel] : gsel;
+    if (u < nunits) ug[c] = rec ? rec[(blk * 2 + gsel) * LBS_REC] / MG : gsel;
     uact[c] = ug[c] >= 0 && xl < XL;
     if (!uact[c]) ux[c] = 0;
     if (uact[c]) {
@@ -620,7 +654,7 @@ __global__ void __launch_bounds__(1024) k_lbs_eval_2_4(const uint16_t* __restric
         if (k != ui[c] && s_lp[ug[c] * MG + k] == ux[c]) uact[c] = false;  // x is another member of the group
     }
   }
-  const uint16_t* Pb = P + (long long)blk * B;
+  const uint16_t* Pb = P + (long long)blk * Npad * B;
   const double* spb = sp + (long long)blk * B;
   constexpr int EPT = 4;
   const int elems = rows_chunk * B;  // <= EPT * 1024
@@ -637,7 +671,7 @@ __global__ void __launch_bounds__(1024) k_lbs_eval_2_4(const uint16_t* __restric
   auto fetch = [&](long long r0) {
     const int nr = (int)((N - r0) < rows_chunk ? (N - r0) : rows_chunk);
 #pragma unroll
-    for (int q = 0; q < EPT; q++) nextv[q] = (rq[q] < nr) ? Pb[(r0 + rq[q]) * K + cq[q]] : (uint16_t)0;
+    for (int q = 0; q < EPT; q++) nextv[q] = (rq[q] < nr) ? Pb[(r0 + rq[q]) * B + cq[q]] : (uint16_t)0;
   };
   double acc[NC];
 #pragma unroll
@@ -657,7 +691,7 @@ __global__ void __launch_bounds__(1024) k_lbs_eval_2_4(const uint16_t* __restric
       const int cmb = u / xslices, mi = cmb % MG, gsel = cmb / MG;
       double m1 = 0.0, m2 = 0.0;
       if (u < nunits) {
-        const int gg = groups ? groups[blk * 2 + gsel] : gsel;
+        const int gg = rec ? rec[(blk * 2 + gsel) * LBS_REC] / MG : gsel;
         if (gg >= 0) {
           double o[3];
           int c3 = 0;
@@ -690,81 +724,377 @@ __global__ void __launch_bounds__(1024) k_lbs_eval_2_4(const uint16_t* __restric
   }
 }
 
-// One workgroup per block: best exchange (largest delta, ties -> smallest (i, j)), applied if delta > 0.
+// ---- the table that is cheaper to evaluate
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+#else
+  return v;
+#endif
+}
+
+__device__ __forceinline__ int uniform(int v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_readfirstlane(v);
+#else
+  return v;
+#endif
+}
+
+// orders the LDS accesses of one wave as they are written (its lanes exchange data through LDS)
+__device__ __forceinline__ void wave_lds_fence() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+#endif
+}
+
+// v_max_f64 / v_min_f64 as they are: fmax / fmin come with a canonicalising instruction for every operand that was
+// loaded from memory
+__device__ __forceinline__ double max_f64(double a, double b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  double r;
+  asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+#else
+  return fmax(a, b);
+#endif
+}
+__device__ __forceinline__ double min_f64(double a, double b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  double r;
+  asm("v_min_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+#else
+  return fmin(a, b);
+#endif
+}
+
+template <int DT, int NKEEP, int MG, int NG, int NM, int LPR>
+__global__ void __launch_bounds__(64 * LBS_WAVES, 4) k_lbs_eval(const uint16_t* __restrict__ P, const double* __restrict__ sp /*[K] score in panel order*/,
+                                                              const int* __restrict__ rec /*[nblk][2][LBS_REC] exchanged positions and their groups*/,
+                                                              long long N, long long Npad, int B, int slices, double* __restrict__ S /*[nsplit][nblk][B][B]*/) {
+  constexpr int RLW = 64 / LPR;          // row lanes of a wave
+  constexpr int RL = LBS_WAVES * RLW;    // ... of a workgroup
+  constexpr int U = LBS_ROWS / RLW;      // rows of a lane per batch
+  constexpr int NC = NG * NM;            // combinations of group and member
+  constexpr int XC = LPR * 4;            // columns of a workgroup
+  static_assert(NG == 1 || NG == 2, "one or two groups per workgroup");
+  constexpr int NCP = (NC + 1) / 2 * 2;  // operands of a row, read in pairs
+  constexpr int ROOM = LBS_ROWS * NCP > NC * (XC + 1) ? LBS_ROWS * NCP : NC * (XC + 1);
+  __shared__ __align__(16) double s_o[LBS_WAVES * ROOM];  // per wave: operands; at the end its sums
+  __shared__ double s_ms[LBS_WAVES * 2 * MG];
+  const int blk = blockIdx.x, nblk = gridDim.x, split = blockIdx.y, nsplit = gridDim.y;
+  const int slice = (int)blockIdx.z % slices, gset = (int)blockIdx.z / slices;
+  const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+  const int rlw = lane % RLW, xl = lane / RLW;
+  const int col0 = slice * XC + 4 * xl;
+  const int colc = col0 < B ? col0 : 0;  // columns past the block compute along and are dropped at the end
+  // operand lane: row ir of the batch; NG = 2: group ih, all members; NG = 1: members ih, ih + 2, ...
+  const int ir = lane % LBS_ROWS, ih = lane / LBS_ROWS;
+  const long long step = (long long)nsplit * RL;
+  const long long rb0 = (long long)split * RL + wave * RLW;
+  // rows rb + rlw + u step of the panel, which is padded to whole batches; rows past N are replaced by zeros
+  const uint16_t* Pb = P + (long long)blk * Npad * B;
+  const int xoff = rlw * B + colc;
+  const uint16_t* prow = Pb + rb0 * B;  // the wave's next row; the values are loaded one row ahead
+  uint2 next = *reinterpret_cast<const uint2*>(prow + xoff);
+  // groups of this workgroup: their number (-1: none), the member that needs no evaluation, the members' columns
+  int wg[NG], wskip[NG], mcol[MG];
+#pragma unroll
+  for (int k = 0; k < NG; k++) {
+    const int g = gset * NG + k;
+    if (NM == MG) {  // first round: positions are columns; the last workgroup of an odd number of groups has one only
+      wg[k] = g < B / MG ? g : -1;
+      wskip[k] = MG;
+      if (NG == 1 || ih == k)
+#pragma unroll
+        for (int i = 0; i < MG; i++) mcol[i] = wg[k] < 0 ? i : g * MG + i;
+    } else {
+      const int* rg = rec + (blk * 2 + g) * LBS_REC;
+      if (rg[0] < 0) return;  // the block is done
+      wg[k] = rg[0] / MG;
+      wskip[k] = rg[0] % MG;
+      if (NG == 1 || ih == k)
+#pragma unroll
+        for (int i = 0; i < MG; i++) mcol[i] = rg[1 + i];
+    }
+  }
+  const int iskip = NG == 2 && ih == 1 ? wskip[NG - 1] : wskip[0];
+  const int irow = (ir % RLW) + (ir / RLW) * (int)step;  // of the batch
+  uint16_t mraw[MG];
+  auto load_members = [&](long long rb) {
+    const uint16_t* src = Pb + rb * B;
+#pragma unroll
+    for (int k = 0; k < MG; k++) mraw[k] = src[irow * B + mcol[k]];
+  };
+  load_members(rb0);
+  double s[4];
+#pragma unroll
+  for (int q = 0; q < 4; q++) s[q] = sp[(long long)blk * B + colc + q];
+  double* sms = s_ms + (wave * 2 + (NG == 2 ? ih : 0)) * MG;  // the members' scores
+#pragma unroll
+  for (int k = 0; k < MG; k++) sms[k] = sp[(long long)blk * B + mcol[k]];
+  double* so = s_o + wave * ROOM;
+  double acc[NC][4];
+#pragma unroll
+  for (int c = 0; c < NC; c++)
+#pragma unroll
+    for (int q = 0; q < 4; q++) acc[c][q] = 0.0;
+  double base[NM];  // operand lanes: what the other members keep besides the operand
+#pragma unroll
+  for (int c = 0; c < NM; c++) base[c] = 0.0;
+
+  for (long long rb = rb0; rb < N; rb += U * step) {
+    {
+      const bool live = rb + irow < N;
+      double v[MG], w[MG];
+      wave_lds_fence();
+#pragma unroll
+      for (int k = 0; k < MG; k++) {
+        v[k] = (double)esp_to_float<DT>(mraw[k]) * sms[k];
+        v[k] = live ? v[k] : 0.0;
+        w[k] = v[k];
+      }
+#pragma unroll
+      for (int a = 0; a <= NKEEP; a++)  // the NKEEP + 1 largest, in order
+#pragma unroll
+        for (int b = MG - 1; b > a; b--) {
+          const double hi = max_f64(w[b - 1], w[b]), lo = min_f64(w[b - 1], w[b]);
+          w[b - 1] = hi;
+          w[b] = lo;
+        }
+#pragma unroll
+      for (int c = 0; c < NM; c++) {
+        if (NG == 1 && (c & 1) != ih) continue;
+        const double vi = (NM < MG && c >= iskip) ? v[c + (NM < MG ? 1 : 0)] : v[c];
+        double kept = vi >= w[0] ? w[1] : w[0];  // the largest without member c
+#pragma unroll
+        for (int k = 1; k < NKEEP - 1; k++) kept = kept + (vi >= w[k] ? w[k + 1] : w[k]);
+        base[c] = base[c] + kept;
+        so[ir * NCP + (NG == 2 ? ih : 0) * NM + c] = vi >= w[NKEEP - 1] ? w[NKEEP] : w[NKEEP - 1];
+      }
+      wave_lds_fence();
+    }
+    const long long rnext = rb + U * step;
+    const bool full = rb + RLW - 1 + (U - 1) * step < N;
+    if (rnext < N) load_members(rnext);
+    const double2* src = reinterpret_cast<const double2*>(so + rlw * NCP);
+#pragma unroll 1
+    for (int u = 0; u < U; u++) {
+      const uint2 raw = next;
+      prow += step * B;
+      next = *reinterpret_cast<const uint2*>(prow + xoff);
+      double x[4];
+      x[0] = (double)esp_to_float<DT>((uint16_t)(raw.x & 0xffffu)) * s[0];
+      x[1] = (double)esp_to_float<DT>((uint16_t)(raw.x >> 16)) * s[1];
+      x[2] = (double)esp_to_float<DT>((uint16_t)(raw.y & 0xffffu)) * s[2];
+      x[3] = (double)esp_to_float<DT>((uint16_t)(raw.y >> 16)) * s[3];
+      if (!full) {  // no such row: adds exactly 0 whatever the scores are
+        const bool live = rb + rlw + u * step < N;
+#pragma unroll
+        for (int q = 0; q < 4; q++) x[q] = live ? x[q] : 0.0;
+      }
+      double o[NCP];
+#pragma unroll
+      for (int c = 0; c < NCP; c += 2) {
+        const double2 t = src[c / 2];
+        o[c] = t.x;
+        o[c + 1] = t.y;
+      }
+#pragma unroll
+      for (int c = 0; c < NC; c++)
+#pragma unroll
+        for (int q = 0; q < 4; q++) acc[c][q] = acc[c][q] + max_f64(o[c], x[q]);
+      src += RLW * NCP / 2;
+    }
+  }
+  // row lanes of the wave: neighbouring lanes, pairwise
+#pragma unroll
+  for (int c = 0; c < NC; c++)
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+      double v = acc[c][q];
+      v = v + dpp_f64<0xB1>(v);  // lane ^ 1
+      v = v + dpp_f64<0x4E>(v);  // lane ^ 2
+      if (RLW == 8) v = v + dpp_f64<0x141>(v);  // the other four of the eight
+      acc[c][q] = v;
+    }
+  // operand lanes: over the 32 rows; NG = 1: the other half of the lanes holds the other members
+#pragma unroll
+  for (int c = 0; c < NM; c++)
+#pragma unroll
+    for (int d = 1; d < LBS_ROWS; d <<= 1) base[c] = base[c] + __shfl_xor(base[c], d);
+  wave_lds_fence();
+  double* red = so;  // [NC][XC + 1]: the wave's sums and, last in a row, its base
+  if (rlw == 0) {
+#pragma unroll
+    for (int c = 0; c < NC; c++)
+#pragma unroll
+      for (int q = 0; q < 4; q++) red[c * (XC + 1) + 4 * xl + q] = acc[c][q];
+  }
+  if (ir == 0) {
+#pragma unroll
+    for (int c = 0; c < NM; c++)
+      if (NG == 2 || (c & 1) == ih) red[((NG == 2 ? ih : 0) * NM + c) * (XC + 1) + XC] = base[c];
+  }
+  __syncthreads();
+  double* Sb = S + ((long long)split * nblk + blk) * B * B;
+  for (int e = tid; e < NC * XC; e += 64 * LBS_WAVES) {
+    const int c = e / XC, x = slice * XC + e % XC;
+    const double* sums = s_o + c * (XC + 1);
+    double t = sums[e % XC], tb = sums[XC];
+#pragma unroll
+    for (int wv = 1; wv < LBS_WAVES; wv++) {
+      t = t + sums[wv * ROOM + e % XC];
+      tb = tb + sums[wv * ROOM + XC];
+    }
+    t = t + tb;
+    const int k = c / NM, g = NG == 2 && k == 1 ? wg[NG - 1] : wg[0], skip = NG == 2 && k == 1 ? wskip[NG - 1] : wskip[0];
+    int i = c % NM;
+    if (NM < MG && i >= skip) i++;
+    if (x < B && g >= 0) Sb[(long long)(g * MG + i) * B + x] = t;
+  }
+}
+
+// One workgroup per block in the given mode: the best exchange (largest delta, ties -> smallest (i, j)), applied if
+// delta > 0.  LBS_FAST first adds the workgroups' sums of the entries evaluated last (all of them in the first round) into
+// V, and leaves the block to the exact table if the best exchange is not proven to be that table's.
+// count[0] / count[1]: blocks in LBS_FAST / LBS_EXACT.
 template <int MG>
-__global__ void __launch_bounds__(256) k_lbs_select(const double* __restrict__ V, int* __restrict__ lp, int* __restrict__ groups,
-                                                     int* __restrict__ done, long long* __restrict__ swaps, long long max_swaps,
-                                                     int B, int* __restrict__ n_active) {
-  const int blk = blockIdx.x;
-  if (done[blk]) return;
+__global__ void __launch_bounds__(1024) k_lbs_select(const double* __restrict__ S, int nsplit, double* __restrict__ V, int* __restrict__ lp,
+                                                      int* __restrict__ rec, int* __restrict__ state, long long* __restrict__ swaps,
+                                                      long long max_swaps, long long N, int B, int first, int mode,
+                                                      const int* __restrict__ not_finite, int* __restrict__ count) {
+  const int blk = blockIdx.x, nblk = gridDim.x;
+  int* recb = rec + blk * 2 * LBS_REC;
+  const int st = state[blk], pa = first ? 0 : recb[0], pb = first ? 0 : recb[LBS_REC];
+  const bool fast = mode == LBS_FAST, bad = *not_finite != 0;
+  if (st != mode) return;
   const int G = B / MG;
   const int tid = threadIdx.x;
   __shared__ int s_lp[256];
-  __shared__ double s_best[256];
-  __shared__ int s_pair[256];
-  for (int i = tid; i < B; i += 256) s_lp[i] = lp[blk * B + i];
-  __syncthreads();
-  const double* Vb = V + (long long)blk * G * MG * B;
-  double best = 0.0;
-  int best_pair = -1;
-  for (int pid = tid; pid < B * B; pid += 256) {  // pid = i * B + j, ascending per thread
-    int i = pid / B, j = pid % B;
-    int a = i / MG, b = j / MG;
-    if (j <= i || a == b) continue;
-    double va2 = Vb[((a * MG) + (i % MG)) * B + s_lp[j]];
-    double vb2 = Vb[((b * MG) + (j % MG)) * B + s_lp[i]];
-    double va = Vb[(a * MG) * B + s_lp[a * MG]];
-    double vb = Vb[(b * MG) * B + s_lp[b * MG]];
-    double delta = (va2 + vb2) - (va + vb);
-    if (delta > 0.0 && (best_pair < 0 || delta > best)) {
-      best = delta;
-      best_pair = pid;
-    }
-  }
-  s_best[tid] = best;
-  s_pair[tid] = best_pair;
-  __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if (tid < s) {
-      double ob = s_best[tid + s];
-      int op = s_pair[tid + s];
-      int mp = s_pair[tid];
-      if (op >= 0 && (mp < 0 || ob > s_best[tid] || (ob == s_best[tid] && op < mp))) {
-        s_best[tid] = ob;
-        s_pair[tid] = op;
-      }
-    }
-    __syncthreads();
-  }
-  if (tid == 0) {
-    int pr = s_pair[0];
-    if (pr < 0) {
-      done[blk] = 1;
-      atomicSub(n_active, 1);
+  __shared__ double s_v[128];  // v(g)
+  __shared__ double s_best[16], s_next[16];
+  __shared__ int s_pair[16];
+  if (tid < B) s_lp[tid] = lp[blk * B + tid];
+  double* Vb = V + (long long)blk * B * B;
+  if (fast) {
+    const double* Sb = S + (long long)blk * B * B;
+    const long long sstride = (long long)nblk * B * B;
+    auto combine = [&](int e) {
+      double t = Sb[e];
+      for (int q = 1; q < nsplit; q++) t = t + Sb[q * sstride + e];
+      Vb[e] = t;
+    };
+    if (first) {
+      for (int e = tid; e < B * B; e += 1024) combine(e);
     } else {
-      int i = pr / B, j = pr % B;
-      int ci = s_lp[i], cj = s_lp[j];
-      lp[blk * B + i] = cj;
-      lp[blk * B + j] = ci;
-      groups[blk * 2 + 0] = i / MG;
-      groups[blk * 2 + 1] = j / MG;
-      long long sw = swaps[blk] + 1;
-      swaps[blk] = sw;
-      if (max_swaps > 0 && sw >= max_swaps) {
-        done[blk] = 1;
-        atomicSub(n_active, 1);
+      for (int e = tid; e < 2 * (MG - 1) * B; e += 1024) {
+        const int r = e / B, x = e - r * B;
+        const int p = r < MG - 1 ? pa : pb;
+        int i = r < MG - 1 ? r : r - (MG - 1);
+        if (i >= p % MG) i++;
+        combine((p / MG * MG + i) * B + x);
       }
+    }
+  }
+  __syncthreads();
+  if (tid < G) s_v[tid] = Vb[(tid * MG) * B + s_lp[tid * MG]];
+  __syncthreads();
+  // best and second best delta of the pairs i < j in different groups
+  double best = -INFINITY, next = -INFINITY;
+  int best_pair = -1;
+  const int tx = tid & 63, ty = tid >> 6;
+  for (int i = ty; i < B; i += 16) {  // pairs i * B + j in ascending order per thread
+    const int a = i / MG;
+    for (int j = (a + 1) * MG + tx; j < B; j += 64) {
+      const int b = j / MG;
+      const double va2 = Vb[i * B + s_lp[j]];
+      const double vb2 = Vb[j * B + s_lp[i]];
+      const double delta = (va2 + vb2) - (s_v[a] + s_v[b]);
+      if (delta > best) {
+        next = best;
+        best = delta;
+        best_pair = i * B + j;
+      } else if (delta > next) {
+        next = delta;
+      }
+    }
+  }
+  auto merge = [&](double od, double on, int op) {
+    const bool take = op >= 0 && (best_pair < 0 || od > best || (od == best && op < best_pair));
+    const double lose = take ? best : od;
+    next = fmax(fmax(next, on), lose);
+    if (take) {
+      best = od;
+      best_pair = op;
+    }
+  };
+#pragma unroll
+  for (int s = 32; s > 0; s >>= 1) {
+    const double od = __shfl_xor(best, s), on = __shfl_xor(next, s);
+    const int op = __shfl_xor(best_pair, s);
+    merge(od, on, op);
+  }
+  if (tx == 0) {
+    s_best[ty] = best;
+    s_next[ty] = next;
+    s_pair[ty] = best_pair;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    for (int w = 1; w < 16; w++) merge(s_best[w], s_next[w], s_pair[w]);
+    int to = LBS_DONE;
+    if (fast) {
+      double vmax = 0.0;
+      bool fine = !bad;
+      for (int g = 0; g < G; g++) {
+        fine = fine && s_v[g] < 1e300;
+        vmax = fmax(vmax, s_v[g]);
+      }
+      const double tol = LBS_TOL * 0x1p-53 * ((double)N + 64.0) * vmax;
+      if (fine && best_pair >= 0 && best > tol && best - next > tol) to = LBS_FAST;
+      else if (!(fine && (best_pair < 0 || best < -tol))) to = LBS_EXACT;
+    } else if (best_pair >= 0 && best > 0.0) {
+      to = LBS_EXACT;
+    }
+    if (to == mode) {  // exchange
+      const int i = best_pair / B, j = best_pair % B;
+      lp[blk * B + i] = s_lp[j];
+      lp[blk * B + j] = s_lp[i];
+      for (int k = 0; k < MG; k++) {
+        const int qa = i / MG * MG + k, qb = j / MG * MG + k;
+        recb[1 + k] = qa == i ? s_lp[j] : s_lp[qa];
+        recb[LBS_REC + 1 + k] = qb == j ? s_lp[i] : s_lp[qb];
+      }
+      recb[0] = i;
+      recb[LBS_REC] = j;
+      const long long sw = swaps[blk] + 1;
+      swaps[blk] = sw;
+      if (max_swaps > 0 && sw >= max_swaps) to = LBS_DONE;
+    }
+    if (to != mode) {
+      state[blk] = to;
+      recb[0] = recb[LBS_REC] = -1;
+      atomicSub(&count[fast ? 0 : 1], 1);
+      if (to == LBS_EXACT) atomicAdd(&count[1], 1);
     }
   }
 }
 
-__global__ void k_lbs_init(int* lp, int* done, long long* swaps, int nblk, int B) {
+__global__ void k_lbs_init(int* lp, int* state, int state0, long long* swaps, int* count, int nblk, int B) {
   int t = blockIdx.x * 256 + threadIdx.x;
   if (t < nblk * B) lp[t] = t % B;
   if (t < nblk) {
-    done[t] = 0;
+    state[t] = state0;
     swaps[t] = 0;
   }
+  if (t < 3) count[t] = t == (state0 == LBS_FAST ? 0 : 1) ? nblk : 0;  // [2]: weights that are not finite
 }
 
 __global__ void k_lbs_final_theta(const int32_t* theta0, const int* lp, int B, long long K, int32_t* theta) {
@@ -900,73 +1230,105 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
 
   // ---- local block shuffle
   if (use_lbs) {
-    const int G = B / m;
-    DevBuf d_P, d_sp, d_lp, d_groups, d_done, d_swaps, d_V, d_nact;
+    // columns of a workgroup (LPR lanes of four) and workgroups per block, see k_lbs_eval: rows are split so that two
+    // workgroups per CU share the two groups that an exchange touches (at least one batch of rows per wave)
+    const int lpr = B <= 32 ? 8 : 16;
+    const int slices = (B + lpr * 4 - 1) / (lpr * 4);
+    const int gsets = m == 4 ? 1 : 2;  // 2:4: both groups in one workgroup
+    const int nsplit = (int)std::max<long long>(1, std::min<long long>(512 / (nblk * slices * gsets), (N + LBS_WAVES * LBS_ROWS - 1) / (LBS_WAVES * LBS_ROWS)));
+    const long long batch = (long long)nsplit * LBS_WAVES * LBS_ROWS;  // rows that all waves of a block take at a time
+    const long long Npad = (N + batch - 1) / batch * batch;
     std::vector<double> sp((size_t)K);
-    for (long long p = 0; p < K; p++) sp[p] = score[theta0[p]];
-    if (d_P.alloc((size_t)N * K * 2) != hipSuccess || d_sp.alloc(K * 8) != hipSuccess || d_lp.alloc(K * 4) != hipSuccess ||
-        d_groups.alloc(nblk * 8) != hipSuccess || d_done.alloc(nblk * 4) != hipSuccess || d_swaps.alloc(nblk * 8) != hipSuccess ||
-        d_V.alloc((size_t)nblk * G * m * B * 8) != hipSuccess || d_nact.alloc(4) != hipSuccess)
+    bool fast = true;
+    for (long long p = 0; p < K; p++) {
+      sp[p] = score[theta0[p]];
+      fast = fast && sp[p] >= 0.0 && std::isfinite(sp[p]);
+    }
+    DevBuf d_P, d_sp, d_lp, d_rec, d_state, d_swaps, d_V, d_S, d_count;
+    const size_t vbytes = (size_t)nblk * B * B * 8;
+    if (d_P.alloc((size_t)(Npad * K + batch * B) * 2) != hipSuccess || d_sp.alloc(K * 8) != hipSuccess || d_lp.alloc(K * 4) != hipSuccess ||
+        d_rec.alloc(nblk * 2 * LBS_REC * 4) != hipSuccess || d_state.alloc(nblk * 4) != hipSuccess || d_swaps.alloc(nblk * 8) != hipSuccess ||
+        d_V.alloc(vbytes) != hipSuccess || d_S.alloc(vbytes * nsplit) != hipSuccess || d_count.alloc(16) != hipSuccess)
       return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation for the block shuffle failed");
     ESP_HIP(ctx, hipMemcpyAsync(d_sp.p, sp.data(), K * 8, hipMemcpyHostToDevice, st));
-    {
-      dim3 grid((unsigned)((N * K + 255) / 256));
-      if (dtype == ESPARSE_F16)
-        hipLaunchKernelGGL(k_build_panel<ESPARSE_F16>, grid, dim3(256), 0, st, W, d_theta0.as<int32_t>(), N, K, d_P.as<uint16_t>());
-      else
-        hipLaunchKernelGGL(k_build_panel<ESPARSE_BF16>, grid, dim3(256), 0, st, W, d_theta0.as<int32_t>(), N, K, d_P.as<uint16_t>());
-      ESP_HIP(ctx, hipGetLastError());
-    }
-    hipLaunchKernelGGL(k_lbs_init, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, d_lp.as<int>(), d_done.as<int>(),
-                       d_swaps.as<long long>(), (int)nblk, B);
-    int nact = (int)nblk;
-    ESP_HIP(ctx, hipMemcpyAsync(d_nact.p, &nact, 4, hipMemcpyHostToDevice, st));
-    // rows per LDS chunk: a multiple of the 16 row lanes, about 4096 metric values (at most 16 per thread)
+    hipLaunchKernelGGL(k_lbs_init, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, d_lp.as<int>(), d_state.as<int>(),
+                       fast ? LBS_FAST : LBS_EXACT, d_swaps.as<long long>(), d_count.as<int>(), (int)nblk, B);
+    hipLaunchKernelGGL(k_build_panel, dim3((unsigned)((N * K + 255) / 256)), dim3(256), 0, st, W, d_theta0.as<int32_t>(), N, Npad, K, B,
+                       dtype == ESPARSE_F16 ? 0x7c00u : 0x7f80u, d_P.as<uint16_t>(), d_count.as<int>() + 2);
+    ESP_HIP(ctx, hipGetLastError());
+    // LDS of the exact evaluation: a chunk of a multiple of 16 rows, about 4096 metric values (at most 16 per thread)
     const int rows_chunk = std::max(16, (4096 / B) / 16 * 16);
     const size_t smem = (size_t)rows_chunk * (B + 1) * 8;
-    bool first = true;
-    long long iter = 0;
-    while (nact > 0) {
-      const int entries = (first ? G : 2) * m * B;
-      const int* grp = first ? nullptr : d_groups.as<int>();
-      if (n == 2 && m == 4 && (B % 64 == 0 || B < 64)) {
-        // 2:4: 8 units per workgroup while every group is evaluated, 2 in the refresh rounds (more workgroups)
-        const int units = (first ? G : 2) * m * (B < 64 ? 1 : B / 64);
-        const int nc = first ? 8 : 2;
-        dim3 grid((unsigned)((units + nc - 1) / nc), (unsigned)nblk);
-        const size_t smem2 = (size_t)rows_chunk * (B + 1) * 8 + (size_t)rows_chunk * nc * 16;
-#define LAUNCH_EVAL24(DTv, NCv)                                                                                             \
-  hipLaunchKernelGGL((k_lbs_eval_2_4<DTv, NCv>), grid, dim3(1024), smem2, st, d_P.as<uint16_t>(), d_sp.as<double>(), d_lp.as<int>(), \
-                     grp, d_done.as<int>(), N, K, B, rows_chunk, d_V.as<double>())
-        if (dtype == ESPARSE_F16) {
-          if (first) LAUNCH_EVAL24(ESPARSE_F16, 8);
-          else LAUNCH_EVAL24(ESPARSE_F16, 2);
-        } else {
-          if (first) LAUNCH_EVAL24(ESPARSE_BF16, 8);
-          else LAUNCH_EVAL24(ESPARSE_BF16, 2);
-        }
-#undef LAUNCH_EVAL24
-      } else {
-        dim3 grid((unsigned)((entries + 63) / 64), (unsigned)nblk);
-#define LAUNCH_EVAL(DT, NK, MGv, ...)                                                                                  \
-  hipLaunchKernelGGL((k_lbs_eval<DT, NK, MGv>), grid, dim3(1024), smem, st, d_P.as<uint16_t>(), d_sp.as<double>(), d_lp.as<int>(), \
-                     grp, d_done.as<int>(), N, K, B, rows_chunk, d_V.as<double>())
-        DISPATCH_DT_NM(dtype, n, LAUNCH_EVAL, 0);
+    int count[2] = {fast ? (int)nblk : 0, fast ? 0 : (int)nblk};
+    for (int mode : {LBS_FAST, LBS_EXACT}) {
+      int& active = count[mode == LBS_FAST ? 0 : 1];
+      bool first = true;
+      long long iter = 0;
+      while (active > 0) {
+        // rounds are queued several at a time: a round after the last exchange of every block only finds that (about
+        // 5 us), a look at the count from the host costs about 25
+        for (int r = 0; r < LBS_ROUNDS_QUEUED; r++) {
+          if (mode == LBS_FAST) {
+#define LAUNCH_EVAL2(DTv, NK, MGv, NGv, NMv, LPRv)                                                                          \
+  hipLaunchKernelGGL((k_lbs_eval<DTv, NK, MGv, NGv, NMv, LPRv>),                                                            \
+                     dim3((unsigned)nblk, (unsigned)nsplit, (unsigned)(slices * (NMv == MGv ? (B / MGv + NGv - 1) / NGv : gsets))), \
+                     dim3(64 * LBS_WAVES), 0, st, d_P.as<uint16_t>(), d_sp.as<double>(), d_rec.as<int>(), N, Npad, B, slices, d_S.as<double>())
+#define LAUNCH_EVAL(DTv, NK, MGv, ...)                                                      \
+  do {                                                                                      \
+    constexpr int NGv = MGv == 4 ? 2 : 1;                                                   \
+    if (first && lpr == 16) LAUNCH_EVAL2(DTv, NK, MGv, NGv, MGv, 16);                       \
+    else if (first) LAUNCH_EVAL2(DTv, NK, MGv, NGv, MGv, 8);                                \
+    else if (lpr == 16) LAUNCH_EVAL2(DTv, NK, MGv, NGv, (MGv - 1), 16);                     \
+    else LAUNCH_EVAL2(DTv, NK, MGv, NGv, (MGv - 1), 8);                                     \
+  } while (0)
+            DISPATCH_DT_NM(dtype, n, LAUNCH_EVAL, 0);
 #undef LAUNCH_EVAL
+#undef LAUNCH_EVAL2
+          } else {
+            const int* rec = first ? nullptr : d_rec.as<int>();
+            if (m == 4 && (B % 64 == 0 || B < 64)) {
+              // 2:4: 8 units per workgroup while every group is evaluated, 2 in the refresh rounds (more workgroups)
+              const int units = (first ? B / m : 2) * m * (B < 64 ? 1 : B / 64);
+              const int nc = first ? 8 : 2;
+              dim3 grid((unsigned)((units + nc - 1) / nc), (unsigned)nblk);
+              const size_t smem2 = smem + (size_t)rows_chunk * nc * 16;
+#define LAUNCH_EXACT24(DTv, NCv)                                                                                             \
+  hipLaunchKernelGGL((k_lbs_exact_2_4<DTv, NCv>), grid, dim3(1024), smem2, st, d_P.as<uint16_t>(), d_sp.as<double>(), d_lp.as<int>(), \
+                     rec, d_state.as<int>(), N, Npad, B, rows_chunk, d_V.as<double>())
+              if (dtype == ESPARSE_F16) {
+                if (first) LAUNCH_EXACT24(ESPARSE_F16, 8);
+                else LAUNCH_EXACT24(ESPARSE_F16, 2);
+              } else {
+                if (first) LAUNCH_EXACT24(ESPARSE_BF16, 8);
+                else LAUNCH_EXACT24(ESPARSE_BF16, 2);
+              }
+#undef LAUNCH_EXACT24
+            } else {
+              dim3 grid((unsigned)(((first ? B / m : 2) * m * B + 63) / 64), (unsigned)nblk);
+#define LAUNCH_EXACT(DT, NK, MGv, ...)                                                                                        \
+  hipLaunchKernelGGL((k_lbs_exact<DT, NK, MGv>), grid, dim3(1024), smem, st, d_P.as<uint16_t>(), d_sp.as<double>(), d_lp.as<int>(), \
+                     rec, d_state.as<int>(), N, Npad, B, rows_chunk, d_V.as<double>())
+              DISPATCH_DT_NM(dtype, n, LAUNCH_EXACT, 0);
+#undef LAUNCH_EXACT
+            }
+          }
+          ESP_HIP(ctx, hipGetLastError());
+#define LAUNCH_SELECT(MGv)                                                                                                     \
+  hipLaunchKernelGGL(k_lbs_select<MGv>, dim3((unsigned)nblk), dim3(1024), 0, st, d_S.as<double>(), nsplit, d_V.as<double>(), d_lp.as<int>(), \
+                     d_rec.as<int>(), d_state.as<int>(), d_swaps.as<long long>(), o->max_swaps, N, B, first ? 1 : 0, (int)mode,  \
+                     d_count.as<int>() + 2, d_count.as<int>())
+          if (m == 4) LAUNCH_SELECT(4);
+          else LAUNCH_SELECT(8);
+#undef LAUNCH_SELECT
+          ESP_HIP(ctx, hipGetLastError());
+          first = false;
+        }
+        iter += LBS_ROUNDS_QUEUED;
+        ESP_HIP(ctx, hipMemcpyAsync(count, d_count.p, 8, hipMemcpyDeviceToHost, st));
+        ESP_HIP(ctx, hipStreamSynchronize(st));
+        if (active > 0 && iter > (long long)B * B * 64)
+          return esp_fail(ctx, ESPARSE_EHIP, "block shuffle did not terminate after %lld rounds", iter);
       }
-      ESP_HIP(ctx, hipGetLastError());
-      if (m == 4)
-        hipLaunchKernelGGL(k_lbs_select<4>, dim3((unsigned)nblk), dim3(256), 0, st, d_V.as<double>(), d_lp.as<int>(), d_groups.as<int>(),
-                           d_done.as<int>(), d_swaps.as<long long>(), o->max_swaps, B, d_nact.as<int>());
-      else
-        hipLaunchKernelGGL(k_lbs_select<8>, dim3((unsigned)nblk), dim3(256), 0, st, d_V.as<double>(), d_lp.as<int>(), d_groups.as<int>(),
-                           d_done.as<int>(), d_swaps.as<long long>(), o->max_swaps, B, d_nact.as<int>());
-      ESP_HIP(ctx, hipGetLastError());
-      ESP_HIP(ctx, hipMemcpyAsync(&nact, d_nact.p, 4, hipMemcpyDeviceToHost, st));
-      ESP_HIP(ctx, hipStreamSynchronize(st));
-      first = false;
-      if (++iter > (long long)B * B * 64)
-        return esp_fail(ctx, ESPARSE_EHIP, "block shuffle did not terminate after %lld rounds", iter);
     }
     hipLaunchKernelGGL(k_lbs_final_theta, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, d_theta0.as<int32_t>(), d_lp.as<int>(), B,
                        K, perm_out);

@@ -127,6 +127,53 @@ def test_prune_max_swaps_and_ties(esp, ctx):
     assert (res.mask.cpu().numpy() == orc.nm_mask(W.numpy(), s, theta, 2, 4)).all()
 
 
+def _check_block_shuffle(esp, ctx, W, s, n, m, B, max_swaps=0):
+    """The exchanges against the oracle's with the rows added in the device's order (16 interleaved sub-sums)."""
+    print(f"lbs N={W.shape[0]} K={W.shape[1]} B={B} {n}:{m} {W.dtype}", flush=True)
+    res = ctx.prune(None, W.cuda(), esp.PruneOpts(n_keep=n, m_group=m, block=B, max_swaps=max_swaps), score=s, want_retained=True)
+    Wn = _np(W)
+    theta, swaps = orc.local_block_shuffle_vectorised(Wn, s, orc.global_naive_shuffle(Wn, s, m), n, m, B, max_swaps,
+                                                      order=("lanes", 16))
+    assert (res.swaps == swaps).all() and (res.perm.cpu().numpy() == theta).all()
+    assert (res.mask.cpu().numpy() == orc.nm_mask_vectorised(Wn, s, theta, n, m)).all()
+    assert res.retained == pytest.approx(orc.retained_metric(Wn, s, theta, n, m), rel=1e-12)
+    return swaps
+
+
+# sizes at the edges of the evaluation kernel: fewer rows than a wave's 32, one more than a batch of rows, more than
+# one batch per wave; blocks of fewer columns than a lane group, of an odd number of groups, of more than 64 columns
+@pytest.mark.parametrize("n,m,B,N", [(2, 4, 8, 1), (2, 4, 12, 33), (2, 4, 36, 257), (2, 4, 64, 1100), (2, 4, 100, 300), (2, 4, 256, 31),
+                                     (4, 8, 16, 7), (4, 8, 24, 257), (4, 8, 40, 530), (4, 8, 72, 64), (4, 8, 128, 300)])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+def test_block_shuffle_edges_of_the_evaluation_kernel(esp, ctx, n, m, B, N, dtype):
+    W = _rand((N, 2 * B), dtype, 31 + N, scale=(2 * B) ** -0.5)
+    s = np.random.default_rng(N + B).lognormal(size=2 * B)
+    _check_block_shuffle(esp, ctx, W, s, n, m, B, max_swaps=6 if B > 64 else 0)
+
+
+# exchanges that the cheaper table cannot decide: equal columns (ties), columns without weights and channels kept in every
+# row (exchanges that change nothing but the rounding), negative scores
+@pytest.mark.parametrize("n,m", [(2, 4), (4, 8)])
+@pytest.mark.parametrize("what", ["equal", "zero", "dominant", "negative"])
+def test_block_shuffle_undecided_exchanges(esp, ctx, n, m, what):
+    N, K, B = 90, 128, 64
+    W = _rand((N, K), torch.float16, 77, scale=K ** -0.5)
+    rng = np.random.default_rng(7)
+    s = rng.lognormal(size=K)
+    some = rng.permutation(K)[:24]
+    if what == "equal":
+        W[:, some] = W[:, some[:1]]
+        s[some] = s[some[0]]
+    elif what == "zero":
+        W[:, some] = 0
+    elif what == "dominant":
+        W[:, some] += 8
+        s[some] *= 100
+    else:
+        s[some] *= -1
+    assert _check_block_shuffle(esp, ctx, W, s, n, m, B).sum() > 0
+
+
 def test_config1_against_stored_oracle_results(esp, ctx):
     """Workload configuration 1, complete, against results the oracle wrote to tests/golden."""
     gold = json.load(open(os.path.join(os.path.dirname(__file__), "golden", "cfg1_oracle.json")))
