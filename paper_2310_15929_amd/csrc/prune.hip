@@ -434,18 +434,55 @@ int esp_stats_device(esparse_ctx* ctx, const void* calib, long long T, long long
 // local block shuffle
 // ------------------------------------------------------------------------------------------------
 // Panel: P[blk][j][c] = |W[j, theta0[blk B + c]]| as raw 16-bit magnitudes: the N x B values of a block are
-// contiguous, so that a block's share (512 KiB for N = 4096, B = 64) stays in the L2 of the XCD that works on it.
-// Npad >= N rows per block; the rows past N are read but never used and stay as they are.
-__global__ void __launch_bounds__(256) k_build_panel(const uint16_t* __restrict__ W, const int32_t* __restrict__ theta0,
-                                                      long long N, long long Npad, long long K, int B, unsigned int inf_bits,
+// contiguous, so that a block's share (512 KiB for N = 4096, B = 64) stays in the L2 of the XCD that works on it, and
+// PT[blk][c][j], the same by columns (the members of a group for consecutive rows).  Npad >= N rows per block; what
+// lies past N is read but never used and stays as it is.
+//
+// A workgroup copies RB whole rows into LDS and gathers from there: a gather from global memory goes through the
+// vector-memory path one lane at a time (52 us for 4096 x 4096).  RB = 0: rows that do not fit the LDS, gathered from
+// global memory, one per workgroup.
+__global__ void __launch_bounds__(512) k_build_panel(const uint16_t* __restrict__ W, const int32_t* __restrict__ theta0,
+                                                      long long N, long long Npad, long long K, int B, int RB, unsigned int inf_bits,
                                                       uint16_t* __restrict__ P, int* __restrict__ not_finite) {
-  long long e = (long long)blockIdx.x * 256 + threadIdx.x;
-  if (e >= N * K) return;
-  long long j = e / K, p = e % K;
-  long long blk = p / B, c = p - blk * B;
-  const unsigned int v = W[j * K + theta0[p]] & 0x7fffu;
-  if (v >= inf_bits) atomicOr(not_finite, 1);
-  P[(blk * Npad + j) * B + c] = (uint16_t)v;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  uint16_t* s_w = reinterpret_cast<uint16_t*>(smem_raw);
+  const int tid = threadIdx.x, rows = RB ? RB : 1;
+  const long long j0 = (long long)blockIdx.x * rows;
+  const int nr = (int)(N - j0 < rows ? N - j0 : rows);
+  if (RB) {
+    const uint16_t* src = W + j0 * K;  // the rows are contiguous; K is a multiple of 4 and W of 16 bytes
+    const long long n4 = nr * K / 4;
+    for (long long e = tid; e < n4; e += 512) reinterpret_cast<uint2*>(s_w)[e] = reinterpret_cast<const uint2*>(src)[e];
+    __syncthreads();
+  }
+  const int q4 = B / 4, nblk = (int)(K / B);  // four columns per thread and step
+  bool bad = false;
+  for (int e = tid; e < nblk * nr * q4; e += 512) {
+    const int c = e % q4, t = e / q4, r = t % nr, blk = t / nr;
+    const int4 col = reinterpret_cast<const int4*>(theta0)[blk * q4 + c];
+    const uint16_t* row = RB ? s_w + (size_t)r * K : W + j0 * K;
+    const unsigned int v0 = row[col.x] & 0x7fffu, v1 = row[col.y] & 0x7fffu, v2 = row[col.z] & 0x7fffu, v3 = row[col.w] & 0x7fffu;
+    bad = bad || v0 >= inf_bits || v1 >= inf_bits || v2 >= inf_bits || v3 >= inf_bits;
+    reinterpret_cast<uint2*>(P + ((long long)blk * Npad + j0 + r) * B)[c] = uint2{v0 | (v1 << 16), v2 | (v3 << 16)};
+  }
+  if (bad) atomicOr(not_finite, 1);
+}
+
+// 64 rows x 64 columns of a block per workgroup, through LDS
+__global__ void __launch_bounds__(256) k_panel_columns(const uint16_t* __restrict__ P, long long Npad, int nblk, int B, uint16_t* __restrict__ PT) {
+  __shared__ uint16_t s_t[64 * 66];
+  const int tid = threadIdx.x, blk = (int)(blockIdx.x % (unsigned)nblk);
+  const long long j0 = (long long)(blockIdx.x / (unsigned)nblk) * 64;
+  const int c0 = (int)blockIdx.y * 64, nc = B - c0 < 64 ? B - c0 : 64;
+  const int nj = (int)(Npad - j0 < 64 ? Npad - j0 : 64);
+  const uint16_t* src = P + ((long long)blk * Npad + j0) * B + c0;
+  const int cx = (tid & 31) * 2, ry = tid >> 5;
+  for (int r = ry; r < nj; r += 8)
+    if (cx < nc) *reinterpret_cast<uint32_t*>(s_t + r * 66 + cx) = *reinterpret_cast<const uint32_t*>(src + (long long)r * B + cx);
+  __syncthreads();
+  uint16_t* dst = PT + ((long long)blk * B + c0) * Npad + j0;
+  for (int c = ry; c < nc; c += 8)
+    if (cx < nj) *reinterpret_cast<uint32_t*>(dst + (long long)c * Npad + cx) = s_t[cx * 66 + c] | ((uint32_t)s_t[(cx + 1) * 66 + c] << 16);
 }
 
 template <int NKEEP, int MG>
@@ -499,10 +536,16 @@ __device__ __forceinline__ double lanes_total(double part) {
 // Replacing the member that the last exchange brought into a group leaves the same other members as before it, so those
 // entries stay valid: NM = MG - 1 members per touched group are re-evaluated.
 //
-// A workgroup (8 waves) takes NG groups, LPR * 4 columns and every nsplit-th set of rows.  A lane owns four columns and
-// every S-th row (S = row lanes of all workgroups of the block), so the panel value and its product with the score are
-// formed once for NG * NM combinations, and an operand that comes out of LDS serves four candidates.  A wave forms the
-// operands of its next 32 rows itself (one lane per row and group: the NKEEP + 1 largest members) and needs no barrier.
+// A workgroup (8 waves) takes NG groups, 16 QC columns and every nsplit-th set of 8 x 32 rows.  A lane owns QC columns and
+// every fourth row of its wave, so the panel value and its product with the score are
+// formed once for NG * NM combinations; the 16 lanes of a row read its operands once and pass them around (read out of LDS
+// by every lane they kept the LDS as busy as the float64 pipes).  A wave forms the
+// operands of its next 32 rows itself (one lane per row and group: the NKEEP + 1 largest members, read from PT - gathered
+// from P they cost the vector-memory path a third of the kernel's time) and needs no barrier.
+//
+// Bound by float64 instructions (a wave's takes 4 clocks of its SIMD, adds, maxima and conversions alike).  64 blocks of
+// 4096 x 64, 2:4: two touched groups 18 us, all groups 142 us (exact table: 142 and 677); 80 blocks of 5120 x 64, 4:8: 57 and
+// 254 us (1034 and 4525).
 #define LBS_WAVES 8
 #define LBS_ROWS 32  // rows whose operands a wave keeps in LDS
 #define LBS_ROUNDS_QUEUED 12
@@ -725,15 +768,38 @@ __global__ void __launch_bounds__(1024) k_lbs_exact_2_4(const uint16_t* __restri
 }
 
 // ---- the table that is cheaper to evaluate
-template <int CTRL>
-__device__ __forceinline__ double dpp_f64(double v) {
+// the value of lane LANE of each row of 16 lanes in all lanes of that row
+template <int LANE>
+__device__ __forceinline__ double row_bcast(double v) {
 #if defined(__HIP_DEVICE_COMPILE__)
   const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x150 + LANE, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x150 + LANE, 0xf, 0xf, true);
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 #else
   return v;
+#endif
+}
+
+// a + b with half of the lanes of each exchanged: lanes 0-31 get a[l] + a[l + 32], lanes 32-63 b[l - 32] + b[l]
+// (HALF), or the same within each pair of 16-lane rows
+template <bool HALF>
+__device__ __forceinline__ double swap_add(double a, double b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+  unsigned int r[4];
+  if (HALF) {
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned int)x, (unsigned int)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned int)(x >> 32), (unsigned int)(y >> 32), false, false);
+    r[0] = lo[0]; r[1] = lo[1]; r[2] = hi[0]; r[3] = hi[1];
+  } else {
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned int)x, (unsigned int)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned int)(x >> 32), (unsigned int)(y >> 32), false, false);
+    r[0] = lo[0]; r[1] = lo[1]; r[2] = hi[0]; r[3] = hi[1];
+  }
+  return __longlong_as_double(((long long)r[2] << 32) | r[0]) + __longlong_as_double(((long long)r[3] << 32) | r[1]);
+#else
+  return a + b;
 #endif
 }
 
@@ -774,37 +840,51 @@ __device__ __forceinline__ double min_f64(double a, double b) {
 #endif
 }
 
-template <int DT, int NKEEP, int MG, int NG, int NM, int LPR>
-__global__ void __launch_bounds__(64 * LBS_WAVES, 4) k_lbs_eval(const uint16_t* __restrict__ P, const double* __restrict__ sp /*[K] score in panel order*/,
+template <int DT, int NKEEP, int MG, int NG, int NM, int QC>
+__global__ void __launch_bounds__(64 * LBS_WAVES, 4) k_lbs_eval(const uint16_t* __restrict__ P, const uint16_t* __restrict__ PT, const double* __restrict__ sp /*[K] score in panel order*/,
                                                               const int* __restrict__ rec /*[nblk][2][LBS_REC] exchanged positions and their groups*/,
                                                               long long N, long long Npad, int B, int slices, double* __restrict__ S /*[nsplit][nblk][B][B]*/) {
-  constexpr int RLW = 64 / LPR;          // row lanes of a wave
-  constexpr int RL = LBS_WAVES * RLW;    // ... of a workgroup
+  constexpr int RLW = 4;                 // rows of a wave at a time, 16 lanes each
   constexpr int U = LBS_ROWS / RLW;      // rows of a lane per batch
   constexpr int NC = NG * NM;            // combinations of group and member
-  constexpr int XC = LPR * 4;            // columns of a workgroup
+  constexpr int XC = 16 * QC;            // columns of a workgroup
   static_assert(NG == 1 || NG == 2, "one or two groups per workgroup");
-  constexpr int NCP = (NC + 1) / 2 * 2;  // operands of a row, read in pairs
+  static_assert(NC <= 16 && (QC == 2 || QC == 4), "a row's operands fit its 16 lanes");
+  constexpr int NCP = NC | 1;            // operands of a row in LDS
   constexpr int ROOM = LBS_ROWS * NCP > NC * (XC + 1) ? LBS_ROWS * NCP : NC * (XC + 1);
   __shared__ __align__(16) double s_o[LBS_WAVES * ROOM];  // per wave: operands; at the end its sums
   __shared__ double s_ms[LBS_WAVES * 2 * MG];
+  __shared__ int s_mc[LBS_WAVES * 2 * MG];
   const int blk = blockIdx.x, nblk = gridDim.x, split = blockIdx.y, nsplit = gridDim.y;
   const int slice = (int)blockIdx.z % slices, gset = (int)blockIdx.z / slices;
   const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
-  const int rlw = lane % RLW, xl = lane / RLW;
-  const int col0 = slice * XC + 4 * xl;
+  const int rlw = lane / 16, xl = lane % 16;
+  const int col0 = slice * XC + QC * xl;
   const int colc = col0 < B ? col0 : 0;  // columns past the block compute along and are dropped at the end
   // operand lane: row ir of the batch; NG = 2: group ih, all members; NG = 1: members ih, ih + 2, ...
   const int ir = lane % LBS_ROWS, ih = lane / LBS_ROWS;
-  const long long step = (long long)nsplit * RL;
-  const long long rb0 = (long long)split * RL + wave * RLW;
-  // rows rb + rlw + u step of the panel, which is padded to whole batches; rows past N are replaced by zeros
+  // batches of 32 rows: rows rb + u RLW + rlw of the panel, which is padded to whole batches; rows past N are replaced
+  // by zeros
+  const long long step = (long long)nsplit * LBS_WAVES * LBS_ROWS;
+  const long long rb0 = (long long)(split * LBS_WAVES + wave) * LBS_ROWS;
   const uint16_t* Pb = P + (long long)blk * Npad * B;
   const int xoff = rlw * B + colc;
-  const uint16_t* prow = Pb + rb0 * B;  // the wave's next row; the values are loaded one row ahead
-  uint2 next = *reinterpret_cast<const uint2*>(prow + xoff);
+  // the values are loaded AHEAD rows ahead: a row takes about 1700 clocks with four waves per SIMD, a load from the
+  // last-level cache as long
+  constexpr int AHEAD = 3;
+  const uint16_t* prow = Pb + rb0 * B;
+  const long long jump = (step - LBS_ROWS) * B;  // from one batch of the wave to the next
+  uint2 next[AHEAD];
+  auto load_row = [&]() {
+    if (QC == 4) return *reinterpret_cast<const uint2*>(prow + xoff);
+    return uint2{*reinterpret_cast<const uint32_t*>(prow + xoff), 0u};
+  };
+#pragma unroll
+  for (int q = 0; q < AHEAD; q++, prow += RLW * B) next[q] = load_row();
   // groups of this workgroup: their number (-1: none), the member that needs no evaluation, the members' columns
-  int wg[NG], wskip[NG], mcol[MG];
+  int wg[NG], wskip[NG];
+  int* smc = s_mc + (wave * 2 + (NG == 2 ? ih : 0)) * MG;  // the lane's group: columns and scores of the members
+  double* sms = s_ms + (wave * 2 + (NG == 2 ? ih : 0)) * MG;
 #pragma unroll
   for (int k = 0; k < NG; k++) {
     const int g = gset * NG + k;
@@ -813,7 +893,7 @@ __global__ void __launch_bounds__(64 * LBS_WAVES, 4) k_lbs_eval(const uint16_t* 
       wskip[k] = MG;
       if (NG == 1 || ih == k)
 #pragma unroll
-        for (int i = 0; i < MG; i++) mcol[i] = wg[k] < 0 ? i : g * MG + i;
+        for (int i = 0; i < MG; i++) smc[i] = wg[k] < 0 ? i : g * MG + i;
     } else {
       const int* rg = rec + (blk * 2 + g) * LBS_REC;
       if (rg[0] < 0) return;  // the block is done
@@ -821,126 +901,132 @@ __global__ void __launch_bounds__(64 * LBS_WAVES, 4) k_lbs_eval(const uint16_t* 
       wskip[k] = rg[0] % MG;
       if (NG == 1 || ih == k)
 #pragma unroll
-        for (int i = 0; i < MG; i++) mcol[i] = rg[1 + i];
+        for (int i = 0; i < MG; i++) smc[i] = rg[1 + i];
     }
   }
   const int iskip = NG == 2 && ih == 1 ? wskip[NG - 1] : wskip[0];
-  const int irow = (ir % RLW) + (ir / RLW) * (int)step;  // of the batch
+  wave_lds_fence();
+  const uint16_t* PTb = PT + (long long)blk * B * Npad + ir;
   uint16_t mraw[MG];
   auto load_members = [&](long long rb) {
-    const uint16_t* src = Pb + rb * B;
 #pragma unroll
-    for (int k = 0; k < MG; k++) mraw[k] = src[irow * B + mcol[k]];
+    for (int k = 0; k < MG; k++) mraw[k] = PTb[smc[k] * Npad + rb];
   };
-  load_members(rb0);
-  double s[4];
+  if (rb0 < N) load_members(rb0);
+  double s[QC];
 #pragma unroll
-  for (int q = 0; q < 4; q++) s[q] = sp[(long long)blk * B + colc + q];
-  double* sms = s_ms + (wave * 2 + (NG == 2 ? ih : 0)) * MG;  // the members' scores
+  for (int q = 0; q < QC; q++) s[q] = sp[(long long)blk * B + colc + q];
 #pragma unroll
-  for (int k = 0; k < MG; k++) sms[k] = sp[(long long)blk * B + mcol[k]];
+  for (int k = 0; k < MG; k++) sms[k] = sp[(long long)blk * B + smc[k]];
   double* so = s_o + wave * ROOM;
-  double acc[NC][4];
+  constexpr int NA = (NC * QC + 3) / 4 * 4;
+  double acc[NA];  // [NC][QC], a multiple of four
 #pragma unroll
-  for (int c = 0; c < NC; c++)
+  for (int f = 0; f < NA; f++) acc[f] = 0.0;
+  constexpr int NB = NG == 2 ? NM : (NM + 1) / 2;  // members of an operand lane
+  double base[NB];  // operand lanes: what the other members keep besides the operand
 #pragma unroll
-    for (int q = 0; q < 4; q++) acc[c][q] = 0.0;
-  double base[NM];  // operand lanes: what the other members keep besides the operand
-#pragma unroll
-  for (int c = 0; c < NM; c++) base[c] = 0.0;
+  for (int c = 0; c < NB; c++) base[c] = 0.0;
 
-  for (long long rb = rb0; rb < N; rb += U * step) {
+  for (long long rb = rb0; rb < N; rb += step) {
     {
-      const bool live = rb + irow < N;
-      double v[MG], w[MG];
+      const bool live = rb + ir < N;
+      double w[NKEEP + 1];  // the largest members, in order
       wave_lds_fence();
+      auto member = [&](int k) {
+        const double v = (double)esp_to_float<DT>(mraw[k]) * sms[k];
+        return live ? v : 0.0;
+      };
+      w[0] = member(0);
 #pragma unroll
-      for (int k = 0; k < MG; k++) {
-        v[k] = (double)esp_to_float<DT>(mraw[k]) * sms[k];
-        v[k] = live ? v[k] : 0.0;
-        w[k] = v[k];
+      for (int k = 1; k < MG; k++) {
+        double v = member(k);
+#pragma unroll
+        for (int q = 0; q <= NKEEP && q < k; q++) {
+          const double hi = max_f64(w[q], v);
+          v = min_f64(w[q], v);
+          w[q] = hi;
+        }
+        if (k <= NKEEP) w[k] = v;
       }
 #pragma unroll
-      for (int a = 0; a <= NKEEP; a++)  // the NKEEP + 1 largest, in order
-#pragma unroll
-        for (int b = MG - 1; b > a; b--) {
-          const double hi = max_f64(w[b - 1], w[b]), lo = min_f64(w[b - 1], w[b]);
-          w[b - 1] = hi;
-          w[b] = lo;
+      for (int q = 0; q < NB; q++) {  // without member i: the largest, with the next one in place of that member
+        const int c = NG == 2 ? q : 2 * q + ih;
+        double v;
+        if (NG == 2) v = member(q);
+        else v = ih ? member(2 * q + 1 < MG ? 2 * q + 1 : 2 * q) : member(2 * q);
+        if (NM < MG) {
+          double vn;
+          if (NG == 2) vn = member(q + 1);
+          else vn = ih ? member(2 * q + 2 < MG ? 2 * q + 2 : 2 * q) : member(2 * q + 1 < MG ? 2 * q + 1 : 2 * q);
+          v = c >= iskip ? vn : v;
         }
+        double kept = v >= w[0] ? w[1] : w[0];
 #pragma unroll
-      for (int c = 0; c < NM; c++) {
-        if (NG == 1 && (c & 1) != ih) continue;
-        const double vi = (NM < MG && c >= iskip) ? v[c + (NM < MG ? 1 : 0)] : v[c];
-        double kept = vi >= w[0] ? w[1] : w[0];  // the largest without member c
-#pragma unroll
-        for (int k = 1; k < NKEEP - 1; k++) kept = kept + (vi >= w[k] ? w[k + 1] : w[k]);
-        base[c] = base[c] + kept;
-        so[ir * NCP + (NG == 2 ? ih : 0) * NM + c] = vi >= w[NKEEP - 1] ? w[NKEEP] : w[NKEEP - 1];
+        for (int k = 1; k < NKEEP - 1; k++) kept = kept + (v >= w[k] ? w[k + 1] : w[k]);
+        base[q] = base[q] + kept;
+        if (c < NM) so[ir * NCP + (NG == 2 ? ih : 0) * NM + c] = v >= w[NKEEP - 1] ? w[NKEEP] : w[NKEEP - 1];
       }
       wave_lds_fence();
     }
-    const long long rnext = rb + U * step;
-    const bool full = rb + RLW - 1 + (U - 1) * step < N;
+    const long long rnext = rb + step;
+    const bool full = rb + LBS_ROWS <= N;
     if (rnext < N) load_members(rnext);
-    const double2* src = reinterpret_cast<const double2*>(so + rlw * NCP);
+    // lane c of a row reads the operand of combination c and hands it to the other 15
+    const double* src = so + rlw * NCP + (xl < NC ? xl : NC - 1);
+    double o_next = *src;
 #pragma unroll 1
     for (int u = 0; u < U; u++) {
-      const uint2 raw = next;
-      prow += step * B;
-      next = *reinterpret_cast<const uint2*>(prow + xoff);
-      double x[4];
-      x[0] = (double)esp_to_float<DT>((uint16_t)(raw.x & 0xffffu)) * s[0];
-      x[1] = (double)esp_to_float<DT>((uint16_t)(raw.x >> 16)) * s[1];
-      x[2] = (double)esp_to_float<DT>((uint16_t)(raw.y & 0xffffu)) * s[2];
-      x[3] = (double)esp_to_float<DT>((uint16_t)(raw.y >> 16)) * s[3];
+      const uint2 raw = next[0];
+#pragma unroll
+      for (int q = 1; q < AHEAD; q++) next[q - 1] = next[q];
+      if (u == U - AHEAD) prow += jump;
+      next[AHEAD - 1] = load_row();
+      prow += RLW * B;
+      const double o = o_next;
+      src += u < U - 1 ? RLW * NCP : 0;
+      o_next = *src;
+      double x[QC];
+#pragma unroll
+      for (int q = 0; q < QC; q++) {
+        const uint32_t two = q < 2 ? raw.x : raw.y;
+        x[q] = (double)esp_to_float<DT>((uint16_t)(q & 1 ? two >> 16 : two & 0xffffu)) * s[q];
+      }
       if (!full) {  // no such row: adds exactly 0 whatever the scores are
-        const bool live = rb + rlw + u * step < N;
+        const bool live = rb + u * RLW + rlw < N;
 #pragma unroll
-        for (int q = 0; q < 4; q++) x[q] = live ? x[q] : 0.0;
+        for (int q = 0; q < QC; q++) x[q] = live ? x[q] : 0.0;
       }
-      double o[NCP];
-#pragma unroll
-      for (int c = 0; c < NCP; c += 2) {
-        const double2 t = src[c / 2];
-        o[c] = t.x;
-        o[c + 1] = t.y;
-      }
-#pragma unroll
-      for (int c = 0; c < NC; c++)
-#pragma unroll
-        for (int q = 0; q < 4; q++) acc[c][q] = acc[c][q] + max_f64(o[c], x[q]);
-      src += RLW * NCP / 2;
+#define LBS_ADD(c)                                                                                         \
+  if constexpr (c < NC) {                                                                                  \
+    const double oc = row_bcast<c>(o);                                                                     \
+    _Pragma("unroll") for (int q = 0; q < QC; q++) acc[c * QC + q] = acc[c * QC + q] + max_f64(oc, x[q]);  \
+  }
+      LBS_ADD(0) LBS_ADD(1) LBS_ADD(2) LBS_ADD(3) LBS_ADD(4) LBS_ADD(5) LBS_ADD(6) LBS_ADD(7)
+#undef LBS_ADD
     }
   }
-  // row lanes of the wave: neighbouring lanes, pairwise
+  // the four rows of the wave: row lane r ends up with the sums number 4 k + {0, 2, 1, 3}[r]
 #pragma unroll
-  for (int c = 0; c < NC; c++)
-#pragma unroll
-    for (int q = 0; q < 4; q++) {
-      double v = acc[c][q];
-      v = v + dpp_f64<0xB1>(v);  // lane ^ 1
-      v = v + dpp_f64<0x4E>(v);  // lane ^ 2
-      if (RLW == 8) v = v + dpp_f64<0x141>(v);  // the other four of the eight
-      acc[c][q] = v;
-    }
+  for (int f = 0; f < NA; f += 4) acc[f / 4] = swap_add<false>(swap_add<true>(acc[f], acc[f + 1]), swap_add<true>(acc[f + 2], acc[f + 3]));
   // operand lanes: over the 32 rows; NG = 1: the other half of the lanes holds the other members
 #pragma unroll
-  for (int c = 0; c < NM; c++)
+  for (int q = 0; q < NB; q++)
 #pragma unroll
-    for (int d = 1; d < LBS_ROWS; d <<= 1) base[c] = base[c] + __shfl_xor(base[c], d);
+    for (int d = 1; d < LBS_ROWS; d <<= 1) base[q] = base[q] + __shfl_xor(base[q], d);
   wave_lds_fence();
   double* red = so;  // [NC][XC + 1]: the wave's sums and, last in a row, its base
-  if (rlw == 0) {
 #pragma unroll
-    for (int c = 0; c < NC; c++)
-#pragma unroll
-      for (int q = 0; q < 4; q++) red[c * (XC + 1) + 4 * xl + q] = acc[c][q];
+  for (int k = 0; k < NA / 4; k++) {
+    const int f = 4 * k + ((rlw & 1) << 1 | rlw >> 1), c = f / QC;
+    if (c < NC) red[c * (XC + 1) + QC * xl + f % QC] = acc[k];
   }
   if (ir == 0) {
 #pragma unroll
-    for (int c = 0; c < NM; c++)
-      if (NG == 2 || (c & 1) == ih) red[((NG == 2 ? ih : 0) * NM + c) * (XC + 1) + XC] = base[c];
+    for (int q = 0; q < NB; q++) {
+      const int c = NG == 2 ? q : 2 * q + ih;
+      if (c < NM) red[((NG == 2 ? ih : 0) * NM + c) * (XC + 1) + XC] = base[q];
+    }
   }
   __syncthreads();
   double* Sb = S + ((long long)split * nblk + blk) * B * B;
@@ -1138,6 +1224,78 @@ __global__ void __launch_bounds__(256) k_nm_mask(const uint16_t* __restrict__ W,
   }
 }
 
+// The same from the panel (after a block shuffle): mask and, if part is given, the retained metric of every group.
+// Workgroup (blk, 64 rows): the rows' values through LDS, a thread takes one group and every (256 / G)-th row; its sums meet in
+// ascending order of the row lanes, then the workgroups' in ascending order (k_add_parts).
+template <int DT, int NKEEP, int MG>
+__global__ void __launch_bounds__(256) k_nm_mask_panel(const uint16_t* __restrict__ P, const double* __restrict__ sp, const int* __restrict__ lp,
+                                                        long long N, long long Npad, long long K, int B, uint8_t* __restrict__ mask,
+                                                        double* __restrict__ part /*[row blocks][K / MG] or null*/) {
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  const int G = B / MG, nblk = (int)(K / B), tid = threadIdx.x, blk = (int)(blockIdx.x % (unsigned)nblk);
+  const long long rowblk = blockIdx.x / (unsigned)nblk;
+  const int stride = B + 2;
+  double* s_sum = reinterpret_cast<double*>(smem_raw);                    // [256]
+  uint16_t* s_p = reinterpret_cast<uint16_t*>(smem_raw + 256 * 8);        // [64][B + 2]
+  const long long j0 = rowblk * 64;
+  const int nr = (int)(N - j0 < 64 ? N - j0 : 64);
+  const uint32_t* src = reinterpret_cast<const uint32_t*>(P + ((long long)blk * Npad + j0) * B);
+  for (int e = tid; e < nr * B / 2; e += 256) {
+    const int r = e / (B / 2), c = e - r * (B / 2);
+    *reinterpret_cast<uint32_t*>(s_p + r * stride + 2 * c) = src[e];
+  }
+  const int lanes = 256 / G, g = tid % G, rl = tid / G;
+  int col[MG];
+  double sc[MG];
+#pragma unroll
+  for (int k = 0; k < MG; k++) {
+    col[k] = lp[blk * B + g * MG + k];
+    sc[k] = sp[(long long)blk * B + col[k]];
+  }
+  __syncthreads();
+  double acc = 0.0;
+  if (rl < lanes)
+    for (int r = rl; r < nr; r += lanes) {
+      double xi[MG];
+#pragma unroll
+      for (int k = 0; k < MG; k++) xi[k] = (double)esp_to_float<DT>(s_p[r * stride + col[k]]) * sc[k];
+      uint32_t out[MG / 4];
+#pragma unroll
+      for (int h = 0; h < MG / 4; h++) out[h] = 0;
+      double kept = 0.0;
+#pragma unroll
+      for (int k = 0; k < MG; k++) {
+        int ahead = 0;
+#pragma unroll
+        for (int q = 0; q < MG; q++) ahead += (xi[q] > xi[k] || (xi[q] == xi[k] && q < k)) ? 1 : 0;
+        out[k / 4] |= (ahead < NKEEP ? 1u : 0u) << (8 * (k % 4));
+        kept = kept + (ahead < NKEEP ? xi[k] : 0.0);
+      }
+      acc = acc + kept;
+      uint32_t* dst = reinterpret_cast<uint32_t*>(mask + (j0 + r) * K + (long long)blk * B + g * MG);
+#pragma unroll
+      for (int h = 0; h < MG / 4; h++) dst[h] = out[h];
+    }
+  if (part) {
+    s_sum[tid] = acc;
+    __syncthreads();
+    if (tid < G) {
+      double t = s_sum[tid];
+      for (int q = 1; q < lanes; q++) t = t + s_sum[q * G + tid];
+      part[rowblk * (K / MG) + (long long)blk * G + tid] = t;
+    }
+  }
+}
+
+__global__ void __launch_bounds__(64) k_add_parts(const double* __restrict__ part, int np, long long n, double* __restrict__ out) {
+  const long long e = (long long)blockIdx.x * 64 + threadIdx.x;
+  if (e >= n) return;
+  double t = part[e];
+#pragma unroll 8
+  for (int q = 1; q < np; q++) t = t + part[q * n + e];
+  out[e] = t;
+}
+
 // retained metric of every group under the final order (eq. 5 terms), rows summed in order
 template <int DT, int NKEEP, int MG>
 __global__ void __launch_bounds__(64) k_group_values(const uint16_t* __restrict__ W, const double* __restrict__ s,
@@ -1230,32 +1388,44 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
 
   // ---- local block shuffle
   if (use_lbs) {
-    // columns of a workgroup (LPR lanes of four) and workgroups per block, see k_lbs_eval: rows are split so that two
+    // columns of a workgroup (16 lanes of qc) and workgroups per block, see k_lbs_eval: rows are split so that two
     // workgroups per CU share the two groups that an exchange touches (at least one batch of rows per wave)
-    const int lpr = B <= 32 ? 8 : 16;
-    const int slices = (B + lpr * 4 - 1) / (lpr * 4);
+    const int qc = B <= 32 ? 2 : 4;
+    const int slices = (B + 16 * qc - 1) / (16 * qc);
     const int gsets = m == 4 ? 1 : 2;  // 2:4: both groups in one workgroup
     const int nsplit = (int)std::max<long long>(1, std::min<long long>(512 / (nblk * slices * gsets), (N + LBS_WAVES * LBS_ROWS - 1) / (LBS_WAVES * LBS_ROWS)));
     const long long batch = (long long)nsplit * LBS_WAVES * LBS_ROWS;  // rows that all waves of a block take at a time
-    const long long Npad = (N + batch - 1) / batch * batch;
+    const long long Npad = (N + LBS_ROWS - 1) / LBS_ROWS * LBS_ROWS;
     std::vector<double> sp((size_t)K);
     bool fast = true;
     for (long long p = 0; p < K; p++) {
       sp[p] = score[theta0[p]];
       fast = fast && sp[p] >= 0.0 && std::isfinite(sp[p]);
     }
-    DevBuf d_P, d_sp, d_lp, d_rec, d_state, d_swaps, d_V, d_S, d_count;
+    DevBuf d_P, d_PT, d_sp, d_lp, d_rec, d_state, d_swaps, d_V, d_S, d_count;
     const size_t vbytes = (size_t)nblk * B * B * 8;
-    if (d_P.alloc((size_t)(Npad * K + batch * B) * 2) != hipSuccess || d_sp.alloc(K * 8) != hipSuccess || d_lp.alloc(K * 4) != hipSuccess ||
+    if (d_P.alloc((size_t)(Npad * K + batch * B) * 2) != hipSuccess || d_PT.alloc((size_t)(Npad * K) * 2) != hipSuccess || d_sp.alloc(K * 8) != hipSuccess || d_lp.alloc(K * 4) != hipSuccess ||
         d_rec.alloc(nblk * 2 * LBS_REC * 4) != hipSuccess || d_state.alloc(nblk * 4) != hipSuccess || d_swaps.alloc(nblk * 8) != hipSuccess ||
         d_V.alloc(vbytes) != hipSuccess || d_S.alloc(vbytes * nsplit) != hipSuccess || d_count.alloc(16) != hipSuccess)
       return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation for the block shuffle failed");
     ESP_HIP(ctx, hipMemcpyAsync(d_sp.p, sp.data(), K * 8, hipMemcpyHostToDevice, st));
     hipLaunchKernelGGL(k_lbs_init, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, d_lp.as<int>(), d_state.as<int>(),
                        fast ? LBS_FAST : LBS_EXACT, d_swaps.as<long long>(), d_count.as<int>(), (int)nblk, B);
-    hipLaunchKernelGGL(k_build_panel, dim3((unsigned)((N * K + 255) / 256)), dim3(256), 0, st, W, d_theta0.as<int32_t>(), N, Npad, K, B,
-                       dtype == ESPARSE_F16 ? 0x7c00u : 0x7f80u, d_P.as<uint16_t>(), d_count.as<int>() + 2);
-    ESP_HIP(ctx, hipGetLastError());
+    {
+      // whole rows of W in LDS: two workgroups per CU where a row leaves the room, else what one workgroup can hold
+      const size_t row_bytes = (size_t)K * 2;
+      const int RB = (int)std::min<size_t>(16, (row_bytes <= 64 * 1024 ? 64 * 1024 : 144 * 1024) / row_bytes);
+      const size_t smem_w = RB * row_bytes;
+      if (smem_w > 64 * 1024)
+        ESP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_build_panel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_w));
+      const int rows = RB ? RB : 1;
+      hipLaunchKernelGGL(k_build_panel, dim3((unsigned)((N + rows - 1) / rows)), dim3(512), smem_w, st, W, d_theta0.as<int32_t>(), N, Npad, K, B,
+                         RB, dtype == ESPARSE_F16 ? 0x7c00u : 0x7f80u, d_P.as<uint16_t>(), d_count.as<int>() + 2);
+      ESP_HIP(ctx, hipGetLastError());
+      hipLaunchKernelGGL(k_panel_columns, dim3((unsigned)(nblk * ((Npad + 63) / 64)), (unsigned)((B + 63) / 64)), dim3(256), 0, st,
+                         d_P.as<uint16_t>(), Npad, (int)nblk, B, d_PT.as<uint16_t>());
+      ESP_HIP(ctx, hipGetLastError());
+    }
     // LDS of the exact evaluation: a chunk of a multiple of 16 rows, about 4096 metric values (at most 16 per thread)
     const int rows_chunk = std::max(16, (4096 / B) / 16 * 16);
     const size_t smem = (size_t)rows_chunk * (B + 1) * 8;
@@ -1269,17 +1439,17 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
         // 5 us), a look at the count from the host costs about 25
         for (int r = 0; r < LBS_ROUNDS_QUEUED; r++) {
           if (mode == LBS_FAST) {
-#define LAUNCH_EVAL2(DTv, NK, MGv, NGv, NMv, LPRv)                                                                          \
-  hipLaunchKernelGGL((k_lbs_eval<DTv, NK, MGv, NGv, NMv, LPRv>),                                                            \
+#define LAUNCH_EVAL2(DTv, NK, MGv, NGv, NMv, QCv)                                                                          \
+  hipLaunchKernelGGL((k_lbs_eval<DTv, NK, MGv, NGv, NMv, QCv>),                                                            \
                      dim3((unsigned)nblk, (unsigned)nsplit, (unsigned)(slices * (NMv == MGv ? (B / MGv + NGv - 1) / NGv : gsets))), \
-                     dim3(64 * LBS_WAVES), 0, st, d_P.as<uint16_t>(), d_sp.as<double>(), d_rec.as<int>(), N, Npad, B, slices, d_S.as<double>())
+                     dim3(64 * LBS_WAVES), 0, st, d_P.as<uint16_t>(), d_PT.as<uint16_t>(), d_sp.as<double>(), d_rec.as<int>(), N, Npad, B, slices, d_S.as<double>())
 #define LAUNCH_EVAL(DTv, NK, MGv, ...)                                                      \
   do {                                                                                      \
     constexpr int NGv = MGv == 4 ? 2 : 1;                                                   \
-    if (first && lpr == 16) LAUNCH_EVAL2(DTv, NK, MGv, NGv, MGv, 16);                       \
-    else if (first) LAUNCH_EVAL2(DTv, NK, MGv, NGv, MGv, 8);                                \
-    else if (lpr == 16) LAUNCH_EVAL2(DTv, NK, MGv, NGv, (MGv - 1), 16);                     \
-    else LAUNCH_EVAL2(DTv, NK, MGv, NGv, (MGv - 1), 8);                                     \
+    if (first && qc == 4) LAUNCH_EVAL2(DTv, NK, MGv, NGv, MGv, 4);                          \
+    else if (first) LAUNCH_EVAL2(DTv, NK, MGv, NGv, MGv, 2);                                \
+    else if (qc == 4) LAUNCH_EVAL2(DTv, NK, MGv, NGv, (MGv - 1), 4);                        \
+    else LAUNCH_EVAL2(DTv, NK, MGv, NGv, (MGv - 1), 2);                                     \
   } while (0)
             DISPATCH_DT_NM(dtype, n, LAUNCH_EVAL, 0);
 #undef LAUNCH_EVAL
@@ -1336,10 +1506,38 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
     if (swaps_out) {
       ESP_HIP(ctx, hipMemcpyAsync(swaps_out, d_swaps.p, nblk * 8, hipMemcpyDeviceToHost, st));
     }
-    ESP_HIP(ctx, hipStreamSynchronize(st));
-  } else {
-    ESP_HIP(ctx, hipMemcpyAsync(perm_out, d_theta0.p, K * 4, hipMemcpyDeviceToDevice, st));
+    // mask and retained metric under the final order, from the panel
+    {
+      const int row_blocks = (int)((N + 63) / 64);
+      const long long ng = K / m;
+      DevBuf d_part, d_gv;
+      if (retained_out && (d_part.alloc((size_t)row_blocks * ng * 8) != hipSuccess || d_gv.alloc(ng * 8) != hipSuccess))
+        return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation failed");
+      const size_t smem_m = 256 * 8 + (size_t)64 * (B + 2) * 2;
+      dim3 grid((unsigned)(nblk * row_blocks));
+#define LAUNCH_MASK(DT, NK, MGv, ...)                                                                                        \
+  hipLaunchKernelGGL((k_nm_mask_panel<DT, NK, MGv>), grid, dim3(256), smem_m, st, d_P.as<uint16_t>(), d_sp.as<double>(), d_lp.as<int>(), N, \
+                     Npad, K, B, mask_out, retained_out ? d_part.as<double>() : nullptr)
+      DISPATCH_DT_NM(dtype, n, LAUNCH_MASK, 0);
+#undef LAUNCH_MASK
+      ESP_HIP(ctx, hipGetLastError());
+      std::vector<double> gv;
+      if (retained_out) {
+        hipLaunchKernelGGL(k_add_parts, dim3((unsigned)((ng + 63) / 64)), dim3(64), 0, st, d_part.as<double>(), row_blocks, ng, d_gv.as<double>());
+        ESP_HIP(ctx, hipGetLastError());
+        gv.resize((size_t)ng);
+        ESP_HIP(ctx, hipMemcpyAsync(gv.data(), d_gv.p, ng * 8, hipMemcpyDeviceToHost, st));
+      }
+      ESP_HIP(ctx, hipStreamSynchronize(st));
+      if (retained_out) {
+        double tot = 0.0;
+        for (long long g = 0; g < ng; g++) tot = tot + gv[g];
+        *retained_out = tot;
+      }
+    }
+    return ESPARSE_OK;
   }
+  ESP_HIP(ctx, hipMemcpyAsync(perm_out, d_theta0.p, K * 4, hipMemcpyDeviceToDevice, st));
 
   // ---- n:m mask under the final order
   {
