@@ -20,45 +20,62 @@ int esp_fail(esparse_ctx* ctx, int code, const char* fmt, ...) {
   return code;
 }
 
-// value = sum_b bins[b] * 2^(unit0 + 16 b), exact, then one round-to-nearest-even to double.
-double esp_exact_bins_to_double(const unsigned long long* bins, int nb, int unit0) {
-  // little-endian limbs of 32 bits, limb i has weight 2^(unit0 + 32 i)
-  const int NL = 2 * 40;
-  unsigned long long limb[NL];
-  for (int i = 0; i < NL; i++) limb[i] = 0;
-  for (int b = 0; b < nb; b++) {
-    unsigned long long v = bins[b];
-    if (!v) continue;
-    int pos = 16 * b;  // bit offset relative to unit0
-    int li = pos / 32, sh = pos % 32;
-    // v << sh spans up to 96 bits: add three 32-bit pieces
-    unsigned long long lo = (v & 0xffffffffull) << sh;  // < 2^64
-    unsigned long long hi = (v >> 32) << sh;            // weight 2^32 more
-    limb[li] += lo & 0xffffffffull;
-    limb[li + 1] += (lo >> 32) + (hi & 0xffffffffull);
-    limb[li + 2] += hi >> 32;
-  }
-  for (int i = 0; i + 1 < NL; i++) {  // carry propagation (each limb holds < 2^40 before this)
-    limb[i + 1] += limb[i] >> 32;
-    limb[i] &= 0xffffffffull;
-  }
-  int top = -1;
-  for (int i = NL - 1; i >= 0 && top < 0; i--)
-    if (limb[i]) {
-      int bit = 31;
-      while (!((limb[i] >> bit) & 1ull)) bit--;
-      top = 32 * i + bit;
+void* Scratch::take(size_t bytes) {
+  bytes = (std::max<size_t>(bytes, 1) + 65535) / 65536 * 65536;
+  auto& kept = ctx_->kept;
+  size_t best = kept.size();
+  for (size_t i = 0; i < kept.size(); i++)  // the smallest that fits and is not wasted on this
+    if (kept[i].bytes >= bytes && kept[i].bytes <= 4 * bytes && (best == kept.size() || kept[i].bytes < kept[best].bytes)) best = i;
+  esparse_ctx::Block b{nullptr, bytes};
+  if (best < kept.size()) {
+    b = kept[best];
+    ctx_->kept_bytes -= b.bytes;
+    kept.erase(kept.begin() + best);
+  } else if (hipMalloc(&b.p, bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    for (auto& k : kept) (void)hipFree(k.p);  // idle blocks of earlier calls
+    kept.clear();
+    ctx_->kept_bytes = 0;
+    if (hipMalloc(&b.p, bytes) != hipSuccess) {
+      (void)hipGetLastError();
+      return nullptr;
     }
-  if (top < 0) return 0.0;
-  auto bit_at = [&](int p) -> int { return p < 0 ? 0 : (int)((limb[p / 32] >> (p % 32)) & 1ull); };
-  // 53 significant bits: positions top .. top-52
-  unsigned long long mant = 0;
-  for (int p = top; p > top - 53; p--) mant = (mant << 1) | (unsigned long long)bit_at(p);
-  int guard = bit_at(top - 53);
-  int sticky = 0;
-  for (int p = top - 54; p >= 0 && !sticky; p--) sticky |= bit_at(p);
-  if (guard && (sticky || (mant & 1ull))) mant++;  // may become 2^53: ldexp handles it
-  return std::ldexp((double)mant, unit0 + top - 52);
+  }
+  mine_.push_back(b);
+  return b.p;
+}
+
+Scratch::~Scratch() {
+  if (!idle_) (void)hipStreamSynchronize(ctx_->stream);
+  auto& kept = ctx_->kept;
+  for (auto& b : mine_) {
+    if (b.bytes > ESP_SCRATCH_KEEP) {
+      (void)hipFree(b.p);
+      continue;
+    }
+    while (ctx_->kept_bytes + b.bytes > ESP_SCRATCH_KEEP) {
+      ctx_->kept_bytes -= kept.front().bytes;
+      (void)hipFree(kept.front().p);
+      kept.erase(kept.begin());
+    }
+    kept.push_back(b);
+    ctx_->kept_bytes += b.bytes;
+  }
+}
+
+void* esp_host_stage(esparse_ctx* ctx, size_t bytes) {
+  if (bytes <= ctx->h_stage_bytes) return ctx->h_stage;
+  if (ctx->h_stage) (void)hipHostFree(ctx->h_stage);
+  ctx->h_stage = nullptr;
+  ctx->h_stage_bytes = 0;
+  bytes = (bytes + (1u << 20) - 1) >> 20 << 20;
+  if (hipHostMalloc(&ctx->h_stage, bytes, hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    ctx->h_stage = nullptr;
+    return nullptr;
+  }
+  ctx->h_stage_bytes = bytes;
+  return ctx->h_stage;
 }
 
 extern "C" {
@@ -78,6 +95,8 @@ int esparse_create(esparse_ctx** out, int device, void* hip_stream) {
 void esparse_destroy(esparse_ctx* ctx) {
   if (!ctx) return;
   if (ctx->d_flags) (void)hipFree(ctx->d_flags);
+  for (auto& k : ctx->kept) (void)hipFree(k.p);
+  if (ctx->h_stage) (void)hipHostFree(ctx->h_stage);
   delete ctx;
 }
 

@@ -17,6 +17,16 @@ struct esparse_ctx {
   // (sparse, dtype, M, N, K) -> variant chosen by esparse_tune
   std::map<std::tuple<int, int, int, long long, long long, long long>, int> tuned;  // (products per launch, mode, dtype, M, N, K) -> variant
   int* d_flags = nullptr;     // 64 ints of device scratch for error flags
+  // device blocks that the offline stages have used and will use again (class Scratch), oldest first, and a pinned host
+  // block for what they send and receive; given back by esparse_destroy
+  struct Block {
+    void* p;
+    size_t bytes;
+  };
+  std::vector<Block> kept;
+  size_t kept_bytes = 0;
+  void* h_stage = nullptr;
+  size_t h_stage_bytes = 0;
 };
 
 int esp_fail(esparse_ctx* ctx, int code, const char* fmt, ...);
@@ -37,7 +47,34 @@ int esp_fail(esparse_ctx* ctx, int code, const char* fmt, ...);
 static inline bool esp_aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 static inline long long esp_round_up(long long v, long long q) { return (v + q - 1) / q * q; }
 
-// device scratch that frees itself (offline stages only)
+// Device scratch of one call of an offline stage.  hipMalloc and hipFree of the dozen blocks of a call cost more than its
+// smaller kernels, so blocks go back to the context at the end of the call, up to ESP_SCRATCH_KEEP bytes in all (the
+// oldest ones make room).  The stream is idle when that happens: the destructor waits unless the call has (idle()).
+#define ESP_SCRATCH_KEEP ((size_t)256 << 20)
+class Scratch {
+ public:
+  explicit Scratch(esparse_ctx* ctx) : ctx_(ctx) {}
+  Scratch(const Scratch&) = delete;
+  Scratch& operator=(const Scratch&) = delete;
+  ~Scratch();
+  // 256-byte aligned; nullptr if there is no memory
+  template <class T>
+  T* get(size_t count) {
+    return reinterpret_cast<T*>(take(count * sizeof(T)));
+  }
+  // the context's stream has been waited for and nothing was launched since
+  void idle() { idle_ = true; }
+
+ private:
+  void* take(size_t bytes);
+  esparse_ctx* ctx_;
+  std::vector<esparse_ctx::Block> mine_;
+  bool idle_ = false;
+};
+// pinned host memory of the context (one block: the next call of this function may move it); nullptr if there is none
+void* esp_host_stage(esparse_ctx* ctx, size_t bytes);
+
+// device scratch that frees itself (measurement aids and the tuner)
 struct DevBuf {
   void* p = nullptr;
   ~DevBuf() {
@@ -126,6 +163,3 @@ int esp_matmul_group_device(esparse_ctx* ctx, int sparse, int count, const void*
                             int dtype, void* const* Y, void* workspace, int variant, int phases);
 bool esp_variant_is_decode_kernel(int v);
 
-// exact accumulation helpers (host)
-// value = sum_b bins[b] * 2^(unit0 + 16*b), rounded once to nearest-even double
-double esp_exact_bins_to_double(const unsigned long long* bins, int nb, int unit0);

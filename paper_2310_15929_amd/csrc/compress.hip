@@ -272,11 +272,12 @@ int esp_compress_device(esparse_ctx* ctx, const void* Wv, const uint8_t* mask, c
   hipStream_t st = ctx->stream;
   int* flags = ctx->d_flags;
   ESP_HIP(ctx, hipMemsetAsync(flags, 0, sizeof(int), st));
-  DevBuf count;
+  Scratch scratch(ctx);
   if (perm) {
-    if (count.alloc(K * 4) != hipSuccess) return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation failed");
-    ESP_HIP(ctx, hipMemsetAsync(count.p, 0, K * 4, st));
-    hipLaunchKernelGGL(k_perm_count, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, perm, K, count.as<int>(), flags);
+    int* count = scratch.get<int>(K);
+    if (!count) return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation failed");
+    ESP_HIP(ctx, hipMemsetAsync(count, 0, K * 4, st));
+    hipLaunchKernelGGL(k_perm_count, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, perm, K, count, flags);
     ESP_HIP(ctx, hipGetLastError());
     int h = 0;
     ESP_HIP(ctx, hipMemcpyAsync(&h, flags, sizeof(int), hipMemcpyDeviceToHost, st));
@@ -317,6 +318,7 @@ int esp_compress_device(esparse_ctx* ctx, const void* Wv, const uint8_t* mask, c
   int h = 0;
   ESP_HIP(ctx, hipMemcpyAsync(&h, flags, sizeof(int), hipMemcpyDeviceToHost, st));
   ESP_HIP(ctx, hipStreamSynchronize(st));
+  scratch.idle();
   if (h & 1) return esp_fail(ctx, ESPARSE_EBADMASK, "a group of %d does not keep exactly %d weights", m, n);
   return ESPARSE_OK;
 }

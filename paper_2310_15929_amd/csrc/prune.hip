@@ -6,17 +6,16 @@
 //   - histogram counts, minima and maxima are integer / ordered-integer atomics;
 //   - sums of squares and column sums of |w| are accumulated EXACTLY: every term is split by its
 //     binary exponent into one of a few 64-bit integer accumulators (16 exponents per accumulator),
-//     and the host adds the accumulators exactly and rounds once;
+//     which are added exactly and rounded once;
 //   - the retained metric of a candidate group is summed over the output rows in a FIXED order (interleaved
 //     sub-sums, see k_lbs_eval) in float64 without contraction, so repeated runs make the
 //     same exchanges; eq. (5) fixes no order for that sum, and the exchanges Algorithm 1 makes do not
 //     hinge on it where candidates are not tied to the last bit (the tests compare them with a plain
 //     ascending-row sum);
-//   - logs, square roots and the sort of K channel means run on the host (K values each).
+//   - logarithms and square roots run on the host; the rank of a channel mean is a count of comparisons.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <numeric>
 #include <thread>
 
 #include "common.h"
@@ -28,17 +27,43 @@
 #define SQ_NB 33
 #define SQ_EOFF 272
 #define SQ_SIG 21
-// |w|: exponent in [-133, 127], at most 11 significant bits
+// |w| = m 2^e with an integer m of at most 11 bits and e in [-133, 120]: bin b counts units of 2^(16 b - AB_OFF)
 #define AB_NB 17
-#define AB_EOFF 144
-#define AB_SIG 10
+#define AB_OFF 144
 
-__device__ __forceinline__ void exact_bin(double v, int eoff, int sig, int* bin, unsigned long long* q) {
-  // v > 0 finite.  bin = floor((e + eoff) / 16); q = v / 2^(16 bin - eoff - sig), an exact integer.
-  int e = ilogb(v);
-  int b = (e + eoff) >> 4;
-  *bin = b;
-  *q = (unsigned long long)ldexp(v, -(16 * b - eoff - sig));
+// value = sum_b bins[b] 2^(16 b - off), bins[b] < 2^63: exact, then one round-to-nearest-even to double
+template <int NB>
+__device__ double exact_bins_to_double(const unsigned long long* __restrict__ bins, int off) {
+  constexpr int ND = NB + 3;  // digits of 16 bits
+  uint16_t d[ND];
+  unsigned long long carry = 0;  // < 2^48
+#pragma unroll
+  for (int i = 0; i < ND; i++) {
+    if (i < NB) carry += bins[i];
+    d[i] = (uint16_t)carry;
+    carry >>= 16;
+  }
+  // the highest digit that is not zero and the four below it, and whether anything is left below those
+  int top = -1;
+  unsigned long long w = 0;
+  uint32_t w4 = 0, below = 0;
+#pragma unroll
+  for (int i = ND - 1; i >= 0; i--) {
+    if (top < 0 && d[i]) top = i;
+    const int k = top - i;
+    if (top >= 0 && k < 4) w |= (unsigned long long)d[i] << (48 - 16 * k);
+    else if (top >= 0 && k == 4) w4 = d[i];
+    else if (top >= 0) below |= d[i];
+  }
+  if (top < 0) return 0.0;
+  const int lz = __clzll((long long)w);  // 0 .. 15
+  if (lz) w = (w << lz) | (w4 >> (16 - lz));
+  below |= (w4 << lz) & 0xffffu;
+  // w: the 64 highest bits, the highest at position 16 top + 15 - lz
+  unsigned long long mant = w >> 11;
+  const uint32_t rest = (uint32_t)w & 0x7ffu;
+  if (rest > 0x400u || (rest == 0x400u && (below || (mant & 1ull)))) mant++;
+  return ldexp((double)mant, 16 * top + 15 - lz - 52 - off);
 }
 
 __device__ __forceinline__ unsigned int ordered_bits(float f) {
@@ -130,7 +155,7 @@ __device__ __forceinline__ void minmax_sumsq_trip(const uint16_t* __restrict__ p
 
 template <int DT, int CPL>
 __global__ void __launch_bounds__(1024) k_minmax_sumsq(const uint16_t* __restrict__ X, long long T, long long K,
-                                                        long long rows_per_block, unsigned int* __restrict__ omin,
+                                                        long long rows_per_block, unsigned int* __restrict__ onmin /*~minimum*/,
                                                         unsigned int* __restrict__ omax,
                                                         unsigned long long* __restrict__ sq /*[K][SQ_NB]*/, int want_sq) {
   constexpr int CH = 32 * CPL;  // channels per block
@@ -173,7 +198,7 @@ __global__ void __launch_bounds__(1024) k_minmax_sumsq(const uint16_t* __restric
   if (tid < CH && r0 < r1) {
     const long long ch = cbase + (long long)(tid & 31) * CPL + (tid >> 5);  // LDS row tid = j * 32 + cl
     if (ch < K) {
-      atomicMin(&omin[ch], s_lo[tid]);
+      atomicMax(&onmin[ch], ~s_lo[tid]);  // so that both start from zero
       atomicMax(&omax[ch], s_hi[tid]);
     }
   }
@@ -250,7 +275,7 @@ __device__ __forceinline__ void hist_trip(const uint16_t* __restrict__ p, long l
 
 template <int DT, int CPL>
 __global__ void __launch_bounds__(1024) k_hist(const uint16_t* __restrict__ X, long long T, long long K,
-                                                long long rows_per_block, int bins, const unsigned int* __restrict__ omin,
+                                                long long rows_per_block, int bins, const unsigned int* __restrict__ onmin,
                                                 const unsigned int* __restrict__ omax, unsigned int* __restrict__ hist /*[K][bins]*/) {
   constexpr int CH = 32 * CPL;
   extern __shared__ unsigned int s_hist[];  // [CH rows][stride]: the row of a channel is j * 32 + cl, the stride odd, so
@@ -267,7 +292,7 @@ __global__ void __launch_bounds__(1024) k_hist(const uint16_t* __restrict__ X, l
     const double nb = (double)bins;
 #pragma unroll
     for (int j = 0; j < CPL; j++) {
-      lo32[j] = float_from_ordered_bits(omin[c + j]);
+      lo32[j] = float_from_ordered_bits(~onmin[c + j]);
       lo[j] = (double)lo32[j];
       wd[j] = (double)float_from_ordered_bits(omax[c + j]) - lo[j];
       // the estimate's factor; a constant channel (width 0) gets NaN, which sends every value to the definition
@@ -293,39 +318,109 @@ __global__ void __launch_bounds__(1024) k_hist(const uint16_t* __restrict__ X, l
 }
 
 // ------------------------------------------------------------------------------------------------
-// exact column sums of |W|: grid (ceil(K/64), row chunks), block 256 = 8 row lanes x 32 channel pairs
+// exact column sums of |W|: grid (ceil(K / 128), row chunks), block 256 = 8 row lanes x 32 lanes of four channels (8-byte
+// loads, eight rows in flight).  fp16: a lane adds its rows as integers of 2^-24 (less than 2^40 each); bf16: by exponent
+// into LDS.  4096 x 4096: 25 -> 12 us, fp16 (one float64 ilogb and ldexp per element and 4-byte loads before).
 // ------------------------------------------------------------------------------------------------
 template <int DT>
 __global__ void __launch_bounds__(256) k_abs_colsum(const uint16_t* __restrict__ W, long long N, long long K,
                                                      long long rows_per_block, unsigned long long* __restrict__ out /*[K][AB_NB]*/) {
-  __shared__ unsigned long long s_acc[64 * AB_NB];
+  __shared__ unsigned long long s_acc[128 * AB_NB];  // channel j of lane cl: row j * 32 + cl
   const int tid = threadIdx.x;
-  for (int i = tid; i < 64 * AB_NB; i += 256) s_acc[i] = 0ull;
+  for (int i = tid; i < 128 * AB_NB; i += 256) s_acc[i] = 0ull;
   __syncthreads();
-  const int cp = tid & 31, rl = tid >> 5;
-  const long long c = (long long)blockIdx.x * 64 + cp * 2;
+  const int cl = tid & 31, rl = tid >> 5;
+  const long long c = (long long)blockIdx.x * 128 + cl * 4;
   if (c < K) {
-    long long r0 = (long long)blockIdx.y * rows_per_block;
-    long long r1 = r0 + rows_per_block < N ? r0 + rows_per_block : N;
-    for (long long r = r0 + rl; r < r1; r += 8) {
-      uint32_t two = *reinterpret_cast<const uint32_t*>(W + r * K + c);
-      double x[2] = {fabs((double)esp_to_float<DT>((uint16_t)(two & 0xffffu))), fabs((double)esp_to_float<DT>((uint16_t)(two >> 16)))};
+    const long long r0 = (long long)blockIdx.y * rows_per_block;
+    const long long r1 = r0 + rows_per_block < N ? r0 + rows_per_block : N;
+    unsigned long long sum[4] = {0ull, 0ull, 0ull, 0ull};
+    auto add = [&](uint2 v) {
 #pragma unroll
-      for (int h = 0; h < 2; h++)
-        if (x[h] > 0.0) {
-          int bi;
-          unsigned long long q;
-          exact_bin(x[h], AB_EOFF, AB_SIG, &bi, &q);
-          atomicAdd(&s_acc[(cp * 2 + h) * AB_NB + bi], q);
+      for (int j = 0; j < 4; j++) {
+        const uint32_t raw = ((j < 2 ? v.x : v.y) >> (16 * (j & 1))) & 0x7fffu;
+        if (DT == ESPARSE_F16) {
+          const uint32_t e = raw >> 10;
+          const uint32_t m = e ? (raw & 0x3ffu) | 0x400u : raw;
+          sum[j] += (unsigned long long)m << (e ? e - 1 : 0);
+        } else {
+          const uint32_t e = raw >> 7;
+          const uint32_t m = e ? (raw & 0x7fu) | 0x80u : raw;
+          const uint32_t pos = (e ? e : 1u) + (AB_OFF - 134);
+          if (m) atomicAdd(&s_acc[(j * 32 + cl) * AB_NB + (pos >> 4)], (unsigned long long)m << (pos & 15u));
         }
+      }
+    };
+    const uint16_t* p = W + (r0 + rl) * K + c;
+    long long r = r0 + rl;
+    for (; r + 56 < r1; r += 64, p += 64 * K) {
+      uint2 v[8];
+#pragma unroll
+      for (int u = 0; u < 8; u++) v[u] = *reinterpret_cast<const uint2*>(p + u * 8 * K);
+#pragma unroll
+      for (int u = 0; u < 8; u++) add(v[u]);
+    }
+    for (; r < r1; r += 8, p += 8 * K) add(*reinterpret_cast<const uint2*>(p));
+    if (DT == ESPARSE_F16) {
+#pragma unroll
+      for (int j = 0; j < 4; j++) {  // units of 2^-24 = bit 120: bin 7, 8 bits up; the upper half 32 bits higher
+        unsigned long long* acc = &s_acc[(j * 32 + cl) * AB_NB];
+        atomicAdd(acc + (AB_OFF - 24) / 16, (sum[j] & 0xffffffffull) << ((AB_OFF - 24) % 16));
+        if (sum[j] >> 32) atomicAdd(acc + (AB_OFF - 24) / 16 + 2, (sum[j] >> 32) << ((AB_OFF - 24) % 16));
+      }
     }
   }
   __syncthreads();
-  const long long cbase = (long long)blockIdx.x * 64;
-  for (int i = tid; i < 64 * AB_NB; i += 256) {
-    long long ch = cbase + i / AB_NB;
-    unsigned long long v = s_acc[i];
+  const long long cbase = (long long)blockIdx.x * 128;
+  for (int i = tid; i < 128 * AB_NB; i += 256) {
+    const int row = i / AB_NB;
+    const long long ch = cbase + (row & 31) * 4 + (row >> 5);
+    const unsigned long long v = s_acc[i];
     if (ch < K && v) atomicAdd(&out[ch * AB_NB + (i % AB_NB)], v);
+  }
+}
+
+// eq. 2: AM_c^2 per channel, rounded once
+__global__ void __launch_bounds__(64) k_sumsq_finish(const unsigned long long* __restrict__ sq, long long K, double* __restrict__ out) {
+  const long long c = (long long)blockIdx.x * 64 + threadIdx.x;
+  if (c < K) out[c] = exact_bins_to_double<SQ_NB>(sq + c * SQ_NB, SQ_EOFF + SQ_SIG);
+}
+
+// channel means of the metric: g_c = (s_c * sum_j |w_jc|) / N
+__global__ void __launch_bounds__(64) k_channel_means(const unsigned long long* __restrict__ bins, const double* __restrict__ score, long long N,
+                                                       long long K, double* __restrict__ g) {
+  const long long c = (long long)blockIdx.x * 64 + threadIdx.x;
+  if (c < K) g[c] = (score[c] * exact_bins_to_double<AB_NB>(bins + c * AB_NB, AB_OFF)) / (double)N;
+}
+
+// Global naive shuffle: the rank of a channel is the number of channels with a larger mean, or the same and a lower number
+// (NaN behind all numbers); rank r goes to position (r mod G) m + r / G.  16 channels per workgroup, the comparisons with
+// all others split over 64 lanes each; K^2 comparisons instead of a sort on the host (4096 channels: 22 us against about 400).
+__global__ void __launch_bounds__(1024) k_naive_shuffle(const double* __restrict__ g, const double* __restrict__ score, int K, int m, int use_gns,
+                                                         int32_t* __restrict__ theta0, double* __restrict__ sp) {
+  __shared__ int s_rank[16];
+  const int tid = threadIdx.x, l = tid & 15, part = tid >> 4;
+  if (tid < 16) s_rank[tid] = 0;
+  __syncthreads();
+  const int c = blockIdx.x * 16 + l;
+  if (use_gns) {
+    const double mine = c < K ? g[c] : 0.0;
+    const bool mine_nan = mine != mine;
+    int ahead = 0;
+#pragma unroll 8
+    for (int q = part; q < K; q += 64) {
+      const double other = g[q];
+      const bool other_nan = other != other;
+      ahead += (other_nan ? (mine_nan && q < c) : (mine_nan || other > mine || (other == mine && q < c))) ? 1 : 0;
+    }
+    atomicAdd(&s_rank[l], ahead);
+  }
+  __syncthreads();
+  if (part == 0 && c < K) {
+    const int G = K / m, r = s_rank[l];
+    const int p = use_gns ? (r % G) * m + r / G : c;
+    theta0[p] = c;
+    sp[p] = score[c];
   }
 }
 
@@ -336,14 +431,24 @@ int esp_stats_device(esparse_ctx* ctx, const void* calib, long long T, long long
                      std::vector<double>* ir, std::vector<double>* am) {
   if (!ir && !am) return ESPARSE_OK;
   hipStream_t st = ctx->stream;
-  DevBuf dmin, dmax, dhist, dsq;
-  if (dmin.alloc(K * 4) != hipSuccess || dmax.alloc(K * 4) != hipSuccess ||
-      dhist.alloc((size_t)K * bins * 4) != hipSuccess || dsq.alloc((size_t)K * SQ_NB * 8) != hipSuccess)
-    return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation for channel statistics failed");
-  ESP_HIP(ctx, hipMemsetAsync(dmin.p, 0xff, K * 4, st));
-  ESP_HIP(ctx, hipMemsetAsync(dmax.p, 0x00, K * 4, st));
-  ESP_HIP(ctx, hipMemsetAsync(dhist.p, 0, (size_t)K * bins * 4, st));
-  ESP_HIP(ctx, hipMemsetAsync(dsq.p, 0, (size_t)K * SQ_NB * 8, st));
+  Scratch scratch(ctx);
+  // zeroed: squares, extrema (the minimum inverted); then what goes to the host: sums of squares, histogram (zeroed)
+  const size_t sq_bytes = (size_t)K * SQ_NB * 8, hist_bytes = (size_t)K * bins * 4;
+  unsigned char* d_all = scratch.get<unsigned char>(sq_bytes + (size_t)K * 8 + (size_t)K * 8 + hist_bytes);
+  if (!d_all) return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation for channel statistics failed");
+  unsigned long long* d_sq = reinterpret_cast<unsigned long long*>(d_all);
+  unsigned int* d_nmin = reinterpret_cast<unsigned int*>(d_all + sq_bytes);
+  unsigned int* d_max = d_nmin + K;
+  double* d_am = reinterpret_cast<double*>(d_all + sq_bytes + (size_t)K * 8);
+  unsigned int* d_hist = reinterpret_cast<unsigned int*>(d_am + K);
+  const size_t out_bytes = (size_t)K * 8 + (ir ? hist_bytes : 0);
+  std::vector<unsigned char> pageable;
+  unsigned char* h_out = reinterpret_cast<unsigned char*>(out_bytes <= ((size_t)32 << 20) ? esp_host_stage(ctx, out_bytes) : nullptr);
+  if (!h_out) {
+    pageable.resize(out_bytes);
+    h_out = pageable.data();
+  }
+  ESP_HIP(ctx, hipMemsetAsync(d_all, 0, sq_bytes + (size_t)K * 16 + hist_bytes, st));
   const uint16_t* X = reinterpret_cast<const uint16_t*>(calib);
   const int cpl = K % 4 == 0 ? 4 : 2;  // channels per lane: 8-byte loads where the rows allow them
   const long long gx = (K + 32 * cpl - 1) / (32 * cpl);
@@ -353,11 +458,9 @@ int esp_stats_device(esparse_ctx* ctx, const void* calib, long long T, long long
   rpb = (rpb + 255) / 256 * 256;
   dim3 grid((unsigned)gx, (unsigned)((T + rpb - 1) / rpb));
 #define ESP_SCAN_A(DTv, CPLv)                                                                                        \
-  hipLaunchKernelGGL((k_minmax_sumsq<DTv, CPLv>), grid, dim3(1024), 0, st, X, T, K, rpb, dmin.as<unsigned int>(),     \
-                     dmax.as<unsigned int>(), dsq.as<unsigned long long>(), am ? 1 : 0)
+  hipLaunchKernelGGL((k_minmax_sumsq<DTv, CPLv>), grid, dim3(1024), 0, st, X, T, K, rpb, d_nmin, d_max, d_sq, am ? 1 : 0)
 #define ESP_SCAN_B(DTv, CPLv)                                                                                        \
-  hipLaunchKernelGGL((k_hist<DTv, CPLv>), grid, dim3(1024), (size_t)32 * CPLv * (bins | 1) * 4, st, X, T, K, rpb, bins,     \
-                     dmin.as<unsigned int>(), dmax.as<unsigned int>(), dhist.as<unsigned int>())
+  hipLaunchKernelGGL((k_hist<DTv, CPLv>), grid, dim3(1024), (size_t)32 * CPLv * (bins | 1) * 4, st, X, T, K, rpb, bins, d_nmin, d_max, d_hist)
   if (dtype == ESPARSE_F16) {
     if (cpl == 4) ESP_SCAN_A(ESPARSE_F16, 4);
     else ESP_SCAN_A(ESPARSE_F16, 2);
@@ -386,46 +489,49 @@ int esp_stats_device(esparse_ctx* ctx, const void* calib, long long T, long long
   }
 #undef ESP_SCAN_A
 #undef ESP_SCAN_B
-  std::vector<unsigned int> hist;
-  std::vector<unsigned long long> sq;
-  if (ir) {
-    hist.resize((size_t)K * bins);
-    ESP_HIP(ctx, hipMemcpyAsync(hist.data(), dhist.p, hist.size() * 4, hipMemcpyDeviceToHost, st));
-  }
   if (am) {
-    sq.resize((size_t)K * SQ_NB);
-    ESP_HIP(ctx, hipMemcpyAsync(sq.data(), dsq.p, sq.size() * 8, hipMemcpyDeviceToHost, st));
+    hipLaunchKernelGGL(k_sumsq_finish, dim3((unsigned)((K + 63) / 64)), dim3(64), 0, st, d_sq, K, d_am);
+    ESP_HIP(ctx, hipGetLastError());
   }
+  ESP_HIP(ctx, hipMemcpyAsync(h_out, d_am, out_bytes, hipMemcpyDeviceToHost, st));
   ESP_HIP(ctx, hipStreamSynchronize(st));
+  scratch.idle();
+  if (am) {
+    // eq. 2: AM_c = sqrt(exact sum of squares rounded once)
+    const double* sums = reinterpret_cast<const double*>(h_out);
+    am->assign((size_t)K, 0.0);
+    for (long long c = 0; c < K; c++) (*am)[c] = std::sqrt(sums[c]);
+  }
   if (ir) {
-    // eq. 1: IR_c = - sum_k p_k ln p_k, ascending k, empty bins skipped
+    // eq. 1: IR_c = - sum_k p_k ln p_k, ascending k, empty bins skipped.  K * bins logarithms on the host (the host's log is
+    // the one the result is defined by); the counts of a channel set repeat, so each thread keeps the terms it has met (a
+    // logarithm of a count below 16384 is taken about once in ten times at T = 262144).
+    const unsigned int* hist = reinterpret_cast<const unsigned int*>(h_out + (size_t)K * 8);
     ir->assign((size_t)K, 0.0);
     auto entropy_of = [&](long long c0, long long c1) {
+      std::vector<double> term(std::min<long long>(T + 1, 16384), 0.0);  // 0: not met yet (p ln p = 0 for p = 1 only)
+      const unsigned int known = (unsigned int)term.size();
       for (long long c = c0; c < c1; c++) {
         double acc = 0.0;
         for (int k = 0; k < bins; k++) {
-          unsigned int nk = hist[(size_t)c * bins + k];
-          if (nk) {
-            double p = (double)nk / (double)T;
-            double t = p * std::log(p);
-            acc = acc + t;
+          const unsigned int nk = hist[(size_t)c * bins + k];
+          if (!nk) continue;
+          double t = nk < known ? term[nk] : 0.0;
+          if (t == 0.0) {
+            const double p = (double)nk / (double)T;
+            t = p * std::log(p);
+            if (nk < known) term[nk] = t;
           }
+          acc = acc + t;
         }
         (*ir)[c] = -acc;
       }
     };
-    // K * bins logarithms on the host (the host's log is the one the result is defined by): channels are independent
     const int nthr = (int)std::max<long long>(1, std::min<long long>(8, K * bins / 65536));
     std::vector<std::thread> pool;
     for (int i = 1; i < nthr; i++) pool.emplace_back(entropy_of, K * i / nthr, K * (i + 1) / nthr);
     entropy_of(0, K / nthr);
     for (auto& th : pool) th.join();
-  }
-  if (am) {
-    // eq. 2: AM_c = sqrt(exact sum of squares rounded once)
-    am->assign((size_t)K, 0.0);
-    for (long long c = 0; c < K; c++)
-      (*am)[c] = std::sqrt(esp_exact_bins_to_double(&sq[(size_t)c * SQ_NB], SQ_NB, -SQ_EOFF - SQ_SIG));
   }
   return ESPARSE_OK;
 }
@@ -1347,44 +1453,36 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
   const long long nblk = use_lbs ? K / B : 0;
   if (swaps_out && !use_lbs && o->block > 0 && K % o->block == 0) memset(swaps_out, 0, sizeof(int64_t) * (K / o->block));
 
-  DevBuf d_s;
-  if (d_s.alloc(K * 8) != hipSuccess) return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation failed");
-  ESP_HIP(ctx, hipMemcpyAsync(d_s.p, score, K * 8, hipMemcpyHostToDevice, st));
+  Scratch scratch(ctx);
+  double* d_s = scratch.get<double>(K);
+  double* d_sp = scratch.get<double>(K);
+  int32_t* d_theta0 = scratch.get<int32_t>(K);
+  // pinned, each part used for one thing: scores, counts, exchanges per block, group values
+  double* h_stage = reinterpret_cast<double*>(esp_host_stage(ctx, (size_t)(K + 8 + nblk + K / m) * 8));
+  if (!d_s || !d_sp || !d_theta0 || !h_stage) return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation failed");
+  memcpy(h_stage, score, (size_t)K * 8);
+  ESP_HIP(ctx, hipMemcpyAsync(d_s, h_stage, (size_t)K * 8, hipMemcpyHostToDevice, st));
 
-  // ---- global naive shuffle: g_c = (s_c * sum_j |w_jc|) / N, stable descending sort, round-robin deal
-  std::vector<int32_t> theta0((size_t)K);
+  // ---- global naive shuffle
+  double* d_g = nullptr;
   if (use_gns) {
-    DevBuf d_cs;
-    if (d_cs.alloc((size_t)K * AB_NB * 8) != hipSuccess) return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation failed");
-    ESP_HIP(ctx, hipMemsetAsync(d_cs.p, 0, (size_t)K * AB_NB * 8, st));
-    long long nchunk = std::max<long long>(1, std::min<long long>(N / 64, 1024 / std::max<long long>(1, (K + 63) / 64) + 1));
-    long long rpb = ((N + nchunk - 1) / nchunk + 7) / 8 * 8;
-    dim3 grid((unsigned)((K + 63) / 64), (unsigned)((N + rpb - 1) / rpb));
+    d_g = scratch.get<double>(K);
+    unsigned long long* d_cs = scratch.get<unsigned long long>((size_t)K * AB_NB);
+    if (!d_g || !d_cs) return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation failed");
+    ESP_HIP(ctx, hipMemsetAsync(d_cs, 0, (size_t)K * AB_NB * 8, st));
+    const long long nchunk = std::max<long long>(1, std::min<long long>(N / 64, 1024 / std::max<long long>(1, (K + 127) / 128) + 1));
+    const long long rpb = ((N + nchunk - 1) / nchunk + 7) / 8 * 8;
+    dim3 grid((unsigned)((K + 127) / 128), (unsigned)((N + rpb - 1) / rpb));
     if (dtype == ESPARSE_F16)
-      hipLaunchKernelGGL(k_abs_colsum<ESPARSE_F16>, grid, dim3(256), 0, st, W, N, K, rpb, d_cs.as<unsigned long long>());
+      hipLaunchKernelGGL(k_abs_colsum<ESPARSE_F16>, grid, dim3(256), 0, st, W, N, K, rpb, d_cs);
     else
-      hipLaunchKernelGGL(k_abs_colsum<ESPARSE_BF16>, grid, dim3(256), 0, st, W, N, K, rpb, d_cs.as<unsigned long long>());
+      hipLaunchKernelGGL(k_abs_colsum<ESPARSE_BF16>, grid, dim3(256), 0, st, W, N, K, rpb, d_cs);
     ESP_HIP(ctx, hipGetLastError());
-    std::vector<unsigned long long> cs((size_t)K * AB_NB);
-    ESP_HIP(ctx, hipMemcpyAsync(cs.data(), d_cs.p, cs.size() * 8, hipMemcpyDeviceToHost, st));
-    ESP_HIP(ctx, hipStreamSynchronize(st));
-    std::vector<double> g((size_t)K);
-    for (long long c = 0; c < K; c++) {
-      double colsum = esp_exact_bins_to_double(&cs[(size_t)c * AB_NB], AB_NB, -AB_EOFF - AB_SIG);
-      double t = score[c] * colsum;
-      g[c] = t / (double)N;
-    }
-    std::vector<int32_t> order((size_t)K);
-    std::iota(order.begin(), order.end(), 0);
-    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return g[a] > g[b]; });
-    const long long G = K / m;
-    for (long long r = 0; r < K; r++) theta0[(size_t)((r % G) * m + r / G)] = order[(size_t)r];
-  } else {
-    std::iota(theta0.begin(), theta0.end(), 0);
+    hipLaunchKernelGGL(k_channel_means, dim3((unsigned)((K + 63) / 64)), dim3(64), 0, st, d_cs, d_s, N, K, d_g);
+    ESP_HIP(ctx, hipGetLastError());
   }
-  DevBuf d_theta0;
-  if (d_theta0.alloc(K * 4) != hipSuccess) return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation failed");
-  ESP_HIP(ctx, hipMemcpyAsync(d_theta0.p, theta0.data(), K * 4, hipMemcpyHostToDevice, st));
+  hipLaunchKernelGGL(k_naive_shuffle, dim3((unsigned)((K + 15) / 16)), dim3(1024), 0, st, d_g, d_s, (int)K, m, use_gns ? 1 : 0, d_theta0, d_sp);
+  ESP_HIP(ctx, hipGetLastError());
 
   // ---- local block shuffle
   if (use_lbs) {
@@ -1396,21 +1494,25 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
     const int nsplit = (int)std::max<long long>(1, std::min<long long>(512 / (nblk * slices * gsets), (N + LBS_WAVES * LBS_ROWS - 1) / (LBS_WAVES * LBS_ROWS)));
     const long long batch = (long long)nsplit * LBS_WAVES * LBS_ROWS;  // rows that all waves of a block take at a time
     const long long Npad = (N + LBS_ROWS - 1) / LBS_ROWS * LBS_ROWS;
-    std::vector<double> sp((size_t)K);
     bool fast = true;
-    for (long long p = 0; p < K; p++) {
-      sp[p] = score[theta0[p]];
-      fast = fast && sp[p] >= 0.0 && std::isfinite(sp[p]);
-    }
-    DevBuf d_P, d_PT, d_sp, d_lp, d_rec, d_state, d_swaps, d_V, d_S, d_count;
-    const size_t vbytes = (size_t)nblk * B * B * 8;
-    if (d_P.alloc((size_t)(Npad * K + batch * B) * 2) != hipSuccess || d_PT.alloc((size_t)(Npad * K) * 2) != hipSuccess || d_sp.alloc(K * 8) != hipSuccess || d_lp.alloc(K * 4) != hipSuccess ||
-        d_rec.alloc(nblk * 2 * LBS_REC * 4) != hipSuccess || d_state.alloc(nblk * 4) != hipSuccess || d_swaps.alloc(nblk * 8) != hipSuccess ||
-        d_V.alloc(vbytes) != hipSuccess || d_S.alloc(vbytes * nsplit) != hipSuccess || d_count.alloc(16) != hipSuccess)
+    for (long long c = 0; c < K; c++) fast = fast && score[c] >= 0.0 && std::isfinite(score[c]);
+    const size_t ventries = (size_t)nblk * B * B;
+    uint16_t* d_P = scratch.get<uint16_t>((size_t)(Npad * K + batch * B));
+    uint16_t* d_PT = scratch.get<uint16_t>((size_t)(Npad * K));
+    double* d_V = scratch.get<double>(ventries);
+    double* d_S = scratch.get<double>(ventries * nsplit);
+    int* d_lp = scratch.get<int>(K);
+    int* d_rec = scratch.get<int>(nblk * 2 * LBS_REC);
+    int* d_state = scratch.get<int>(nblk);
+    long long* d_swaps = scratch.get<long long>(nblk);
+    int* d_count = scratch.get<int>(4);
+    if (!d_P || !d_PT || !d_V || !d_S || !d_lp || !d_rec || !d_state || !d_swaps || !d_count)
       return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation for the block shuffle failed");
-    ESP_HIP(ctx, hipMemcpyAsync(d_sp.p, sp.data(), K * 8, hipMemcpyHostToDevice, st));
-    hipLaunchKernelGGL(k_lbs_init, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, d_lp.as<int>(), d_state.as<int>(),
-                       fast ? LBS_FAST : LBS_EXACT, d_swaps.as<long long>(), d_count.as<int>(), (int)nblk, B);
+    int* count = reinterpret_cast<int*>(h_stage + K);
+    long long* h_swaps = reinterpret_cast<long long*>(h_stage + K + 8);
+    double* h_gv = h_stage + K + 8 + nblk;
+    hipLaunchKernelGGL(k_lbs_init, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, d_lp, d_state,
+                       fast ? LBS_FAST : LBS_EXACT, d_swaps, d_count, (int)nblk, B);
     {
       // whole rows of W in LDS: two workgroups per CU where a row leaves the room, else what one workgroup can hold
       const size_t row_bytes = (size_t)K * 2;
@@ -1419,17 +1521,18 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
       if (smem_w > 64 * 1024)
         ESP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_build_panel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_w));
       const int rows = RB ? RB : 1;
-      hipLaunchKernelGGL(k_build_panel, dim3((unsigned)((N + rows - 1) / rows)), dim3(512), smem_w, st, W, d_theta0.as<int32_t>(), N, Npad, K, B,
-                         RB, dtype == ESPARSE_F16 ? 0x7c00u : 0x7f80u, d_P.as<uint16_t>(), d_count.as<int>() + 2);
+      hipLaunchKernelGGL(k_build_panel, dim3((unsigned)((N + rows - 1) / rows)), dim3(512), smem_w, st, W, d_theta0, N, Npad, K, B,
+                         RB, dtype == ESPARSE_F16 ? 0x7c00u : 0x7f80u, d_P, d_count + 2);
       ESP_HIP(ctx, hipGetLastError());
       hipLaunchKernelGGL(k_panel_columns, dim3((unsigned)(nblk * ((Npad + 63) / 64)), (unsigned)((B + 63) / 64)), dim3(256), 0, st,
-                         d_P.as<uint16_t>(), Npad, (int)nblk, B, d_PT.as<uint16_t>());
+                         d_P, Npad, (int)nblk, B, d_PT);
       ESP_HIP(ctx, hipGetLastError());
     }
     // LDS of the exact evaluation: a chunk of a multiple of 16 rows, about 4096 metric values (at most 16 per thread)
     const int rows_chunk = std::max(16, (4096 / B) / 16 * 16);
     const size_t smem = (size_t)rows_chunk * (B + 1) * 8;
-    int count[2] = {fast ? (int)nblk : 0, fast ? 0 : (int)nblk};
+    count[0] = fast ? (int)nblk : 0;
+    count[1] = fast ? 0 : (int)nblk;
     for (int mode : {LBS_FAST, LBS_EXACT}) {
       int& active = count[mode == LBS_FAST ? 0 : 1];
       bool first = true;
@@ -1442,7 +1545,7 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
 #define LAUNCH_EVAL2(DTv, NK, MGv, NGv, NMv, QCv)                                                                          \
   hipLaunchKernelGGL((k_lbs_eval<DTv, NK, MGv, NGv, NMv, QCv>),                                                            \
                      dim3((unsigned)nblk, (unsigned)nsplit, (unsigned)(slices * (NMv == MGv ? (B / MGv + NGv - 1) / NGv : gsets))), \
-                     dim3(64 * LBS_WAVES), 0, st, d_P.as<uint16_t>(), d_PT.as<uint16_t>(), d_sp.as<double>(), d_rec.as<int>(), N, Npad, B, slices, d_S.as<double>())
+                     dim3(64 * LBS_WAVES), 0, st, d_P, d_PT, d_sp, d_rec, N, Npad, B, slices, d_S)
 #define LAUNCH_EVAL(DTv, NK, MGv, ...)                                                      \
   do {                                                                                      \
     constexpr int NGv = MGv == 4 ? 2 : 1;                                                   \
@@ -1455,7 +1558,7 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
 #undef LAUNCH_EVAL
 #undef LAUNCH_EVAL2
           } else {
-            const int* rec = first ? nullptr : d_rec.as<int>();
+            const int* rec = first ? nullptr : d_rec;
             if (m == 4 && (B % 64 == 0 || B < 64)) {
               // 2:4: 8 units per workgroup while every group is evaluated, 2 in the refresh rounds (more workgroups)
               const int units = (first ? B / m : 2) * m * (B < 64 ? 1 : B / 64);
@@ -1463,8 +1566,8 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
               dim3 grid((unsigned)((units + nc - 1) / nc), (unsigned)nblk);
               const size_t smem2 = smem + (size_t)rows_chunk * nc * 16;
 #define LAUNCH_EXACT24(DTv, NCv)                                                                                             \
-  hipLaunchKernelGGL((k_lbs_exact_2_4<DTv, NCv>), grid, dim3(1024), smem2, st, d_P.as<uint16_t>(), d_sp.as<double>(), d_lp.as<int>(), \
-                     rec, d_state.as<int>(), N, Npad, B, rows_chunk, d_V.as<double>())
+  hipLaunchKernelGGL((k_lbs_exact_2_4<DTv, NCv>), grid, dim3(1024), smem2, st, d_P, d_sp, d_lp, \
+                     rec, d_state, N, Npad, B, rows_chunk, d_V)
               if (dtype == ESPARSE_F16) {
                 if (first) LAUNCH_EXACT24(ESPARSE_F16, 8);
                 else LAUNCH_EXACT24(ESPARSE_F16, 2);
@@ -1476,17 +1579,17 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
             } else {
               dim3 grid((unsigned)(((first ? B / m : 2) * m * B + 63) / 64), (unsigned)nblk);
 #define LAUNCH_EXACT(DT, NK, MGv, ...)                                                                                        \
-  hipLaunchKernelGGL((k_lbs_exact<DT, NK, MGv>), grid, dim3(1024), smem, st, d_P.as<uint16_t>(), d_sp.as<double>(), d_lp.as<int>(), \
-                     rec, d_state.as<int>(), N, Npad, B, rows_chunk, d_V.as<double>())
+  hipLaunchKernelGGL((k_lbs_exact<DT, NK, MGv>), grid, dim3(1024), smem, st, d_P, d_sp, d_lp, \
+                     rec, d_state, N, Npad, B, rows_chunk, d_V)
               DISPATCH_DT_NM(dtype, n, LAUNCH_EXACT, 0);
 #undef LAUNCH_EXACT
             }
           }
           ESP_HIP(ctx, hipGetLastError());
 #define LAUNCH_SELECT(MGv)                                                                                                     \
-  hipLaunchKernelGGL(k_lbs_select<MGv>, dim3((unsigned)nblk), dim3(1024), 0, st, d_S.as<double>(), nsplit, d_V.as<double>(), d_lp.as<int>(), \
-                     d_rec.as<int>(), d_state.as<int>(), d_swaps.as<long long>(), o->max_swaps, N, B, first ? 1 : 0, (int)mode,  \
-                     d_count.as<int>() + 2, d_count.as<int>())
+  hipLaunchKernelGGL(k_lbs_select<MGv>, dim3((unsigned)nblk), dim3(1024), 0, st, d_S, nsplit, d_V, d_lp, \
+                     d_rec, d_state, d_swaps, o->max_swaps, N, B, first ? 1 : 0, (int)mode,  \
+                     d_count + 2, d_count)
           if (m == 4) LAUNCH_SELECT(4);
           else LAUNCH_SELECT(8);
 #undef LAUNCH_SELECT
@@ -1494,77 +1597,78 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
           first = false;
         }
         iter += LBS_ROUNDS_QUEUED;
-        ESP_HIP(ctx, hipMemcpyAsync(count, d_count.p, 8, hipMemcpyDeviceToHost, st));
+        ESP_HIP(ctx, hipMemcpyAsync(count, d_count, 8, hipMemcpyDeviceToHost, st));
         ESP_HIP(ctx, hipStreamSynchronize(st));
         if (active > 0 && iter > (long long)B * B * 64)
           return esp_fail(ctx, ESPARSE_EHIP, "block shuffle did not terminate after %lld rounds", iter);
       }
     }
-    hipLaunchKernelGGL(k_lbs_final_theta, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, d_theta0.as<int32_t>(), d_lp.as<int>(), B,
+    hipLaunchKernelGGL(k_lbs_final_theta, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, d_theta0, d_lp, B,
                        K, perm_out);
     ESP_HIP(ctx, hipGetLastError());
     if (swaps_out) {
-      ESP_HIP(ctx, hipMemcpyAsync(swaps_out, d_swaps.p, nblk * 8, hipMemcpyDeviceToHost, st));
+      ESP_HIP(ctx, hipMemcpyAsync(h_swaps, d_swaps, nblk * 8, hipMemcpyDeviceToHost, st));
     }
     // mask and retained metric under the final order, from the panel
     {
       const int row_blocks = (int)((N + 63) / 64);
       const long long ng = K / m;
-      DevBuf d_part, d_gv;
-      if (retained_out && (d_part.alloc((size_t)row_blocks * ng * 8) != hipSuccess || d_gv.alloc(ng * 8) != hipSuccess))
-        return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation failed");
+      double* d_part = retained_out ? scratch.get<double>((size_t)row_blocks * ng) : nullptr;
+      double* d_gv = retained_out ? scratch.get<double>(ng) : nullptr;
+      if (retained_out && (!d_part || !d_gv)) return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation failed");
       const size_t smem_m = 256 * 8 + (size_t)64 * (B + 2) * 2;
       dim3 grid((unsigned)(nblk * row_blocks));
 #define LAUNCH_MASK(DT, NK, MGv, ...)                                                                                        \
-  hipLaunchKernelGGL((k_nm_mask_panel<DT, NK, MGv>), grid, dim3(256), smem_m, st, d_P.as<uint16_t>(), d_sp.as<double>(), d_lp.as<int>(), N, \
-                     Npad, K, B, mask_out, retained_out ? d_part.as<double>() : nullptr)
+  hipLaunchKernelGGL((k_nm_mask_panel<DT, NK, MGv>), grid, dim3(256), smem_m, st, d_P, d_sp, d_lp, N, \
+                     Npad, K, B, mask_out, d_part)
       DISPATCH_DT_NM(dtype, n, LAUNCH_MASK, 0);
 #undef LAUNCH_MASK
       ESP_HIP(ctx, hipGetLastError());
-      std::vector<double> gv;
       if (retained_out) {
-        hipLaunchKernelGGL(k_add_parts, dim3((unsigned)((ng + 63) / 64)), dim3(64), 0, st, d_part.as<double>(), row_blocks, ng, d_gv.as<double>());
+        hipLaunchKernelGGL(k_add_parts, dim3((unsigned)((ng + 63) / 64)), dim3(64), 0, st, d_part, row_blocks, ng, d_gv);
         ESP_HIP(ctx, hipGetLastError());
-        gv.resize((size_t)ng);
-        ESP_HIP(ctx, hipMemcpyAsync(gv.data(), d_gv.p, ng * 8, hipMemcpyDeviceToHost, st));
+        ESP_HIP(ctx, hipMemcpyAsync(h_gv, d_gv, ng * 8, hipMemcpyDeviceToHost, st));
       }
       ESP_HIP(ctx, hipStreamSynchronize(st));
+      scratch.idle();
+      if (swaps_out) memcpy(swaps_out, h_swaps, nblk * 8);
       if (retained_out) {
         double tot = 0.0;
-        for (long long g = 0; g < ng; g++) tot = tot + gv[g];
+        for (long long g = 0; g < ng; g++) tot = tot + h_gv[g];
         *retained_out = tot;
       }
     }
     return ESPARSE_OK;
   }
-  ESP_HIP(ctx, hipMemcpyAsync(perm_out, d_theta0.p, K * 4, hipMemcpyDeviceToDevice, st));
+  ESP_HIP(ctx, hipMemcpyAsync(perm_out, d_theta0, K * 4, hipMemcpyDeviceToDevice, st));
 
   // ---- n:m mask under the final order
   {
     dim3 grid((unsigned)((N * (K / m) + 255) / 256));
 #define LAUNCH_MASK(DT, NK, MGv, ...) \
-  hipLaunchKernelGGL((k_nm_mask<DT, NK, MGv>), grid, dim3(256), 0, st, W, d_s.as<double>(), perm_out, N, K, mask_out)
+  hipLaunchKernelGGL((k_nm_mask<DT, NK, MGv>), grid, dim3(256), 0, st, W, d_s, perm_out, N, K, mask_out)
     DISPATCH_DT_NM(dtype, n, LAUNCH_MASK, 0);
 #undef LAUNCH_MASK
     ESP_HIP(ctx, hipGetLastError());
   }
   if (retained_out) {
-    DevBuf d_gv;
     const long long ng = K / m;
-    if (d_gv.alloc(ng * 8) != hipSuccess) return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation failed");
+    double* d_gv = scratch.get<double>(ng);
+    if (!d_gv) return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation failed");
     dim3 grid((unsigned)((ng + 3) / 4));
 #define LAUNCH_GV(DT, NK, MGv, ...) \
-  hipLaunchKernelGGL((k_group_values<DT, NK, MGv>), grid, dim3(64), 0, st, W, d_s.as<double>(), perm_out, N, K, d_gv.as<double>())
+  hipLaunchKernelGGL((k_group_values<DT, NK, MGv>), grid, dim3(64), 0, st, W, d_s, perm_out, N, K, d_gv)
     DISPATCH_DT_NM(dtype, n, LAUNCH_GV, 0);
 #undef LAUNCH_GV
     ESP_HIP(ctx, hipGetLastError());
     std::vector<double> gv((size_t)ng);
-    ESP_HIP(ctx, hipMemcpyAsync(gv.data(), d_gv.p, ng * 8, hipMemcpyDeviceToHost, st));
+    ESP_HIP(ctx, hipMemcpyAsync(gv.data(), d_gv, ng * 8, hipMemcpyDeviceToHost, st));
     ESP_HIP(ctx, hipStreamSynchronize(st));
     double tot = 0.0;
     for (long long g = 0; g < ng; g++) tot = tot + gv[g];
     *retained_out = tot;
   }
   ESP_HIP(ctx, hipStreamSynchronize(st));
+  scratch.idle();
   return ESPARSE_OK;
 }

@@ -174,6 +174,45 @@ def test_block_shuffle_undecided_exchanges(esp, ctx, n, m, what):
     assert _check_block_shuffle(esp, ctx, W, s, n, m, B).sum() > 0
 
 
+# column sums and ranks: fewer rows than a row lane's batch and a remainder, channels past a workgroup's 128 (16), values
+# over the whole range of the type with zeros and subnormal ones, equal means
+@pytest.mark.parametrize("N,K", [(1, 36), (7, 132), (70, 264), (129, 40)])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+def test_naive_shuffle_over_the_range_of_the_type(esp, ctx, N, K, dtype):
+    rng = np.random.default_rng(N + K)
+    bits = rng.integers(0, 0x7c00 if dtype == torch.float16 else 0x7f80, size=(N, K)).astype(np.int16)
+    bits[:, 3] = bits[:, 9]
+    bits[:, 5] = 0
+    W = torch.from_numpy(bits).view(dtype)
+    s = rng.lognormal(size=K)
+    s[3] = s[9]
+    print(f"gns N={N} K={K} {dtype}", flush=True)
+    res = ctx.prune(None, W.cuda(), esp.PruneOpts(block=K, flags=esp.USE_NORM | esp.USE_GNS), score=s)
+    assert (res.perm.cpu().numpy() == orc.global_naive_shuffle(_np(W), s, 4)).all()
+
+
+def test_prune_scratch_is_shared_by_calls_and_streams(esp, ctx):
+    """One context, shapes that grow and shrink, two streams in turn: every call as on a context of its own."""
+    rng = np.random.default_rng(3)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for i, (N, K, B, n, m) in enumerate([(64, 256, 64, 2, 4), (300, 512, 32, 4, 8), (64, 256, 64, 2, 4), (40, 128, 64, 2, 4)]):
+        W, s = _rand((N, K), torch.float16, 90 + N).cuda(), rng.lognormal(size=K)
+        Xc = _rand((200, K), torch.float16, 91 + K).cuda()
+        torch.cuda.synchronize()
+        opts = esp.PruneOpts(n_keep=n, m_group=m, block=B)
+        with torch.cuda.stream(streams[i % 2]):
+            a = ctx.prune(None, W, opts, score=s)
+            ca = ctx.compress(W, a.mask, a.perm, n, m)
+            b = ctx.prune(Xc, W, opts)
+        own = esp.Context(0)
+        a2, b2 = own.prune(None, W, opts, score=s), own.prune(Xc, W, opts)
+        cb = own.compress(W, a2.mask, a2.perm, n, m)
+        own.close()
+        for x, y in ((a, a2), (b, b2)):
+            assert torch.equal(x.perm, y.perm) and torch.equal(x.mask, y.mask) and (x.score == y.score).all()
+        assert torch.equal(ca.native, cb.native)
+
+
 def test_config1_against_stored_oracle_results(esp, ctx):
     """Workload configuration 1, complete, against results the oracle wrote to tests/golden."""
     gold = json.load(open(os.path.join(os.path.dirname(__file__), "golden", "cfg1_oracle.json")))
