@@ -269,6 +269,38 @@ def test_compress_2_4_bit_exact(esp, ctx, N, K, dtype):
     assert (nat[nv.nbytes:].view(np.uint16) == nm).all()
 
 
+# rows and channels that end inside a tile, a 64-channel step, a mask or index word; rows that fill the LDS, rows that do
+# not fit it; identity order; a permutation that is none leaves the outputs as they are
+@pytest.mark.parametrize("n,m", [(2, 4), (4, 8)])
+@pytest.mark.parametrize("N,K", [(17, 8), (33, 264), (16, 320), (50, 1064), (7, 36872), (3, 81920)])
+def test_compress_edges_of_the_row_kernel(esp, ctx, N, K, n, m):
+    W = _rand((N, K), torch.float16, 33)
+    rng = np.random.default_rng(N + K)
+    s = np.abs(rng.standard_normal(K)) + 0.1
+    theta = rng.permutation(K) if K != 320 else np.arange(K)
+    mask = orc.nm_mask_vectorised(_np(W), s, theta, n, m)
+    th = None if K == 320 else torch.tensor(theta, dtype=torch.int32).cuda()
+    print(f"compress N={N} K={K} {n}:{m}", flush=True)
+    mk = torch.tensor(mask).cuda()
+    comp = ctx.compress(W.cuda(), mk, th, n, m)
+    values, meta = orc.compress_vectorised(_bits(W).reshape(N, K), theta, mask, n, m)
+    assert (_bits(comp.values).reshape(values.shape) == values).all()
+    assert (comp.meta.cpu().numpy().view(meta.dtype).reshape(meta.shape) == meta).all()
+    nv, nm = (orc.native_tiling if m == 4 else orc.native_tiling_4_8)(values, meta, N, K)
+    nat = comp.native.cpu().numpy()
+    assert nat.size == esp.compressed_size(N, K, n, m)[2] == nv.nbytes + nm.nbytes
+    assert (nat[:nv.nbytes].view(nv.dtype) == nv).all() and (nat[nv.nbytes:].view(nm.dtype) == nm).all()
+    assert torch.equal(ctx.compress(W.cuda(), mk, th, n, m, canonical=False).native, comp.native)
+    assert torch.equal(ctx.compress(W.cuda(), mk, th, n, m, native=False).values, comp.values)
+    if th is not None:
+        bad = th.clone()
+        bad[0] = K
+        before = comp.native.clone()
+        Wd = W.cuda()
+        rc = ctx._lib.esparse_compress(ctx._h, Wd.data_ptr(), mk.data_ptr(), bad.data_ptr(), N, K, 0, n, m, None, None, comp.native.data_ptr())
+        assert rc == -6 and torch.equal(before, comp.native)
+
+
 def test_compress_4_8_and_derived_mask_and_errors(esp, ctx):
     N, K = 20, 64
     W = _rand((N, K), torch.float16, 32)
