@@ -268,7 +268,8 @@ __global__ void __launch_bounds__(256) k_gather_x(GatherArgs args, long long M, 
 // 16-byte reads and gathers through theta out of LDS (the element-wise gather above reads 2 bytes per
 // lane from 64 different cache lines per instruction).  Rows are padded by 8 elements so that the TOK
 // tokens of one channel sit in different banks.  Lane l of a wave works on token l % TOK and 8-channel
-// unit l / TOK, so consecutive lanes write consecutive 16-byte units of X'.  Needs K % 8 == 0.
+// unit l / TOK, so consecutive lanes write consecutive 16-byte units of X'.  K % 8 == 4: the rows are copied 8 bytes at a
+// time (333 x 3020: 5.8 us against 7.3 element by element).  The first entries of theta are on their way with the rows.
 template <int TOK>
 __global__ void __launch_bounds__(512) k_gather_rows(const uint16_t* __restrict__ X, const int32_t* __restrict__ perm, long long M,
                                                       long long Mp, long long K, long long Kp, uint4* __restrict__ Xf) {
@@ -285,42 +286,63 @@ __global__ void __launch_bounds__(512) k_gather_rows(const uint16_t* __restrict_
   if (t0 >= Mp) return;
   const int stride = (int)K + 8;
   const long long nrows = (M - t0) < TOK ? (M - t0 > 0 ? M - t0 : 0) : TOK;
-  const int kc = (int)(K / 8);  // 16-byte chunks per row
-  const uint4* src = reinterpret_cast<const uint4*>(X + t0 * K);
-  for (int i = tid; i < (int)nrows * kc; i += 512) {
-    const int row = i / kc, col = i - row * kc;
-    s_rows4[(row * stride) / 8 + col] = src[i];
-  }
-  __syncthreads();
   constexpr int UPW = 64 / TOK;  // units per wave and pass
   const int lane = tid & 63, wave = tid >> 6;
   const int c = lane % TOK, q = lane / TOK;
+  const int nunits = (int)(Kp / 8), u0 = wave * UPW + q;
+  int4 p0 = {0, 0, 0, 0}, p1 = {0, 0, 0, 0};
+  auto load_theta = [&](int u) {
+    const int k0 = u * 8;
+    if (k0 < K) {  // K % 4 == 0: a unit has eight, four or no real channels
+      p0 = *reinterpret_cast<const int4*>(perm + k0);
+      if (k0 + 8 <= K) p1 = *reinterpret_cast<const int4*>(perm + k0 + 4);
+    }
+  };
+  if (perm) load_theta(u0);
+  if ((K & 7) == 0) {
+    const int kc = (int)(K / 8);  // 16-byte chunks per row
+    const uint4* src = reinterpret_cast<const uint4*>(X + t0 * K);
+    for (int i = tid; i < (int)nrows * kc; i += 512) {
+      const int row = i / kc, col = i - row * kc;
+      s_rows4[(row * stride) / 8 + col] = src[i];
+    }
+  } else {
+    const int kc = (int)(K / 4);
+    const uint2* src = reinterpret_cast<const uint2*>(X + t0 * K);
+    for (int i = tid; i < (int)nrows * kc; i += 512) {
+      const int row = i / kc, col = i - row * kc;
+      reinterpret_cast<uint2*>(s_rows4)[(row * stride) / 4 + col] = src[i];
+    }
+  }
+  __syncthreads();
   const long long t = t0 + c;
   const long long ns = Kp / 32;
   const long long obase = (t / 16) * ns * 64 + (t % 16);
   const uint16_t* row = s_rows + c * stride;
   const bool live = t < M;
-  const int nunits = (int)(Kp / 8);
-  for (int u = wave * UPW + q; u < nunits; u += 8 * UPW) {
+  for (int u = u0; u < nunits; u += 8 * UPW) {
     const int k0 = u * 8;
     uint16_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (live && k0 < K) {  // K % 8 == 0: a unit is entirely inside or outside the real channels
+    if (live && k0 < K) {
+      const bool whole = k0 + 8 <= K;
       if (perm) {
-        const int4 p0 = *reinterpret_cast<const int4*>(perm + k0);
-        const int4 p1 = *reinterpret_cast<const int4*>(perm + k0 + 4);
         v[0] = row[p0.x];
         v[1] = row[p0.y];
         v[2] = row[p0.z];
         v[3] = row[p0.w];
-        v[4] = row[p1.x];
-        v[5] = row[p1.y];
-        v[6] = row[p1.z];
-        v[7] = row[p1.w];
+        if (whole) {
+          v[4] = row[p1.x];
+          v[5] = row[p1.y];
+          v[6] = row[p1.z];
+          v[7] = row[p1.w];
+        }
       } else {
 #pragma unroll
-        for (int e = 0; e < 8; e++) v[e] = row[k0 + e];
+        for (int e = 0; e < 8; e++)
+          if (e < 4 || whole) v[e] = row[k0 + e];
       }
     }
+    if (perm && u + 8 * UPW < nunits) load_theta(u + 8 * UPW);
     uint4 o;
     o.x = v[0] | ((uint32_t)v[1] << 16);
     o.y = v[2] | ((uint32_t)v[3] << 16);
@@ -505,9 +527,9 @@ __global__ void __launch_bounds__(256) k_mm_wave_tile(const uint4* __restrict__ 
 // the result does not depend on timing and no global synchronisation is needed.
 // grid = ceil(row tiles / RT), block = 64 * NW.
 // ------------------------------------------------------------------------------------------------
-// FOLD (one or two tokens, MT = 1): there is no staged copy and no staging launch; the workgroup applies the channel
+// FOLD (few tokens and channels, MT = 1): there is no staged copy and no staging launch; the workgroup applies the channel
 // re-ordering of Section 3.3 itself: it gathers X[t, theta[p]] for all p into LDS (2 Kp bytes per token, the layout of the
-// compact copy) while its first weight loads are under way, and the waves read their activation operands from there.
+// compact copy), and the waves read their activation operands from there.
 template <int DT, int SPARSE, int MT, int RT, int NW, int IDXM, bool FOLD = false>
 __global__ void __launch_bounds__(NW * 64) k_mm_ksplit(KsplitArgs args, long long M, long long N, long long Mp, long long Np,
                                                         long long Kp, int mc) {
@@ -518,12 +540,21 @@ __global__ void __launch_bounds__(NW * 64) k_mm_ksplit(KsplitArgs args, long lon
   uint16_t* __restrict__ Y = args.Y[blockIdx.y];
   extern __shared__ floatx4_t s_red[];  // [NW][RT * MT][64]; FOLD: followed by the gathered activations [Kp / 8][mc]
   uint4* s_x = reinterpret_cast<uint4*>(s_red + NW * RT * MT * 64);
+  __shared__ uint4 s_lut[SPARSE == 2 ? LUT48_CODES : 1];  // 4:8: the byte-permute selectors of every pattern code
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const long long nrt = Np / 16, ntt = Mp / 16, nks = Kp / 64;
+  const long long rt0 = (long long)blockIdx.x * RT;
+  long long rts[RT];
+#pragma unroll
+  for (int i = 0; i < RT; i++) rts[i] = (rt0 + i < nrt) ? rt0 + i : nrt - 1;
   if (FOLD) {
     const uint16_t* __restrict__ X = args.X[blockIdx.y];
     const int32_t* __restrict__ perm = args.perm[blockIdx.y];
     const long long K = args.K;
-    for (long long u = threadIdx.x; u < Kp / 8; u += NW * 64) {
-      const long long k0 = u * 8;
+    const int units = (int)(Kp / 8);
+    for (int e = tid; e < units * mc; e += NW * 64) {  // 8-channel unit u of token c
+      const int c = e / units, u = e - c * units;
+      const long long k0 = (long long)u * 8;
       int p[8];
       if (perm && k0 + 8 <= K) {
         const int4 p0 = *reinterpret_cast<const int4*>(perm + k0);
@@ -531,33 +562,24 @@ __global__ void __launch_bounds__(NW * 64) k_mm_ksplit(KsplitArgs args, long lon
         p[0] = p0.x, p[1] = p0.y, p[2] = p0.z, p[3] = p0.w, p[4] = p1.x, p[5] = p1.y, p[6] = p1.z, p[7] = p1.w;
       } else {
 #pragma unroll
-        for (int e = 0; e < 8; e++) p[e] = k0 + e < K ? (perm ? perm[k0 + e] : (int)(k0 + e)) : -1;
+        for (int q = 0; q < 8; q++) p[q] = k0 + q < K ? (perm ? perm[k0 + q] : (int)(k0 + q)) : -1;
       }
-      for (int c = 0; c < mc; c++) {
-        uint16_t v[8];
+      uint16_t v[8];
 #pragma unroll
-        for (int e = 0; e < 8; e++) v[e] = (c < M && p[e] >= 0) ? X[(long long)c * K + p[e]] : (uint16_t)0;
-        uint4 o;
-        o.x = v[0] | ((uint32_t)v[1] << 16);
-        o.y = v[2] | ((uint32_t)v[3] << 16);
-        o.z = v[4] | ((uint32_t)v[5] << 16);
-        o.w = v[6] | ((uint32_t)v[7] << 16);
-        s_x[u * mc + c] = o;
-      }
+      for (int q = 0; q < 8; q++) v[q] = (c < M && p[q] >= 0) ? X[(long long)c * K + p[q]] : (uint16_t)0;
+      uint4 o;
+      o.x = v[0] | ((uint32_t)v[1] << 16);
+      o.y = v[2] | ((uint32_t)v[3] << 16);
+      o.z = v[4] | ((uint32_t)v[5] << 16);
+      o.w = v[6] | ((uint32_t)v[7] << 16);
+      s_x[u * mc + c] = o;
     }
     __syncthreads();
   }
-  __shared__ uint4 s_lut[SPARSE == 2 ? LUT48_CODES : 1];  // 4:8: the byte-permute selectors of every pattern code
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (SPARSE == 2) {
     fill_expand_lut<1>(s_lut, tid);
     __syncthreads();
   }
-  const long long nrt = Np / 16, ntt = Mp / 16, nks = Kp / 64;
-  const long long rt0 = (long long)blockIdx.x * RT;
-  long long rts[RT];
-#pragma unroll
-  for (int i = 0; i < RT; i++) rts[i] = (rt0 + i < nrt) ? rt0 + i : nrt - 1;
 
   floatx4_t acc[RT][MT];
 #pragma unroll
@@ -1930,13 +1952,14 @@ static void launch_wave_tile(const Variant& v, dim3 grid, hipStream_t st, const 
 #undef LAUNCH
 }
 
-// Whether the decode kernel gathers the activations through theta itself (no staged copy, no staging launch): one or two
+// Whether the decode kernel gathers the activations through theta itself (no staged copy, no staging launch): at most 16
 // tokens, a variant that keeps K inside the workgroup, the gathered copy (2 Kp bytes per token) fits beside the reduction
 // buffer in the 64 KiB of LDS a launch may ask for without further ado - and the gather is cheap enough: every workgroup
-// repeats it, so it pays while workgroups x channels stays small (4096 x 4096: 7.0 us against 6.5 + 2.1 for the staging
-// launch; 36864 x 9216, 2304 workgroups: 77 us against 58 + 2.3, hence the limits).
+// repeats it, so it pays while workgroups x channels x tokens stays small (4096 x 4096, one token: 7.0 us against 6.5 + 2.1
+// for the staging launch; 36864 x 9216, 2304 workgroups: 77 us against 58 + 2.3, hence the limits; 16 tokens x 512
+// channels, 32 workgroups: a call 14.6 -> 11.5 us, one launch of 6 us instead of two of 3.5 and 3.9 and the gap).
 static bool ksplit_folds(const Variant& v, long long M, long long Np, long long Kp) {
-  if (v.kind != KIND_KSPLIT || v.split_mode != 0 || M > 2) return false;
+  if (v.kind != KIND_KSPLIT || v.split_mode != 0 || M > 16) return false;
   const long long mc = compact_tokens(M), groups = (Np / 16 + v.rt - 1) / v.rt;
   if (Kp * mc > 10240 || groups * Kp * mc > 3000000) return false;
   const size_t red = (size_t)v.nw * v.rt * 64 * 16, gathered = (size_t)2 * Kp * mc;
@@ -2172,7 +2195,7 @@ static hipError_t launch_gather_rows(int device, hipStream_t st, const uint16_t*
 static int stage_activations(esparse_ctx* ctx, const void* X, const int32_t* perm, long long M, long long K, long long Mp,
                              long long Kp, uint4* Xf, int mc) {
   const uint16_t* Xh = reinterpret_cast<const uint16_t*>(X);
-  const int tok = (M >= 64 && K % 8 == 0) ? gather_rows_tok(Mp, K) : 0;
+  const int tok = M >= 64 ? gather_rows_tok(Mp, K) : 0;
   if (tok) {
     hipStream_t st = ctx->stream;
     switch (tok) {

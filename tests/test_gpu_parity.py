@@ -533,6 +533,51 @@ def test_spmm_theta_gathered_in_the_kernel_equals_staged(esp, ctx, M, K):
     assert ran > 4
 
 
+# up to 16 tokens of few channels are gathered inside the decode kernel as well: token counts that are no power of two, channels
+# that end inside a unit, waves without a step of their own, groups, each pattern and the dense product
+@pytest.mark.parametrize("M,K", [(3, 64), (5, 1004), (9, 640), (16, 512), (16, 640), (7, 1280)])
+@pytest.mark.parametrize("n,m", [(2, 4), (4, 8)])
+def test_few_tokens_gathered_in_the_kernel_equal_staged(esp, ctx, M, K, n, m):
+    K = K // m * m
+    N, count = 72, 3
+    rng = np.random.default_rng(M + K)
+    X = _rand((M, K), torch.float16, 61).cuda()
+    comps, perms = [], []
+    for i in range(count):
+        W = _rand((N, K), torch.float16, 62 + i, scale=K ** -0.5)
+        theta = rng.permutation(K)
+        mask = orc.nm_mask_vectorised(_np(W), np.ones(K), theta, n, m)
+        perms.append(torch.tensor(theta, dtype=torch.int32).cuda())
+        comps.append(ctx.compress(W.cuda(), torch.tensor(mask).cuda(), perms[-1], n, m))
+        ref = orc.spmm_ref(_np(X), _np(W), theta, mask)
+        for v in [-1] + [v for v in range(esp.num_variants()) if esp.variant_name(v).startswith("ksplit") and "_k" not in esp.variant_name(v)]:
+            try:
+                Y = ctx.spmm(X, comps[-1], perms[-1], variant=v)
+            except esp.EsparseError:
+                continue
+            assert orc.rowwise_rel_error(_np(Y).astype(np.float64), ref).max() <= TOL[torch.float16]
+            ws = torch.zeros(esp.spmm_workspace(M, N, K) + 256, dtype=torch.uint8, device="cuda")
+            ws = ws[(-ws.data_ptr()) % 256:]
+            ctx.stage_activations(X, perms[-1], N, ws=ws)
+            assert torch.equal(ctx.spmm_staged(M, comps[-1], ws, torch.empty_like(Y), variant=v), Y)
+    for Y, comp, perm in zip(ctx.spmm_group([X] * count, comps, perms), comps, perms):
+        assert torch.equal(Y, ctx.spmm(X, comp, perm))
+
+
+# rows of X that are a multiple of 8 but not of 16 bytes go through the row staging 8 bytes at a time
+@pytest.mark.parametrize("M,K", [(64, 4), (65, 68), (130, 3020), (600, 516)])
+@pytest.mark.parametrize("with_perm", [True, False])
+def test_row_staging_of_odd_row_lengths(esp, ctx, M, K, with_perm):
+    N = 48
+    W, X = _rand((N, K), torch.bfloat16, 71, scale=K ** -0.5), _rand((M, K), torch.bfloat16, 72)
+    theta = np.random.default_rng(K).permutation(K) if with_perm else np.arange(K)
+    mask = orc.nm_mask_vectorised(_np(W), np.ones(K), theta, 2, 4)
+    th = torch.tensor(theta, dtype=torch.int32).cuda()
+    comp = ctx.compress(W.cuda(), torch.tensor(mask).cuda(), th, 2, 4)
+    Y = ctx.spmm(X.cuda(), comp, th if with_perm else None)
+    assert orc.rowwise_rel_error(_np(Y), orc.spmm_ref(_np(X), _np(W), theta, mask)).max() <= TOL[torch.bfloat16]
+
+
 @pytest.mark.parametrize("M", [8, 100, 300])
 def test_spmm_replayed_from_a_hip_graph(esp, ctx, M):
     """The calls enqueue kernels only (no allocation, no memset, no synchronisation), so a caller may capture them
