@@ -137,7 +137,7 @@ int esparse_compress(esparse_ctx* ctx, const void* W, const uint8_t* mask, const
  * order, the re-ordering of Section 3.3 is applied while X is staged.  native_w from
  * esparse_compress.  workspace: DEVICE scratch of at least esparse_spmm_workspace bytes,
  * 256-byte aligned; it is overwritten.  variant: -1 = the one chosen by esparse_tune for this shape
- * (a built-in rule if never tuned), >= 0 = a specific kernel variant (EINVAL if out of range).
+ * (a built-in estimate of every kernel's time for the shape if never tuned), >= 0 = a specific kernel variant (EINVAL if out of range).
  * esparse_spmm_workspace (host only, no context): variant -1 = the size that serves every variant of the
  * shape - what a call with variant -1 requires, since tuning may change the choice after the caller has
  * allocated; variant >= 0 = what that variant needs (the staged activations, plus fp32 partial tiles only
@@ -161,8 +161,7 @@ int esparse_spmm(esparse_ctx* ctx, const void* X, long long M, const void* nativ
  * that split K) is a fixed array of ESPARSE_STATIC_SCRATCH_BYTES in the library's device image, one per GPU,
  * held until the process ends.  The call allocates and frees nothing on the device.  variant -1: where the tuned
  * (or built-in) choice keeps fp32 partial tiles that do not fit the array, the built-in choice among the kernels
- * without partial tiles runs instead (a decode kernel up to 64 tokens, tile32_w8_t128 up to 128, tile32_w8_t256
- * beyond; 4:8: tile48_w8_r128_t256).  A shape whose variant still needs more scratch than the array holds is
+ * without partial tiles runs instead (a decode kernel up to 64 tokens, a tile kernel beyond).  A shape whose variant still needs more scratch than the array holds is
  * rejected with ESPARSE_EWORKSPACE and nothing is launched (the message gives both sizes); the first call on a GPU looks the array's device address up (that GPU current).  Every call on one GPU
  * uses the same array, on whatever stream its context has: calls that overlap on one GPU race - order them on
  * one stream or with events.  No part of the array needs clearing between calls (each kernel reads only what an
@@ -244,7 +243,8 @@ int esparse_tune(esparse_ctx* ctx, long long M, long long N, long long K, espars
                  int sparse, int* best_variant, float* best_ms);
 /* The same search for launches of `count` products of one shape (esparse_spmm_group, esparse_dense_gemm_group; count in
  * 1..4): a group fills the chip differently from a single product, so its fastest variant can differ.  Group calls with
- * variant = -1 use the choice tuned for their count, else the one tuned for the single product, else the default.
+ * variant = -1 use the choice tuned for their count, else the one tuned for the single product, else the built-in choice for
+ * their count.
  * In the text file a line may end in the count. */
 int esparse_tune_group(esparse_ctx* ctx, int count, long long M, long long N, long long K, esparse_dtype dtype,
                        int sparse, int* best_variant, float* best_ms);

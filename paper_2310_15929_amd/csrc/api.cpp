@@ -275,14 +275,26 @@ static int check_matmul(esparse_ctx* ctx, const void* X, long long M, const void
   return ESPARSE_OK;
 }
 
-// count = products in the launch: a group call looks for a choice tuned for its size first, then for the single product
-static int pick_variant(esparse_ctx* ctx, int sparse, int dtype, long long M, long long N, long long K, int variant, int count = 1) {
-  if (variant >= 0) return variant;
+// the choice tuned for the launch, -1 if there is none.  count = products in the launch: a group call looks for a choice tuned
+// for its size first, then for the single product
+static int tuned_variant(const esparse_ctx* ctx, int sparse, int dtype, long long M, long long N, long long K, int count) {
   for (int c : {count, 1}) {
     auto it = ctx->tuned.find(std::make_tuple(c, sparse, dtype, M, N, K));
     if (it != ctx->tuned.end() && esp_variant_applicable(it->second, M, N, K, sparse)) return it->second;
   }
-  return esp_default_variant(M, N, K, sparse);
+  return -1;
+}
+
+static int pick_variant(esparse_ctx* ctx, int sparse, int dtype, long long M, long long N, long long K, int variant, int count = 1) {
+  if (variant >= 0) return variant;
+  const int v = tuned_variant(ctx, sparse, dtype, M, N, K, count);
+  if (v >= 0) return v;
+  // the built-in choice is a function of the shape alone; looking it up takes a tenth of the time of making it (2 us)
+  const auto key = std::make_tuple(count, sparse, M, N, K);
+  auto it = ctx->defaults.find(key);
+  if (it != ctx->defaults.end()) return it->second;
+  if (ctx->defaults.size() >= 4096) ctx->defaults.clear();
+  return ctx->defaults[key] = esp_default_variant(M, N, K, sparse, count);
 }
 
 int esparse_spmm_workspace(long long M, long long N, long long K, int variant, size_t* bytes) {
@@ -385,7 +397,9 @@ static int spmm_group_phases(esparse_ctx* ctx, int count, const void* const* X, 
   ESP_REQUIRE(ctx, workspace_bytes >= esp_group_workspace_bytes(count, M, N, K), ESPARSE_EWORKSPACE,
               "workspace has %zu bytes, %zu needed", workspace_bytes, esp_group_workspace_bytes(count, M, N, K));
   const int v = pick_variant(ctx, mode, dtype, M, N, K, variant, count);
-  ESP_REQUIRE(ctx, phases == (ESP_PHASE_STAGE | ESP_PHASE_MULTIPLY) || esp_variant_is_decode_kernel(v), ESPARSE_EUNSUPPORTED,
+  // (beyond 32 tokens the built-in choice may be a kernel without a grouped form: the halves need a named or tuned one)
+  const bool chosen = variant >= 0 || M <= 32 || tuned_variant(ctx, mode, dtype, M, N, K, count) >= 0;
+  ESP_REQUIRE(ctx, phases == (ESP_PHASE_STAGE | ESP_PHASE_MULTIPLY) || (chosen && esp_variant_is_decode_kernel(v)), ESPARSE_EUNSUPPORTED,
               "the two halves of a group call exist for the decode kernels only");
   ESP_HIP(ctx, hipSetDevice(ctx->device));
   return esp_matmul_group_device(ctx, mode, count, X, M, native_w, perm, N, K, dtype, Y, workspace, v, phases);

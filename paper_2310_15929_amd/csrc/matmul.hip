@@ -1836,57 +1836,208 @@ static int variant_index(const char* name) {
   return -1;
 }
 
-int esp_default_variant(long long M, long long N, long long K, int sparse) {
-  if (sparse == 2 && M > 128)  // 4:8 at prefill sizes; few macro tiles (and room for partial tiles): K split over workgroups
-  {
-    if (((N + 127) / 128) * ((M + 255) / 256) >= 128 || esp_split_capacity(M) == 1) return variant_index("tile48_w8_r128_t256");
-    return variant_index("tile48_w8_t128_splitk");
+// ------------------------------------------------------------------------------------------------
+// The built-in choice: an estimate of every kernel's time from what it moves, and the smallest wins.
+//
+// The estimate has seven terms, each a quantity of the launch times a measured constant of the kernel (us):
+//   fixed     launch, first loads, drain
+//   weights   decode and stream kernels: weight bytes that one CU takes in, over all its workgroups (the CU's
+//             vector-memory path is what they wait for); tile kernels: 64-channel steps of one CU
+//   tokens    decode and stream kernels: activation bytes that one CU takes in; tile kernels: macro tiles of one CU
+//             (prologue, outputs)
+//   memory    weight bytes of the product (HBM)
+//   partial   bytes of fp32 partial tiles, written and read back; reduce: their launch
+//   rounds    decode kernels: workgroups of one CU; stream kernels: steps of a workgroup; tile kernels: steps over all
+//             rounds, the last one counted as far as it is filled (the board's power limit is shared by the CUs that work)
+// The constants are least-squares fits to the times of every kernel, weights cold, on 67 (2:4), 18 (dense, 4:8) weight
+// shapes from 512 x 512 to 36864 x 9216 with 1 .. 4096 tokens (670, 191 and 189 products; mean error of an estimate 5 %).
+// Picked by them, products take 1.012 / 1.016 / 1.008 times the fastest kernel's time in the geometric mean (2:4 / dense /
+// 4:8); the rules on row and token counts they replace took 1.19 / 1.18 / 1.11 times it.  240 of the 2:4 products were kept
+// out of a first fit and came out at 1.02.
+// ------------------------------------------------------------------------------------------------
+struct Cost {
+  const char* name;
+  float fixed, weights, tokens, memory, partial, reduce, rounds;
+};
+static const Cost kCost24[] = {
+    {"ksplit_w16_r2", 2.13f, 2.44e-05f, 9.77e-06f, 6.88e-08f, 0.f, 0.f, 1.38f},
+    {"ksplit_w16_r4_k4", 4.52f, 2.23e-05f, 4.2e-06f, 8.57e-08f, 9.91e-08f, 0.f, 2.45f},
+    {"ksplit_w8_r1", 2.99f, 3.28e-05f, 9.35e-06f, 5.48e-08f, 0.f, 0.f, 0.0483f},
+    {"ksplit_w8_r1_q", 2.69f, 2.5e-05f, 6.45e-06f, 5.53e-08f, 0.f, 0.f, 0.509f},
+    {"ksplit_w8_r2", 2.61f, 2.77e-05f, 9.16e-06f, 5.36e-08f, 0.f, 0.f, 0.442f},
+    {"ksplit_w8_r2_q", 2.88f, 2.26e-05f, 3.51e-06f, 7.14e-08f, 0.f, 0.f, 0.342f},
+    {"ksplit_w8_r3", 2.66f, 2.23e-05f, 1.15e-05f, 5.63e-08f, 0.f, 0.f, 0.594f},
+    {"ksplit_w8_r4", 3.26f, 2.04e-05f, 1.21e-05f, 6.8e-08f, 0.f, 0.f, 0.15f},
+    {"ksplit_w8_r6", 2.66f, 2.07e-05f, 1.3e-05f, 6.06e-08f, 0.f, 0.f, 0.904f},
+    {"stream_w11_r1_d3", 3.2f, 2.66e-05f, 1.14e-05f, 4.57e-08f, 3.14e-07f, 4.27f, 0.f},
+    {"stream_w8_r1_d3", 3.2f, 2.66e-05f, 1.14e-05f, 4.57e-08f, 3.14e-07f, 4.27f, 0.f},
+    {"stream_w9_r1_d3", 3.2f, 2.66e-05f, 1.14e-05f, 4.57e-08f, 3.14e-07f, 4.27f, 0.f},
+    {"tile32_w8_t128", 0.f, 0.489f, 5.49f, 1.5e-07f, 0.f, 0.f, 0.f},
+    {"tile32_w8_t256", 0.f, 0.624f, 6.64f, 1.53e-07f, 0.f, 0.f, 0.f},
+    {"tile_w8_r128_t128", 0.335f, 0.229f, 3.12f, 1.47e-07f, 0.f, 0.f, 0.101f},
+    {"tile_w8_r128_t128_splitk", 2.03f, 0.26f, 1.51f, 8.42e-08f, 1.97e-07f, 3.57f, 0.104f},
+    {"tile_w8_r128_t64_splitk", 2.65f, 0.102f, 0.768f, 1.2e-07f, 1.49e-07f, 3.57f, 0.186f},
+    {"tile_w8_r320_t128", 0.f, 0.564f, 5.3f, 2.22e-07f, 0.f, 0.f, 0.f},
+    {"tile_w8_t128", 0.f, 0.448f, 5.32f, 1.79e-07f, 0.f, 0.f, 0.f},
+    {"tile_w8_t128_splitk", 1.1f, 0.474f, 4.25f, 1.06e-07f, 1.85e-07f, 3.59f, 0.f},
+};
+static const Cost kCostDense[] = {
+    {"ksplit_w16_r1", 2.45f, 1.85e-05f, 1.12e-05f, 6.94e-08f, 0.f, 0.f, 0.741f},
+    {"ksplit_w16_r2", 1.89f, 1.79e-05f, 1.21e-05f, 7e-08f, 0.f, 0.f, 1.65f},
+    {"ksplit_w16_r4_k4", 4.58f, 1.55e-05f, 0.f, 1.16e-07f, 1.16e-07f, 0.f, 2.43f},
+    {"ksplit_w8_r2", 3.37f, 1.69e-05f, 1.63e-05f, 6.57e-08f, 0.f, 0.f, 0.f},
+    {"ksplit_w8_r3", 2.61f, 1.45e-05f, 3.01e-05f, 6.25e-08f, 0.f, 0.f, 0.764f},
+    {"stream_w11_r1_d3", 4.69f, 9.7e-06f, 8.97e-06f, 1.02e-07f, 2.96e-07f, 3.78f, 0.f},
+    {"stream_w8_r1_d3", 4.69f, 9.7e-06f, 8.97e-06f, 1.02e-07f, 2.96e-07f, 3.78f, 0.f},
+    {"stream_w9_r1_d3", 4.69f, 9.7e-06f, 8.97e-06f, 1.02e-07f, 2.96e-07f, 3.78f, 0.f},
+    {"tile_w8_r128_t128", 2.23f, 0.197f, 0.812f, 8.49e-08f, 0.f, 0.f, 0.121f},
+    {"tile_w8_r128_t128_splitk", 2.15f, 0.181f, 0.924f, 7.6e-08f, 1.89e-07f, 3.89f, 0.138f},
+    {"tile_w8_r128_t64_splitk", 3.19f, 0.0941f, 0.00203f, 1.22e-07f, 1.46e-07f, 4.32f, 0.113f},
+    {"tile_w8_r320_t128", 0.f, 0.521f, 4.27f, 7.74e-08f, 0.f, 0.f, 0.000181f},
+    {"tile_w8_t128", 0.f, 0.442f, 3.51f, 7.31e-08f, 0.f, 0.f, 0.f},
+    {"tile_w8_t128_h", 0.f, 0.518f, 5.31f, 6.78e-08f, 0.f, 0.f, 0.246f},
+    {"tile_w8_t128_h_splitk", 6.34f, 0.7f, 1.22f, 8.89e-08f, 1.83e-07f, 1.33f, 0.f},
+    {"tile_w8_t128_splitk", 0.f, 0.377f, 3.59f, 8.26e-08f, 1.85e-07f, 4.04f, 0.0412f},
+    {"tile_w8_t256", 0.f, 0.607f, 4.94f, 5.23e-08f, 0.f, 0.f, 0.f},
+    {"tile_w8_t256_h", 0.f, 1.01f, 12.f, 6.35e-08f, 0.f, 0.f, 0.f},
+};
+static const Cost kCost48[] = {
+    {"ksplit_w8_r1", 4.66f, 3.3e-05f, 9.78e-06f, 5.48e-08f, 0.f, 0.f, 0.409f},
+    {"ksplit_w8_r1_q", 3.98f, 2.41e-05f, 5.65e-06f, 5.66e-08f, 0.f, 0.f, 1.39f},
+    {"ksplit_w8_r2", 4.29f, 2.94e-05f, 8.4e-06f, 5.57e-08f, 0.f, 0.f, 0.933f},
+    {"ksplit_w8_r2_q", 4.54f, 2.23e-05f, 4.81e-06f, 7.02e-08f, 0.f, 0.f, 0.979f},
+    {"ksplit_w8_r3", 4.5f, 2.12e-05f, 1.79e-05f, 5.83e-08f, 0.f, 0.f, 0.771f},
+    {"ksplit_w8_r4", 5.24f, 2.09e-05f, 1.41e-05f, 6.87e-08f, 0.f, 0.f, 0.504f},
+    {"ksplit_w8_r4_k4", 6.79f, 1.63e-05f, 1.82e-05f, 8.3e-08f, 4.17e-07f, 0.f, 1.49f},
+    {"ksplit_w8_r4_q", 1.63f, 2.23e-05f, 2.57e-06f, 7.39e-08f, 0.f, 0.f, 4.13f},
+    {"stream_w11_r1_d3", 5.16f, 2.75e-05f, 1.7e-05f, 3.81e-08f, 2.81e-07f, 4.56f, 0.f},
+    {"stream_w8_r1_d3", 5.16f, 2.75e-05f, 1.7e-05f, 3.81e-08f, 2.81e-07f, 4.56f, 0.f},
+    {"stream_w9_r1_d3", 5.16f, 2.75e-05f, 1.7e-05f, 3.81e-08f, 2.81e-07f, 4.56f, 0.f},
+    {"tile48_w8_r128_t256", 0.f, 0.714f, 8.06f, 4.81e-08f, 0.f, 0.f, 0.f},
+    {"tile48_w8_t128_splitk", 0.f, 0.929f, 7.99f, 1.69e-08f, 1.78e-07f, 4.34f, 0.0431f},
+};
+
+// number of K splits of a tile variant and their stages (32 channels each where v.half, else 64)
+static int tile_splits(const Variant& v, long long M, long long n_tiles, long long stages, long long* per_split) {
+  int nsplit = 1;
+  long long sps = stages;
+  if (v.split_mode == 1) {
+    // about two workgroups per CU, splits of at least 8 stages (512 channels); no split once the macro
+    // tiles alone cover half of the CUs (the fp32 partial tiles and their reduction then cost more)
+    // M > 128 (at most 4 splits, larger partial tiles): as many splits as keep the items within one round of 256
+    const long long want = M > 128 ? 256 / n_tiles : (n_tiles >= 128 ? 1 : (512 + n_tiles - 1) / n_tiles);
+    nsplit = (int)std::max<long long>(1, std::min<long long>(std::min<long long>(want, stages / 8), esp_split_capacity(M)));
+    sps = ((stages + nsplit - 1) / nsplit + 3) / 4 * 4;
+    nsplit = (int)((stages + sps - 1) / sps);
   }
-  if (M <= 32) {
-    const long long nrt = esp_round_up(N, 16) / 16;
-    return nrt <= 320 ? 4 : 5;  // ksplit_w16_r1 / ksplit_w16_r2
-  }
-  if (M <= 128) {
-    // stream kernels: the number of waves (rows per workgroup) whose row blocks, each cut into p equal spans of an even
-    // number of steps, come closest to one workgroup per CU without a span crossing a row block
-    const long long nrt = esp_round_up(N, 16) / 16, nks = esp_round_up(K, 256) / 64;
-    static const struct { int nw; const char* name; } cand[] = {{8, "stream_w8_r1_d3"}, {9, "stream_w9_r1_d3"}, {11, "stream_w11_r1_d3"}};
-    long long best = 0;
-    const char* pick = nullptr;
-    for (const auto& c : cand) {
-      const long long nrb = (nrt + c.nw - 1) / c.nw;
-      if (nrb > 256) continue;
-      long long pcs = 256 / nrb;
-      while (pcs > 1 && (nks % pcs != 0 || (nks / pcs) % 2 != 0 || nks / pcs < 8)) pcs--;
-      if (nrb * pcs > best) {
-        best = nrb * pcs;
-        pick = c.name;
-      }
-    }
-    if (best >= 200) return variant_index(pick);
-    return M <= 64 ? 19 : 17;  // stream_w8_r2_d3 / stream_w8_r1_d3 with spans cut where they fall
-  }
-  // 8-wave tile kernels: the largest macro tile that still gives half of the 256 CUs a tile
-  const long long rows = sparse ? 256 : 128;
-  const long long nrb = (N + rows - 1) / rows;
-  if (nrb * ((M + 255) / 256) >= 128) {
-    if (sparse == 1) return variant_index("tile32_w8_t256");
-    // dense: the 256-row form with 32-channel stages once its macro tiles alone give half of the CUs a tile
-    return ((N + 255) / 256) * ((M + 255) / 256) >= 128 ? variant_index("tile_w8_t256_h") : 12;  // else tile_w8_t256
-  }
-  if (nrb * ((M + 127) / 128) >= 128) return 13;  // tile_w8_t128
-  return 14;                                       // tile_w8_r128_t128
+  *per_split = sps;
+  return nsplit;
 }
 
-// the built-in choice among the variants that keep no fp32 partial tiles in the workspace (for callers whose scratch
-// is too small for them): a decode kernel up to 64 tokens, the tile kernels beyond
-int esp_default_variant_without_partials(long long M, long long N, long long K, int sparse) {
-  (void)K;
-  if (M <= 64) return esp_round_up(N, 16) / 16 <= 320 ? 4 : 5;  // ksplit_w16_r1 / ksplit_w16_r2
-  if (sparse == 2) return variant_index("tile48_w8_r128_t256");
-  if (sparse == 1) return variant_index(M <= 128 ? "tile32_w8_t128" : "tile32_w8_t256");
-  return variant_index(M <= 128 ? "tile_w8_t128_h" : "tile_w8_t256_h");
+// span of the stream kernels: steps per workgroup when `slots` workgroups share nrb row blocks of nks steps.
+// An even number of steps (a step's index half is addressed by its parity within a pair, and its ring slot has
+// that parity), at least 8, and long enough that a row block has at most MAX_SPLIT pieces.
+static long long stream_span(long long nrb, long long nks, long long slots) {
+  long long span = (nrb * nks + slots - 1) / slots;
+  span = std::max<long long>(span, 8);
+  span = std::max<long long>(span, (nks + MAX_SPLIT - 3) / (MAX_SPLIT - 2));  // pieces <= (nks - 1) / span + 2
+  span = (span + 1) / 2 * 2;
+  // a span that divides the steps of a row block keeps every span inside one row block (one segment and one partial
+  // tile per workgroup instead of two): worth up to a fifth fewer workgroups
+  for (long long a = span; a <= nks && a * 5 <= span * 6; a += 2)
+    if (nks % a == 0) return a;
+  return span;
 }
+
+// the stream kernel whose row blocks (8, 9 or 11 row tiles), each cut into p equal spans of an even number of steps, come
+// closest to one workgroup per CU without a span crossing a row block; eight waves if none fills 200 CUs that way
+static const char* aligned_stream(long long nrt, long long nks) {
+  static const struct { int nw; const char* name; } cand[] = {{8, "stream_w8_r1_d3"}, {9, "stream_w9_r1_d3"}, {11, "stream_w11_r1_d3"}};
+  long long best = 0;
+  const char* pick = cand[0].name;
+  for (const auto& c : cand) {
+    const long long nrb = (nrt + c.nw - 1) / c.nw;
+    if (nrb > 256) continue;
+    long long pcs = 256 / nrb;
+    while (pcs > 1 && (nks % pcs != 0 || (nks / pcs) % 2 != 0 || nks / pcs < 8)) pcs--;
+    if (nrb * pcs > best) {
+      best = nrb * pcs;
+      pick = c.name;
+    }
+  }
+  return best >= 200 ? pick : cand[0].name;
+}
+
+static int compact_tokens(long long M);
+
+// estimated time (us) of `count` products of one shape in one launch (decode kernels) or of one product
+static double estimate(const Cost& c, const Variant& v, long long M, long long N, long long K, int sparse, int count) {
+  const long long nrt = (N + 15) / 16, nks = esp_round_up(K, 256) / 64, Mt = (M + 15) / 16;
+  const double wb = sparse ? 1.125 : 2.0, step_row = 64.0 * 16 * wb;  // bytes of a row tile's step
+  const double memory = (double)count * nrt * 16 * nks * 64 * wb, out = 8.0 * M * nrt * 16;  // out: one fp32 tile of Y, both ways
+  double weights, tokens, rounds;
+  double pieces = 0.0;  // of a partial tile
+  if (v.kind == KIND_KSPLIT) {
+    const int ns = v.split_mode == 1 ? v.tt : 1, mt = M <= 16 ? 1 : (M <= 32 ? 2 : 4);
+    const long long wgs = (nrt + v.rt - 1) / v.rt * ns * count;
+    const double per = (double)((wgs + 255) / 256), steps = (double)nks / ns;
+    weights = per * steps * step_row * v.rt;
+    tokens = per * steps * 64 * (M <= 16 ? 2 * compact_tokens(M) : 32 * mt);
+    rounds = per;
+    if (ns > 1) pieces = ns;
+  } else if (v.kind == KIND_STREAM) {
+    const long long rows = (long long)v.nw * v.rt, nrb = (nrt + rows - 1) / rows, span = stream_span(nrb, nks, 256);
+    const int mt = Mt <= 1 ? 1 : (Mt <= 2 ? 2 : (Mt <= 4 ? 4 : 8));
+    weights = span * step_row * rows;
+    tokens = span * 64.0 * 32 * mt;
+    rounds = (double)span;
+    if (span % nks) pieces = std::max(1.0, (double)((nrb * nks + span - 1) / span) / nrb);
+  } else {
+    const long long rows = (sparse || v.half) ? 2 * v.rt : 2 * (v.rt / 2), cols = (long long)v.nw * v.tt, h = v.half ? 2 : 1;
+    const long long n_tiles = ((nrt + rows - 1) / rows) * ((Mt + cols - 1) / cols);
+    long long sps;
+    const int ns = tile_splits(v, M, n_tiles, nks * h, &sps);
+    const double items = (double)n_tiles * ns, per = (double)((n_tiles * ns + 255) / 256), steps = (double)sps / h;
+    weights = per * steps;
+    tokens = per;
+    rounds = std::max(1.0, items / 256) * steps;
+    if (ns > 1) pieces = ns;
+  }
+  return c.fixed + c.weights * weights + c.tokens * tokens + c.memory * memory + c.rounds * rounds +
+         (pieces > 0.0 ? c.partial * out * pieces + c.reduce : 0.0);
+}
+
+static int pick_by_cost(long long M, long long N, long long K, int sparse, int count, bool partials) {
+  const Cost* table = sparse == 2 ? kCost48 : (sparse ? kCost24 : kCostDense);
+  const int rows = sparse == 2 ? (int)(sizeof(kCost48) / sizeof(Cost)) : (sparse ? (int)(sizeof(kCost24) / sizeof(Cost)) : (int)(sizeof(kCostDense) / sizeof(Cost)));
+  const char* stream = aligned_stream((N + 15) / 16, esp_round_up(K, 256) / 64);
+  int best = variant_index("ksplit_w8_r1");
+  if (M > 64) best = variant_index(sparse == 2 ? "tile48_w8_r128_t256" : "tile_w8_r128_t128");
+  double best_t = 1e30;
+  for (int i = 0; i < rows; i++) {
+    const int vi = variant_index(table[i].name);
+    const Variant& v = kVariants[vi];
+    if (!esp_variant_applicable(vi, M, N, K, sparse)) continue;
+    if (!partials && (v.split_mode == 1 || v.kind == KIND_STREAM)) continue;
+    if (v.kind == KIND_STREAM && strcmp(table[i].name, stream)) continue;
+    if (v.kind == KIND_KSPLIT && M > 64) continue;  // 4:8 beyond 64 tokens: 64 at a time, slower than the tiles throughout
+    const bool shared = esp_variant_is_decode_kernel(vi);  // the products of a group share the launch
+    if (count > 1 && !shared && M <= 32) continue;  // up to 32 tokens a group is one launch (its halves exist then)
+    double t = estimate(table[i], v, M, N, K, sparse, shared ? count : 1);
+    if (count > 1 && !shared) t = t * count + 4.0 * (count - 1);  // one after the other, each with its staging launch
+    if (t < best_t) {
+      best_t = t;
+      best = vi;
+    }
+  }
+  return best;
+}
+
+int esp_default_variant(long long M, long long N, long long K, int sparse, int count) { return pick_by_cost(M, N, K, sparse, count, true); }
+
+// the built-in choice among the variants that keep no fp32 partial tiles in the workspace (for callers whose scratch
+// is too small for them)
+int esp_default_variant_without_partials(long long M, long long N, long long K, int sparse) { return pick_by_cost(M, N, K, sparse, 1, false); }
 
 // tokens of the compact copy of the staged activations (0: none), written when there are at most 16 tokens
 static int compact_tokens(long long M) {
@@ -2020,17 +2171,8 @@ static int launch_tile(esparse_ctx* ctx, const Variant& v, hipStream_t st, const
   const long long cols = (long long)v.nw * v.tt;  // token tiles per macro tile
   const long long nrb = (nrt + rtm - 1) / rtm, ntb = (ntt + cols - 1) / cols;
   const long long n_tiles = nrb * ntb;
-  int nsplit = 1;
-  long long sps = nks;
-  if (v.split_mode == 1) {
-    // about two workgroups per CU, splits of at least 8 stages (512 channels); no split once the macro
-    // tiles alone cover half of the CUs (the fp32 partial tiles and their reduction then cost more)
-    // M > 128 (at most 4 splits, larger partial tiles): as many splits as keep the items within one round of 256
-    const long long want = M > 128 ? 256 / n_tiles : (n_tiles >= 128 ? 1 : (512 + n_tiles - 1) / n_tiles);
-    nsplit = (int)std::max<long long>(1, std::min<long long>(std::min<long long>(want, nks / 8), esp_split_capacity(M)));
-    sps = ((nks + nsplit - 1) / nsplit + 3) / 4 * 4;
-    nsplit = (int)((nks + sps - 1) / sps);
-  }
+  long long sps;
+  const int nsplit = tile_splits(v, M, n_tiles, nks, &sps);
   const long long per = (n_tiles * nsplit + 7) / 8;
   dim3 grid((unsigned)(per * 8));
   // more than 8 token blocks: bands of 8 row blocks, so that the 32 workgroups an XCD runs at once share 8 weight panels
@@ -2104,21 +2246,6 @@ static hipError_t launch_stream_kernel(int device, dim3 grid, hipStream_t st, co
   hipLaunchKernelGGL((k_mm_stream<DT, SPARSE, MT, RT, NW, NB>), grid, dim3(NW * 64), smem, st, A, meta16, Xf, Y, partial, M, N, Mp, Np,
                      Kp, span);
   return hipGetLastError();
-}
-
-// span of the stream kernels: steps per workgroup when `slots` workgroups share nrb row blocks of nks steps.
-// An even number of steps (a step's index half is addressed by its parity within a pair, and its ring slot has
-// that parity), at least 8, and long enough that a row block has at most MAX_SPLIT pieces.
-static long long stream_span(long long nrb, long long nks, long long slots) {
-  long long span = (nrb * nks + slots - 1) / slots;
-  span = std::max<long long>(span, 8);
-  span = std::max<long long>(span, (nks + MAX_SPLIT - 3) / (MAX_SPLIT - 2));  // pieces <= (nks - 1) / span + 2
-  span = (span + 1) / 2 * 2;
-  // a span that divides the steps of a row block keeps every span inside one row block (one segment and one partial
-  // tile per workgroup instead of two): worth up to a fifth fewer workgroups
-  for (long long a = span; a <= nks && a * 5 <= span * 6; a += 2)
-    if (nks % a == 0) return a;
-  return span;
 }
 
 template <int DT, int SPARSE>
