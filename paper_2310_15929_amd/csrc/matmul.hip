@@ -24,6 +24,7 @@
 //     operand of the dense instruction for token tile tt and step s; the channel re-ordering theta
 //     of Section 3.3 is applied here (X'[t, p] = X[t, theta[p]]), zero padded in both directions.
 #include <algorithm>
+#include <type_traits>
 #include <cstring>
 #include <cstdlib>
 #include <atomic>
@@ -269,7 +270,7 @@ __global__ void __launch_bounds__(256) k_gather_x(GatherArgs args, long long M, 
 // lane from 64 different cache lines per instruction).  Rows are padded by 8 elements so that the TOK
 // tokens of one channel sit in different banks.  Lane l of a wave works on token l % TOK and 8-channel
 // unit l / TOK, so consecutive lanes write consecutive 16-byte units of X'.  K % 8 == 4: the rows are copied 8 bytes at a
-// time (333 x 3020: 5.8 us against 7.3 element by element).  The first entries of theta are on their way with the rows.
+// time (333 x 3020: 5.8 us against 7.3 element by element).
 template <int TOK>
 __global__ void __launch_bounds__(512) k_gather_rows(const uint16_t* __restrict__ X, const int32_t* __restrict__ perm, long long M,
                                                       long long Mp, long long K, long long Kp, uint4* __restrict__ Xf) {
@@ -286,71 +287,66 @@ __global__ void __launch_bounds__(512) k_gather_rows(const uint16_t* __restrict_
   if (t0 >= Mp) return;
   const int stride = (int)K + 8;
   const long long nrows = (M - t0) < TOK ? (M - t0 > 0 ? M - t0 : 0) : TOK;
-  constexpr int UPW = 64 / TOK;  // units per wave and pass
-  const int lane = tid & 63, wave = tid >> 6;
-  const int c = lane % TOK, q = lane / TOK;
-  const int nunits = (int)(Kp / 8), u0 = wave * UPW + q;
-  int4 p0 = {0, 0, 0, 0}, p1 = {0, 0, 0, 0};
-  auto load_theta = [&](int u) {
-    const int k0 = u * 8;
-    if (k0 < K) {  // K % 4 == 0: a unit has eight, four or no real channels
-      p0 = *reinterpret_cast<const int4*>(perm + k0);
-      if (k0 + 8 <= K) p1 = *reinterpret_cast<const int4*>(perm + k0 + 4);
+  auto run = [&](auto eights) {
+    constexpr bool E8 = decltype(eights)::value;  // K % 8 == 0: a unit is entirely inside or outside the real channels
+    if (E8) {
+      const int kc = (int)(K / 8);  // 16-byte chunks per row
+      const uint4* src = reinterpret_cast<const uint4*>(X + t0 * K);
+      for (int i = tid; i < (int)nrows * kc; i += 512) {
+        const int row = i / kc, col = i - row * kc;
+        s_rows4[(row * stride) / 8 + col] = src[i];
+      }
+    } else {
+      const int kc = (int)(K / 4);
+      const uint2* src = reinterpret_cast<const uint2*>(X + t0 * K);
+      for (int i = tid; i < (int)nrows * kc; i += 512) {
+        const int row = i / kc, col = i - row * kc;
+        reinterpret_cast<uint2*>(s_rows4)[(row * stride) / 4 + col] = src[i];
+      }
     }
-  };
-  if (perm) load_theta(u0);
-  if ((K & 7) == 0) {
-    const int kc = (int)(K / 8);  // 16-byte chunks per row
-    const uint4* src = reinterpret_cast<const uint4*>(X + t0 * K);
-    for (int i = tid; i < (int)nrows * kc; i += 512) {
-      const int row = i / kc, col = i - row * kc;
-      s_rows4[(row * stride) / 8 + col] = src[i];
-    }
-  } else {
-    const int kc = (int)(K / 4);
-    const uint2* src = reinterpret_cast<const uint2*>(X + t0 * K);
-    for (int i = tid; i < (int)nrows * kc; i += 512) {
-      const int row = i / kc, col = i - row * kc;
-      reinterpret_cast<uint2*>(s_rows4)[(row * stride) / 4 + col] = src[i];
-    }
-  }
-  __syncthreads();
-  const long long t = t0 + c;
-  const long long ns = Kp / 32;
-  const long long obase = (t / 16) * ns * 64 + (t % 16);
-  const uint16_t* row = s_rows + c * stride;
-  const bool live = t < M;
-  for (int u = u0; u < nunits; u += 8 * UPW) {
-    const int k0 = u * 8;
-    uint16_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (live && k0 < K) {
-      const bool whole = k0 + 8 <= K;
-      if (perm) {
-        v[0] = row[p0.x];
-        v[1] = row[p0.y];
-        v[2] = row[p0.z];
-        v[3] = row[p0.w];
-        if (whole) {
+    __syncthreads();
+    constexpr int UPW = 64 / TOK;  // units per wave and pass
+    const int lane = tid & 63, wave = tid >> 6;
+    const int c = lane % TOK, q = lane / TOK;
+    const long long t = t0 + c;
+    const long long ns = Kp / 32;
+    const long long obase = (t / 16) * ns * 64 + (t % 16);
+    const uint16_t* row = s_rows + c * stride;
+    const bool live = t < M;
+    const int nunits = (int)(Kp / 8);
+    for (int u = wave * UPW + q; u < nunits; u += 8 * UPW) {
+      const int k0 = u * 8;
+      uint16_t v[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+      if (live && k0 < K) {
+        const bool whole = E8 || k0 + 8 <= K;  // else four channels
+        if (perm) {
+          const int4 p0 = *reinterpret_cast<const int4*>(perm + k0);
+          const int4 p1 = *reinterpret_cast<const int4*>(perm + (whole ? k0 + 4 : k0));
+          v[0] = row[p0.x];
+          v[1] = row[p0.y];
+          v[2] = row[p0.z];
+          v[3] = row[p0.w];
           v[4] = row[p1.x];
           v[5] = row[p1.y];
           v[6] = row[p1.z];
           v[7] = row[p1.w];
-        }
-      } else {
+        } else {
 #pragma unroll
-        for (int e = 0; e < 8; e++)
-          if (e < 4 || whole) v[e] = row[k0 + e];
+          for (int e = 0; e < 8; e++) v[e] = row[whole || e < 4 ? k0 + e : k0];
+        }
+        if (!E8 && !whole) v[4] = v[5] = v[6] = v[7] = 0;
       }
+      uint4 o;
+      o.x = v[0] | ((uint32_t)v[1] << 16);
+      o.y = v[2] | ((uint32_t)v[3] << 16);
+      o.z = v[4] | ((uint32_t)v[5] << 16);
+      o.w = v[6] | ((uint32_t)v[7] << 16);
+      // unit u = 4 s32 + g of token tile t / 16: X' unit (tt ns + s32) 64 + 16 g + t % 16
+      Xf[obase + (long long)(u >> 2) * 64 + (u & 3) * 16] = o;
     }
-    if (perm && u + 8 * UPW < nunits) load_theta(u + 8 * UPW);
-    uint4 o;
-    o.x = v[0] | ((uint32_t)v[1] << 16);
-    o.y = v[2] | ((uint32_t)v[3] << 16);
-    o.z = v[4] | ((uint32_t)v[5] << 16);
-    o.w = v[6] | ((uint32_t)v[7] << 16);
-    // unit u = 4 s32 + g of token tile t / 16: X' unit (tt ns + s32) 64 + 16 g + t % 16
-    Xf[obase + (long long)(u >> 2) * 64 + (u & 3) * 16] = o;
-  }
+  };
+  if ((K & 7) == 0) run(std::true_type{});
+  else run(std::false_type{});
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -771,6 +767,46 @@ __global__ void __launch_bounds__(NW * 64) k_mm_ksplit(KsplitArgs args, long lon
   }
 }
 
+// Rows of Y start at any element if N is no multiple of 8.  A wave then puts a token's outputs into its LDS slice at the
+// offset (modulo 8) that they have in Y, so that whole 16-byte pieces of Y are 16-byte pieces of the slice; only the first
+// and last piece of a token leave element by element.  Stored straight from the accumulators such rows left 2 bytes per
+// lane and instruction: 1024 x 5003 x 4096, 2:4, the 256-token tile 83.6 -> 75.6 us, the 128-token one 65.2 -> 59.7 (52.3 with 5008
+// outputs, whose rows share no line); 333 x 5003 x 3020 34.1 -> 32.8.
+__device__ __forceinline__ unsigned row_shift(long long t, long long N, long long n0) { return (unsigned)(t * N + n0) & 7u; }
+
+__device__ __forceinline__ void slice_put(unsigned char* row, unsigned feature, unsigned shift, uint2 v) {
+  uint16_t* d = reinterpret_cast<uint16_t*>(row) + feature + shift;
+  d[0] = (uint16_t)v.x;
+  d[1] = (uint16_t)(v.x >> 16);
+  d[2] = (uint16_t)v.y;
+  d[3] = (uint16_t)(v.y >> 16);
+}
+
+// TOKENS rows of FEATS outputs (row_bytes >= 2 FEATS + 16 apart) to tokens t0 .., features n0 .. of Y
+template <int TOKENS, int FEATS>
+__device__ __forceinline__ void store_rows_any(uint16_t* __restrict__ Y, long long M, long long N, long long t0, long long n0,
+                                               const unsigned char* slice, unsigned row_bytes, unsigned lane) {
+  constexpr unsigned W = FEATS / 8 + 1;
+  const int cnt = (int)(N - n0 < FEATS ? N - n0 : FEATS);
+  for (unsigned q = lane; q < TOKENS * W; q += 64) {
+    const unsigned tl = q / W, w = q - tl * W;
+    const long long t = t0 + tl;
+    if (t >= M) continue;
+    const unsigned shift = row_shift(t, N, n0);
+    const int i0 = 8 * (int)w - (int)shift;  // the piece's first output
+    const uint4 v = *reinterpret_cast<const uint4*>(slice + tl * row_bytes + 16 * w);
+    uint16_t* dst = Y + t * N + n0 + i0;
+    if (i0 >= 0 && i0 + 8 <= cnt) {
+      *reinterpret_cast<uint4*>(dst) = v;
+    } else {
+      const uint32_t d[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+      for (int e = 0; e < 8; e++)
+        if (i0 + e >= 0 && i0 + e < cnt) dst[e] = (uint16_t)(d[e / 2] >> (16 * (e & 1)));
+    }
+  }
+}
+
 // ------------------------------------------------------------------------------------------------
 // variant "tile" (prefill sizes, MFMA-bound): a workgroup of 4 waves (2 x 2) owns a macro tile of
 // RTM row tiles x 2*TC token tiles (of 16); each wave owns TR x TC tiles (sparse: TR = TC = 8, i.e.
@@ -1098,7 +1134,7 @@ __device__ __attribute__((always_inline)) void tile_pipeline(
 #endif
 
   const int c = (int)(st.lane & 15), g = (int)(st.lane >> 4);
-  if (nsplit == 1 && (N & 7) == 0) {
+  if (nsplit == 1) {
     // Outputs through LDS: a wave transposes its TR x TC tiles, CH tokens at a time, in a private slice of the (now idle)
     // operand rings and stores runs of 32 TR bytes (the wave's 16 TR output features of one token) in 16-byte pieces;
     // stored straight from the accumulators a lane would write 8 bytes of 16 different rows of Y per instruction.
@@ -1123,6 +1159,8 @@ __device__ __attribute__((always_inline)) void tile_pipeline(
     }
     const long long t_wave = (tt_base + st.wc * TC) * 16, n_wave = (rt_macro + st.wr * TR) * 16;
     __syncthreads();  // every wave is done with the rings
+    auto leave = [&](auto wide) {
+      constexpr bool WIDE = decltype(wide)::value;
 #pragma unroll
     for (int ph = 0; ph < PHASES; ph++)
 #pragma unroll
@@ -1137,11 +1175,14 @@ __device__ __attribute__((always_inline)) void tile_pipeline(
               uint2 v;
               v.x = esp_from_float<DT>(a[0]) | ((uint32_t)esp_from_float<DT>(a[1]) << 16);
               v.y = esp_from_float<DT>(a[2]) | ((uint32_t)esp_from_float<DT>(a[3]) << 16);
-              *reinterpret_cast<uint2*>(ep + (16 * jj + c) * ROWB + (16 * i + 4 * g) * 2) = v;
+              if constexpr (WIDE) *reinterpret_cast<uint2*>(ep + (16 * jj + c) * ROWB + (16 * i + 4 * g) * 2) = v;
+              else slice_put(ep + (16 * jj + c) * ROWB, 16 * i + 4 * g, row_shift(t_wave + 16 * (j0 + jj) + c, N, n_wave), v);
             }
         }
         __syncthreads();
-        if (mine) {
+        if (mine && !WIDE) {
+          store_rows_any<CHT * 16, TR * 16>(Y, M, N, t_wave + 16 * j0, n_wave, ep, ROWB, st.lane);
+        } else if (mine) {
           constexpr int PIECES = CHT * 16 * TR * 2;  // 16-byte pieces of the pass
 #pragma unroll
           for (int p = 0; p < (PIECES + 63) / 64; p++) {
@@ -1156,6 +1197,9 @@ __device__ __attribute__((always_inline)) void tile_pipeline(
         }
         __syncthreads();
       }
+    };
+    if ((N & 7) == 0) leave(std::true_type{});
+    else leave(std::false_type{});
     return;
   }
 #pragma unroll
@@ -1166,10 +1210,8 @@ __device__ __attribute__((always_inline)) void tile_pipeline(
     for (int j = 0; j < TC; j++) {
       const long long tt = tt_base + st.wc * TC + j;
       if (tt >= ntt) continue;
-      if (nsplit > 1)  // fp32 partial tile of this K split; k_reduce_splits adds the splits in ascending order
-        *reinterpret_cast<floatx4_t*>(partial + ((long long)split * Mp + tt * 16 + c) * Np + rt * 16 + g * 4) = st.acc[i][j];
-      else
-        store_y4<DT>(Y, M, N, tt * 16 + c, rt * 16 + g * 4, st.acc[i][j]);
+      // fp32 partial tile of this K split; k_reduce_splits adds the splits in ascending order
+      *reinterpret_cast<floatx4_t*>(partial + ((long long)split * Mp + tt * 16 + c) * Np + rt * 16 + g * 4) = st.acc[i][j];
     }
   }
 }
@@ -1429,8 +1471,9 @@ __global__ void __launch_bounds__(512) k_mm_tile32(const uint4* __restrict__ A, 
     ep = (st.wave & 3u) == 0 ? reinterpret_cast<unsigned char*>(s_a0)
                              : ((st.wave & 3u) == 1 ? reinterpret_cast<unsigned char*>(s_a1)
                                                     : ((st.wave & 3u) == 2 ? reinterpret_cast<unsigned char*>(s_a2) : reinterpret_cast<unsigned char*>(s_b0)));
-  const bool wide = (N & 7) == 0 && nsplit == 1;  // 16-byte stores of 8 output features
-  if (wide) {
+  if (nsplit == 1) {
+    auto leave = [&](auto wide) {
+      constexpr bool WIDE = decltype(wide)::value;  // 16-byte stores of 8 output features
 #pragma unroll
     for (int ph = 0; ph < PHASES; ph++)
 #pragma unroll
@@ -1444,11 +1487,14 @@ __global__ void __launch_bounds__(512) k_mm_tile32(const uint4* __restrict__ A, 
               uint2 v;
               v.x = esp_from_float<DT>(acc[i][j][4 * a]) | ((uint32_t)esp_from_float<DT>(acc[i][j][4 * a + 1]) << 16);
               v.y = esp_from_float<DT>(acc[i][j][4 * a + 2]) | ((uint32_t)esp_from_float<DT>(acc[i][j][4 * a + 3]) << 16);
-              *reinterpret_cast<uint2*>(ep + r32 * EP_ROW + (32 * i + 8 * a + 4 * h) * 2) = v;
+              if constexpr (WIDE) *reinterpret_cast<uint2*>(ep + r32 * EP_ROW + (32 * i + 8 * a + 4 * h) * 2) = v;
+              else slice_put(ep + r32 * EP_ROW, 32 * i + 8 * a + 4 * h, row_shift(t_wave + 32 * j + r32, N, n_wave), v);
             }
         }
         __syncthreads();
-        if (mine) {
+        if (mine && !WIDE) {
+          store_rows_any<32, 128>(Y, M, N, t_wave + 32 * j, n_wave, ep, EP_ROW, st.lane);
+        } else if (mine) {
 #pragma unroll
           for (int p = 0; p < 8; p++) {
             const unsigned tl = p * 4u + (st.lane >> 4), piece = st.lane & 15u;
@@ -1460,6 +1506,9 @@ __global__ void __launch_bounds__(512) k_mm_tile32(const uint4* __restrict__ A, 
         }
         __syncthreads();
       }
+    };
+    if ((N & 7) == 0) leave(std::true_type{});
+    else leave(std::false_type{});
   } else {
 #pragma unroll
     for (int j = 0; j < TJ; j++)
@@ -1470,11 +1519,7 @@ __global__ void __launch_bounds__(512) k_mm_tile32(const uint4* __restrict__ A, 
           const long long t = t_wave + 32 * j + r32;
           const long long n = n_wave + 32 * i + 8 * a + 4 * h;
           const floatx4_t v = {acc[i][j][4 * a], acc[i][j][4 * a + 1], acc[i][j][4 * a + 2], acc[i][j][4 * a + 3]};
-          if (nsplit > 1) {
-            if (t < Mp && n < Np) *reinterpret_cast<floatx4_t*>(partial + ((long long)split * Mp + t) * Np + n) = v;
-          } else {
-            store_y4<DT>(Y, M, N, t, n, v);
-          }
+          if (t < Mp && n < Np) *reinterpret_cast<floatx4_t*>(partial + ((long long)split * Mp + t) * Np + n) = v;
         }
   }
 }

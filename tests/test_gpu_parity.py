@@ -564,6 +564,39 @@ def test_few_tokens_gathered_in_the_kernel_equal_staged(esp, ctx, M, K, n, m):
         assert torch.equal(Y, ctx.spmm(X, comp, perm))
 
 
+# row lengths of Y that are no multiple of 8 outputs leave the tile kernels word by word: odd, 2 and 4 modulo 8, a last tile of
+# one output, fewer outputs than a wave owns; a guard behind Y and every kernel that takes the shape
+@pytest.mark.parametrize("N", [1, 30, 129, 260, 321])
+@pytest.mark.parametrize("mode", ["2:4", "4:8", "dense"])
+def test_tile_kernels_store_rows_of_any_length(esp, ctx, N, mode):
+    M, K = 150, 512
+    n, m = (4, 8) if mode == "4:8" else (2, 4)
+    W, X = _rand((N, K), torch.float16, 81, scale=K ** -0.5), _rand((M, K), torch.float16, 82)
+    theta = np.random.default_rng(N).permutation(K) if mode != "dense" else np.arange(K)
+    if mode == "dense":
+        ref = orc.dense_ref(_np(X), _np(W))
+        packed = ctx.dense_pack(W.cuda())
+    else:
+        mask = orc.nm_mask_vectorised(_np(W), np.ones(K), theta, n, m)
+        ref = orc.spmm_ref(_np(X), _np(W), theta, mask)
+        th = torch.tensor(theta, dtype=torch.int32).cuda()
+        comp = ctx.compress(W.cuda(), torch.tensor(mask).cuda(), th, n, m)
+    Xd, ran = X.cuda(), 0
+    for v in range(esp.num_variants()):
+        if not esp.variant_name(v).startswith("tile"):
+            continue
+        buf = torch.full((M * N + 64,), 7.0, dtype=torch.float16, device="cuda")
+        Y = buf[:M * N].view(M, N)
+        try:
+            ctx.dense_gemm(Xd, packed, N, variant=v, out=Y) if mode == "dense" else ctx.spmm(Xd, comp, th, variant=v, out=Y)
+        except esp.EsparseError:
+            continue
+        ran += 1
+        assert orc.rowwise_rel_error(_np(Y), ref).max() <= TOL[torch.float16], esp.variant_name(v)
+        assert (buf[M * N:] == 7.0).all(), esp.variant_name(v)
+    assert ran >= 3
+
+
 # rows of X that are a multiple of 8 but not of 16 bytes go through the row staging 8 bytes at a time
 @pytest.mark.parametrize("M,K", [(64, 4), (65, 68), (130, 3020), (600, 516)])
 @pytest.mark.parametrize("with_perm", [True, False])
