@@ -88,7 +88,7 @@ int esparse_channel_stats(esparse_ctx* ctx, const void* calib, long long T, long
  * score_out double[K] (s_c = IR_c + alpha AM_c), swaps_out int64[K/block] (exchanges made per
  * block), retained_out double[1] (objective of eq. 5: total metric kept).
  * Ties: equal metric -> lower position kept; equal channel means -> lower channel first; equal
- * improvements -> smallest (i, j).  Synchronises and allocates internal scratch. */
+ * improvements -> smallest (i, j).  Synchronises.  Internal scratch is kept by the context for the next call, 256 MiB of it at most, until esparse_destroy. */
 int esparse_prune(esparse_ctx* ctx, const void* calib, long long T, const void* W, long long N,
                   long long K, esparse_dtype dtype, const esparse_prune_opts* opts,
                   int32_t* perm_out, uint8_t* mask_out, double* score_out, int64_t* swaps_out,
@@ -204,7 +204,7 @@ int esparse_dense_gemm_staged(esparse_ctx* ctx, long long M, const void* packed_
  * ramp-up; the linear layers that read the same hidden state (q/k/v, gate/up) have the same shape.  This
  * call runs count (1..4) products Y[i] = X[i][:, perm[i]] . W'_i^T, all with the same M, N, K, dtype
  * and n:m, through one staging launch and one multiply launch when a decode kernel serves the shape
- * (the default up to 32 tokens), and one after the other otherwise.  X, native_w, perm, Y: HOST arrays of count
+ * (the default up to 32 tokens; beyond, where the built-in estimate prefers it), and one after the other otherwise.  X, native_w, perm, Y: HOST arrays of count
  * DEVICE pointers (perm may be NULL = identity for all, or hold NULL entries); members may share X.
  * workspace: DEVICE, 256-byte aligned, at least esparse_spmm_group_workspace bytes.  Results are
  * bitwise those of esparse_spmm with the same variant.  Errors as esparse_spmm; count outside 1..4:
