@@ -68,7 +68,7 @@ void* esp_host_stage(esparse_ctx* ctx, size_t bytes) {
   if (ctx->h_stage) (void)hipHostFree(ctx->h_stage);
   ctx->h_stage = nullptr;
   ctx->h_stage_bytes = 0;
-  bytes = (bytes + (1u << 20) - 1) >> 20 << 20;
+  bytes = (bytes + 65535) / 65536 * 65536;
   if (hipHostMalloc(&ctx->h_stage, bytes, hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
     ctx->h_stage = nullptr;

@@ -2054,13 +2054,26 @@ static double estimate(const Cost& c, const Variant& v, long long M, long long N
 
 static int pick_by_cost(long long M, long long N, long long K, int sparse, int count, bool partials) {
   const Cost* table = sparse == 2 ? kCost48 : (sparse ? kCost24 : kCostDense);
+  // the rows' variants, looked up by name once (a first call on a shape pays for the estimate)
+  struct Rows {
+    int vi[3][32];
+    Rows() {
+      const Cost* tables[3] = {kCostDense, kCost24, kCost48};
+      const size_t n[3] = {sizeof(kCostDense) / sizeof(Cost), sizeof(kCost24) / sizeof(Cost), sizeof(kCost48) / sizeof(Cost)};
+      for (int m = 0; m < 3; m++)
+        for (size_t i = 0; i < n[m]; i++) vi[m][i] = variant_index(tables[m][i].name);
+    }
+  };
+  static_assert(sizeof(kCostDense) / sizeof(Cost) <= 32 && sizeof(kCost24) / sizeof(Cost) <= 32 && sizeof(kCost48) / sizeof(Cost) <= 32, "room for the rows");
+  static const Rows looked_up;
+  const int* variants = looked_up.vi[sparse == 2 ? 2 : (sparse ? 1 : 0)];
   const int rows = sparse == 2 ? (int)(sizeof(kCost48) / sizeof(Cost)) : (sparse ? (int)(sizeof(kCost24) / sizeof(Cost)) : (int)(sizeof(kCostDense) / sizeof(Cost)));
   const char* stream = aligned_stream((N + 15) / 16, esp_round_up(K, 256) / 64);
   int best = variant_index("ksplit_w8_r1");
   if (M > 64) best = variant_index(sparse == 2 ? "tile48_w8_r128_t256" : "tile_w8_r128_t128");
   double best_t = 1e30;
   for (int i = 0; i < rows; i++) {
-    const int vi = variant_index(table[i].name);
+    const int vi = variants[i];
     const Variant& v = kVariants[vi];
     if (!esp_variant_applicable(vi, M, N, K, sparse)) continue;
     if (!partials && (v.split_mode == 1 || v.kind == KIND_STREAM)) continue;
