@@ -94,7 +94,6 @@ int esparse_create(esparse_ctx** out, int device, void* hip_stream) {
 
 void esparse_destroy(esparse_ctx* ctx) {
   if (!ctx) return;
-  if (ctx->d_flags) (void)hipFree(ctx->d_flags);
   for (auto& k : ctx->kept) (void)hipFree(k.p);
   if (ctx->h_stage) (void)hipHostFree(ctx->h_stage);
   delete ctx;
@@ -122,7 +121,6 @@ static int check_pattern(esparse_ctx* ctx, int n, int m) {
 
 static int bind_device(esparse_ctx* ctx) {
   ESP_HIP(ctx, hipSetDevice(ctx->device));
-  if (!ctx->d_flags) ESP_HIP(ctx, hipMalloc((void**)&ctx->d_flags, 64 * sizeof(int)));
   return ESPARSE_OK;
 }
 

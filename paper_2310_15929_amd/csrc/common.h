@@ -17,7 +17,6 @@ struct esparse_ctx {
   // (sparse, dtype, M, N, K) -> variant chosen by esparse_tune
   std::map<std::tuple<int, int, int, long long, long long, long long>, int> tuned;  // (products per launch, mode, dtype, M, N, K) -> variant
   std::map<std::tuple<int, int, long long, long long, long long>, int> defaults;  // built-in choices looked up before (count, mode, M, N, K)
-  int* d_flags = nullptr;     // 64 ints of device scratch for error flags
   // device blocks that the offline stages have used and will use again (class Scratch), oldest first, and a pinned host
   // block for what they send and receive; given back by esparse_destroy
   struct Block {
