@@ -283,16 +283,16 @@ static int tuned_variant(const esparse_ctx* ctx, int sparse, int dtype, long lon
   return -1;
 }
 
-static int pick_variant(esparse_ctx* ctx, int sparse, int dtype, long long M, long long N, long long K, int variant, int count = 1) {
+static int pick_variant(esparse_ctx* ctx, int sparse, int dtype, long long M, long long N, long long K, int variant, int count = 1, bool grouped = false) {
   if (variant >= 0) return variant;
   const int v = tuned_variant(ctx, sparse, dtype, M, N, K, count);
   if (v >= 0) return v;
   // the built-in choice is a function of the shape alone; looking it up takes a tenth of the time of making it (2 us)
-  const auto key = std::make_tuple(count, sparse, M, N, K);
+  const auto key = std::make_tuple(grouped ? -count : count, sparse, M, N, K);
   auto it = ctx->defaults.find(key);
   if (it != ctx->defaults.end()) return it->second;
   if (ctx->defaults.size() >= 4096) ctx->defaults.clear();
-  return ctx->defaults[key] = esp_default_variant(M, N, K, sparse, count);
+  return ctx->defaults[key] = esp_default_variant(M, N, K, sparse, count, grouped);
 }
 
 int esparse_spmm_workspace(long long M, long long N, long long K, int variant, size_t* bytes) {
@@ -394,7 +394,7 @@ static int spmm_group_phases(esparse_ctx* ctx, int count, const void* const* X, 
   if (M == 0) return ESPARSE_OK;
   ESP_REQUIRE(ctx, workspace_bytes >= esp_group_workspace_bytes(count, M, N, K), ESPARSE_EWORKSPACE,
               "workspace has %zu bytes, %zu needed", workspace_bytes, esp_group_workspace_bytes(count, M, N, K));
-  const int v = pick_variant(ctx, mode, dtype, M, N, K, variant, count);
+  const int v = pick_variant(ctx, mode, dtype, M, N, K, variant, count, true);
   // (beyond 32 tokens the built-in choice may be a kernel without a grouped form: the halves need a named or tuned one)
   const bool chosen = variant >= 0 || M <= 32 || tuned_variant(ctx, mode, dtype, M, N, K, count) >= 0;
   ESP_REQUIRE(ctx, phases == (ESP_PHASE_STAGE | ESP_PHASE_MULTIPLY) || (chosen && esp_variant_is_decode_kernel(v)), ESPARSE_EUNSUPPORTED,
@@ -439,7 +439,8 @@ int esparse_dense_gemm_group(esparse_ctx* ctx, int count, const void* const* X, 
               "workspace has %zu bytes, %zu needed", workspace_bytes, esp_group_workspace_bytes(count, M, N, K));
   ESP_HIP(ctx, hipSetDevice(ctx->device));
   return esp_matmul_group_device(ctx, 0, count, X, M, packed_w, nullptr, N, K, dtype, Y, workspace,
-                                 pick_variant(ctx, 0, dtype, M, N, K, variant, count), ESP_PHASE_STAGE | ESP_PHASE_MULTIPLY);
+                                 pick_variant(ctx, 0, dtype, M, N, K, variant, count, count > 1),
+                                 ESP_PHASE_STAGE | ESP_PHASE_MULTIPLY);
 }
 
 int esparse_dense_packed_size(long long N, long long K, size_t* bytes) {

@@ -2052,7 +2052,9 @@ static double estimate(const Cost& c, const Variant& v, long long M, long long N
          (pieces > 0.0 ? c.partial * out * pieces + c.reduce : 0.0);
 }
 
-static int pick_by_cost(long long M, long long N, long long K, int sparse, int count, bool partials) {
+// grouped: for the group calls of the sparse product, whose two halves need a decode kernel; up to 32 tokens they get one whatever the
+// count
+static int pick_by_cost(long long M, long long N, long long K, int sparse, int count, bool grouped, bool partials) {
   const Cost* table = sparse == 2 ? kCost48 : (sparse ? kCost24 : kCostDense);
   // the rows' variants, looked up by name once (a first call on a shape pays for the estimate)
   struct Rows {
@@ -2080,7 +2082,7 @@ static int pick_by_cost(long long M, long long N, long long K, int sparse, int c
     if (v.kind == KIND_STREAM && strcmp(table[i].name, stream)) continue;
     if (v.kind == KIND_KSPLIT && M > 64) continue;  // 4:8 beyond 64 tokens: 64 at a time, slower than the tiles throughout
     const bool shared = esp_variant_is_decode_kernel(vi);  // the products of a group share the launch
-    if (count > 1 && !shared && M <= 32) continue;  // up to 32 tokens a group is one launch (its halves exist then)
+    if (grouped && !shared && M <= 32) continue;  // up to 32 tokens a group is one launch, and its halves exist
     double t = estimate(table[i], v, M, N, K, sparse, shared ? count : 1);
     if (count > 1 && !shared) t = t * count + 4.0 * (count - 1);  // one after the other, each with its staging launch
     if (t < best_t) {
@@ -2091,11 +2093,15 @@ static int pick_by_cost(long long M, long long N, long long K, int sparse, int c
   return best;
 }
 
-int esp_default_variant(long long M, long long N, long long K, int sparse, int count) { return pick_by_cost(M, N, K, sparse, count, true); }
+int esp_default_variant(long long M, long long N, long long K, int sparse, int count, bool grouped) {
+  return pick_by_cost(M, N, K, sparse, count, grouped, true);
+}
 
 // the built-in choice among the variants that keep no fp32 partial tiles in the workspace (for callers whose scratch
 // is too small for them)
-int esp_default_variant_without_partials(long long M, long long N, long long K, int sparse) { return pick_by_cost(M, N, K, sparse, 1, false); }
+int esp_default_variant_without_partials(long long M, long long N, long long K, int sparse) {
+  return pick_by_cost(M, N, K, sparse, 1, false, false);
+}
 
 // tokens of the compact copy of the staged activations (0: none), written when there are at most 16 tokens
 static int compact_tokens(long long M) {

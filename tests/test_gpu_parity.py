@@ -377,6 +377,21 @@ def _spmm_case(esp, ctx, M, N, K, dtype, seed, use_perm=True):
     assert orc.rowwise_rel_error(_np(Y), Yref).max() <= TOL[dtype]
 
 
+def _device_case(ctx, M, N, K, n, m, seed, dtype=torch.float16):
+    """A case made on the device (sizes the CPU oracle would take seconds for): X, theta, compressed weights, float64 reference."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    X = torch.randn(M, K, device="cuda", generator=g).to(dtype)
+    W = (torch.randn(N, K, device="cuda", generator=g) * K ** -0.5).to(dtype)
+    perm = torch.randperm(K, device="cuda", generator=g).to(torch.int32)
+    Wp = W[:, perm.long()]
+    top = Wp.abs().reshape(N, -1, m).argsort(dim=2, descending=True, stable=True)[:, :, :n]
+    mask = torch.zeros(N, K // m, m, dtype=torch.uint8, device="cuda").scatter_(2, top, 1).reshape(N, K)
+    comp = ctx.compress(W, mask, perm, n, m, canonical=False)
+    ref = X.double()[:, perm.long()] @ (Wp * mask).double().t().contiguous()
+    return X, perm, comp, ref.cpu().numpy()
+
+
 @pytest.mark.parametrize("M", [1, 8, 16, 33, 130])
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
 def test_spmm_small_ragged(esp, ctx, M, dtype):
@@ -860,6 +875,21 @@ def test_spmm_4_8_one_hot_reads_back_weights(esp, ctx):
 
 
 # ---------------------------------------------------------------- several products of one shape in one call
+# a group of one at shapes where a single product's built-in choice is no decode kernel: the halves exist all the same
+@pytest.mark.parametrize("M,N,K,n,m", [(24, 4096, 11008, 2, 4), (27, 1172, 13928, 2, 4), (16, 5120, 13824, 4, 8)])
+def test_halves_of_a_group_of_one(esp, ctx, M, N, K, n, m):
+    print(f"halves M={M} N={N} K={K} {n}:{m}", flush=True)
+    X, perm, comp, ref = _device_case(ctx, M, N, K, n, m, 41)
+    whole = ctx.spmm_group([X], [comp], [perm])[0]
+    ws = torch.zeros(esp.spmm_workspace(M, N, K) + 256, dtype=torch.uint8, device="cuda")
+    ws = ws[(-ws.data_ptr()) % 256:]
+    out = torch.empty_like(whole)
+    ctx.stage_activations_group([X], [perm], comp, ws)
+    ctx.spmm_group_staged(M, [comp], ws, [out])
+    assert orc.rowwise_rel_error(_np(out), ref).max() <= TOL[X.dtype]
+    assert (_bits(out) == _bits(whole)).all()
+
+
 @pytest.mark.parametrize("n,m", [(2, 4), (4, 8)])
 @pytest.mark.parametrize("M", [1, 20, 64, 100])
 def test_spmm_group_equals_single_products(esp, ctx, M, n, m):

@@ -119,6 +119,25 @@ def test_argument_errors_need_no_gpu():
     assert lib.esparse_read_rate(ctx._h, 16, C.byref(rate)) == -1                         # fewer than 4 KiB
 
 
+def test_halves_of_a_group_up_to_32_tokens_have_a_decode_kernel():
+    """Whatever the shape and the count, the built-in choice for the halves of a group call of at most 32 tokens is a kernel
+    that has halves.  The context names a device that does not exist: an accepted call ends there (EHIP), before any launch."""
+    lib = esp.load_library()
+    ctx = esp.Context(1000)
+    fake = C.c_void_p(1 << 20)
+    for M in (1, 2, 7, 16, 17, 24, 32):
+        for N in (16, 512, 1172, 4096, 5120, 11008, 36864):
+            for K in (64, 512, 4096, 9216, 13928, 22016):
+                for count in (1, 2, 3, 4):
+                    a = (C.c_void_p * count)(*[fake] * count)
+                    for n, m in ((2, 4), (4, 8)):
+                        args = (M, N, K, count, n)
+                        assert lib.esparse_stage_activations_group(ctx._h, count, a, M, None, N, K, 0, n, m, fake, 1 << 40, -1) == -4, args
+                        assert lib.esparse_spmm_group_staged(ctx._h, count, M, a, N, K, 0, n, m, a, fake, 1 << 40, -1) == -4, args
+    a = (C.c_void_p * 1)(fake)
+    assert lib.esparse_stage_activations_group(ctx._h, 1, a, 33, None, 4096, 4096, 0, 2, 4, fake, 1 << 40, -1) == -2
+
+
 def test_tune_table_text_roundtrip(tmp_path):
     ctx = esp.Context(0)
     p = tmp_path / "t.txt"
