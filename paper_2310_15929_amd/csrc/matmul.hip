@@ -2181,6 +2181,13 @@ static bool ksplit_folds(const Variant& v, long long M, long long Np, long long 
   return red + gathered <= 64 * 1024;
 }
 
+// A kernel that gathers for itself reads X while others of its workgroups write Y: outputs that overlap an input (a layer
+// applied in place) keep the staged copy, which is complete before the product starts.
+static bool overlap(const void* X, const void* Y, long long M, long long N, long long K) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(X), y = reinterpret_cast<uintptr_t>(Y);
+  return x < y + (uintptr_t)M * N * 2 && y < x + (uintptr_t)M * K * 2;
+}
+
 template <int DT, int SPARSE, int MT>
 static void launch_ksplit(const Variant& v, hipStream_t st, KsplitArgs args, int count, long long M, long long N, long long Mp,
                           long long Np, long long Kp, int mc, int nsplit, bool fold) {
@@ -2458,8 +2465,8 @@ int esp_matmul_device(esparse_ctx* ctx, int sparse, const void* X, long long M, 
   const Variant& v = kVariants[variant];
   const long long nrt = Np / 16, ntt = Mp / 16, nks = Kp / 64;
   int rc;
-  // one or two tokens through a decode kernel, both halves in one call: the kernel gathers through theta itself
-  const bool fold = phases == (ESP_PHASE_STAGE | ESP_PHASE_MULTIPLY) && ksplit_folds(v, M, Np, Kp);
+  // few tokens through a decode kernel, both halves in one call: the kernel gathers through theta itself
+  const bool fold = phases == (ESP_PHASE_STAGE | ESP_PHASE_MULTIPLY) && ksplit_folds(v, M, Np, Kp) && !overlap(X, Yv, M, N, K);
   if ((phases & ESP_PHASE_STAGE) && !fold && (rc = stage_activations(ctx, X, perm, M, K, Mp, Kp, Xf, compact_tokens(M)))) return rc;
   if (!(phases & ESP_PHASE_MULTIPLY)) return ESPARSE_OK;
 
@@ -2561,7 +2568,8 @@ int esp_matmul_group_device(esparse_ctx* ctx, int sparse, int count, const void*
   const size_t xbytes = staged_bytes(M, K);
   GatherArgs ga = {};
   KsplitArgs ka = {};
-  const bool fold = phases == (ESP_PHASE_STAGE | ESP_PHASE_MULTIPLY) && ksplit_folds(v, M, Np, Kp);
+  bool fold = phases == (ESP_PHASE_STAGE | ESP_PHASE_MULTIPLY) && ksplit_folds(v, M, Np, Kp);
+  for (int i = 0; i < count * count && fold; i++) fold = !overlap(X[i / count], Y[i % count], M, N, K);
   ka.K = K;
   for (int i = 0; i < count; i++) {
     uint4* Xf = reinterpret_cast<uint4*>(ws + WS_HEADER_BYTES + (size_t)i * xbytes);

@@ -579,6 +579,29 @@ def test_few_tokens_gathered_in_the_kernel_equal_staged(esp, ctx, M, K, n, m):
         assert torch.equal(Y, ctx.spmm(X, comp, perm))
 
 
+# a square layer applied in place, whole and overlapping by some rows, alone and in a group whose members share an input
+@pytest.mark.parametrize("M", [2, 4, 8])
+def test_outputs_that_overlap_the_input(esp, ctx, M):
+    N = K = 512
+    cases = [_device_case(ctx, M, N, K, 2, 4, 51 + i) for i in range(3)]
+    X = cases[0][0]
+    apart = [ctx.spmm(X, c[2], c[1]) for c in cases]
+    print(f"in place M={M}", flush=True)
+    for shift in (0, M // 2, -(M // 2), M):
+        buf = torch.zeros(3 * M, K, dtype=X.dtype, device="cuda")
+        Xi = buf[M:2 * M]
+        Xi.copy_(X)
+        Y = buf[M + shift:2 * M + shift]
+        ctx.spmm(Xi, cases[0][2], cases[0][1], out=Y)
+        assert (_bits(Y) == _bits(apart[0])).all(), shift
+        Xi.copy_(X)
+        outs = [torch.empty_like(X), Y, torch.empty_like(X)]
+        named = [esp.variant_name(v) for v in range(esp.num_variants())].index("ksplit_w8_r1")
+        ctx.spmm_group([Xi] * 3, [c[2] for c in cases], [c[1] for c in cases], variant=named, outs=outs)
+        for o, c in zip(outs, cases):
+            assert (_bits(o) == _bits(ctx.spmm(X, c[2], c[1], variant=named))).all(), shift
+
+
 # row lengths of Y that are no multiple of 8 outputs leave the tile kernels word by word: odd, 2 and 4 modulo 8, a last tile of
 # one output, fewer outputs than a wave owns; a guard behind Y and every kernel that takes the shape
 @pytest.mark.parametrize("N", [1, 30, 129, 260, 321])
