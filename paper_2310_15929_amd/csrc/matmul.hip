@@ -2172,11 +2172,13 @@ static void launch_wave_tile(const Variant& v, dim3 grid, hipStream_t st, const 
 // buffer in the 64 KiB of LDS a launch may ask for without further ado - and the gather is cheap enough: every workgroup
 // repeats it, so it pays while workgroups x channels x tokens stays small (4096 x 4096, one token: 7.0 us against 6.5 + 2.1
 // for the staging launch; 36864 x 9216, 2304 workgroups: 77 us against 58 + 2.3, hence the limits; 16 tokens x 512
-// channels, 32 workgroups: a call 14.6 -> 11.5 us, one launch of 6 us instead of two of 3.5 and 3.9 and the gap).
+// channels, 32 workgroups: a call 14.6 -> 11.5 us, one launch of 6 us instead of two of 3.5 and 3.9 and the gap).  Beyond two
+// tokens at most 9216 channels x tokens: over 10 decode kernels and 512 to 16384 rows the launches take 0.69 to 1.02 times those of
+// the staged form there, and up to 1.07 times at 10240 (8 tokens, 4096 x 1280, ksplit_w8_r1: 6.5 -> 6.9 us).
 static bool ksplit_folds(const Variant& v, long long M, long long Np, long long Kp) {
   if (v.kind != KIND_KSPLIT || v.split_mode != 0 || M > 16) return false;
   const long long mc = compact_tokens(M), groups = (Np / 16 + v.rt - 1) / v.rt;
-  if (Kp * mc > 10240 || groups * Kp * mc > 3000000) return false;
+  if (Kp * mc > (M > 2 ? 9216 : 10240) || groups * Kp * mc > 3000000) return false;
   const size_t red = (size_t)v.nw * v.rt * 64 * 16, gathered = (size_t)2 * Kp * mc;
   return red + gathered <= 64 * 1024;
 }
