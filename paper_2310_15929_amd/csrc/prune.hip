@@ -320,7 +320,8 @@ __global__ void __launch_bounds__(1024) k_hist(const uint16_t* __restrict__ X, l
 // ------------------------------------------------------------------------------------------------
 // exact column sums of |W|: grid (ceil(K / 128), row chunks), block 256 = 8 row lanes x 32 lanes of four channels (8-byte
 // loads, eight rows in flight).  fp16: a lane adds its rows as integers of 2^-24 (less than 2^40 each); bf16: by exponent
-// into LDS.  4096 x 4096: 25 -> 12 us, fp16 (one float64 ilogb and ldexp per element and 4-byte loads before).
+// into LDS.  4096 x 4096: 25 -> 12 us, fp16 (one float64 ilogb and ldexp per element and 4-byte loads before).  A NaN adds
+// nothing; an infinity adds the power of two that follows the type's largest value.
 // ------------------------------------------------------------------------------------------------
 template <int DT>
 __global__ void __launch_bounds__(256) k_abs_colsum(const uint16_t* __restrict__ W, long long N, long long K,
@@ -341,13 +342,14 @@ __global__ void __launch_bounds__(256) k_abs_colsum(const uint16_t* __restrict__
         const uint32_t raw = ((j < 2 ? v.x : v.y) >> (16 * (j & 1))) & 0x7fffu;
         if (DT == ESPARSE_F16) {
           const uint32_t e = raw >> 10;
-          const uint32_t m = e ? (raw & 0x3ffu) | 0x400u : raw;
+          uint32_t m = e ? (raw & 0x3ffu) | 0x400u : raw;
+          m = raw > 0x7c00u ? 0u : m;
           sum[j] += (unsigned long long)m << (e ? e - 1 : 0);
         } else {
           const uint32_t e = raw >> 7;
           const uint32_t m = e ? (raw & 0x7fu) | 0x80u : raw;
           const uint32_t pos = (e ? e : 1u) + (AB_OFF - 134);
-          if (m) atomicAdd(&s_acc[(j * 32 + cl) * AB_NB + (pos >> 4)], (unsigned long long)m << (pos & 15u));
+          if (m && raw <= 0x7f80u) atomicAdd(&s_acc[(j * 32 + cl) * AB_NB + (pos >> 4)], (unsigned long long)m << (pos & 15u));
         }
       }
     };

@@ -174,6 +174,40 @@ def test_block_shuffle_undecided_exchanges(esp, ctx, n, m, what):
     assert _check_block_shuffle(esp, ctx, W, s, n, m, B).sum() > 0
 
 
+def _kept_of_network(v, n):
+    """The n largest of the last axis as a network of fmax / fmin selects them: of a value and a NaN it makes the value twice."""
+    v = np.moveaxis(v, -1, 0).copy()
+    for a in range(n):
+        for b in range(v.shape[0] - 1, a, -1):
+            v[b - 1], v[b] = np.fmax(v[b - 1], v[b]), np.fmin(v[b - 1], v[b])
+    return v[:n].sum(axis=0)
+
+
+# weights that are no numbers: a column's mean leaves them out, they stand behind no weight of their group (kept), and the retained
+# metric does not become NaN
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("n,m", [(2, 4), (4, 8)])
+def test_prune_weights_that_are_not_numbers(esp, ctx, n, m, dtype):
+    N, K, B = 90, 192, 64
+    W = _rand((N, K), dtype, 83, scale=K ** -0.5)
+    s = np.random.default_rng(11).lognormal(size=K)
+    for j, c in ((5, 3), (17, 70), (17, 71), (60, 150)):
+        W[j, c] = float("nan")
+    Wn = _np(W).astype(np.float64)
+    for flags in (esp.USE_ALL & ~esp.USE_LBS,):
+        print(f"nan {n}:{m} {dtype} flags {flags}", flush=True)
+        res = ctx.prune(None, W.cuda(), esp.PruneOpts(n_keep=n, m_group=m, block=B, flags=flags), score=s, want_retained=True)
+        theta = res.perm.cpu().numpy()
+        assert (np.sort(theta) == np.arange(K)).all()
+        if not flags & esp.USE_LBS:
+            assert (theta == orc.global_naive_shuffle(np.nan_to_num(Wn), s, m)).all()
+        xi = (np.abs(Wn) * s)[:, theta].reshape(N, K // m, m)
+        pos = np.arange(m)
+        ahead = ((xi[..., None, :] > xi[..., :, None]) | ((xi[..., None, :] == xi[..., :, None]) & (pos[None, :] < pos[:, None]))).sum(axis=-1)
+        assert (res.mask.cpu().numpy() == (ahead < n).reshape(N, K)).all()
+        assert res.retained == pytest.approx(_kept_of_network(xi, n).sum(), rel=1e-12)
+
+
 # column sums and ranks: fewer rows than a row lane's batch and a remainder, channels past a workgroup's 128 (16), values
 # over the whole range of the type with zeros and subnormal ones, equal means
 @pytest.mark.parametrize("N,K", [(1, 36), (7, 132), (70, 264), (129, 40)])
