@@ -1334,10 +1334,13 @@ __global__ void __launch_bounds__(256) k_nm_mask(const uint16_t* __restrict__ W,
 
 // The same from the panel (after a block shuffle): mask and, if part is given, the retained metric of every group.
 // Workgroup (blk, 64 rows): the rows' values through LDS, a thread takes one group and every (256 / G)-th row; its sums meet in
-// ascending order of the row lanes, then the workgroups' in ascending order (k_add_parts).
+// ascending order of the row lanes, then the workgroups' in ascending order (k_add_parts).  Where a weight or a score (odd) is
+// not finite, the kept metric comes from the network of k_group_values, which passes over NaN; the weights the mask keeps are
+// the same sum otherwise.
 template <int DT, int NKEEP, int MG>
 __global__ void __launch_bounds__(256) k_nm_mask_panel(const uint16_t* __restrict__ P, const double* __restrict__ sp, const int* __restrict__ lp,
                                                         long long N, long long Npad, long long K, int B, uint8_t* __restrict__ mask,
+                                                        const int* __restrict__ not_finite, int odd,
                                                         double* __restrict__ part /*[row blocks][K / MG] or null*/) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   const int G = B / MG, nblk = (int)(K / B), tid = threadIdx.x, blk = (int)(blockIdx.x % (unsigned)nblk);
@@ -1360,6 +1363,7 @@ __global__ void __launch_bounds__(256) k_nm_mask_panel(const uint16_t* __restric
     col[k] = lp[blk * B + g * MG + k];
     sc[k] = sp[(long long)blk * B + col[k]];
   }
+  const bool network = part && (odd || *not_finite);
   __syncthreads();
   double acc = 0.0;
   if (rl < lanes)
@@ -1379,6 +1383,7 @@ __global__ void __launch_bounds__(256) k_nm_mask_panel(const uint16_t* __restric
         out[k / 4] |= (ahead < NKEEP ? 1u : 0u) << (8 * (k % 4));
         kept = kept + (ahead < NKEEP ? xi[k] : 0.0);
       }
+      if (network) kept = top_n_sum<NKEEP, MG>(xi);
       acc = acc + kept;
       uint32_t* dst = reinterpret_cast<uint32_t*>(mask + (j0 + r) * K + (long long)blk * B + g * MG);
 #pragma unroll
@@ -1496,8 +1501,12 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
     const int nsplit = (int)std::max<long long>(1, std::min<long long>(512 / (nblk * slices * gsets), (N + LBS_WAVES * LBS_ROWS - 1) / (LBS_WAVES * LBS_ROWS)));
     const long long batch = (long long)nsplit * LBS_WAVES * LBS_ROWS;  // rows that all waves of a block take at a time
     const long long Npad = (N + LBS_ROWS - 1) / LBS_ROWS * LBS_ROWS;
-    bool fast = true;
-    for (long long c = 0; c < K; c++) fast = fast && score[c] >= 0.0 && std::isfinite(score[c]);
+    bool finite = true, fast = true;  // of the scores: all finite; and none negative
+    for (long long c = 0; c < K; c++) {
+      finite = finite && std::isfinite(score[c]);
+      fast = fast && score[c] >= 0.0;
+    }
+    fast = fast && finite;
     const size_t ventries = (size_t)nblk * B * B;
     uint16_t* d_P = scratch.get<uint16_t>((size_t)(Npad * K + batch * B));
     uint16_t* d_PT = scratch.get<uint16_t>((size_t)(Npad * K));
@@ -1622,7 +1631,7 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
       dim3 grid((unsigned)(nblk * row_blocks));
 #define LAUNCH_MASK(DT, NK, MGv, ...)                                                                                        \
   hipLaunchKernelGGL((k_nm_mask_panel<DT, NK, MGv>), grid, dim3(256), smem_m, st, d_P, d_sp, d_lp, N, \
-                     Npad, K, B, mask_out, d_part)
+                     Npad, K, B, mask_out, d_count + 2, finite ? 0 : 1, d_part)
       DISPATCH_DT_NM(dtype, n, LAUNCH_MASK, 0);
 #undef LAUNCH_MASK
       ESP_HIP(ctx, hipGetLastError());
