@@ -661,6 +661,13 @@ __device__ __forceinline__ double lanes_total(double part) {
 #define LBS_TOL 64.0
 enum { LBS_FAST = 0, LBS_DONE = 1, LBS_EXACT = 2 };  // state of a block
 
+// group of the first (0) or second (1) exchanged position of a block; -1: none
+template <int MG>
+__device__ __forceinline__ int exchanged_group(const int* __restrict__ rec, int blk, int which) {
+  const int p = rec[(blk * 2 + which) * LBS_REC];
+  return p < 0 ? -1 : p / MG;
+}
+
 // ---- the exact table
 // V[blk][g][i][x] = retained metric of group g of block blk with its i-th member replaced by panel
 // column x of the block (x == the member itself gives v(g)).  grid (entries / 64, blocks), block 1024 =
@@ -696,7 +703,7 @@ __global__ void __launch_bounds__(1024) k_lbs_exact(const uint16_t* __restrict__
   for (int k = 0; k < MG; k++) cols[k] = 0;
   if (active) {
     int gsel = eid / per_group;
-    g = rec ? rec[(blk * 2 + gsel) * LBS_REC] / MG : gsel;
+    g = rec ? exchanged_group<MG>(rec, blk, gsel) : gsel;
     i = (eid / B) % MG;
     x = eid % B;
     if (g < 0) active = false;
@@ -796,7 +803,7 @@ __global__ void __launch_bounds__(1024) k_lbs_exact_2_4(const uint16_t* __restri
     ui[c] = cmb % MG;
     const int gsel = cmb / MG;
     ug[c] = -1;
-    if (u < nunits) ug[c] = rec ? rec[(blk * 2 + gsel) * LBS_REC] / MG : gsel;
+    if (u < nunits) ug[c] = rec ? exchanged_group<MG>(rec, blk, gsel) : gsel;
     uact[c] = ug[c] >= 0 && xl < XL;
     if (!uact[c]) ux[c] = 0;
     if (uact[c]) {
@@ -842,7 +849,7 @@ __global__ void __launch_bounds__(1024) k_lbs_exact_2_4(const uint16_t* __restri
       const int cmb = u / xslices, mi = cmb % MG, gsel = cmb / MG;
       double m1 = 0.0, m2 = 0.0;
       if (u < nunits) {
-        const int gg = rec ? rec[(blk * 2 + gsel) * LBS_REC] / MG : gsel;
+        const int gg = rec ? exchanged_group<MG>(rec, blk, gsel) : gsel;
         if (gg >= 0) {
           double o[3];
           int c3 = 0;
