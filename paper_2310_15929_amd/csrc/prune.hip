@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <numeric>
 #include <thread>
 
 #include "common.h"
@@ -398,6 +399,9 @@ __global__ void __launch_bounds__(64) k_channel_means(const unsigned long long* 
 // Global naive shuffle: the rank of a channel is the number of channels with a larger mean, or the same and a lower number
 // (NaN behind all numbers); rank r goes to position (r mod G) m + r / G.  16 channels per workgroup, the comparisons with
 // all others split over 64 lanes each; K^2 comparisons instead of a sort on the host (4096 channels: 22 us against about 400).
+// Beyond RANK_ON_DEVICE channels the host sorts (whole prune calls without a block shuffle, 16 rows, sorted / compared: 196608
+// channels 14.7 / 16.7 ms, 262144 20 / 29, 524288 44 / 138: the comparisons grow fourfold with each doubling; 131072: 7.6 compared).
+#define RANK_ON_DEVICE (3ll << 16)
 __global__ void __launch_bounds__(1024) k_naive_shuffle(const double* __restrict__ g, const double* __restrict__ score, int K, int m, int use_gns,
                                                          int32_t* __restrict__ theta0, double* __restrict__ sp) {
   __shared__ int s_rank[16];
@@ -1495,8 +1499,23 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
     hipLaunchKernelGGL(k_channel_means, dim3((unsigned)((K + 63) / 64)), dim3(64), 0, st, d_cs, d_s, N, K, d_g);
     ESP_HIP(ctx, hipGetLastError());
   }
-  hipLaunchKernelGGL(k_naive_shuffle, dim3((unsigned)((K + 15) / 16)), dim3(1024), 0, st, d_g, d_s, (int)K, m, use_gns ? 1 : 0, d_theta0, d_sp);
-  ESP_HIP(ctx, hipGetLastError());
+  if (use_gns && K > RANK_ON_DEVICE) {
+    std::vector<double> g((size_t)K);
+    std::vector<int32_t> order((size_t)K), theta0((size_t)K);
+    ESP_HIP(ctx, hipMemcpyAsync(g.data(), d_g, (size_t)K * 8, hipMemcpyDeviceToHost, st));
+    ESP_HIP(ctx, hipStreamSynchronize(st));
+    std::iota(order.begin(), order.end(), 0);
+    std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return g[a] > g[b] || (g[a] == g[a] && g[b] != g[b]); });
+    const long long G = K / m;
+    for (long long r = 0; r < K; r++) theta0[(size_t)((r % G) * m + r / G)] = order[(size_t)r];
+    for (long long p = 0; p < K; p++) g[(size_t)p] = score[theta0[(size_t)p]];
+    ESP_HIP(ctx, hipMemcpyAsync(d_theta0, theta0.data(), (size_t)K * 4, hipMemcpyHostToDevice, st));
+    ESP_HIP(ctx, hipMemcpyAsync(d_sp, g.data(), (size_t)K * 8, hipMemcpyHostToDevice, st));
+    ESP_HIP(ctx, hipStreamSynchronize(st));  // the host copies end here
+  } else {
+    hipLaunchKernelGGL(k_naive_shuffle, dim3((unsigned)((K + 15) / 16)), dim3(1024), 0, st, d_g, d_s, (int)K, m, use_gns ? 1 : 0, d_theta0, d_sp);
+    ESP_HIP(ctx, hipGetLastError());
+  }
 
   // ---- local block shuffle
   if (use_lbs) {

@@ -244,6 +244,34 @@ def test_naive_shuffle_over_the_range_of_the_type(esp, ctx, N, K, dtype):
     assert (res.perm.cpu().numpy() == orc.global_naive_shuffle(_np(W), s, 4)).all()
 
 
+# the ranks are counted on the device up to 3 x 2^16 channels and sorted on the host beyond: both sides of the line, equal means and
+# scores that are no numbers (behind all others, lower channel first)
+@pytest.mark.parametrize("K", [64, 3 << 16, (3 << 16) + 64, 3 << 18])
+def test_naive_shuffle_ranks(esp, ctx, K):
+    W = _rand((3, K), torch.float16, 37, scale=0.02)
+    rng = np.random.default_rng(K)
+    s = rng.lognormal(size=K)
+    same, nan = rng.permutation(K)[:40].reshape(2, 20)
+    W[:, same] = W[:, same[:1]]
+    s[same] = s[same[0]]
+    s[nan] = np.nan
+    for m in (4, 8):
+        print(f"ranks K={K} m={m}", flush=True)
+        res = ctx.prune(None, W.cuda(), esp.PruneOpts(n_keep=m // 2, m_group=m, block=64, flags=esp.USE_NORM | esp.USE_GNS), score=s)
+        order = np.argsort(-((s * np.abs(_np(W).astype(np.float64)).sum(axis=0)) / 3), kind="stable")
+        theta = np.empty(K, dtype=np.int64)
+        theta[(np.arange(K) % (K // m)) * m + np.arange(K) // (K // m)] = order
+        assert (res.perm.cpu().numpy() == theta).all()
+    if K > 3 << 16:  # and the scores in that order reach the block shuffle
+        s[nan] = 0.5
+        opts = esp.PruneOpts(block=64, max_swaps=1)
+        res = ctx.prune(None, W.cuda(), opts, score=s)
+        theta, swaps = orc.local_block_shuffle_vectorised(_np(W), s, orc.global_naive_shuffle(_np(W), s, 4), 2, 4, 64, 1,
+                                                          blocks=[0, 7, K // 64 - 1], order=("lanes", 16))
+        for b in (0, 7, K // 64 - 1):
+            assert (res.perm.cpu().numpy()[64 * b:64 * b + 64] == theta[64 * b:64 * b + 64]).all() and res.swaps[b] == swaps[b]
+
+
 def test_prune_scratch_is_shared_by_calls_and_streams(esp, ctx):
     """One context, shapes that grow and shrink, two streams in turn: every call as on a context of its own."""
     rng = np.random.default_rng(3)
