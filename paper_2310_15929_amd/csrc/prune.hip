@@ -1534,17 +1534,24 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
     }
     fast = fast && finite;
     const size_t ventries = (size_t)nblk * B * B;
-    uint16_t* d_P = scratch.get<uint16_t>((size_t)(Npad * K + batch * B));
-    uint16_t* d_PT = scratch.get<uint16_t>((size_t)(Npad * K));
+    // the cheaper table looks ahead past the panel's end and needs the panel by columns and its workgroups' sums as well: where
+    // the device has no room for them (2 more bytes per weight), the exact table does without
+    uint16_t* d_P = scratch.get<uint16_t>((size_t)(Npad * K + (fast ? batch * B : 0)));
+    if (!d_P && fast) {
+      fast = false;
+      d_P = scratch.get<uint16_t>((size_t)(Npad * K));
+    }
     double* d_V = scratch.get<double>(ventries);
-    double* d_S = scratch.get<double>(ventries * nsplit);
     int* d_lp = scratch.get<int>(K);
     int* d_rec = scratch.get<int>(nblk * 2 * LBS_REC);
     int* d_state = scratch.get<int>(nblk);
     long long* d_swaps = scratch.get<long long>(nblk);
     int* d_count = scratch.get<int>(4);
-    if (!d_P || !d_PT || !d_V || !d_S || !d_lp || !d_rec || !d_state || !d_swaps || !d_count)
+    if (!d_P || !d_V || !d_lp || !d_rec || !d_state || !d_swaps || !d_count)
       return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation for the block shuffle failed");
+    double* d_S = fast ? scratch.get<double>(ventries * nsplit) : nullptr;
+    uint16_t* d_PT = d_S ? scratch.get<uint16_t>((size_t)(Npad * K)) : nullptr;
+    fast = d_PT != nullptr;
     int* count = reinterpret_cast<int*>(h_stage + K);
     long long* h_swaps = reinterpret_cast<long long*>(h_stage + K + 8);
     double* h_gv = h_stage + K + 8 + nblk;
@@ -1561,9 +1568,11 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
       hipLaunchKernelGGL(k_build_panel, dim3((unsigned)((N + rows - 1) / rows)), dim3(512), smem_w, st, W, d_theta0, N, Npad, K, B,
                          RB, dtype == ESPARSE_F16 ? 0x7c00u : 0x7f80u, d_P, d_count + 2);
       ESP_HIP(ctx, hipGetLastError());
-      hipLaunchKernelGGL(k_panel_columns, dim3((unsigned)(nblk * ((Npad + 63) / 64)), (unsigned)((B + 63) / 64)), dim3(256), 0, st,
-                         d_P, Npad, (int)nblk, B, d_PT);
-      ESP_HIP(ctx, hipGetLastError());
+      if (fast) {
+        hipLaunchKernelGGL(k_panel_columns, dim3((unsigned)(nblk * ((Npad + 63) / 64)), (unsigned)((B + 63) / 64)), dim3(256), 0, st,
+                           d_P, Npad, (int)nblk, B, d_PT);
+        ESP_HIP(ctx, hipGetLastError());
+      }
     }
     // LDS of the exact evaluation: a chunk of a multiple of 16 rows, about 4096 metric values (at most 16 per thread)
     const int rows_chunk = std::max(16, (4096 / B) / 16 * 16);
@@ -1650,9 +1659,11 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
     {
       const int row_blocks = (int)((N + 63) / 64);
       const long long ng = K / m;
-      double* d_part = retained_out ? scratch.get<double>((size_t)row_blocks * ng) : nullptr;
       double* d_gv = retained_out ? scratch.get<double>(ng) : nullptr;
-      if (retained_out && (!d_part || !d_gv)) return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation failed");
+      if (retained_out && !d_gv) return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation failed");
+      // the workgroups' sums (8 / m bytes per column and 64 rows) take the place of the panel by columns, which nothing reads any more
+      double* d_part = nullptr;
+      if (retained_out) d_part = d_PT ? reinterpret_cast<double*>(d_PT) : scratch.get<double>((size_t)row_blocks * ng);
       const size_t smem_m = 256 * 8 + (size_t)64 * (B + 2) * 2;
       dim3 grid((unsigned)(nblk * row_blocks));
 #define LAUNCH_MASK(DT, NK, MGv, ...)                                                                                        \
@@ -1662,7 +1673,11 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
 #undef LAUNCH_MASK
       ESP_HIP(ctx, hipGetLastError());
       if (retained_out) {
-        hipLaunchKernelGGL(k_add_parts, dim3((unsigned)((ng + 63) / 64)), dim3(64), 0, st, d_part, row_blocks, ng, d_gv);
+#define LAUNCH_GV(DT, NK, MGv, ...) \
+  hipLaunchKernelGGL((k_group_values<DT, NK, MGv>), dim3((unsigned)((ng + 3) / 4)), dim3(64), 0, st, W, d_s, perm_out, N, K, d_gv)
+        if (d_part) hipLaunchKernelGGL(k_add_parts, dim3((unsigned)((ng + 63) / 64)), dim3(64), 0, st, d_part, row_blocks, ng, d_gv);
+        else DISPATCH_DT_NM(dtype, n, LAUNCH_GV, 0);
+#undef LAUNCH_GV
         ESP_HIP(ctx, hipGetLastError());
         ESP_HIP(ctx, hipMemcpyAsync(h_gv, d_gv, ng * 8, hipMemcpyDeviceToHost, st));
       }

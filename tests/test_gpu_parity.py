@@ -272,6 +272,35 @@ def test_naive_shuffle_ranks(esp, ctx, K):
             assert (res.perm.cpu().numpy()[64 * b:64 * b + 64] == theta[64 * b:64 * b + 64]).all() and res.swaps[b] == swaps[b]
 
 
+# where the device has room for one panel but not for the two of the cheaper table, the exact table works alone: same result.
+# All but 3.25 GiB of the card are taken; the panel of 32768 x 32768 weights needs 2 GiB
+def test_prune_with_room_for_one_panel(esp):
+    N = K = 32768
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    W = torch.randn(N, K, device="cuda", generator=g, dtype=torch.float16) * 2 ** -7
+    s = np.random.default_rng(5).lognormal(size=K)
+    opts = esp.PruneOpts(block=64, max_swaps=1)
+    first = esp.Context(0)
+    want = first.prune(None, W, opts, score=s, want_retained=True)
+    first.close()
+    mask = torch.empty_like(want.mask)  # the call's own outputs come from what torch keeps
+    del mask
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    print(f"free {free >> 20} MiB", flush=True)
+    hold = torch.empty(free - (13 << 28), dtype=torch.uint8, device="cuda")
+    try:
+        ctx = esp.Context(0)
+        got = ctx.prune(None, W, opts, score=s, want_retained=True)
+        ctx.close()
+    finally:
+        del hold
+        torch.cuda.empty_cache()
+    assert torch.equal(got.perm, want.perm) and torch.equal(got.mask, want.mask) and (got.swaps == want.swaps).all()
+    assert got.retained == pytest.approx(want.retained, rel=1e-12) and want.swaps.sum() == K // 64
+
+
 def test_prune_scratch_is_shared_by_calls_and_streams(esp, ctx):
     """One context, shapes that grow and shrink, two streams in turn: every call as on a context of its own."""
     rng = np.random.default_rng(3)
