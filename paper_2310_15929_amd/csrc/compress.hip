@@ -291,8 +291,8 @@ __device__ __forceinline__ bool kept_by_value(const uint16_t* wrow, const int (&
 
 template <int NKEEP, int MG, bool MASK, bool PERM, int THREADS>
 __global__ void __launch_bounds__(THREADS) k_compress_rows(const uint16_t* __restrict__ W, const uint8_t* __restrict__ mask,
-                                                        const int32_t* __restrict__ perm, long long N, long long K, long long Np, int RB,
-                                                        int nkb /*256-channel steps*/, uint16_t* __restrict__ values, void* __restrict__ meta,
+                                                        const int32_t* __restrict__ perm, long long N, long long K, long long Np,
+                                                        long long first_row /*multiple of 128*/, int RB, int nkb /*256-channel steps*/, uint16_t* __restrict__ values, void* __restrict__ meta,
                                                         unsigned char* __restrict__ native, const int* __restrict__ bad_perm,
                                                         int* __restrict__ host_flags) {
   constexpr int GU = MG == 4 ? 4 : 2;       // groups per 16-byte unit
@@ -303,7 +303,7 @@ __global__ void __launch_bounds__(THREADS) k_compress_rows(const uint16_t* __res
   // the 16 / RB workgroups of a row tile are numbered 8 apart: they run on one XCD at about the same time, and their pieces of
   // the native form leave its L2 as whole lines
   const int per = 16 / RB;
-  const long long row0 = ((long long)(blockIdx.x / (8 * per)) * 8 + blockIdx.x % 8) * 16 + (blockIdx.x / 8) % per * RB;
+  const long long row0 = first_row + ((long long)(blockIdx.x / (8 * per)) * 8 + blockIdx.x % 8) * 16 + (blockIdx.x / 8) % per * RB;
   if (row0 >= Np) return;
   const int k4 = (int)(K / 4);
   const int work = RB * nkb * 4;
@@ -511,15 +511,18 @@ int esp_compress_device(esparse_ctx* ctx, const void* Wv, const uint8_t* mask, c
   while (RB && RB < 4 && 2 * RB * row_bytes <= (row_bytes <= 64 * 1024 ? 64 * 1024 : 159 * 1024)) RB *= 2;
   if (RB) {
     const size_t smem = (size_t)RB * row_bytes;
-    const long long per = 16 / RB, tiles = (Np + 15) / 16;
-    const dim3 grid((unsigned)((tiles + 7) / 8 * 8 * per));
+    // a launch has fewer than 2^32 threads (more are cut off without an error): 2^31 at most, in several launches if need be
+    const long long per = 16 / RB, tiles = (Np + 15) / 16, tiles_at_once = (1ll << 21) / per;
 #define LAUNCH_THREADS(NK, MGv, MASKv, PERMv, THv)                                                                             \
   do {                                                                                                                         \
     if (smem > 64 * 1024)                                                                                                      \
       ESP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_compress_rows<NK, MGv, MASKv, PERMv, THv>),            \
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));                                \
-    hipLaunchKernelGGL((k_compress_rows<NK, MGv, MASKv, PERMv, THv>), grid, dim3(THv), smem, st, W, mask, perm, N, K, Np, RB, (int)(Kp / 256), \
-                       reinterpret_cast<uint16_t*>(values_out), meta_out, reinterpret_cast<unsigned char*>(native_out), bad_perm, host_flags); \
+    for (long long t0 = 0; t0 < tiles; t0 += tiles_at_once)                                                                    \
+      hipLaunchKernelGGL((k_compress_rows<NK, MGv, MASKv, PERMv, THv>),                                                        \
+                         dim3((unsigned)((std::min(tiles - t0, tiles_at_once) + 7) / 8 * 8 * per)), dim3(THv), smem, st, W, mask, perm, N, K, Np, \
+                         t0 * 16, RB, (int)(Kp / 256), reinterpret_cast<uint16_t*>(values_out), meta_out,                      \
+                         reinterpret_cast<unsigned char*>(native_out), bad_perm, host_flags);                                  \
   } while (0)
 // 16 waves per CU whatever the LDS leaves room for
 #define LAUNCH_ROWS(NK, MGv, MASKv, PERMv)                                       \

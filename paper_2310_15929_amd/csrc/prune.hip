@@ -554,12 +554,12 @@ int esp_stats_device(esparse_ctx* ctx, const void* calib, long long T, long long
 // vector-memory path one lane at a time (52 us for 4096 x 4096).  RB = 0: rows that do not fit the LDS, gathered from
 // global memory, one per workgroup.
 __global__ void __launch_bounds__(512) k_build_panel(const uint16_t* __restrict__ W, const int32_t* __restrict__ theta0,
-                                                      long long N, long long Npad, long long K, int B, int RB, unsigned int inf_bits,
+                                                      long long N, long long Npad, long long K, long long first_row, int B, int RB, unsigned int inf_bits,
                                                       uint16_t* __restrict__ P, int* __restrict__ not_finite) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   uint16_t* s_w = reinterpret_cast<uint16_t*>(smem_raw);
   const int tid = threadIdx.x, rows = RB ? RB : 1;
-  const long long j0 = (long long)blockIdx.x * rows;
+  const long long j0 = first_row + (long long)blockIdx.x * rows;
   const int nr = (int)(N - j0 < rows ? N - j0 : rows);
   if (RB) {
     const uint16_t* src = W + j0 * K;  // the rows are contiguous; K is a multiple of 4 and W of 16 bytes
@@ -1564,9 +1564,11 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
       const size_t smem_w = RB * row_bytes;
       if (smem_w > 64 * 1024)
         ESP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_build_panel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_w));
-      const int rows = RB ? RB : 1;
-      hipLaunchKernelGGL(k_build_panel, dim3((unsigned)((N + rows - 1) / rows)), dim3(512), smem_w, st, W, d_theta0, N, Npad, K, B,
-                         RB, dtype == ESPARSE_F16 ? 0x7c00u : 0x7f80u, d_P, d_count + 2);
+      const long long rows = RB ? RB : 1;
+      // a launch has fewer than 2^32 threads (more are cut off without an error): 2^31 at most, in several launches if need be
+      for (long long j = 0; j < N; j += rows << 22)
+        hipLaunchKernelGGL(k_build_panel, dim3((unsigned)((std::min(N - j, rows << 22) + rows - 1) / rows)), dim3(512), smem_w, st, W, d_theta0,
+                           N, Npad, K, j, B, RB, dtype == ESPARSE_F16 ? 0x7c00u : 0x7f80u, d_P, d_count + 2);
       ESP_HIP(ctx, hipGetLastError());
       if (fast) {
         hipLaunchKernelGGL(k_panel_columns, dim3((unsigned)(nblk * ((Npad + 63) / 64)), (unsigned)((B + 63) / 64)), dim3(256), 0, st,

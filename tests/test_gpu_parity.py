@@ -411,6 +411,45 @@ def test_compress_edges_of_the_row_kernel(esp, ctx, N, K, n, m):
         assert rc == -6 and torch.equal(before, comp.native)
 
 
+def _kept_in_order(W, mask, n):
+    """The kept values of each group of a matrix of one or two groups, in position order, and their positions (torch)."""
+    N, K = W.shape
+    m = 2 * n
+    pos = torch.arange(m, device="cuda", dtype=torch.uint8)
+    at = torch.where(mask.reshape(N, K // m, m) != 0, pos, pos + m).sort(dim=2).values[:, :, :n].long()
+    return W.reshape(N, K // m, m).gather(2, at).reshape(N, -1), at
+
+
+# so many rows that a launch of a few rows per workgroup has more threads than a launch can have (2^32)
+@pytest.mark.parametrize("n,m", [(2, 4), (4, 8)])
+def test_compress_and_prune_very_many_rows(esp, ctx, n, m):
+    N, K = (1 << 27) + 1000, 8
+    g = torch.Generator(device="cuda")
+    g.manual_seed(2)
+    W = torch.empty(N, K, dtype=torch.float16, device="cuda").normal_(generator=g)
+    s = np.array([1.0, 3.0, 0.5, 2.0, 1.5, 0.25, 2.5, 0.75])
+    print(f"rows {N} {n}:{m}", flush=True)
+    res = ctx.prune(None, W, esp.PruneOpts(n_keep=n, m_group=m, block=8, max_swaps=1, flags=esp.USE_ALL if m == 4 else esp.USE_ALL & ~esp.USE_LBS), score=s)
+    perm = res.perm.long()
+    sc = torch.tensor(s, device="cuda")[perm]
+    comp = ctx.compress(W, res.mask, res.perm, n, m, native=False)
+    for lo in range(0, N, 1 << 24):
+        Wp = W[lo:lo + (1 << 24)][:, perm]
+        mask = res.mask[lo:lo + (1 << 24)]
+        xi = (Wp.double().abs() * sc).reshape(-1, K // m, m)
+        keep = torch.zeros(xi.shape, dtype=torch.uint8, device="cuda").scatter_(2, xi.argsort(dim=2, descending=True, stable=True)[:, :, :n], 1)
+        assert torch.equal(keep.reshape(mask.shape), mask), lo
+        values, at = _kept_in_order(Wp, mask, n)
+        assert torch.equal(comp.values[lo:lo + (1 << 24)], values), lo
+        rows = values.shape[0]
+        meta = comp.meta[lo * 4 if m == 4 else lo:][:rows * 4 if m == 4 else rows]
+        if m == 4:
+            want = sum(at.reshape(rows, 4)[:, f] << (2 * f) for f in range(4))
+            assert torch.equal(meta.view(torch.int32).long(), want), lo
+        else:
+            assert torch.equal(meta.long(), (1 << at.reshape(rows, 4)).sum(dim=1)), lo
+
+
 def test_compress_4_8_and_derived_mask_and_errors(esp, ctx):
     N, K = 20, 64
     W = _rand((N, K), torch.float16, 32)
