@@ -5,6 +5,7 @@
 #include <cstdio>
 #include <cstring>
 #include <cmath>
+#include <new>
 
 #include "common.h"
 
@@ -20,45 +21,48 @@ int esp_fail(esparse_ctx* ctx, int code, const char* fmt, ...) {
   return code;
 }
 
+// drops block i of those kept, oldest first
+static esparse_ctx::Block drop_kept(esparse_ctx* ctx, int i) {
+  const esparse_ctx::Block b = ctx->kept[i];
+  for (; i + 1 < ctx->n_kept; i++) ctx->kept[i] = ctx->kept[i + 1];
+  ctx->n_kept--;
+  ctx->kept_bytes -= b.bytes;
+  return b;
+}
+
 void* Scratch::take(size_t bytes) {
+  if (n_mine_ == (int)(sizeof(mine_) / sizeof(mine_[0]))) return nullptr;
   bytes = (std::max<size_t>(bytes, 1) + 65535) / 65536 * 65536;
-  auto& kept = ctx_->kept;
-  size_t best = kept.size();
-  for (size_t i = 0; i < kept.size(); i++)  // the smallest that fits and is not wasted on this
-    if (kept[i].bytes >= bytes && kept[i].bytes <= 4 * bytes && (best == kept.size() || kept[i].bytes < kept[best].bytes)) best = i;
+  const auto* kept = ctx_->kept;
+  int best = -1;
+  for (int i = 0; i < ctx_->n_kept; i++)  // the smallest that fits and is not wasted on this
+    if (kept[i].bytes >= bytes && kept[i].bytes <= 4 * bytes && (best < 0 || kept[i].bytes < kept[best].bytes)) best = i;
   esparse_ctx::Block b{nullptr, bytes};
-  if (best < kept.size()) {
-    b = kept[best];
-    ctx_->kept_bytes -= b.bytes;
-    kept.erase(kept.begin() + best);
+  if (best >= 0) {
+    b = drop_kept(ctx_, best);
   } else if (hipMalloc(&b.p, bytes) != hipSuccess) {
     (void)hipGetLastError();
-    for (auto& k : kept) (void)hipFree(k.p);  // idle blocks of earlier calls
-    kept.clear();
-    ctx_->kept_bytes = 0;
+    while (ctx_->n_kept) (void)hipFree(drop_kept(ctx_, 0).p);  // idle blocks of earlier calls
     if (hipMalloc(&b.p, bytes) != hipSuccess) {
       (void)hipGetLastError();
       return nullptr;
     }
   }
-  mine_.push_back(b);
+  mine_[n_mine_++] = b;
   return b.p;
 }
 
 Scratch::~Scratch() {
   if (!idle_) (void)hipStreamSynchronize(ctx_->stream);
-  auto& kept = ctx_->kept;
-  for (auto& b : mine_) {
+  for (int i = 0; i < n_mine_; i++) {
+    const esparse_ctx::Block b = mine_[i];
     if (b.bytes > ESP_SCRATCH_KEEP) {
       (void)hipFree(b.p);
       continue;
     }
-    while (ctx_->kept_bytes + b.bytes > ESP_SCRATCH_KEEP) {
-      ctx_->kept_bytes -= kept.front().bytes;
-      (void)hipFree(kept.front().p);
-      kept.erase(kept.begin());
-    }
-    kept.push_back(b);
+    while (ctx_->kept_bytes + b.bytes > ESP_SCRATCH_KEEP || ctx_->n_kept == (int)(sizeof(ctx_->kept) / sizeof(ctx_->kept[0])))
+      (void)hipFree(drop_kept(ctx_, 0).p);
+    ctx_->kept[ctx_->n_kept++] = b;
     ctx_->kept_bytes += b.bytes;
   }
 }
@@ -78,6 +82,22 @@ void* esp_host_stage(esparse_ctx* ctx, size_t bytes) {
   return ctx->h_stage;
 }
 
+// runs a call that uses host containers: no exception leaves the C entry
+template <class F>
+static int guarded(esparse_ctx* ctx, F call) noexcept {
+  try {
+    return call();
+  } catch (const std::bad_alloc&) {
+    try {
+      return esp_fail(ctx, ESPARSE_ENOMEM, "out of host memory");
+    } catch (...) {
+      return ESPARSE_ENOMEM;
+    }
+  } catch (...) {
+    return ESPARSE_EHIP;
+  }
+}
+
 extern "C" {
 
 const char* esparse_version(void) { return "esparse-gfx950 0.1"; }
@@ -94,7 +114,7 @@ int esparse_create(esparse_ctx** out, int device, void* hip_stream) {
 
 void esparse_destroy(esparse_ctx* ctx) {
   if (!ctx) return;
-  for (auto& k : ctx->kept) (void)hipFree(k.p);
+  for (int i = 0; i < ctx->n_kept; i++) (void)hipFree(ctx->kept[i].p);
   if (ctx->h_stage) (void)hipHostFree(ctx->h_stage);
   delete ctx;
 }
@@ -135,12 +155,14 @@ int esparse_channel_stats(esparse_ctx* ctx, const void* calib, long long T, long
   ESP_REQUIRE(ctx, bins >= 1 && bins <= 256, ESPARSE_EINVAL, "bins = %d outside [1, 256]", bins);
   ESP_REQUIRE(ctx, esp_aligned16(calib), ESPARSE_EINVAL, "calib is not 16-byte aligned");
   if ((rc = bind_device(ctx))) return rc;
-  std::vector<double> ir, am;
-  if ((rc = esp_stats_device(ctx, calib, T, K, dtype, bins, ir_out ? &ir : nullptr, am_out ? &am : nullptr)))
-    return rc;
-  if (ir_out) memcpy(ir_out, ir.data(), sizeof(double) * K);
-  if (am_out) memcpy(am_out, am.data(), sizeof(double) * K);
-  return ESPARSE_OK;
+  return guarded(ctx, [&] {
+    std::vector<double> ir, am;
+    const int rc = esp_stats_device(ctx, calib, T, K, dtype, bins, ir_out ? &ir : nullptr, am_out ? &am : nullptr);
+    if (rc) return rc;
+    if (ir_out) memcpy(ir_out, ir.data(), sizeof(double) * K);
+    if (am_out) memcpy(am_out, am.data(), sizeof(double) * K);
+    return (int)ESPARSE_OK;
+  });
 }
 
 static int check_prune_args(esparse_ctx* ctx, const void* W, long long N, long long K, int dtype,
@@ -181,7 +203,7 @@ int esparse_prune_with_scores(esparse_ctx* ctx, const double* score, const void*
   if (rc) return rc;
   ESP_REQUIRE(ctx, score, ESPARSE_EINVAL, "score is null");
   if ((rc = bind_device(ctx))) return rc;
-  return esp_prune_device(ctx, score, W, N, K, dtype, opts, perm_out, mask_out, swaps_out, retained_out);
+  return guarded(ctx, [&] { return esp_prune_device(ctx, score, W, N, K, dtype, opts, perm_out, mask_out, swaps_out, retained_out); });
 }
 
 int esparse_prune(esparse_ctx* ctx, const void* calib, long long T, const void* W, long long N,
@@ -199,22 +221,24 @@ int esparse_prune(esparse_ctx* ctx, const void* calib, long long T, const void* 
   ESP_REQUIRE(ctx, esp_aligned16(calib), ESPARSE_EINVAL, "calib is not 16-byte aligned");
   if ((rc = bind_device(ctx))) return rc;
   const bool use_e = opts->flags & ESPARSE_USE_ENTROPY, use_n = opts->flags & ESPARSE_USE_NORM;
-  std::vector<double> ir, am;
-  if ((rc = esp_stats_device(ctx, calib, T, K, dtype, opts->bins, use_e ? &ir : nullptr, use_n ? &am : nullptr)))
-    return rc;
-  // eq. 3: s_c = IR_c + alpha * AM_c, each term behind its switch
-  std::vector<double> s((size_t)K, 0.0);
-  for (long long c = 0; c < K; c++) {
-    double v = 0.0;
-    if (use_e) v = v + ir[c];
-    if (use_n) {
-      double t = opts->alpha * am[c];
-      v = v + t;
+  return guarded(ctx, [&] {
+    std::vector<double> ir, am;
+    int rc = esp_stats_device(ctx, calib, T, K, dtype, opts->bins, use_e ? &ir : nullptr, use_n ? &am : nullptr);
+    if (rc) return rc;
+    // eq. 3: s_c = IR_c + alpha * AM_c, each term behind its switch
+    std::vector<double> s((size_t)K, 0.0);
+    for (long long c = 0; c < K; c++) {
+      double v = 0.0;
+      if (use_e) v = v + ir[c];
+      if (use_n) {
+        double t = opts->alpha * am[c];
+        v = v + t;
+      }
+      s[c] = v;
     }
-    s[c] = v;
-  }
-  if (score_out) memcpy(score_out, s.data(), sizeof(double) * K);
-  return esp_prune_device(ctx, s.data(), W, N, K, dtype, opts, perm_out, mask_out, swaps_out, retained_out);
+    if (score_out) memcpy(score_out, s.data(), sizeof(double) * K);
+    return esp_prune_device(ctx, s.data(), W, N, K, dtype, opts, perm_out, mask_out, swaps_out, retained_out);
+  });
 }
 
 int esparse_compressed_size(long long N, long long K, int n, int m, esparse_dtype dtype,
@@ -291,8 +315,13 @@ static int pick_variant(esparse_ctx* ctx, int sparse, int dtype, long long M, lo
   const auto key = std::make_tuple(grouped ? -count : count, sparse, M, N, K);
   auto it = ctx->defaults.find(key);
   if (it != ctx->defaults.end()) return it->second;
-  if (ctx->defaults.size() >= 4096) ctx->defaults.clear();
-  return ctx->defaults[key] = esp_default_variant(M, N, K, sparse, count, grouped);
+  const int made = esp_default_variant(M, N, K, sparse, count, grouped);
+  try {
+    if (ctx->defaults.size() >= 4096) ctx->defaults.clear();
+    ctx->defaults[key] = made;
+  } catch (...) {  // no host memory to remember it in
+  }
+  return made;
 }
 
 int esparse_spmm_workspace(long long M, long long N, long long K, int variant, size_t* bytes) {
@@ -595,12 +624,12 @@ static int tune_impl(esparse_ctx* ctx, int count, long long M, long long N, long
 
 int esparse_tune(esparse_ctx* ctx, long long M, long long N, long long K, esparse_dtype dtype, int sparse, int* best_variant,
                  float* best_ms) {
-  return tune_impl(ctx, 1, M, N, K, dtype, sparse, best_variant, best_ms);
+  return guarded(ctx, [&] { return tune_impl(ctx, 1, M, N, K, dtype, sparse, best_variant, best_ms); });
 }
 
 int esparse_tune_group(esparse_ctx* ctx, int count, long long M, long long N, long long K, esparse_dtype dtype, int sparse,
                        int* best_variant, float* best_ms) {
-  return tune_impl(ctx, count, M, N, K, dtype, sparse, best_variant, best_ms);
+  return guarded(ctx, [&] { return tune_impl(ctx, count, M, N, K, dtype, sparse, best_variant, best_ms); });
 }
 
 int esparse_output_error(esparse_ctx* ctx, const void* Yref, const void* Y, long long M, long long N, esparse_dtype dtype,
@@ -615,7 +644,7 @@ int esparse_output_error(esparse_ctx* ctx, const void* Yref, const void* Y, long
   if (M == 0 || N == 0) return ESPARSE_OK;
   ESP_REQUIRE(ctx, Yref && Y, ESPARSE_EINVAL, "Yref / Y is null");
   ESP_HIP(ctx, hipSetDevice(ctx->device));
-  return esp_output_error_device(ctx, Yref, Y, M * N, dtype, err_num, err_den);
+  return guarded(ctx, [&] { return esp_output_error_device(ctx, Yref, Y, M * N, dtype, err_num, err_den); });
 }
 
 int esparse_matrix_rate(esparse_ctx* ctx, int sparse, esparse_dtype dtype, int random_operands, int mix, double* tflops) {

@@ -23,7 +23,8 @@ struct esparse_ctx {
     void* p;
     size_t bytes;
   };
-  std::vector<Block> kept;
+  Block kept[32];
+  int n_kept = 0;
   size_t kept_bytes = 0;
   void* h_stage = nullptr;
   size_t h_stage_bytes = 0;
@@ -68,7 +69,8 @@ class Scratch {
  private:
   void* take(size_t bytes);
   esparse_ctx* ctx_;
-  std::vector<esparse_ctx::Block> mine_;
+  esparse_ctx::Block mine_[32];  // more than any call takes
+  int n_mine_ = 0;
   bool idle_ = false;
 };
 // pinned host memory of the context (one block: the next call of this function may move it); nullptr if there is none
@@ -124,6 +126,7 @@ __device__ __forceinline__ uint16_t esp_from_float(float f) {
 
 // ---- entry points implemented in the kernel files (host side launchers) ----------------------
 // statistics / prune
+void esp_entropies(const unsigned int* hist, long long K, int bins, long long T, double* out);  // host
 int esp_stats_device(esparse_ctx* ctx, const void* calib, long long T, long long K, int dtype,
                      int bins, std::vector<double>* ir, std::vector<double>* am);
 int esp_prune_device(esparse_ctx* ctx, const double* score_host, const void* W, long long N,

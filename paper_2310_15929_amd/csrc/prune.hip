@@ -16,6 +16,8 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <memory>
+#include <new>
 #include <numeric>
 #include <thread>
 
@@ -430,6 +432,43 @@ __global__ void __launch_bounds__(1024) k_naive_shuffle(const double* __restrict
   }
 }
 
+// eq. 1: IR_c = - sum_k p_k ln p_k, ascending k, empty bins skipped.  K * bins logarithms on the host (the host's log is
+// the one the result is defined by); the counts of a channel set repeat, so each thread keeps the terms it has met (a
+// logarithm of a count below 16384 is taken about once in ten times at T = 262144).  Without memory for the terms or without
+// another thread the work is done all the same.
+void esp_entropies(const unsigned int* hist, long long K, int bins, long long T, double* out) {
+  const unsigned int known = (unsigned int)std::min<long long>(T + 1, 16384);
+  auto entropy_of = [=](long long c0, long long c1) {
+    std::unique_ptr<double[]> term(new (std::nothrow) double[known]());  // 0: not met yet (p ln p = 0 for p = 1 only)
+    for (long long c = c0; c < c1; c++) {
+      double acc = 0.0;
+      for (int k = 0; k < bins; k++) {
+        const unsigned int nk = hist[(size_t)c * bins + k];
+        if (!nk) continue;
+        const bool keep = term && nk < known;
+        double t = keep ? term[nk] : 0.0;
+        if (t == 0.0) {
+          const double p = (double)nk / (double)T;
+          t = p * std::log(p);
+          if (keep) term[nk] = t;
+        }
+        acc = acc + t;
+      }
+      out[c] = -acc;
+    }
+  };
+  const int nthr = (int)std::max<long long>(1, std::min<long long>(8, K * bins / 65536));
+  std::thread pool[8];
+  int started = 1;
+  try {
+    for (; started < nthr; started++) pool[started] = std::thread(entropy_of, K * started / nthr, K * (started + 1) / nthr);
+  } catch (...) {  // no thread to be had: its share and the rest are done here
+  }
+  entropy_of(0, K / nthr);
+  entropy_of(K * started / nthr, K);
+  for (int i = 1; i < started; i++) pool[i].join();
+}
+
 // ------------------------------------------------------------------------------------------------
 // host driver of the statistics
 // ------------------------------------------------------------------------------------------------
@@ -437,6 +476,7 @@ int esp_stats_device(esparse_ctx* ctx, const void* calib, long long T, long long
                      std::vector<double>* ir, std::vector<double>* am) {
   if (!ir && !am) return ESPARSE_OK;
   hipStream_t st = ctx->stream;
+  std::vector<unsigned char> pageable;
   Scratch scratch(ctx);
   // zeroed: squares, extrema (the minimum inverted); then what goes to the host: sums of squares, histogram (zeroed)
   const size_t sq_bytes = (size_t)K * SQ_NB * 8, hist_bytes = (size_t)K * bins * 4;
@@ -448,7 +488,6 @@ int esp_stats_device(esparse_ctx* ctx, const void* calib, long long T, long long
   double* d_am = reinterpret_cast<double*>(d_all + sq_bytes + (size_t)K * 8);
   unsigned int* d_hist = reinterpret_cast<unsigned int*>(d_am + K);
   const size_t out_bytes = (size_t)K * 8 + (ir ? hist_bytes : 0);
-  std::vector<unsigned char> pageable;
   unsigned char* h_out = reinterpret_cast<unsigned char*>(out_bytes <= ((size_t)32 << 20) ? esp_host_stage(ctx, out_bytes) : nullptr);
   if (!h_out) {
     pageable.resize(out_bytes);
@@ -509,35 +548,8 @@ int esp_stats_device(esparse_ctx* ctx, const void* calib, long long T, long long
     for (long long c = 0; c < K; c++) (*am)[c] = std::sqrt(sums[c]);
   }
   if (ir) {
-    // eq. 1: IR_c = - sum_k p_k ln p_k, ascending k, empty bins skipped.  K * bins logarithms on the host (the host's log is
-    // the one the result is defined by); the counts of a channel set repeat, so each thread keeps the terms it has met (a
-    // logarithm of a count below 16384 is taken about once in ten times at T = 262144).
-    const unsigned int* hist = reinterpret_cast<const unsigned int*>(h_out + (size_t)K * 8);
     ir->assign((size_t)K, 0.0);
-    auto entropy_of = [&](long long c0, long long c1) {
-      std::vector<double> term(std::min<long long>(T + 1, 16384), 0.0);  // 0: not met yet (p ln p = 0 for p = 1 only)
-      const unsigned int known = (unsigned int)term.size();
-      for (long long c = c0; c < c1; c++) {
-        double acc = 0.0;
-        for (int k = 0; k < bins; k++) {
-          const unsigned int nk = hist[(size_t)c * bins + k];
-          if (!nk) continue;
-          double t = nk < known ? term[nk] : 0.0;
-          if (t == 0.0) {
-            const double p = (double)nk / (double)T;
-            t = p * std::log(p);
-            if (nk < known) term[nk] = t;
-          }
-          acc = acc + t;
-        }
-        (*ir)[c] = -acc;
-      }
-    };
-    const int nthr = (int)std::max<long long>(1, std::min<long long>(8, K * bins / 65536));
-    std::vector<std::thread> pool;
-    for (int i = 1; i < nthr; i++) pool.emplace_back(entropy_of, K * i / nthr, K * (i + 1) / nthr);
-    entropy_of(0, K / nthr);
-    for (auto& th : pool) th.join();
+    esp_entropies(reinterpret_cast<const unsigned int*>(h_out + (size_t)K * 8), K, bins, T, ir->data());
   }
   return ESPARSE_OK;
 }

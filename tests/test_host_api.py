@@ -3,6 +3,8 @@ answers its closed-form size queries and rejects bad arguments before touching t
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -136,6 +138,30 @@ def test_halves_of_a_group_up_to_32_tokens_have_a_decode_kernel():
                         assert lib.esparse_spmm_group_staged(ctx._h, count, M, a, N, K, 0, n, m, a, fake, 1 << 40, -1) == -4, args
     a = (C.c_void_p * 1)(fake)
     assert lib.esparse_stage_activations_group(ctx._h, 1, a, 33, None, 4096, 4096, 0, 2, 4, fake, 1 << 40, -1) == -2
+
+
+@pytest.mark.parametrize("room_mib", [64, 1])
+def test_entropies_without_threads_or_memory(room_mib):
+    """The host part of the channel statistics on 8 threads, and where the address space has no room for another thread's
+    stack (std::thread then throws): same values."""
+    code = f"""
+import ctypes as C, resource, numpy as np, sys
+lib = C.CDLL({binding._LIB_PATH!r})
+f = lib._Z13esp_entropiesPKjxixPd
+f.argtypes = [C.c_void_p, C.c_longlong, C.c_int, C.c_longlong, C.c_void_p]; f.restype = None
+K, bins, T = 6000, 100, 40000
+hist = np.random.default_rng(1).multinomial(T, np.full(bins, 1 / bins), size=K).astype(np.uint32)
+hist[0] = 0; hist[0, 5] = T
+p = hist / T
+want = -np.where(hist > 0, p * np.log(np.where(hist > 0, p, 1.0)), 0.0).sum(axis=1)
+out = np.full(K, 7.0)
+now = int(open('/proc/self/statm').read().split()[0]) * 4096
+resource.setrlimit(resource.RLIMIT_AS, (now + ({room_mib} << 20), resource.RLIM_INFINITY))
+f(hist.ctypes.data, K, bins, T, out.ctypes.data)
+resource.setrlimit(resource.RLIMIT_AS, (resource.RLIM_INFINITY, resource.RLIM_INFINITY))
+sys.exit(0 if np.abs(out - want).max() < 1e-13 else 3)
+"""
+    assert subprocess.run([sys.executable, "-c", code], timeout=60).returncode == 0
 
 
 def test_tune_table_text_roundtrip(tmp_path):
