@@ -69,6 +69,7 @@ Scratch::~Scratch() {
 
 void* esp_host_stage(esparse_ctx* ctx, size_t bytes) {
   if (bytes <= ctx->h_stage_bytes) return ctx->h_stage;
+  if (bytes > ESP_STAGE_KEEP) return nullptr;
   if (ctx->h_stage) (void)hipHostFree(ctx->h_stage);
   ctx->h_stage = nullptr;
   ctx->h_stage_bytes = 0;

@@ -73,7 +73,9 @@ class Scratch {
   int n_mine_ = 0;
   bool idle_ = false;
 };
-// pinned host memory of the context (one block: the next call of this function may move it); nullptr if there is none
+// pinned host memory of the context (one block: the next call of this function may move it); nullptr if there is none or for
+// more than ESP_STAGE_KEEP bytes, the most that a context holds
+#define ESP_STAGE_KEEP ((size_t)32 << 20)
 void* esp_host_stage(esparse_ctx* ctx, size_t bytes);
 
 // device scratch that frees itself (measurement aids and the tuner)

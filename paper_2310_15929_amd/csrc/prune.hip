@@ -488,7 +488,7 @@ int esp_stats_device(esparse_ctx* ctx, const void* calib, long long T, long long
   double* d_am = reinterpret_cast<double*>(d_all + sq_bytes + (size_t)K * 8);
   unsigned int* d_hist = reinterpret_cast<unsigned int*>(d_am + K);
   const size_t out_bytes = (size_t)K * 8 + (ir ? hist_bytes : 0);
-  unsigned char* h_out = reinterpret_cast<unsigned char*>(out_bytes <= ((size_t)32 << 20) ? esp_host_stage(ctx, out_bytes) : nullptr);
+  unsigned char* h_out = reinterpret_cast<unsigned char*>(esp_host_stage(ctx, out_bytes));
   if (!h_out) {
     pageable.resize(out_bytes);
     h_out = pageable.data();
@@ -1483,13 +1483,20 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
   const long long nblk = use_lbs ? K / B : 0;
   if (swaps_out && !use_lbs && o->block > 0 && K % o->block == 0) memset(swaps_out, 0, sizeof(int64_t) * (K / o->block));
 
+  // pinned, each part used for one thing: scores, counts, exchanges per block, group values (beyond the largest pinned block
+  // from pageable memory)
+  std::vector<double> pageable;
   Scratch scratch(ctx);
   double* d_s = scratch.get<double>(K);
   double* d_sp = scratch.get<double>(K);
   int32_t* d_theta0 = scratch.get<int32_t>(K);
-  // pinned, each part used for one thing: scores, counts, exchanges per block, group values
-  double* h_stage = reinterpret_cast<double*>(esp_host_stage(ctx, (size_t)(K + 8 + nblk + K / m) * 8));
-  if (!d_s || !d_sp || !d_theta0 || !h_stage) return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation failed");
+  const size_t stage_count = (size_t)(K + 8 + nblk + K / m);
+  double* h_stage = reinterpret_cast<double*>(esp_host_stage(ctx, stage_count * 8));
+  if (!h_stage) {
+    pageable.resize(stage_count);
+    h_stage = pageable.data();
+  }
+  if (!d_s || !d_sp || !d_theta0) return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation failed");
   memcpy(h_stage, score, (size_t)K * 8);
   ESP_HIP(ctx, hipMemcpyAsync(d_s, h_stage, (size_t)K * 8, hipMemcpyHostToDevice, st));
 

@@ -245,8 +245,8 @@ def test_naive_shuffle_over_the_range_of_the_type(esp, ctx, N, K, dtype):
 
 
 # the ranks are counted on the device up to 3 x 2^16 channels and sorted on the host beyond: both sides of the line, equal means and
-# scores that are no numbers (behind all others, lower channel first)
-@pytest.mark.parametrize("K", [64, 3 << 16, (3 << 16) + 64, 3 << 18])
+# scores that are no numbers (behind all others, lower channel first); the last needs more staging memory than a context pins
+@pytest.mark.parametrize("K", [64, 3 << 16, (3 << 16) + 64, 1 << 22])
 def test_naive_shuffle_ranks(esp, ctx, K):
     W = _rand((3, K), torch.float16, 37, scale=0.02)
     rng = np.random.default_rng(K)
