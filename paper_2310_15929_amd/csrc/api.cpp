@@ -312,7 +312,7 @@ static int pick_variant(esparse_ctx* ctx, int sparse, int dtype, long long M, lo
   if (variant >= 0) return variant;
   const int v = tuned_variant(ctx, sparse, dtype, M, N, K, count);
   if (v >= 0) return v;
-  // the built-in choice is a function of the shape alone; looking it up takes a tenth of the time of making it (2 us)
+  // the built-in choice is a function of the shape alone (made in 0.3 us, on a first call in 2)
   const auto key = std::make_tuple(grouped ? -count : count, sparse, M, N, K);
   auto it = ctx->defaults.find(key);
   if (it != ctx->defaults.end()) return it->second;

@@ -1775,7 +1775,7 @@ struct Variant {
   int half;        // tile kind: 1 = dense only, stages of 32 channels and the macro tile of the sparse form
   int four8;       // tile kind: 1 = 4:8 only, bitmaps expanded to dense operands in registers, dense instruction
 };
-static const Variant kVariants[] = {
+static constexpr Variant kVariants[] = {
     {"wave_r2_t1_splitk", KIND_WAVE, 2, 1, 1, 0},
     {"wave_r2_t2_splitk", KIND_WAVE, 2, 2, 1, 0},
     {"wave_r4_t2", KIND_WAVE, 4, 2, 0, 0},
@@ -1842,16 +1842,12 @@ static const Variant kVariants[] = {
     {"tile48_w8_t128", KIND_TILE, 8, 2, 0, 4, 0, 0, 0, 0, 1},
     {"tile48_w8_t128_splitk", KIND_TILE, 8, 2, 1, 4, 0, 0, 0, 0, 1},  // ... with K split over workgroups (M <= 512)
 };
-static const int kNumVariants = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
+static constexpr int kNumVariants = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
 
 int esp_num_variants() { return kNumVariants; }
 const char* esp_variant_name(int v) { return kVariants[v].name; }
 
-bool esp_variant_applicable(int v, long long M, long long N, long long K, int sparse) {
-  (void)N;
-  (void)K;
-  if (v < 0 || v >= kNumVariants) return false;
-  const Variant& var = kVariants[v];
+static bool applicable(const Variant& var, long long M, int sparse) {
   if (var.four8 && (sparse != 2 || M < 64)) return false;
   if (sparse == 2 && var.kind == KIND_STREAM) return M <= 128 && var.tt == 4;  // the stream kernels with a ring of four slots
   if (sparse == 2 && !var.four8) {
@@ -1875,9 +1871,18 @@ bool esp_variant_applicable(int v, long long M, long long N, long long K, int sp
   return true;
 }
 
-static int variant_index(const char* name) {
-  for (int v = 0; v < kNumVariants; v++)
-    if (!strcmp(kVariants[v].name, name)) return v;
+bool esp_variant_applicable(int v, long long M, long long N, long long K, int sparse) {
+  (void)N;
+  (void)K;
+  return v >= 0 && v < kNumVariants && applicable(kVariants[v], M, sparse);
+}
+
+static constexpr int variant_index(const char* name) {
+  for (int v = 0; v < kNumVariants; v++) {
+    const char *a = kVariants[v].name, *b = name;
+    while (*a && *a == *b) a++, b++;
+    if (*a == *b) return v;
+  }
   return -1;
 }
 
@@ -1904,7 +1909,7 @@ struct Cost {
   const char* name;
   float fixed, weights, tokens, memory, partial, reduce, rounds;
 };
-static const Cost kCost24[] = {
+static constexpr Cost kCost24[] = {
     {"ksplit_w16_r2", 2.13f, 2.44e-05f, 9.77e-06f, 6.88e-08f, 0.f, 0.f, 1.38f},
     {"ksplit_w16_r4_k4", 4.52f, 2.23e-05f, 4.2e-06f, 8.57e-08f, 9.91e-08f, 0.f, 2.45f},
     {"ksplit_w8_r1", 2.99f, 3.28e-05f, 9.35e-06f, 5.48e-08f, 0.f, 0.f, 0.0483f},
@@ -1926,7 +1931,7 @@ static const Cost kCost24[] = {
     {"tile_w8_t128", 0.f, 0.448f, 5.32f, 1.79e-07f, 0.f, 0.f, 0.f},
     {"tile_w8_t128_splitk", 1.1f, 0.474f, 4.25f, 1.06e-07f, 1.85e-07f, 3.59f, 0.f},
 };
-static const Cost kCostDense[] = {
+static constexpr Cost kCostDense[] = {
     {"ksplit_w16_r1", 2.45f, 1.85e-05f, 1.12e-05f, 6.94e-08f, 0.f, 0.f, 0.741f},
     {"ksplit_w16_r2", 1.89f, 1.79e-05f, 1.21e-05f, 7e-08f, 0.f, 0.f, 1.65f},
     {"ksplit_w16_r4_k4", 4.58f, 1.55e-05f, 0.f, 1.16e-07f, 1.16e-07f, 0.f, 2.43f},
@@ -1946,7 +1951,7 @@ static const Cost kCostDense[] = {
     {"tile_w8_t256", 0.f, 0.607f, 4.94f, 5.23e-08f, 0.f, 0.f, 0.f},
     {"tile_w8_t256_h", 0.f, 1.01f, 12.f, 6.35e-08f, 0.f, 0.f, 0.f},
 };
-static const Cost kCost48[] = {
+static constexpr Cost kCost48[] = {
     {"ksplit_w8_r1", 4.66f, 3.3e-05f, 9.78e-06f, 5.48e-08f, 0.f, 0.f, 0.409f},
     {"ksplit_w8_r1_q", 3.98f, 2.41e-05f, 5.65e-06f, 5.66e-08f, 0.f, 0.f, 1.39f},
     {"ksplit_w8_r2", 4.29f, 2.94e-05f, 8.4e-06f, 5.57e-08f, 0.f, 0.f, 0.933f},
@@ -1994,26 +1999,27 @@ static long long stream_span(long long nrb, long long nks, long long slots) {
   return span;
 }
 
-// the stream kernel whose row blocks (8, 9 or 11 row tiles), each cut into p equal spans of an even number of steps, come
-// closest to one workgroup per CU without a span crossing a row block; eight waves if none fills 200 CUs that way
-static const char* aligned_stream(long long nrt, long long nks) {
-  static const struct { int nw; const char* name; } cand[] = {{8, "stream_w8_r1_d3"}, {9, "stream_w9_r1_d3"}, {11, "stream_w11_r1_d3"}};
+// waves of the stream kernel whose row blocks (8, 9 or 11 row tiles), each cut into p equal spans of an even number of steps,
+// come closest to one workgroup per CU without a span crossing a row block; eight if none fills 200 CUs that way
+static int aligned_stream(long long nrt, long long nks) {
   long long best = 0;
-  const char* pick = cand[0].name;
-  for (const auto& c : cand) {
-    const long long nrb = (nrt + c.nw - 1) / c.nw;
+  int pick = 8;
+  for (int nw : {8, 9, 11}) {
+    const long long nrb = (nrt + nw - 1) / nw;
     if (nrb > 256) continue;
     long long pcs = 256 / nrb;
     while (pcs > 1 && (nks % pcs != 0 || (nks / pcs) % 2 != 0 || nks / pcs < 8)) pcs--;
     if (nrb * pcs > best) {
       best = nrb * pcs;
-      pick = c.name;
+      pick = nw;
     }
   }
-  return best >= 200 ? pick : cand[0].name;
+  return best >= 200 ? pick : 8;
 }
 
 static int compact_tokens(long long M);
+
+static bool is_decode_kernel(const Variant& v) { return v.kind == KIND_KSPLIT && v.split_mode == 0; }
 
 // estimated time (us) of `count` products of one shape in one launch (decode kernels) or of one product
 static double estimate(const Cost& c, const Variant& v, long long M, long long N, long long K, int sparse, int count) {
@@ -2052,42 +2058,52 @@ static double estimate(const Cost& c, const Variant& v, long long M, long long N
          (pieces > 0.0 ? c.partial * out * pieces + c.reduce : 0.0);
 }
 
+// The rows with their variants beside them, joined by the compiler: a row whose name no variant has does not compile, and a choice
+// reads one stretch of memory (out of cold caches, as on the first call on a shape, 1.8 us; 3.0 with look-ups by name).
+struct CostRow {
+  Cost cost;
+  Variant v;
+  int index;
+};
+struct CostRows {
+  CostRow row[24];
+  int n;
+};
+template <size_t N>
+static constexpr CostRows with_variants(const Cost (&table)[N]) {
+  static_assert(N <= sizeof(CostRows::row) / sizeof(CostRow), "room for the rows");
+  CostRows out{};
+  out.n = (int)N;
+  for (size_t i = 0; i < N; i++) {
+    const int v = variant_index(table[i].name);
+    out.row[i] = CostRow{table[i], kVariants[v], v};  // a name that no variant has ends the compilation here
+  }
+  return out;
+}
+static constexpr CostRows kRows24 = with_variants(kCost24), kRowsDense = with_variants(kCostDense), kRows48 = with_variants(kCost48);
+
 // grouped: for the group calls of the sparse product, whose two halves need a decode kernel; up to 32 tokens they get one whatever the
 // count
 static int pick_by_cost(long long M, long long N, long long K, int sparse, int count, bool grouped, bool partials) {
-  const Cost* table = sparse == 2 ? kCost48 : (sparse ? kCost24 : kCostDense);
-  // the rows' variants, looked up by name once (a first call on a shape pays for the estimate)
-  struct Rows {
-    int vi[3][32];
-    Rows() {
-      const Cost* tables[3] = {kCostDense, kCost24, kCost48};
-      const size_t n[3] = {sizeof(kCostDense) / sizeof(Cost), sizeof(kCost24) / sizeof(Cost), sizeof(kCost48) / sizeof(Cost)};
-      for (int m = 0; m < 3; m++)
-        for (size_t i = 0; i < n[m]; i++) vi[m][i] = variant_index(tables[m][i].name);
-    }
-  };
-  static_assert(sizeof(kCostDense) / sizeof(Cost) <= 32 && sizeof(kCost24) / sizeof(Cost) <= 32 && sizeof(kCost48) / sizeof(Cost) <= 32, "room for the rows");
-  static const Rows looked_up;
-  const int* variants = looked_up.vi[sparse == 2 ? 2 : (sparse ? 1 : 0)];
-  const int rows = sparse == 2 ? (int)(sizeof(kCost48) / sizeof(Cost)) : (sparse ? (int)(sizeof(kCost24) / sizeof(Cost)) : (int)(sizeof(kCostDense) / sizeof(Cost)));
-  const char* stream = aligned_stream((N + 15) / 16, esp_round_up(K, 256) / 64);
-  int best = variant_index("ksplit_w8_r1");
-  if (M > 64) best = variant_index(sparse == 2 ? "tile48_w8_r128_t256" : "tile_w8_r128_t128");
+  constexpr int kDecode = variant_index("ksplit_w8_r1"), kTile = variant_index("tile_w8_r128_t128"), kTile48 = variant_index("tile48_w8_r128_t256");
+  static_assert(kDecode >= 0 && kTile >= 0 && kTile48 >= 0, "kernels that take every shape of their token counts");
+  const CostRows& rows = sparse == 2 ? kRows48 : (sparse ? kRows24 : kRowsDense);
+  const int stream_waves = M <= 128 ? aligned_stream((N + 15) / 16, esp_round_up(K, 256) / 64) : 0;
+  int best = M <= 64 ? kDecode : (sparse == 2 ? kTile48 : kTile);
   double best_t = 1e30;
-  for (int i = 0; i < rows; i++) {
-    const int vi = variants[i];
-    const Variant& v = kVariants[vi];
-    if (!esp_variant_applicable(vi, M, N, K, sparse)) continue;
-    if (!partials && (v.split_mode == 1 || v.kind == KIND_STREAM)) continue;
-    if (v.kind == KIND_STREAM && strcmp(table[i].name, stream)) continue;
-    if (v.kind == KIND_KSPLIT && M > 64) continue;  // 4:8 beyond 64 tokens: 64 at a time, slower than the tiles throughout
-    const bool shared = esp_variant_is_decode_kernel(vi);  // the products of a group share the launch
+  for (int i = 0; i < rows.n; i++) {
+    const CostRow& r = rows.row[i];
+    if (!applicable(r.v, M, sparse)) continue;
+    if (!partials && (r.v.split_mode == 1 || r.v.kind == KIND_STREAM)) continue;
+    if (r.v.kind == KIND_STREAM && r.v.nw != stream_waves) continue;
+    if (r.v.kind == KIND_KSPLIT && M > 64) continue;  // 4:8 beyond 64 tokens: 64 at a time, slower than the tiles throughout
+    const bool shared = is_decode_kernel(r.v);  // the products of a group share the launch
     if (grouped && !shared && M <= 32) continue;  // up to 32 tokens a group is one launch, and its halves exist
-    double t = estimate(table[i], v, M, N, K, sparse, shared ? count : 1);
+    double t = estimate(r.cost, r.v, M, N, K, sparse, shared ? count : 1);
     if (count > 1 && !shared) t = t * count + 4.0 * (count - 1);  // one after the other, each with its staging launch
     if (t < best_t) {
       best_t = t;
-      best = vi;
+      best = r.index;
     }
   }
   return best;
@@ -2603,5 +2619,5 @@ int esp_matmul_group_device(esparse_ctx* ctx, int sparse, int count, const void*
 }
 
 bool esp_variant_is_decode_kernel(int v) {
-  return v >= 0 && v < kNumVariants && kVariants[v].kind == KIND_KSPLIT && kVariants[v].split_mode == 0;
+  return v >= 0 && v < kNumVariants && is_decode_kernel(kVariants[v]);
 }

@@ -2,6 +2,7 @@
 answers its closed-form size queries and rejects bad arguments before touching the GPU."""
 import ctypes as C
 import os
+import random
 import re
 import subprocess
 import sys
@@ -138,6 +139,28 @@ def test_halves_of_a_group_up_to_32_tokens_have_a_decode_kernel():
                         assert lib.esparse_spmm_group_staged(ctx._h, count, M, a, N, K, 0, n, m, a, fake, 1 << 40, -1) == -4, args
     a = (C.c_void_p * 1)(fake)
     assert lib.esparse_stage_activations_group(ctx._h, 1, a, 33, None, 4096, 4096, 0, 2, 4, fake, 1 << 40, -1) == -2
+
+
+def test_built_in_choices_can_run():
+    """Over all sizes: the built-in choice is a kernel that takes the shape; a group of at most 32 tokens gets one with a grouped
+    form; where no partial tiles fit, it is one that keeps none."""
+    lib = esp.load_library()
+    ll, i, b = C.c_longlong, C.c_int, C.c_bool
+    pick, without, fits = lib._Z19esp_default_variantxxxiib, lib._Z36esp_default_variant_without_partialsxxxi, lib._Z22esp_variant_applicableixxxi
+    pick.argtypes, without.argtypes, fits.argtypes, fits.restype = [ll, ll, ll, i, i, b], [ll, ll, ll, i], [i, ll, ll, ll, i], b
+    names = [esp.variant_name(v) for v in range(esp.num_variants())]
+    rng = random.Random(5)
+    for _ in range(4000):
+        M, N, K = int(2 ** rng.uniform(0, 20)), int(2 ** rng.uniform(0, 18)), 8 * int(2 ** rng.uniform(0, 14))
+        for sparse in (0, 1, 2):
+            for count in (1, 2, 4):
+                for grouped in (False, True):
+                    v = pick(M, N, K, sparse, count, grouped)
+                    assert 0 <= v < len(names) and fits(v, M, N, K, sparse), (M, N, K, sparse, count)
+                    if grouped and M <= 32:
+                        assert names[v].startswith("ksplit") and "_k" not in names[v]
+            v = without(M, N, K, sparse)
+            assert fits(v, M, N, K, sparse) and not any(p in names[v] for p in ("splitk", "stream", "_k")), (M, N, K, sparse, names[v])
 
 
 @pytest.mark.parametrize("room_mib", [64, 1])
