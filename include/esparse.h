@@ -178,7 +178,9 @@ int esparse_spmm_static(esparse_ctx* ctx, const void* X, long long M, const void
  * matrix with several weight matrices sharing one perm, or that time the multiply alone:
  * esparse_stage_activations writes X[:, perm] in the kernels' operand order into the workspace
  * (sized by esparse_spmm_workspace(M, N, K) for the largest N that will use it);
- * esparse_spmm_staged multiplies what the workspace holds.  Same errors as esparse_spmm. */
+ * esparse_spmm_staged multiplies what the workspace holds (the staged activations stay; a kernel that splits K over
+ * workgroups - the built-in choice may be one at any M - writes its partial tiles behind them, so calls that share a workspace
+ * are ordered on one stream or with events).  Same errors as esparse_spmm. */
 int esparse_stage_activations(esparse_ctx* ctx, const void* X, long long M, const int32_t* perm,
                               long long N, long long K, esparse_dtype dtype, void* workspace,
                               size_t workspace_bytes);
@@ -211,7 +213,8 @@ int esparse_dense_gemm_staged(esparse_ctx* ctx, long long M, const void* packed_
  * (the default up to 32 tokens; beyond, where the built-in estimate prefers it), and one after the other otherwise.  X, native_w, perm, Y: HOST arrays of count
  * DEVICE pointers (perm may be NULL = identity for all, or hold NULL entries); members may share X.
  * workspace: DEVICE, 256-byte aligned, at least esparse_spmm_group_workspace bytes.  Results are
- * bitwise those of esparse_spmm with the same variant.  Errors as esparse_spmm; count outside 1..4:
+ * bitwise those of esparse_spmm with the same named variant (the built-in choice, variant -1, depends on count, and
+ * kernels add in different orders).  Errors as esparse_spmm; count outside 1..4:
  * EINVAL.  Does not synchronise. */
 int esparse_spmm_group_workspace(int count, long long M, long long N, long long K, size_t* bytes);
 int esparse_spmm_group(esparse_ctx* ctx, int count, const void* const* X, long long M,

@@ -207,7 +207,7 @@ struct KsplitArgs {
   uint16_t* Y[ESP_MAX_GROUP];
   float* partial;  // single products with K split over workgroups (gridDim.z > 1): fp32 partial tiles [split][Mp][Np]
   int sps;         // ... and the steps per split
-  // FOLD kernels (one or two tokens): the activations in original channel order and theta; the workgroup gathers them itself
+  // FOLD kernels (few tokens): the activations in original channel order and theta; the workgroup gathers them itself
   const uint16_t* X[ESP_MAX_GROUP];
   const int32_t* perm[ESP_MAX_GROUP];
   long long K;
@@ -1899,11 +1899,14 @@ static constexpr int variant_index(const char* name) {
 //   partial   bytes of fp32 partial tiles, written and read back; reduce: their launch
 //   rounds    decode kernels: workgroups of one CU; stream kernels: steps of a workgroup; tile kernels: steps over all
 //             rounds, the last one counted as far as it is filled (the board's power limit is shared by the CUs that work)
-// The constants are least-squares fits to the times of every kernel, weights cold, on 67 (2:4), 18 (dense, 4:8) weight
-// shapes from 512 x 512 to 36864 x 9216 with 1 .. 4096 tokens (670, 191 and 189 products; mean error of an estimate 5 %).
-// Picked by them, products take 1.012 / 1.016 / 1.008 times the fastest kernel's time in the geometric mean (2:4 / dense /
-// 4:8); the rules on row and token counts they replace took 1.19 / 1.18 / 1.11 times it.  240 of the 2:4 products were kept
-// out of a first fit and came out at 1.02.
+// The constants are least-squares fits to the times of every kernel, weights cold, on 35 (2:4), 18 (dense) and 17 (4:8) weight
+// shapes from 512 x 512 to 36864 x 9216 with 1 .. 4096 tokens (670, 191 and 189 products; mean error of an estimate 5 %);
+// profiles/kernel_choice_times.csv and kernel_choice_fit.py beside it hold the times and make the constants again.
+// Picked by them, products take 1.012 / 1.016 / 1.008 times the time of the fastest of all kernels in the geometric mean (2:4 /
+// dense / 4:8) and 1.25 / 1.22 / 1.17 times it at worst; the rules on row and token counts they replace took 1.19 / 1.17 / 1.11 times
+// it, 2.9 / 2.8 / 2.0 at worst.  That is on the products of the fit, except that 240 of the 2:4 ones were kept out of a first fit and
+// came out at 1.02.  The estimate loses to the old rule by more than 3 % on 16, 3 and 12 of them: up to 12 % (512 x 2048 x 2048), 6 to
+// 10 % on matrices of a few MB at 20 to 32 tokens; the 4:8 ones are the same kernel timed twice.
 // ------------------------------------------------------------------------------------------------
 struct Cost {
   const char* name;
@@ -2189,7 +2192,7 @@ static void launch_wave_tile(const Variant& v, dim3 grid, hipStream_t st, const 
 // repeats it, so it pays while workgroups x channels x tokens stays small (4096 x 4096, one token: 7.0 us against 6.5 + 2.1
 // for the staging launch; 36864 x 9216, 2304 workgroups: 77 us against 58 + 2.3, hence the limits; 16 tokens x 512
 // channels, 32 workgroups: a call 14.6 -> 11.5 us, one launch of 6 us instead of two of 3.5 and 3.9 and the gap).  Beyond two
-// tokens at most 9216 channels x tokens: over 10 decode kernels and 512 to 16384 rows the launches take 0.69 to 1.02 times those of
+// tokens at most 9216 channels x tokens: over 11 decode kernels and 512 to 16384 rows the launches take 0.69 to 1.02 times those of
 // the staged form there, and up to 1.07 times at 10240 (8 tokens, 4096 x 1280, ksplit_w8_r1: 6.5 -> 6.9 us).
 static bool ksplit_folds(const Variant& v, long long M, long long Np, long long Kp) {
   if (v.kind != KIND_KSPLIT || v.split_mode != 0 || M > 16) return false;
