@@ -16,7 +16,10 @@ int esp_fail(esparse_ctx* ctx, int code, const char* fmt, ...) {
     va_start(ap, fmt);
     vsnprintf(buf, sizeof buf, fmt, ap);
     va_end(ap);
-    ctx->err = buf;
+    try {
+      ctx->err = buf;
+    } catch (...) {  // no host memory for the message
+    }
   }
   return code;
 }
@@ -89,13 +92,9 @@ static int guarded(esparse_ctx* ctx, F call) noexcept {
   try {
     return call();
   } catch (const std::bad_alloc&) {
-    try {
-      return esp_fail(ctx, ESPARSE_ENOMEM, "out of host memory");
-    } catch (...) {
-      return ESPARSE_ENOMEM;
-    }
+    return esp_fail(ctx, ESPARSE_ENOMEM, "out of host memory");
   } catch (...) {
-    return ESPARSE_EHIP;
+    return esp_fail(ctx, ESPARSE_EHIP, "unexpected exception");
   }
 }
 
@@ -690,19 +689,22 @@ int esparse_tune_load(esparse_ctx* ctx, const char* path) {
   if (!ctx || !path) return ESPARSE_EINVAL;
   FILE* f = fopen(path, "r");
   if (!f) return esp_fail(ctx, ESPARSE_EINVAL, "cannot open %s", path);
-  char line[256];
-  while (fgets(line, sizeof line, f)) {
-    if (line[0] == '#') continue;
-    int sp, dt, count = 1;
-    long long M, N, K;
-    char name[128];
-    const int got = sscanf(line, "%d %d %lld %lld %lld %127s %d", &sp, &dt, &M, &N, &K, name, &count);
-    if (got < 6 || count < 1 || count > 4) continue;
-    for (int v = 0; v < esp_num_variants(); v++)
-      if (!strcmp(name, esp_variant_name(v))) ctx->tuned[std::make_tuple(count, sp, dt, M, N, K)] = v;
-  }
+  const int rc = guarded(ctx, [&] {
+    char line[256];
+    while (fgets(line, sizeof line, f)) {
+      if (line[0] == '#') continue;
+      int sp, dt, count = 1;
+      long long M, N, K;
+      char name[128];
+      const int got = sscanf(line, "%d %d %lld %lld %lld %127s %d", &sp, &dt, &M, &N, &K, name, &count);
+      if (got < 6 || count < 1 || count > 4) continue;
+      for (int v = 0; v < esp_num_variants(); v++)
+        if (!strcmp(name, esp_variant_name(v))) ctx->tuned[std::make_tuple(count, sp, dt, M, N, K)] = v;
+    }
+    return (int)ESPARSE_OK;
+  });
   fclose(f);
-  return ESPARSE_OK;
+  return rc;
 }
 
 }  // extern "C"
