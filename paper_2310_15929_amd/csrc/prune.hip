@@ -645,34 +645,40 @@ __device__ __forceinline__ double lanes_total(double part) {
 // ------------------------------------------------------------------------------------------------
 // The exchanges are found with a table of its own that is cheaper to evaluate and proven close enough.
 //
-// What a candidate x adds to a row depends on the group's other members only through the NKEEP largest of them,
-// o_0 >= o_1 >= ...: the row keeps o_0 + .. + o_(NKEEP-2) + max(o_(NKEEP-1), x).  Summed over the rows, the first part is
-// one number per (group, member) and the second takes a maximum and an addition per row and candidate - two float64
-// operations instead of 5 (2:4) or about 60 (4:8).  The sum is that of the exact table in another order: with no negative
-// value both are within (N + 4) 2^-53 of the real one, relatively, and a group's value with a member replaced is at
-// most twice the largest v(g) (a channel's column is nowhere larger than its own group's largest).  So two deltas of
+// With the members of a row in order, w_0 >= w_1 >= ..., and n = NKEEP: what a candidate x adds in place of member i depends on
+// whether i is among the n largest.  If not, the others keep w_0 + .. + w_(n-2) and max(w_(n-1), x); if it is, they keep
+// the n largest without i and max(w_n, x).  With L = max(w_n, x) and D = max(w_(n-1), x) - L, both the same for all members, the
+// value of the group with member i replaced by x is
+//   base_i + sum over the rows of L + sum over the rows where i is not among the n largest of D,
+// base_i a number per member.  That is four float64 operations per row and candidate for the whole group and a product of a matrix
+// of zeros and ones with D, four members at a time on the matrix instruction (which runs on the float64 pipes: 16 clocks against 4 of an
+// addition), where the exact table takes 5 operations (2:4) or about 60 (4:8) per member.
+//
+// With no negative value all terms are at least zero, so the sum, in whatever order, is within (N + 6) 2^-53 of the real one, relatively,
+// and what base_i loses where the n largest without i come from a subtraction is below 4 2^-53 v(g) in all; the exact
+// table's is within (N + 4) 2^-53.  A group's value with a member replaced is at most twice the largest v(g) (a channel's column is
+// nowhere larger than its own group's largest).  So two deltas of
 // this table that differ by more than LBS_TOL (N + 64) 2^-53 max v(g) are in the same order in the exact table (four
-// values of both deltas, in both tables: 32 (N + 4) 2^-53 max v(g) and roundings; LBS_TOL is twice that), and a delta is
+// values of both deltas, in both tables: 32 (N + 8) 2^-53 max v(g) and roundings; LBS_TOL is twice that), and a delta is
 // above or below zero in both if it is farther than that from it.  A round whose best exchange is not proven that way - a
 // tie, an exchange that moves the total by rounding only, weights or scores that are not finite or scores below zero -
 // leaves the block to the exact table from there on, so the exchanges made are those of the exact table in every case.
 //
 // Replacing the member that the last exchange brought into a group leaves the same other members as before it, so those
-// entries stay valid: NM = MG - 1 members per touched group are re-evaluated.
+// entries stay valid and are not written again.
 //
-// A workgroup (8 waves) takes NG groups, 16 QC columns and every nsplit-th set of 8 x 32 rows.  A lane owns QC columns and
-// every fourth row of its wave, so the panel value and its product with the score are
-// formed once for NG * NM combinations; the 16 lanes of a row read its operands once and pass them around (read out of LDS
-// by every lane they kept the LDS as busy as the float64 pipes).  A wave forms the
-// operands of its next 32 rows itself (one lane per row and group: the NKEEP + 1 largest members, read from PT - gathered
+// A workgroup (8 waves) takes NG groups and 16 QC columns, a wave an equal share of the rows.  A lane owns QC columns and
+// every fourth row of its wave, so the panel value and its product with the score are formed once for NG groups.  A wave forms the
+// operands of its next 32 rows itself (one lane per row and group, members read from PT - gathered
 // from P they cost the vector-memory path a third of the kernel's time) and needs no barrier.
 //
-// Bound by float64 instructions (a wave's takes 4 clocks of its SIMD, adds, maxima and conversions alike).  64 blocks of
-// 4096 x 64, 2:4: two touched groups 18 us, all groups 142 us (exact table: 142 and 677); 80 blocks of 5120 x 64, 4:8: 57 and
-// 254 us (1034 and 4525).
+// Bound by float64 instructions.  64 blocks of 4096 x 64, 2:4: all groups 139 us (exact table 677), a round of two touched groups
+// 12 of its 17 us (k_lbs_rounds; with two operations per row, candidate and member 18, exact 142); 80 blocks of 5120 x 64, 4:8: 227 (4525) and 50
+// of 58 us (two operations per member: 254 and 57; exact 1034).
 #define LBS_WAVES 8
 #define LBS_ROWS 32  // rows whose operands a wave keeps in LDS
 #define LBS_ROUNDS_QUEUED 12
+#define LBS_ROUNDS_MAX 64     // times block^2: a block shuffle that has not ended by then is reported
 #define LBS_REC 12  // ints per touched group: exchanged position (-1: none), columns of the members
 #define LBS_TOL 64.0
 enum { LBS_FAST = 0, LBS_DONE = 1, LBS_EXACT = 2 };  // state of a block
@@ -899,47 +905,33 @@ __global__ void __launch_bounds__(1024) k_lbs_exact_2_4(const uint16_t* __restri
 }
 
 // ---- the table that is cheaper to evaluate
-// the value of lane LANE of each row of 16 lanes in all lanes of that row
-template <int LANE>
-__device__ __forceinline__ double row_bcast(double v) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x150 + LANE, 0xf, 0xf, true);
-  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x150 + LANE, 0xf, 0xf, true);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-#else
-  return v;
-#endif
-}
-
-// a + b with half of the lanes of each exchanged: lanes 0-31 get a[l] + a[l + 32], lanes 32-63 b[l - 32] + b[l]
-// (HALF), or the same within each pair of 16-lane rows
-template <bool HALF>
-__device__ __forceinline__ double swap_add(double a, double b) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
-  unsigned int r[4];
-  if (HALF) {
-    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned int)x, (unsigned int)y, false, false);
-    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned int)(x >> 32), (unsigned int)(y >> 32), false, false);
-    r[0] = lo[0]; r[1] = lo[1]; r[2] = hi[0]; r[3] = hi[1];
-  } else {
-    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned int)x, (unsigned int)y, false, false);
-    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned int)(x >> 32), (unsigned int)(y >> 32), false, false);
-    r[0] = lo[0]; r[1] = lo[1]; r[2] = hi[0]; r[3] = hi[1];
-  }
-  return __longlong_as_double(((long long)r[2] << 32) | r[0]) + __longlong_as_double(((long long)r[3] << 32) | r[1]);
-#else
-  return a + b;
-#endif
-}
-
 __device__ __forceinline__ int uniform(int v) {
 #if defined(__HIP_DEVICE_COMPILE__)
   return __builtin_amdgcn_readfirstlane(v);
 #else
   return v;
 #endif
+}
+
+// the value of lane `at` (wave-uniform)
+__device__ __forceinline__ int lane_of(int v, int at) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_readlane(v, at);
+#else
+  return v;
+#endif
+}
+__device__ __forceinline__ double lane_of(double v, int at) {
+  const long long b = __double_as_longlong(v);
+  return __longlong_as_double(((long long)lane_of((int)(b >> 32), at) << 32) | (unsigned int)lane_of((int)b, at));
+}
+
+// the same value, but nothing that is formed from it is moved ahead of this place (kept in registers through a loop whose body needs them all)
+__device__ __forceinline__ int opaque(int v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(v));
+#endif
+  return v;
 }
 
 // orders the LDS accesses of one wave as they are written (its lanes exchange data through LDS)
@@ -971,210 +963,277 @@ __device__ __forceinline__ double min_f64(double a, double b) {
 #endif
 }
 
-template <int DT, int NKEEP, int MG, int NG, int NM, int QC>
-__global__ void __launch_bounds__(64 * LBS_WAVES, 4) k_lbs_eval(const uint16_t* __restrict__ P, const uint16_t* __restrict__ PT, const double* __restrict__ sp /*[K] score in panel order*/,
-                                                              const int* __restrict__ rec /*[nblk][2][LBS_REC] exchanged positions and their groups*/,
-                                                              long long N, long long Npad, int B, int slices, double* __restrict__ S /*[nsplit][nblk][B][B]*/) {
-  constexpr int RLW = 4;                 // rows of a wave at a time, 16 lanes each
-  constexpr int U = LBS_ROWS / RLW;      // rows of a lane per batch
-  constexpr int NC = NG * NM;            // combinations of group and member
-  constexpr int XC = 16 * QC;            // columns of a workgroup
-  static_assert(NG == 1 || NG == 2, "one or two groups per workgroup");
-  static_assert(NC <= 16 && (QC == 2 || QC == 4), "a row's operands fit its 16 lanes");
-  constexpr int NCP = NC | 1;            // operands of a row in LDS
-  constexpr int ROOM = LBS_ROWS * NCP > NC * (XC + 1) ? LBS_ROWS * NCP : NC * (XC + 1);
-  __shared__ __align__(16) double s_o[LBS_WAVES * ROOM];  // per wave: operands; at the end its sums
-  __shared__ double s_ms[LBS_WAVES * 2 * MG];
-  __shared__ int s_mc[LBS_WAVES * 2 * MG];
-  const int blk = blockIdx.x, nblk = gridDim.x, split = blockIdx.y, nsplit = gridDim.y;
-  const int slice = (int)blockIdx.z % slices, gset = (int)blockIdx.z / slices;
-  const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
-  const int rlw = lane / 16, xl = lane % 16;
-  const int col0 = slice * XC + QC * xl;
-  const int colc = col0 < B ? col0 : 0;  // columns past the block compute along and are dropped at the end
-  // operand lane: row ir of the batch; NG = 2: group ih, all members; NG = 1: members ih, ih + 2, ...
-  const int ir = lane % LBS_ROWS, ih = lane / LBS_ROWS;
-  // batches of 32 rows: rows rb + u RLW + rlw of the panel, which is padded to whole batches; rows past N are replaced
-  // by zeros
-  const long long step = (long long)nsplit * LBS_WAVES * LBS_ROWS;
-  const long long rb0 = (long long)(split * LBS_WAVES + wave) * LBS_ROWS;
-  const uint16_t* Pb = P + (long long)blk * Npad * B;
-  const int xoff = rlw * B + colc;
-  // the values are loaded AHEAD rows ahead: a row takes about 1700 clocks with four waves per SIMD, a load from the
-  // last-level cache as long
-  constexpr int AHEAD = 3;
-  const uint16_t* prow = Pb + rb0 * B;
-  const long long jump = (step - LBS_ROWS) * B;  // from one batch of the wave to the next
-  uint2 next[AHEAD];
-  auto load_row = [&]() {
-    if (QC == 4) return *reinterpret_cast<const uint2*>(prow + xoff);
-    return uint2{*reinterpret_cast<const uint32_t*>(prow + xoff), 0u};
-  };
-#pragma unroll
-  for (int q = 0; q < AHEAD; q++, prow += RLW * B) next[q] = load_row();
-  // groups of this workgroup: their number (-1: none), the member that needs no evaluation, the members' columns
-  int wg[NG], wskip[NG];
-  int* smc = s_mc + (wave * 2 + (NG == 2 ? ih : 0)) * MG;  // the lane's group: columns and scores of the members
-  double* sms = s_ms + (wave * 2 + (NG == 2 ? ih : 0)) * MG;
-#pragma unroll
-  for (int k = 0; k < NG; k++) {
-    const int g = gset * NG + k;
-    if (NM == MG) {  // first round: positions are columns; the last workgroup of an odd number of groups has one only
-      wg[k] = g < B / MG ? g : -1;
-      wskip[k] = MG;
-      if (NG == 1 || ih == k)
-#pragma unroll
-        for (int i = 0; i < MG; i++) smc[i] = wg[k] < 0 ? i : g * MG + i;
-    } else {
-      const int* rg = rec + (blk * 2 + g) * LBS_REC;
-      if (rg[0] < 0) return;  // the block is done
-      wg[k] = rg[0] / MG;
-      wskip[k] = rg[0] % MG;
-      if (NG == 1 || ih == k)
-#pragma unroll
-        for (int i = 0; i < MG; i++) smc[i] = rg[1 + i];
-    }
+// the largest of 2^STEPS neighbouring lanes in each of them (STEPS = 3, 4 or 6)
+template <int CTRL>
+__device__ __forceinline__ double dpp_max(double v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, 0xf, 0xf, true), hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, 0xf, 0xf, true);
+  return fmax(v, __longlong_as_double(((long long)hi << 32) | (unsigned int)lo));
+#else
+  return v;
+#endif
+}
+template <int STEPS>
+__device__ __forceinline__ double lanes_max(double v) {
+  v = dpp_max<0xb1>(v);   // lanes 1 0 3 2
+  v = dpp_max<0x4e>(v);   // lanes 2 3 0 1
+  v = dpp_max<0x141>(v);  // lane 7 - l of each 8
+  if (STEPS > 3) v = dpp_max<0x140>(v);  // lane 15 - l of each 16
+  if (STEPS > 4) {
+    v = fmax(v, __shfl_xor(v, 16));
+    v = fmax(v, __shfl_xor(v, 32));
   }
-  const int iskip = NG == 2 && ih == 1 ? wskip[NG - 1] : wskip[0];
-  wave_lds_fence();
-  const uint16_t* PTb = PT + (long long)blk * B * Npad + ir;
-  uint16_t mraw[MG];
-  auto load_members = [&](long long rb) {
-#pragma unroll
-    for (int k = 0; k < MG; k++) mraw[k] = PTb[smc[k] * Npad + rb];
-  };
-  if (rb0 < N) load_members(rb0);
-  double s[QC];
-#pragma unroll
-  for (int q = 0; q < QC; q++) s[q] = sp[(long long)blk * B + colc + q];
-#pragma unroll
-  for (int k = 0; k < MG; k++) sms[k] = sp[(long long)blk * B + smc[k]];
-  double* so = s_o + wave * ROOM;
-  constexpr int NA = (NC * QC + 3) / 4 * 4;
-  double acc[NA];  // [NC][QC], a multiple of four
-#pragma unroll
-  for (int f = 0; f < NA; f++) acc[f] = 0.0;
-  constexpr int NB = NG == 2 ? NM : (NM + 1) / 2;  // members of an operand lane
-  double base[NB];  // operand lanes: what the other members keep besides the operand
-#pragma unroll
-  for (int c = 0; c < NB; c++) base[c] = 0.0;
+  return v;
+}
 
-  for (long long rb = rb0; rb < N; rb += step) {
-    {
-      const bool live = rb + ir < N;
-      double w[NKEEP + 1];  // the largest members, in order
-      wave_lds_fence();
-      auto member = [&](int k) {
-        const double v = (double)esp_to_float<DT>(mraw[k]) * sms[k];
-        return live ? v : 0.0;
-      };
+// c + the sum over the four rows k = lane / 16 of a[m][k] b[k][x], m = lane % 4 on the A side, x = lane % 16 on the B side; the result for
+// (m, x) is in lane 16 m + x (v_mfma_f64_4x4x4: four independent blocks of four columns; measured with one-hot operands)
+__device__ __forceinline__ double mfma_rows(double a, double b, double c) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+#else
+  return c + a * b;
+#endif
+}
+
+// what a wave of k_lbs_eval or k_lbs_rounds takes: all members of NG groups, 16 QC columns
+template <int MG, int NG, int QC>
+struct LbsShape {
+  static_assert((NG == 2 || NG == 4) && (MG == 4 || MG == 8) && (QC == 2 || QC == 4), "");
+  static constexpr int RLW = 4;             // rows of a wave at a time, 16 lanes each
+  static constexpr int U = LBS_ROWS / RLW;  // ... per batch
+  static constexpr int NC = NG * MG;        // combinations of group and member
+  static constexpr int NS = MG / 4;         // matrix instructions per group and column
+  static constexpr int GL = NG / 2;         // groups of an operand lane
+  static constexpr int XC = 16 * QC;        // columns
+  static constexpr int SUMS = NC * (XC + 1);                       // doubles: a wave's sums, the last of a row its base
+  static constexpr int OPS = LBS_ROWS * (2 * NG + NG * MG / 2);    // doubles: a wave's operands
+  static constexpr int LDS = LBS_WAVES * OPS > LBS_WAVES / 2 * SUMS ? LBS_WAVES * OPS : LBS_WAVES / 2 * SUMS;
+};
+
+// the QC values of a lane in the row at `p`
+template <int QC>
+__device__ __forceinline__ uint2 lbs_row(const uint16_t* __restrict__ p) {
+  if (QC == 4) return *reinterpret_cast<const uint2*>(p);
+  return uint2{*reinterpret_cast<const uint32_t*>(p), 0u};
+}
+
+// rows of one wave, a multiple of 16: wave w of a block's waves takes rows [w n, w n + n)
+__host__ __device__ __forceinline__ long long lbs_wave_rows(long long N, long long waves) { return (N + 16 * waves - 1) / (16 * waves) * 16; }
+
+// A workgroup's sums over its waves' rows [r0, r0 + nrows).  prow: the lane's place in the wave's first rows; next: its values
+// there, loaded.  smc, sms: the wave's columns and scores of the members, [NG][MG].  At the end s_o holds, complete after the barrier the function ends with, LBS_WAVES / 2
+// partial sums [NC][XC + 1] (lbs_sum adds them).
+template <int DT, int NKEEP, int MG, int NG, int QC>
+__device__ __forceinline__ void lbs_sums(const uint16_t* __restrict__ prow, uint2& next, const double (&s)[QC],
+                                         const uint16_t* __restrict__ PTb, const int* smc, const double* sms, long long r0, long long nrows, long long N,
+                                         long long Npad, int B, double* s_o, int wave, int lane) {
+  using Sh = LbsShape<MG, NG, QC>;
+  constexpr int RLW = Sh::RLW, XC = Sh::XC, NS = Sh::NS, GL = Sh::GL;
+  const int rlw = lane / 16, xl = lane % 16;
+  const int ir = lane % LBS_ROWS, ih = lane / LBS_ROWS;  // operand lane: row ir of the batch, groups ih, ih + 2
+  double* sw = s_o + wave * Sh::OPS;                                            // [row][NG][2]: the NKEEP-th and the next largest member
+  uint32_t* sm = reinterpret_cast<uint32_t*>(sw + LBS_ROWS * 2 * NG);           // [row][NG][MG]: upper half of 0.0 or 1.0
+  const long long r1 = r0 + nrows < N ? r0 + nrows : N;
+  uint16_t mraw[GL][MG];
+  auto load_members = [&](long long rb) {
+    const long long r = rb + ir < N ? rb + ir : N - 1;
+#pragma unroll
+    for (int h = 0; h < GL; h++)
+#pragma unroll
+      for (int k = 0; k < MG; k++) mraw[h][k] = PTb[smc[(ih + 2 * h) * MG + k] * Npad + r];
+  };
+  if (r0 < r1) load_members(r0);
+  double acc[NG][NS][QC], low[NG][QC];  // sum of D for the members that are not among the NKEEP largest; sum of max(o', x)
+#pragma unroll
+  for (int g = 0; g < NG; g++)
+#pragma unroll
+    for (int q = 0; q < QC; q++) {
+      low[g][q] = 0.0;
+#pragma unroll
+      for (int t = 0; t < NS; t++) acc[g][t][q] = 0.0;
+    }
+  double base[GL][MG];  // operand lanes: what the other members keep besides the candidate's place
+#pragma unroll
+  for (int h = 0; h < GL; h++)
+#pragma unroll
+    for (int k = 0; k < MG; k++) base[h][k] = 0.0;
+
+  for (long long rb = r0; rb < r1; rb += LBS_ROWS) {
+    const bool live = rb + ir < r1;
+    wave_lds_fence();
+#pragma unroll
+    for (int h = 0; h < GL; h++) {
+      const double* sc = sms + (ih + 2 * h) * MG;
+      double w[NKEEP + 1];  // the largest members in order
+      int raw[MG];
+#pragma unroll
+      for (int k = 0; k < MG; k++) raw[k] = live ? mraw[h][k] : 0;
+      auto member = [&](int k) { return (double)esp_to_float<DT>((uint16_t)raw[k]) * sc[k]; };
       w[0] = member(0);
 #pragma unroll
       for (int k = 1; k < MG; k++) {
-        double v = member(k);
+        double t = member(k);
 #pragma unroll
         for (int q = 0; q <= NKEEP && q < k; q++) {
-          const double hi = max_f64(w[q], v);
-          v = min_f64(w[q], v);
+          const double hi = max_f64(w[q], t);
+          t = min_f64(w[q], t);
           w[q] = hi;
         }
-        if (k <= NKEEP) w[k] = v;
+        if (k <= NKEEP) w[k] = t;
       }
+      double most = w[0];
 #pragma unroll
-      for (int q = 0; q < NB; q++) {  // without member i: the largest, with the next one in place of that member
-        const int c = NG == 2 ? q : 2 * q + ih;
-        double v;
-        if (NG == 2) v = member(q);
-        else v = ih ? member(2 * q + 1 < MG ? 2 * q + 1 : 2 * q) : member(2 * q);
-        if (NM < MG) {
-          double vn;
-          if (NG == 2) vn = member(q + 1);
-          else vn = ih ? member(2 * q + 2 < MG ? 2 * q + 2 : 2 * q) : member(2 * q + 1 < MG ? 2 * q + 1 : 2 * q);
-          v = c >= iskip ? vn : v;
-        }
-        double kept = v >= w[0] ? w[1] : w[0];
+      for (int k = 1; k < NKEEP - 1; k++) most = most + w[k];
+      const double all = most + w[NKEEP - 1];
+      uint32_t out[MG];
 #pragma unroll
-        for (int k = 1; k < NKEEP - 1; k++) kept = kept + (v >= w[k] ? w[k + 1] : w[k]);
-        base[q] = base[q] + kept;
-        if (c < NM) so[ir * NCP + (NG == 2 ? ih : 0) * NM + c] = v >= w[NKEEP - 1] ? w[NKEEP] : w[NKEEP - 1];
+      for (int k = 0; k < MG; k++) {
+        raw[k] = opaque(raw[k]);  // formed a second time: kept, the values would push sums out of the registers
+        const double v = member(k);
+        const bool top = v >= w[NKEEP - 1];
+        base[h][k] = base[h][k] + (top ? all - v : most);
+        out[k] = top ? 0u : 0x3ff00000u;
       }
-      wave_lds_fence();
+      const int at = ir * NG + ih + 2 * h;
+      *reinterpret_cast<double2*>(sw + at * 2) = double2{w[NKEEP - 1], w[NKEEP]};
+#pragma unroll
+      for (int k = 0; k < MG; k += 4) *reinterpret_cast<uint4*>(sm + at * MG + k) = uint4{out[k], out[k + 1], out[k + 2], out[k + 3]};
     }
-    const long long rnext = rb + step;
-    const bool full = rb + LBS_ROWS <= N;
-    if (rnext < N) load_members(rnext);
-    // lane c of a row reads the operand of combination c and hands it to the other 15
-    const double* src = so + rlw * NCP + (xl < NC ? xl : NC - 1);
-    double o_next = *src;
+    wave_lds_fence();
+    if (rb + LBS_ROWS < r1) load_members(rb + LBS_ROWS);
+    const int nu = r0 + nrows - rb < LBS_ROWS ? Sh::U / 2 : Sh::U;
+    const bool full = rb + nu * RLW <= N;
+    const double* wrow = sw + rlw * 2 * NG;
+    const uint32_t* mrow = sm + rlw * NG * MG + lane % 4;
+    // (The next row's values are loaded one step of four ahead: with four waves per SIMD a step takes as long as a load from the caches.
+    // Registers moved on from step to step would wait for the newest load all the same, and unrolled steps take a
+    // second set of registers for the results of the matrix instruction.)
 #pragma unroll 1
-    for (int u = 0; u < U; u++) {
-      const uint2 raw = next[0];
-#pragma unroll
-      for (int q = 1; q < AHEAD; q++) next[q - 1] = next[q];
-      if (u == U - AHEAD) prow += jump;
-      next[AHEAD - 1] = load_row();
+    for (int u = 0; u < nu; u++) {
+      const uint2 raw = next;
       prow += RLW * B;
-      const double o = o_next;
-      src += u < U - 1 ? RLW * NCP : 0;
-      o_next = *src;
+      next = lbs_row<QC>(prow);
+      double2 o[NG];
+      double m[NG][NS];
+#pragma unroll
+      for (int g = 0; g < NG; g++) {
+        o[g] = *reinterpret_cast<const double2*>(wrow + 2 * g);
+#pragma unroll
+        for (int t = 0; t < NS; t++) m[g][t] = __longlong_as_double((long long)mrow[g * MG + 4 * t] << 32);
+      }
+      wrow += RLW * 2 * NG;
+      mrow += RLW * NG * MG;
       double x[QC];
 #pragma unroll
       for (int q = 0; q < QC; q++) {
         const uint32_t two = q < 2 ? raw.x : raw.y;
         x[q] = (double)esp_to_float<DT>((uint16_t)(q & 1 ? two >> 16 : two & 0xffffu)) * s[q];
       }
-      if (!full) {  // no such row: adds exactly 0 whatever the scores are
-        const bool live = rb + u * RLW + rlw < N;
+      if (!full) {  // no such row: adds exactly 0
+        const bool there = rb + u * RLW + rlw < N;
 #pragma unroll
-        for (int q = 0; q < QC; q++) x[q] = live ? x[q] : 0.0;
+        for (int q = 0; q < QC; q++) x[q] = there ? x[q] : 0.0;
       }
-#define LBS_ADD(c)                                                                                         \
-  if constexpr (c < NC) {                                                                                  \
-    const double oc = row_bcast<c>(o);                                                                     \
-    _Pragma("unroll") for (int q = 0; q < QC; q++) acc[c * QC + q] = acc[c * QC + q] + max_f64(oc, x[q]);  \
-  }
-      LBS_ADD(0) LBS_ADD(1) LBS_ADD(2) LBS_ADD(3) LBS_ADD(4) LBS_ADD(5) LBS_ADD(6) LBS_ADD(7)
-#undef LBS_ADD
+#pragma unroll
+      for (int g = 0; g < NG; g++)
+#pragma unroll
+        for (int q = 0; q < QC; q++) {
+          const double hi = max_f64(o[g].x, x[q]), lo = max_f64(o[g].y, x[q]);
+          low[g][q] = low[g][q] + lo;
+#pragma unroll
+          for (int t = 0; t < NS; t++) acc[g][t][q] = mfma_rows(m[g][t], hi - lo, acc[g][t][q]);
+        }
     }
   }
-  // the four rows of the wave: row lane r ends up with the sums number 4 k + {0, 2, 1, 3}[r]
 #pragma unroll
-  for (int f = 0; f < NA; f += 4) acc[f / 4] = swap_add<false>(swap_add<true>(acc[f], acc[f + 1]), swap_add<true>(acc[f + 2], acc[f + 3]));
-  // operand lanes: over the 32 rows; NG = 1: the other half of the lanes holds the other members
+  for (int g = 0; g < NG; g++)
 #pragma unroll
-  for (int q = 0; q < NB; q++)
+    for (int t = 0; t < NS; t++)
 #pragma unroll
-    for (int d = 1; d < LBS_ROWS; d <<= 1) base[q] = base[q] + __shfl_xor(base[q], d);
-  wave_lds_fence();
-  double* red = so;  // [NC][XC + 1]: the wave's sums and, last in a row, its base
+      for (int q = 0; q < QC; q++) acc[g][t][q] = mfma_rows(1.0, low[g][q], acc[g][t][q]);
 #pragma unroll
-  for (int k = 0; k < NA / 4; k++) {
-    const int f = 4 * k + ((rlw & 1) << 1 | rlw >> 1), c = f / QC;
-    if (c < NC) red[c * (XC + 1) + QC * xl + f % QC] = acc[k];
-  }
-  if (ir == 0) {
+  for (int h = 0; h < GL; h++)
 #pragma unroll
-    for (int q = 0; q < NB; q++) {
-      const int c = NG == 2 ? q : 2 * q + ih;
-      if (c < NM) red[((NG == 2 ? ih : 0) * NM + c) * (XC + 1) + XC] = base[q];
+    for (int k = 0; k < MG; k++)
+#pragma unroll
+      for (int d = 1; d < LBS_ROWS; d <<= 1) base[h][k] = base[h][k] + __shfl_xor(base[h][k], d);
+  // the upper half of the waves leaves its sums in LDS, the lower half adds its own
+  double* red = s_o + (wave % (LBS_WAVES / 2)) * Sh::SUMS;
+#pragma unroll
+  for (int half = 1; half >= 0; half--) {
+    __syncthreads();  // half = 1: nobody needs operands any more
+    if (wave / (LBS_WAVES / 2) == half) {
+      auto leave = [&](double* to, double v) { *to = half ? v : v + *to; };
+#pragma unroll
+      for (int g = 0; g < NG; g++)
+#pragma unroll
+        for (int t = 0; t < NS; t++)
+#pragma unroll
+          for (int q = 0; q < QC; q++) leave(red + (g * MG + 4 * t + rlw) * (XC + 1) + QC * xl + q, acc[g][t][q]);
+      if (ir == 0)
+#pragma unroll
+        for (int h = 0; h < GL; h++)
+#pragma unroll
+          for (int k = 0; k < MG; k++) leave(red + ((ih + 2 * h) * MG + k) * (XC + 1) + XC, base[h][k]);
     }
   }
   __syncthreads();
+}
+
+// the sum of combination c and column x
+template <int MG, int NG, int QC>
+__device__ __forceinline__ double lbs_sum(const double* s_o, int c, int x) {
+  using Sh = LbsShape<MG, NG, QC>;
+  const double* sums = s_o + c * (Sh::XC + 1);
+  double t = sums[x], tb = sums[Sh::XC];
+#pragma unroll
+  for (int w = 1; w < LBS_WAVES / 2; w++) {
+    t = t + sums[w * Sh::SUMS + x];
+    tb = tb + sums[w * Sh::SUMS + Sh::XC];
+  }
+  return t + tb;
+}
+
+// FIRST: groups gset NG .. of every block; else the two groups of the last exchange
+template <int DT, int NKEEP, int MG, int NG, bool FIRST, int QC>
+__global__ void __launch_bounds__(64 * LBS_WAVES, 4) k_lbs_eval(const uint16_t* __restrict__ P, const uint16_t* __restrict__ PT, const double* __restrict__ sp /*[K] score in panel order*/,
+                                                              const int* __restrict__ rec /*[nblk][2][LBS_REC] exchanged positions and their groups*/,
+                                                              long long N, long long Npad, int B, int slices, double* __restrict__ S /*[nsplit][nblk][B][B]*/) {
+  static_assert(FIRST || NG == 2, "");
+  using Sh = LbsShape<MG, NG, QC>;
+  constexpr int NC = Sh::NC, XC = Sh::XC;
+  __shared__ __align__(16) double s_o[Sh::LDS];
+  __shared__ double s_ms[LBS_WAVES * NC];
+  __shared__ int s_mc[LBS_WAVES * NC];
+  const int blk = blockIdx.x, nblk = gridDim.x, split = blockIdx.y, nsplit = gridDim.y;
+  const int slice = (int)blockIdx.z % slices, gset = (int)blockIdx.z / slices;
+  const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+  const int col0 = slice * XC + QC * (lane % 16);
+  const int colc = col0 < B ? col0 : 0;  // columns past the block compute along and are dropped at the end
+  if (!FIRST && rec[blk * 2 * LBS_REC] < 0) return;  // the block is done
+  const long long nrows = lbs_wave_rows(N, nsplit * LBS_WAVES), r0 = (split * LBS_WAVES + wave) * nrows;
+  const uint16_t* prow = P + ((long long)blk * Npad + r0 + lane / 16) * B + colc;
+  uint2 next = lbs_row<QC>(prow);
+  int* smc = s_mc + wave * NC;
+  double* sms = s_ms + wave * NC;
+  if (lane < NC) {  // first round: positions are columns; past the last group: its first one again, dropped at the end
+    const int g = gset * NG + lane / MG;
+    const int c = FIRST ? (g < B / MG ? g : 0) * MG + lane % MG : rec[(blk * 2 + lane / MG) * LBS_REC + 1 + lane % MG];
+    smc[lane] = c;
+    sms[lane] = sp[(long long)blk * B + c];
+  }
+  wave_lds_fence();
+  double s[QC];
+#pragma unroll
+  for (int q = 0; q < QC; q++) s[q] = sp[(long long)blk * B + colc + q];
+  lbs_sums<DT, NKEEP, MG, NG, QC>(prow, next, s, PT + (long long)blk * B * Npad, smc, sms, r0, nrows, N, Npad, B, s_o, wave, lane);
   double* Sb = S + ((long long)split * nblk + blk) * B * B;
   for (int e = tid; e < NC * XC; e += 64 * LBS_WAVES) {
-    const int c = e / XC, x = slice * XC + e % XC;
-    const double* sums = s_o + c * (XC + 1);
-    double t = sums[e % XC], tb = sums[XC];
-#pragma unroll
-    for (int wv = 1; wv < LBS_WAVES; wv++) {
-      t = t + sums[wv * ROOM + e % XC];
-      tb = tb + sums[wv * ROOM + XC];
-    }
-    t = t + tb;
-    const int k = c / NM, g = NG == 2 && k == 1 ? wg[NG - 1] : wg[0], skip = NG == 2 && k == 1 ? wskip[NG - 1] : wskip[0];
-    int i = c % NM;
-    if (NM < MG && i >= skip) i++;
-    if (x < B && g >= 0) Sb[(long long)(g * MG + i) * B + x] = t;
+    const int c = e / XC, x = slice * XC + e % XC, k = c / MG, i = c % MG;
+    const int p = FIRST ? 0 : rec[(blk * 2 + k) * LBS_REC], g = FIRST ? gset * NG + k : p / MG;
+    if (x < B && g < B / MG && (FIRST || i != p % MG)) Sb[(long long)(g * MG + i) * B + x] = lbs_sum<MG, NG, QC>(s_o, c, e % XC);
   }
 }
 
@@ -1304,14 +1363,210 @@ __global__ void __launch_bounds__(1024) k_lbs_select(const double* __restrict__ 
   }
 }
 
-__global__ void k_lbs_init(int* lp, int* state, int state0, long long* swaps, int* count, int nblk, int B) {
+// ---- the rounds in one launch
+// After the first table the exchanges of a block depend on that block alone.  A team of workgroups takes a block through
+// all its rounds: each workgroup evaluates its rows for the touched groups, reads the sums of the whole team and makes the same choice as all
+// others from its own copy of the table (V, in LDS) and of the positions.  A launch per kernel and round left the chip idle for about 12 of 28 us
+// (launches, first loads behind a chain of three, a selection by 64 workgroups on tables in global memory) and kept every
+// block waiting for the one with the most exchanges.
+//
+// Exchange of the sums: through agent-scope accesses only (they pass by the caches that are not coherent between XCDs).  A
+// place holds LBS_EMPTY, no sum's bits, until its owner has written it, and the readers look until it does not: no
+// counter, one trip through memory.  Three buffers in turn: in round r the owner empties its places of buffer (r + 1) mod 3 and waits for these stores before it
+// writes its sums of round r.  Whoever sees those therefore finds emptied places in round r + 1, and whoever empties has seen every
+// member's sums of round r - 1, which come after that member's last read of that buffer (round r - 2).  Buffer 0 is empty at the start.
+//
+// Waiting: workgroups are dispatched in the order of their numbers, in turn to the 8 XCDs (b mod 8); a team is consecutive
+// numbers of one XCD, at most 32 of the 64 workgroups that an XCD holds at a time.  So at most the last team of an XCD is there
+// in part, all others finish without anyone's help and make room, also beside another launch of this kernel.  Only progress hangs
+// on that: a wait ends after LBS_WAIT_TICKS or once another one has ended that way, the block then stays in LBS_FAST as it was before
+// the launch and the caller goes on with a launch per round.
+#define LBS_EMPTY 0xffffffffffffffffull
+#define LBS_WAIT_TICKS 5000000ull  // of 10 ns
+#define LBS_TEAM_MAX 32
+#define LBS_XCD_GROUPS 64          // workgroups of an XCD at a time, two per CU
+#define LBS_TEAM_BLOCK 64          // largest block: V in LDS
+
+template <int DT, int NKEEP, int MG, int QC>
+__global__ void __launch_bounds__(64 * LBS_WAVES, 4) k_lbs_rounds(const uint16_t* __restrict__ P, const uint16_t* __restrict__ PT, const double* __restrict__ sp,
+                                                                const double* __restrict__ V, int* __restrict__ lp, int* __restrict__ rec, int* __restrict__ state,
+                                                                long long* __restrict__ swaps, long long max_swaps, long long N, long long Npad, int nblk, int B,
+                                                                int T, unsigned long long* __restrict__ S /*[3][nblk][T][2 MG][B]*/, int* __restrict__ gave_up,
+                                                                const int* __restrict__ not_finite, int* __restrict__ count) {
+  using Sh = LbsShape<MG, 2, QC>;
+  constexpr int NC = Sh::NC, XC = Sh::XC, NT = 64 * LBS_WAVES;
+  constexpr int VS = XC + 1;  // a row of V in LDS: a column's entries stand in different banks
+  __shared__ __align__(16) double s_o[Sh::LDS];
+  __shared__ double s_V[XC * VS];
+  __shared__ double s_ms[LBS_WAVES * NC];
+  __shared__ int s_mc[LBS_WAVES * NC];
+  __shared__ double s_sp[XC], s_best[LBS_WAVES], s_next[LBS_WAVES];
+  __shared__ int s_lp[XC], s_pair[LBS_WAVES], s_go;
+  const int tid = threadIdx.x, wave = uniform(tid >> 6);
+  const int j8 = (int)blockIdx.x / 8, blk = j8 / T * 8 + (int)blockIdx.x % 8, member = j8 % T;
+  if (blk >= nblk || state[blk] != LBS_FAST) return;  // a team's members read the same
+  int pa = rec[blk * 2 * LBS_REC], pb = rec[(blk * 2 + 1) * LBS_REC];  // positions exchanged last
+  const bool bad = *not_finite != 0;
+  long long sw = swaps[blk];
+  if (tid < B) {
+    s_lp[tid] = lp[blk * B + tid];
+    s_sp[tid] = sp[(long long)blk * B + tid];
+  }
+  if (tid == 0) s_go = 1;
+  for (int e = tid; e < B * B; e += NT) s_V[e / B * VS + e % B] = V[(long long)blk * B * B + e];
+  const long long nrows = lbs_wave_rows(N, T * LBS_WAVES), r0 = (member * LBS_WAVES + wave) * nrows;
+  const uint16_t* first_row = P + ((long long)blk * Npad + r0) * B;  // the wave's
+  const uint16_t* PTb = PT + (long long)blk * B * Npad;
+  uint2 next;
+  auto column = [&](int lane) { return QC * (lane % 16) < B ? QC * (lane % 16) : 0; };
+  auto load_first = [&](int lane) { next = lbs_row<QC>(first_row + (lane / 16 * B + column(lane))); };
+  load_first(tid & 63);
+  __syncthreads();
+  const int per = 2 * MG * B;  // sums of a member and round
+  const double tol_n = LBS_TOL * 0x1p-53 * ((double)N + 64.0);
+  int to = LBS_FAST;
+  for (int round = 0; to == LBS_FAST; round++) {
+    if (round >= B * B * LBS_ROUNDS_MAX) return;  // the caller reports it
+    // ---- this workgroup's rows
+    {
+      unsigned long long* Se = S + (((long long)((round + 1) % 3) * nblk + blk) * T + member) * per;
+      for (int e = opaque(tid); e < per; e += NT) __hip_atomic_store(Se + e, LBS_EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int lane = opaque(tid & 63), colc = column(lane);
+      int* smc = s_mc + wave * NC;
+      double* sms = s_ms + wave * NC;
+      if (lane < NC) {
+        const int c = s_lp[(lane / MG == 0 ? pa : pb) / MG * MG + lane % MG];
+        smc[lane] = c;
+        sms[lane] = s_sp[c];
+      }
+      double s[QC];
+#pragma unroll
+      for (int q = 0; q < QC; q++) s[q] = s_sp[colc + q];
+      wave_lds_fence();
+      lbs_sums<DT, NKEEP, MG, 2, QC>(first_row + (lane / 16 * B + colc), next, s, PTb, smc, sms, r0, nrows, N, Npad, B, s_o, wave, lane);
+    }
+    // ---- the team's sums, the touched entries of the table
+#if defined(__HIP_DEVICE_COMPILE__)
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the emptied places of this wave have arrived
+#endif
+    __syncthreads();
+    unsigned long long* Sb = S + ((long long)(round % 3) * nblk + blk) * T * per;
+    for (int e = opaque(tid); e < NC * XC; e += NT) {
+      const int c = e / XC, x = e % XC;
+      unsigned long long bits = (unsigned long long)__double_as_longlong(lbs_sum<MG, 2, QC>(s_o, c, x));
+      if (bits == LBS_EMPTY) bits = 0x7ff8000000000000ull;  // another NaN
+      if (x < B) __hip_atomic_store(Sb + (long long)member * per + c * B + x, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // the first rows of the next round do not depend on the exchange: on their way meanwhile
+    load_first(opaque(tid & 63));
+    for (int e = opaque(tid); e < per; e += NT) {
+      const int r = e / B, x = e - r * B, p = r < MG ? pa : pb, i = r % MG;
+      if (i == p % MG) continue;  // the other members are what they were
+      double t = 0.0;
+      for (int q0 = 0; q0 < T; q0 += 4) {
+        unsigned long long v[4];
+        auto look = [&]() {
+#pragma unroll
+          for (int q = 0; q < 4; q++)
+            v[q] = __hip_atomic_load(Sb + (long long)(q0 + q < T ? q0 + q : q0) * per + e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          return v[0] != LBS_EMPTY && v[1] != LBS_EMPTY && v[2] != LBS_EMPTY && v[3] != LBS_EMPTY;
+        };
+        if (!look()) {
+          const unsigned long long t0 = wall_clock64();
+          while (!look()) {
+            if (__hip_atomic_load(gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 || wall_clock64() - t0 > LBS_WAIT_TICKS) {
+              __hip_atomic_store(gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              s_go = 0;
+              break;
+            }
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+          const double d = __longlong_as_double((long long)v[q]);
+          t = q0 + q == 0 ? d : (q0 + q < T ? t + d : t);
+        }
+      }
+      s_V[(p / MG * MG + i) * VS + x] = t;
+    }
+    __syncthreads();
+    if (!s_go) return;
+    // ---- best and second best delta of the pairs i < j in different groups, as in k_lbs_select (of equal ones the best is also the
+    // second best: no exchange is made then, so which of them is taken does not matter)
+    const int lane = opaque(tid & 63), j = lane < B ? lane : 0, b = j / MG;
+    const int lpj = s_lp[j];
+    const double vb = s_V[(b * MG) * VS + s_lp[b * MG]];
+    double best = -INFINITY, second = -INFINITY;
+    int pair = 0;
+#pragma unroll
+    for (int k = 0; k < XC / LBS_WAVES; k++) {
+      const int i = wave + k * LBS_WAVES < B ? wave + k * LBS_WAVES : B - 1;  // (again: no j comes after the last group)
+      const double sum = s_V[i * VS + lpj] + s_V[j * VS + lane_of(lpj, i)];
+      double delta = sum - (lane_of(vb, i) + vb);
+      delta = j / MG > i / MG ? delta : -INFINITY;
+      second = max_f64(second, min_f64(best, delta));
+      pair = delta > best ? i * B + j : pair;
+      best = max_f64(best, delta);
+    }
+    {
+      const double top = lanes_max<6>(best);
+      const int win = __ffsll((unsigned long long)__ballot(best == top)) - 1;
+      second = lanes_max<6>(lane == win ? second : best);
+      if (lane == (win < 0 ? 0 : win)) {
+        s_best[wave] = top;
+        s_next[wave] = second;
+        s_pair[wave] = pair;
+      }
+    }
+    const int gl = lane % 16 * MG < B ? lane % 16 : 0;
+    const double vg = s_V[(gl * MG) * VS + s_lp[gl * MG]];
+    const bool fine = !bad && __all(vg < 1e300);
+    const double tol = tol_n * lanes_max<4>(vg);
+    __syncthreads();
+    {
+      const double mine = s_best[lane % LBS_WAVES];
+      best = lanes_max<3>(mine);
+      const int win = __ffsll((unsigned long long)__ballot(mine == best)) - 1;
+      second = lanes_max<3>(lane % LBS_WAVES == win ? s_next[lane % LBS_WAVES] : mine);
+      pair = s_pair[win < 0 ? 0 : win];
+    }
+    if (fine && best > tol && best - second > tol) {  // exchange
+      pa = uniform(pair / B);
+      pb = uniform(pair % B);
+      __syncthreads();  // everyone has read the positions
+      if (tid == 0) {
+        const int c = s_lp[pa];
+        s_lp[pa] = s_lp[pb];
+        s_lp[pb] = c;
+      }
+      sw++;
+      if (max_swaps > 0 && sw >= max_swaps) to = LBS_DONE;
+      __syncthreads();
+    } else {
+      to = fine && best < -tol ? LBS_DONE : LBS_EXACT;
+    }
+  }
+  if (member == 0) {
+    if (tid < B) lp[blk * B + tid] = s_lp[tid];
+    if (tid == 0) {
+      swaps[blk] = sw;
+      state[blk] = to;
+      rec[blk * 2 * LBS_REC] = rec[(blk * 2 + 1) * LBS_REC] = -1;
+      atomicSub(&count[0], 1);
+      if (to == LBS_EXACT) atomicAdd(&count[1], 1);
+    }
+  }
+}
+
+__global__ void k_lbs_init(int* lp, int* state, int state0, long long* swaps, int* count, unsigned long long* meet /*of the teams*/, long long empty /*of its places*/, int nblk, int B) {
   int t = blockIdx.x * 256 + threadIdx.x;
   if (t < nblk * B) lp[t] = t % B;
+  for (long long e = t; e < empty; e += (long long)gridDim.x * 256) meet[e] = LBS_EMPTY;
   if (t < nblk) {
     state[t] = state0;
     swaps[t] = 0;
   }
-  if (t < 3) count[t] = t == (state0 == LBS_FAST ? 0 : 1) ? nblk : 0;  // [2]: weights that are not finite
+  if (t < 4) count[t] = t == (state0 == LBS_FAST ? 0 : 1) ? nblk : 0;  // [2]: weights that are not finite; [3]: a team gave up waiting
 }
 
 __global__ void k_lbs_final_theta(const int32_t* theta0, const int* lp, int B, long long K, int32_t* theta) {
@@ -1542,9 +1797,12 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
     // workgroups per CU share the two groups that an exchange touches (at least one batch of rows per wave)
     const int qc = B <= 32 ? 2 : 4;
     const int slices = (B + 16 * qc - 1) / (16 * qc);
-    const int gsets = m == 4 ? 1 : 2;  // 2:4: both groups in one workgroup
-    const int nsplit = (int)std::max<long long>(1, std::min<long long>(512 / (nblk * slices * gsets), (N + LBS_WAVES * LBS_ROWS - 1) / (LBS_WAVES * LBS_ROWS)));
-    const long long batch = (long long)nsplit * LBS_WAVES * LBS_ROWS;  // rows that all waves of a block take at a time
+    const int nsplit = (int)std::max<long long>(1, std::min<long long>(512 / (nblk * slices), (N + LBS_WAVES * LBS_ROWS - 1) / (LBS_WAVES * LBS_ROWS)));
+    // teams of k_lbs_rounds: as many workgroups as fill the places of an XCD, which takes every eighth block
+    const bool teams = B <= LBS_TEAM_BLOCK;
+    const int team = (int)std::max<long long>(1, std::min<long long>(std::min<long long>(LBS_XCD_GROUPS / ((nblk + 7) / 8), LBS_TEAM_MAX),
+                                                                     (N + LBS_WAVES * LBS_ROWS - 1) / (LBS_WAVES * LBS_ROWS)));
+    const long long batch = (long long)std::max(nsplit, team) * LBS_WAVES * LBS_ROWS;  // rows that are read past the panel's end, at most
     const long long Npad = (N + LBS_ROWS - 1) / LBS_ROWS * LBS_ROWS;
     bool finite = true, fast = true;  // of the scores: all finite; and none negative
     for (long long c = 0; c < K; c++) {
@@ -1571,11 +1829,13 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
     double* d_S = fast ? scratch.get<double>(ventries * nsplit) : nullptr;
     uint16_t* d_PT = d_S ? scratch.get<uint16_t>((size_t)(Npad * K)) : nullptr;
     fast = d_PT != nullptr;
+    const long long meet = 2ll * K * m * team;  // places of the teams' sums, one of three buffers
+    unsigned long long* d_meet = fast && teams ? scratch.get<unsigned long long>((size_t)(3 * meet)) : nullptr;
     int* count = reinterpret_cast<int*>(h_stage + K);
     long long* h_swaps = reinterpret_cast<long long*>(h_stage + K + 8);
     double* h_gv = h_stage + K + 8 + nblk;
-    hipLaunchKernelGGL(k_lbs_init, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, d_lp, d_state,
-                       fast ? LBS_FAST : LBS_EXACT, d_swaps, d_count, (int)nblk, B);
+    hipLaunchKernelGGL(k_lbs_init, dim3((unsigned)std::max<long long>((K + 255) / 256, d_meet ? 512 : 0)), dim3(256), 0, st, d_lp, d_state,
+                       fast ? LBS_FAST : LBS_EXACT, d_swaps, d_count, d_meet, d_meet ? meet : 0, (int)nblk, B);
     {
       // whole rows of W in LDS: two workgroups per CU where a row leaves the room, else what one workgroup can hold
       const size_t row_bytes = (size_t)K * 2;
@@ -1607,19 +1867,21 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
       while (active > 0) {
         // rounds are queued several at a time: a round after the last exchange of every block only finds that (about
         // 5 us), a look at the count from the host costs about 25
-        for (int r = 0; r < LBS_ROUNDS_QUEUED; r++) {
+        // With teams the first round is followed by all others in one launch.
+        const bool all_rounds = mode == LBS_FAST && first && d_meet;
+        for (int r = 0; r < (all_rounds ? 1 : LBS_ROUNDS_QUEUED); r++) {
           if (mode == LBS_FAST) {
-#define LAUNCH_EVAL2(DTv, NK, MGv, NGv, NMv, QCv)                                                                          \
-  hipLaunchKernelGGL((k_lbs_eval<DTv, NK, MGv, NGv, NMv, QCv>),                                                            \
-                     dim3((unsigned)nblk, (unsigned)nsplit, (unsigned)(slices * (NMv == MGv ? (B / MGv + NGv - 1) / NGv : gsets))), \
+#define LAUNCH_EVAL2(DTv, NK, MGv, NGv, FIRSTv, QCv)                                                                       \
+  hipLaunchKernelGGL((k_lbs_eval<DTv, NK, MGv, NGv, FIRSTv, QCv>),                                                         \
+                     dim3((unsigned)nblk, (unsigned)nsplit, (unsigned)(slices * (FIRSTv ? (B / MGv + NGv - 1) / NGv : 1))), \
                      dim3(64 * LBS_WAVES), 0, st, d_P, d_PT, d_sp, d_rec, N, Npad, B, slices, d_S)
 #define LAUNCH_EVAL(DTv, NK, MGv, ...)                                                      \
   do {                                                                                      \
-    constexpr int NGv = MGv == 4 ? 2 : 1;                                                   \
-    if (first && qc == 4) LAUNCH_EVAL2(DTv, NK, MGv, NGv, MGv, 4);                          \
-    else if (first) LAUNCH_EVAL2(DTv, NK, MGv, NGv, MGv, 2);                                \
-    else if (qc == 4) LAUNCH_EVAL2(DTv, NK, MGv, NGv, (MGv - 1), 4);                        \
-    else LAUNCH_EVAL2(DTv, NK, MGv, NGv, (MGv - 1), 2);                                     \
+    constexpr int NGv = 2;                                                   \
+    if (first && qc == 4) LAUNCH_EVAL2(DTv, NK, MGv, NGv, true, 4);                         \
+    else if (first) LAUNCH_EVAL2(DTv, NK, MGv, NGv, true, 2);                               \
+    else if (qc == 4) LAUNCH_EVAL2(DTv, NK, MGv, 2, false, 4);                              \
+    else LAUNCH_EVAL2(DTv, NK, MGv, 2, false, 2);                                           \
   } while (0)
             DISPATCH_DT_NM(dtype, n, LAUNCH_EVAL, 0);
 #undef LAUNCH_EVAL
@@ -1663,10 +1925,24 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
           ESP_HIP(ctx, hipGetLastError());
           first = false;
         }
+        if (all_rounds) {
+#define LAUNCH_ROUNDS2(DTv, NK, MGv, QCv)                                                                                             \
+  hipLaunchKernelGGL((k_lbs_rounds<DTv, NK, MGv, QCv>), dim3((unsigned)((nblk + 7) / 8 * 8 * team)), dim3(64 * LBS_WAVES), 0, st, d_P, d_PT, d_sp, \
+                     d_V, d_lp, d_rec, d_state, d_swaps, o->max_swaps, N, Npad, (int)nblk, B, team, d_meet, d_count + 3, d_count + 2, d_count)
+#define LAUNCH_ROUNDS(DTv, NK, MGv, ...)               \
+  do {                                                 \
+    if (qc == 4) LAUNCH_ROUNDS2(DTv, NK, MGv, 4);      \
+    else LAUNCH_ROUNDS2(DTv, NK, MGv, 2);              \
+  } while (0)
+          DISPATCH_DT_NM(dtype, n, LAUNCH_ROUNDS, 0);
+#undef LAUNCH_ROUNDS
+#undef LAUNCH_ROUNDS2
+          ESP_HIP(ctx, hipGetLastError());
+        }
         iter += LBS_ROUNDS_QUEUED;
         ESP_HIP(ctx, hipMemcpyAsync(count, d_count, 8, hipMemcpyDeviceToHost, st));
         ESP_HIP(ctx, hipStreamSynchronize(st));
-        if (active > 0 && iter > (long long)B * B * 64)
+        if (active > 0 && iter > (long long)B * B * LBS_ROUNDS_MAX)
           return esp_fail(ctx, ESPARSE_EHIP, "block shuffle did not terminate after %lld rounds", iter);
       }
     }
