@@ -203,7 +203,7 @@ int esparse_prune_with_scores(esparse_ctx* ctx, const double* score, const void*
   if (rc) return rc;
   ESP_REQUIRE(ctx, score, ESPARSE_EINVAL, "score is null");
   if ((rc = bind_device(ctx))) return rc;
-  return guarded(ctx, [&] { return esp_prune_device(ctx, score, W, N, K, dtype, opts, perm_out, mask_out, swaps_out, retained_out); });
+  return guarded(ctx, [&] { return esp_prune_device(ctx, score, nullptr, W, N, K, dtype, opts, perm_out, mask_out, nullptr, swaps_out, retained_out); });
 }
 
 int esparse_prune(esparse_ctx* ctx, const void* calib, long long T, const void* W, long long N,
@@ -220,25 +220,8 @@ int esparse_prune(esparse_ctx* ctx, const void* calib, long long T, const void* 
   ESP_REQUIRE(ctx, std::isfinite(opts->alpha), ESPARSE_EINVAL, "alpha is not finite");
   ESP_REQUIRE(ctx, esp_aligned16(calib), ESPARSE_EINVAL, "calib is not 16-byte aligned");
   if ((rc = bind_device(ctx))) return rc;
-  const bool use_e = opts->flags & ESPARSE_USE_ENTROPY, use_n = opts->flags & ESPARSE_USE_NORM;
-  return guarded(ctx, [&] {
-    std::vector<double> ir, am;
-    int rc = esp_stats_device(ctx, calib, T, K, dtype, opts->bins, use_e ? &ir : nullptr, use_n ? &am : nullptr);
-    if (rc) return rc;
-    // eq. 3: s_c = IR_c + alpha * AM_c, each term behind its switch
-    std::vector<double> s((size_t)K, 0.0);
-    for (long long c = 0; c < K; c++) {
-      double v = 0.0;
-      if (use_e) v = v + ir[c];
-      if (use_n) {
-        double t = opts->alpha * am[c];
-        v = v + t;
-      }
-      s[c] = v;
-    }
-    if (score_out) memcpy(score_out, s.data(), sizeof(double) * K);
-    return esp_prune_device(ctx, s.data(), W, N, K, dtype, opts, perm_out, mask_out, swaps_out, retained_out);
-  });
+  const EspCalib in = {calib, T, opts->bins, opts->alpha, (opts->flags & ESPARSE_USE_ENTROPY) != 0, (opts->flags & ESPARSE_USE_NORM) != 0};
+  return guarded(ctx, [&] { return esp_prune_device(ctx, nullptr, &in, W, N, K, dtype, opts, perm_out, mask_out, score_out, swaps_out, retained_out); });
 }
 
 int esparse_compressed_size(long long N, long long K, int n, int m, esparse_dtype dtype,

@@ -131,9 +131,18 @@ __device__ __forceinline__ uint16_t esp_from_float(float f) {
 void esp_entropies(const unsigned int* hist, long long K, int bins, long long T, double* out);  // host
 int esp_stats_device(esparse_ctx* ctx, const void* calib, long long T, long long K, int dtype,
                      int bins, std::vector<double>* ir, std::vector<double>* am);
-int esp_prune_device(esparse_ctx* ctx, const double* score_host, const void* W, long long N,
+// calibration features and the switches of eq. 3
+struct EspCalib {
+  const void* calib;
+  long long T;
+  int bins;
+  double alpha;
+  bool entropy, norm;
+};
+// score_host, or the scores of `calib` (then score_out receives them, if given)
+int esp_prune_device(esparse_ctx* ctx, const double* score_host, const EspCalib* calib, const void* W, long long N,
                      long long K, int dtype, const esparse_prune_opts* o, int32_t* perm_out,
-                     uint8_t* mask_out, int64_t* swaps_out, double* retained_out);
+                     uint8_t* mask_out, double* score_out, int64_t* swaps_out, double* retained_out);
 // compression
 int esp_compress_device(esparse_ctx* ctx, const void* W, const uint8_t* mask, const int32_t* perm,
                         long long N, long long K, int dtype, int n, int m, void* values_out,

@@ -12,7 +12,8 @@
 //     same exchanges; eq. (5) fixes no order for that sum, and the exchanges Algorithm 1 makes do not
 //     hinge on it where candidates are not tied to the last bit (the tests compare them with a plain
 //     ascending-row sum);
-//   - logarithms and square roots run on the host; the rank of a channel mean is a count of comparisons.
+//   - logarithms are the host's (square roots are correctly rounded anywhere); the rank of a channel mean is a count of
+//     comparisons.
 #include <algorithm>
 #include <cmath>
 #include <cstring>
@@ -279,12 +280,15 @@ __device__ __forceinline__ void hist_trip(const uint16_t* __restrict__ p, long l
 template <int DT, int CPL>
 __global__ void __launch_bounds__(1024) k_hist(const uint16_t* __restrict__ X, long long T, long long K,
                                                 long long rows_per_block, int bins, const unsigned int* __restrict__ onmin,
-                                                const unsigned int* __restrict__ omax, unsigned int* __restrict__ hist /*[K][bins]*/) {
+                                                const unsigned int* __restrict__ omax, unsigned int* __restrict__ hist /*[K][bins]*/,
+                                                unsigned int* __restrict__ most /*[gridDim.x] no count of these channels is larger*/) {
   constexpr int CH = 32 * CPL;
+  __shared__ unsigned int s_most;
   extern __shared__ unsigned int s_hist[];  // [CH rows][stride]: the row of a channel is j * 32 + cl, the stride odd, so
   const int stride = bins | 1;              // that the column lanes of one instruction start in 32 different banks
   const int tid = threadIdx.x, cl = tid & 31, rl = tid >> 5;
   for (int i = tid; i < CH * stride; i += 1024) s_hist[i] = 0u;
+  if (tid == 0) s_most = 0u;
   __syncthreads();
   const long long c = ((long long)blockIdx.x * 32 + cl) * CPL;
   const long long r0 = (long long)blockIdx.y * rows_per_block;
@@ -312,12 +316,17 @@ __global__ void __launch_bounds__(1024) k_hist(const uint16_t* __restrict__ X, l
   }
   __syncthreads();
   const long long cbase = (long long)blockIdx.x * CH;
+  unsigned int mine = 0u;
   for (int i = tid; i < CH * bins; i += 1024) {
     const int row = i / bins, b = i - row * bins;
     const long long ch = cbase + (long long)(row & 31) * CPL + (row >> 5);
     const unsigned int v = s_hist[row * stride + b];
     if (ch < K && v) atomicAdd(&hist[ch * bins + b], v);
+    if (ch < K) mine = v > mine ? v : mine;
   }
+  atomicMax(&s_most, mine);
+  __syncthreads();
+  if (tid == 0) atomicAdd(&most[blockIdx.x], s_most);  // the workgroups' largest counts, added up
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -389,6 +398,49 @@ __global__ void __launch_bounds__(256) k_abs_colsum(const uint16_t* __restrict__
 __global__ void __launch_bounds__(64) k_sumsq_finish(const unsigned long long* __restrict__ sq, long long K, double* __restrict__ out) {
   const long long c = (long long)blockIdx.x * 64 + threadIdx.x;
   if (c < K) out[c] = exact_bins_to_double<SQ_NB>(sq + c * SQ_NB, SQ_EOFF + SQ_SIG);
+}
+
+// The terms p ln p of eq. 1 for counts below T, taken on the host (the logarithm that the result is defined by is the host's) while the
+// scans run: as many as the counts can be, into device memory.  Gathered from host memory every one would be a trip over the bus.
+__global__ void __launch_bounds__(256) k_fetch_terms(const double* __restrict__ host_terms, long long T, const unsigned int* __restrict__ most, int nmost,
+                                                      double* __restrict__ terms) {
+  __shared__ unsigned int s_most;
+  if (threadIdx.x == 0) s_most = 0u;
+  __syncthreads();
+  unsigned int mine = 0u;
+  for (int i = threadIdx.x; i < nmost; i += 256) mine = most[i] > mine ? most[i] : mine;
+  atomicMax(&s_most, mine);
+  __syncthreads();
+  const long long n = (long long)s_most + 1 < T ? (long long)s_most + 1 : T;
+  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long long)gridDim.x * 256) terms[i] = host_terms[i];
+}
+
+// eq. 1 and 3: s_c = IR_c + alpha AM_c, each term behind its switch; IR_c adds its terms in ascending order of the bins.
+// 16 channels per workgroup: their terms into LDS, then one thread each.
+__global__ void __launch_bounds__(256) k_scores(const unsigned int* __restrict__ hist /*[K][bins] or null*/, const double* __restrict__ terms, long long T,
+                                                 int bins, const unsigned long long* __restrict__ sq /*or null*/, double alpha, long long K,
+                                                 double* __restrict__ out) {
+  extern __shared__ double s_term[];  // [16][bins | 1]
+  const int tid = threadIdx.x, stride = bins | 1;
+  const long long c0 = (long long)blockIdx.x * 16;
+  if (hist)
+    for (int i = tid; i < 16 * bins; i += 256) {
+      const int row = i / bins;
+      const unsigned int n = c0 + row < K ? hist[c0 * bins + i] : 0u;
+      s_term[row * stride + i - row * bins] = n && n < T ? terms[n] : 0.0;  // an empty bin adds nothing, one with all tokens 1 ln 1
+    }
+  __syncthreads();
+  const long long c = c0 + tid;
+  if (tid >= 16 || c >= K) return;
+  double v = 0.0;
+  if (hist) {
+    double acc = 0.0;
+#pragma unroll 10
+    for (int b = 0; b < bins; b++) acc = acc + s_term[tid * stride + b];
+    v = v + -acc;
+  }
+  if (sq) v = v + alpha * sqrt(exact_bins_to_double<SQ_NB>(sq + c * SQ_NB, SQ_EOFF + SQ_SIG));
+  out[c] = v;
 }
 
 // channel means of the metric: g_c = (s_c * sum_j |w_jc|) / N
@@ -472,40 +524,43 @@ void esp_entropies(const unsigned int* hist, long long K, int bins, long long T,
 // ------------------------------------------------------------------------------------------------
 // host driver of the statistics
 // ------------------------------------------------------------------------------------------------
-int esp_stats_device(esparse_ctx* ctx, const void* calib, long long T, long long K, int dtype, int bins,
-                     std::vector<double>* ir, std::vector<double>* am) {
-  if (!ir && !am) return ESPARSE_OK;
+// what the scans leave on the device: zeroed ahead of them (the minimum is kept inverted)
+struct Scans {
+  unsigned long long* sq;  // [K][SQ_NB]
+  unsigned int *nmin, *max;  // [K] each
+  unsigned int* most;        // [nmost]
+  double* sums;              // [K], not zeroed
+  unsigned int* hist;        // [K][bins], right behind sums
+  size_t nmost;
+};
+
+static int launch_scans(esparse_ctx* ctx, Scratch& scratch, const void* calib, long long T, long long K, int dtype, int bins, bool want_hist, bool want_sq,
+                        Scans* out) {
   hipStream_t st = ctx->stream;
-  std::vector<unsigned char> pageable;
-  Scratch scratch(ctx);
-  // zeroed: squares, extrema (the minimum inverted); then what goes to the host: sums of squares, histogram (zeroed)
-  const size_t sq_bytes = (size_t)K * SQ_NB * 8, hist_bytes = (size_t)K * bins * 4;
-  unsigned char* d_all = scratch.get<unsigned char>(sq_bytes + (size_t)K * 8 + (size_t)K * 8 + hist_bytes);
+  const int cpl = K % 4 == 0 ? 4 : 2;  // channels per lane: 8-byte loads where the rows allow them
+  const long long gx = (K + 32 * cpl - 1) / (32 * cpl);
+  const size_t nmost = (size_t)(gx + 1) / 2 * 2;  // keeps what follows aligned to 8 bytes
+  const size_t sq_bytes = (size_t)K * SQ_NB * 8, hist_bytes = (size_t)K * bins * 4, all = sq_bytes + (size_t)K * 8 + nmost * 4 + (size_t)K * 8 + hist_bytes;
+  unsigned char* d_all = scratch.get<unsigned char>(all);
   if (!d_all) return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation for channel statistics failed");
   unsigned long long* d_sq = reinterpret_cast<unsigned long long*>(d_all);
   unsigned int* d_nmin = reinterpret_cast<unsigned int*>(d_all + sq_bytes);
   unsigned int* d_max = d_nmin + K;
-  double* d_am = reinterpret_cast<double*>(d_all + sq_bytes + (size_t)K * 8);
-  unsigned int* d_hist = reinterpret_cast<unsigned int*>(d_am + K);
-  const size_t out_bytes = (size_t)K * 8 + (ir ? hist_bytes : 0);
-  unsigned char* h_out = reinterpret_cast<unsigned char*>(esp_host_stage(ctx, out_bytes));
-  if (!h_out) {
-    pageable.resize(out_bytes);
-    h_out = pageable.data();
-  }
-  ESP_HIP(ctx, hipMemsetAsync(d_all, 0, sq_bytes + (size_t)K * 16 + hist_bytes, st));
+  unsigned int* d_most = d_max + K;
+  double* d_sums = reinterpret_cast<double*>(d_most + nmost);
+  unsigned int* d_hist = reinterpret_cast<unsigned int*>(d_sums + K);
+  *out = Scans{d_sq, d_nmin, d_max, d_most, d_sums, d_hist, nmost};
+  ESP_HIP(ctx, hipMemsetAsync(d_all, 0, all, st));
   const uint16_t* X = reinterpret_cast<const uint16_t*>(calib);
-  const int cpl = K % 4 == 0 ? 4 : 2;  // channels per lane: 8-byte loads where the rows allow them
-  const long long gx = (K + 32 * cpl - 1) / (32 * cpl);
   // about 1024 workgroups (four per CU over the two that fit at once), whole trips of 256 rows
   const long long nchunk = std::max<long long>(1, std::min<long long>((T + 255) / 256, 1024 / gx + 1));
   long long rpb = (T + nchunk - 1) / nchunk;
   rpb = (rpb + 255) / 256 * 256;
   dim3 grid((unsigned)gx, (unsigned)((T + rpb - 1) / rpb));
 #define ESP_SCAN_A(DTv, CPLv)                                                                                        \
-  hipLaunchKernelGGL((k_minmax_sumsq<DTv, CPLv>), grid, dim3(1024), 0, st, X, T, K, rpb, d_nmin, d_max, d_sq, am ? 1 : 0)
+  hipLaunchKernelGGL((k_minmax_sumsq<DTv, CPLv>), grid, dim3(1024), 0, st, X, T, K, rpb, d_nmin, d_max, d_sq, want_sq ? 1 : 0)
 #define ESP_SCAN_B(DTv, CPLv)                                                                                        \
-  hipLaunchKernelGGL((k_hist<DTv, CPLv>), grid, dim3(1024), (size_t)32 * CPLv * (bins | 1) * 4, st, X, T, K, rpb, bins, d_nmin, d_max, d_hist)
+  hipLaunchKernelGGL((k_hist<DTv, CPLv>), grid, dim3(1024), (size_t)32 * CPLv * (bins | 1) * 4, st, X, T, K, rpb, bins, d_nmin, d_max, d_hist, d_most)
   if (dtype == ESPARSE_F16) {
     if (cpl == 4) ESP_SCAN_A(ESPARSE_F16, 4);
     else ESP_SCAN_A(ESPARSE_F16, 2);
@@ -514,7 +569,7 @@ int esp_stats_device(esparse_ctx* ctx, const void* calib, long long T, long long
     else ESP_SCAN_A(ESPARSE_BF16, 2);
   }
   ESP_HIP(ctx, hipGetLastError());
-  if (ir) {
+  if (want_hist) {
     // 32 * 4 channels x 256 bins x 4 bytes = 128 KiB of LDS at most
     const size_t smem = (size_t)32 * cpl * (bins | 1) * 4;
     if (smem > 48 * 1024) {
@@ -534,11 +589,30 @@ int esp_stats_device(esparse_ctx* ctx, const void* calib, long long T, long long
   }
 #undef ESP_SCAN_A
 #undef ESP_SCAN_B
+  return ESPARSE_OK;
+}
+
+int esp_stats_device(esparse_ctx* ctx, const void* calib, long long T, long long K, int dtype, int bins,
+                     std::vector<double>* ir, std::vector<double>* am) {
+  if (!ir && !am) return ESPARSE_OK;
+  hipStream_t st = ctx->stream;
+  std::vector<unsigned char> pageable;
+  Scratch scratch(ctx);
+  // what goes to the host: sums of squares, histogram
+  const size_t out_bytes = (size_t)K * 8 + (ir ? (size_t)K * bins * 4 : 0);
+  unsigned char* h_out = reinterpret_cast<unsigned char*>(esp_host_stage(ctx, out_bytes));
+  if (!h_out) {
+    pageable.resize(out_bytes);
+    h_out = pageable.data();
+  }
+  Scans sc;
+  const int rc = launch_scans(ctx, scratch, calib, T, K, dtype, bins, ir != nullptr, am != nullptr, &sc);
+  if (rc) return rc;
   if (am) {
-    hipLaunchKernelGGL(k_sumsq_finish, dim3((unsigned)((K + 63) / 64)), dim3(64), 0, st, d_sq, K, d_am);
+    hipLaunchKernelGGL(k_sumsq_finish, dim3((unsigned)((K + 63) / 64)), dim3(64), 0, st, sc.sq, K, sc.sums);
     ESP_HIP(ctx, hipGetLastError());
   }
-  ESP_HIP(ctx, hipMemcpyAsync(h_out, d_am, out_bytes, hipMemcpyDeviceToHost, st));
+  ESP_HIP(ctx, hipMemcpyAsync(h_out, sc.sums, out_bytes, hipMemcpyDeviceToHost, st));
   ESP_HIP(ctx, hipStreamSynchronize(st));
   scratch.idle();
   if (am) {
@@ -550,6 +624,64 @@ int esp_stats_device(esparse_ctx* ctx, const void* calib, long long T, long long
   if (ir) {
     ir->assign((size_t)K, 0.0);
     esp_entropies(reinterpret_cast<const unsigned int*>(h_out + (size_t)K * 8), K, bins, T, ir->data());
+  }
+  return ESPARSE_OK;
+}
+
+// terms[n] = p ln p of a count n of T, for n < T (0 for 0); by several threads, without them by this one
+static void entropy_terms(long long T, double* terms) {
+  auto fill = [=](long long n0, long long n1) {
+    for (long long n = n0; n < n1; n++) {
+      const double p = (double)n / (double)T;
+      terms[n] = n ? p * std::log(p) : 0.0;
+    }
+  };
+  const int nthr = (int)std::max<long long>(1, std::min<long long>(8, T / 4096));
+  std::thread pool[8];
+  int started = 1;
+  try {
+    for (; started < nthr; started++) pool[started] = std::thread(fill, T * started / nthr, T * (started + 1) / nthr);
+  } catch (...) {  // no thread to be had: its share and the rest are done here
+  }
+  fill(0, T / nthr);
+  fill(T * started / nthr, T);
+  for (int i = 1; i < started; i++) pool[i].join();
+}
+
+// The scores of eq. 3 on the device, without a look from the host: terms (T of them, pinned) are taken while the scans run.
+static int launch_scores(esparse_ctx* ctx, Scratch& scratch, const EspCalib& in, long long K, int dtype, double* h_terms, double* d_score) {
+  hipStream_t st = ctx->stream;
+  Scans sc;
+  const int rc = launch_scans(ctx, scratch, in.calib, in.T, K, dtype, in.bins, in.entropy, in.norm, &sc);
+  if (rc) return rc;
+  double* d_terms = nullptr;
+  if (in.entropy) {
+    d_terms = scratch.get<double>((size_t)in.T);
+    if (!d_terms) return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation for channel statistics failed");
+    entropy_terms(in.T, h_terms);
+    hipLaunchKernelGGL(k_fetch_terms, dim3((unsigned)std::min<long long>(256, (in.T + 255) / 256)), dim3(256), 0, st, h_terms, in.T, sc.most, (int)sc.nmost, d_terms);
+    ESP_HIP(ctx, hipGetLastError());
+  }
+  hipLaunchKernelGGL(k_scores, dim3((unsigned)((K + 15) / 16)), dim3(256), in.entropy ? (size_t)16 * (in.bins | 1) * 8 : 0, st, in.entropy ? sc.hist : nullptr, d_terms,
+                     in.T, in.bins, in.norm ? sc.sq : nullptr, in.alpha, K, d_score);
+  ESP_HIP(ctx, hipGetLastError());
+  return ESPARSE_OK;
+}
+
+// The same on the host, for any T, K and alpha.
+static int scores_on_host(esparse_ctx* ctx, const EspCalib& in, long long K, int dtype, std::vector<double>& s) {
+  std::vector<double> ir, am;
+  const int rc = esp_stats_device(ctx, in.calib, in.T, K, dtype, in.bins, in.entropy ? &ir : nullptr, in.norm ? &am : nullptr);
+  if (rc) return rc;
+  s.assign((size_t)K, 0.0);
+  for (long long c = 0; c < K; c++) {
+    double v = 0.0;
+    if (in.entropy) v = v + ir[c];
+    if (in.norm) {
+      double t = in.alpha * am[c];
+      v = v + t;
+    }
+    s[c] = v;
   }
   return ESPARSE_OK;
 }
@@ -567,7 +699,7 @@ int esp_stats_device(esparse_ctx* ctx, const void* calib, long long T, long long
 // global memory, one per workgroup.
 __global__ void __launch_bounds__(512) k_build_panel(const uint16_t* __restrict__ W, const int32_t* __restrict__ theta0,
                                                       long long N, long long Npad, long long K, long long first_row, int B, int RB, unsigned int inf_bits,
-                                                      uint16_t* __restrict__ P, int* __restrict__ not_finite) {
+                                                      const double* __restrict__ sp, uint16_t* __restrict__ P, int* __restrict__ not_finite) {
   extern __shared__ __align__(16) unsigned char smem_raw[];
   uint16_t* s_w = reinterpret_cast<uint16_t*>(smem_raw);
   const int tid = threadIdx.x, rows = RB ? RB : 1;
@@ -581,6 +713,8 @@ __global__ void __launch_bounds__(512) k_build_panel(const uint16_t* __restrict_
   }
   const int q4 = B / 4, nblk = (int)(K / B);  // four columns per thread and step
   bool bad = false;
+  if (j0 == 0)  // the scores as well
+    for (long long c = tid; c < K; c += 512) bad = bad || !(fabs(sp[c]) < INFINITY);
   for (int e = tid; e < nblk * nr * q4; e += 512) {
     const int c = e % q4, t = e / q4, r = t % nr, blk = t / nr;
     const int4 col = reinterpret_cast<const int4*>(theta0)[blk * q4 + c];
@@ -1727,8 +1861,8 @@ __global__ void __launch_bounds__(64) k_group_values(const uint16_t* __restrict_
     else KERNEL(ESPARSE_BF16, 4, 8, __VA_ARGS__);                                   \
   } while (0)
 
-int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long long N, long long K, int dtype,
-                     const esparse_prune_opts* o, int32_t* perm_out, uint8_t* mask_out, int64_t* swaps_out,
+int esp_prune_device(esparse_ctx* ctx, const double* score, const EspCalib* calib, const void* Wv, long long N, long long K, int dtype,
+                     const esparse_prune_opts* o, int32_t* perm_out, uint8_t* mask_out, double* score_out, int64_t* swaps_out,
                      double* retained_out) {
   hipStream_t st = ctx->stream;
   const uint16_t* W = reinterpret_cast<const uint16_t*>(Wv);
@@ -1738,22 +1872,51 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
   const long long nblk = use_lbs ? K / B : 0;
   if (swaps_out && !use_lbs && o->block > 0 && K % o->block == 0) memset(swaps_out, 0, sizeof(int64_t) * (K / o->block));
 
+  // Scores from calibration features: on the device, so that nothing comes back to the host before the end, where the host has the terms
+  // of eq. 1 in time (a term takes a thread 8 ns and the scans 0.9 ps per token and channel: T <= 64 K), a score below zero can be
+  // ruled out (the cheaper table of exchanges needs that) and the channels are ranked on the device.
+  // 4096 channels, 262144 tokens: 350 us between the scans and the shuffle, 20 now.
+  std::vector<double> host_score;
+  size_t terms = calib && calib->entropy ? (size_t)calib->T : 0;
+  const size_t results = (size_t)(K + 8 + nblk + K / m);
+  bool on_device = calib && K <= RANK_ON_DEVICE && (!calib->entropy || calib->T <= 64 * K) && (!calib->norm || calib->alpha >= 0.0);
+  on_device = on_device && esp_host_stage(ctx, (results + terms) * 8);
+  if (!on_device) terms = 0;
+  if (calib && !on_device) {
+    const int rc = scores_on_host(ctx, *calib, K, dtype, host_score);
+    if (rc) return rc;
+    score = host_score.data();
+    if (score_out) memcpy(score_out, score, (size_t)K * 8);
+  }
+
   // pinned, each part used for one thing: scores, counts, exchanges per block, group values (beyond the largest pinned block
-  // from pageable memory)
+  // from pageable memory), terms of eq. 1
   std::vector<double> pageable;
   Scratch scratch(ctx);
   double* d_s = scratch.get<double>(K);
   double* d_sp = scratch.get<double>(K);
   int32_t* d_theta0 = scratch.get<int32_t>(K);
-  const size_t stage_count = (size_t)(K + 8 + nblk + K / m);
-  double* h_stage = reinterpret_cast<double*>(esp_host_stage(ctx, stage_count * 8));
+  double* h_stage = reinterpret_cast<double*>(esp_host_stage(ctx, (results + terms) * 8));
   if (!h_stage) {
-    pageable.resize(stage_count);
+    pageable.resize(results);
     h_stage = pageable.data();
   }
   if (!d_s || !d_sp || !d_theta0) return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation failed");
-  memcpy(h_stage, score, (size_t)K * 8);
-  ESP_HIP(ctx, hipMemcpyAsync(d_s, h_stage, (size_t)K * 8, hipMemcpyHostToDevice, st));
+  if (on_device) {
+    const int rc = launch_scores(ctx, scratch, *calib, K, dtype, h_stage + results, d_s);
+    if (rc) return rc;
+  } else {
+    memcpy(h_stage, score, (size_t)K * 8);
+    ESP_HIP(ctx, hipMemcpyAsync(d_s, h_stage, (size_t)K * 8, hipMemcpyHostToDevice, st));
+  }
+  // device scores to the caller, with the results at the end
+  auto fetch_scores = [&]() -> int {
+    if (on_device && score_out) ESP_HIP(ctx, hipMemcpyAsync(h_stage, d_s, (size_t)K * 8, hipMemcpyDeviceToHost, st));
+    return ESPARSE_OK;
+  };
+  auto leave_scores = [&]() {
+    if (on_device && score_out) memcpy(score_out, h_stage, (size_t)K * 8);
+  };
 
   // ---- global naive shuffle
   double* d_g = nullptr;
@@ -1804,8 +1967,8 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
                                                                      (N + LBS_WAVES * LBS_ROWS - 1) / (LBS_WAVES * LBS_ROWS)));
     const long long batch = (long long)std::max(nsplit, team) * LBS_WAVES * LBS_ROWS;  // rows that are read past the panel's end, at most
     const long long Npad = (N + LBS_ROWS - 1) / LBS_ROWS * LBS_ROWS;
-    bool finite = true, fast = true;  // of the scores: all finite; and none negative
-    for (long long c = 0; c < K; c++) {
+    bool finite = true, fast = true;  // of the scores: all finite (on the device: k_build_panel looks); and none negative
+    for (long long c = 0; c < K && score; c++) {
       finite = finite && std::isfinite(score[c]);
       fast = fast && score[c] >= 0.0;
     }
@@ -1847,120 +2010,92 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
       // a launch has fewer than 2^32 threads (more are cut off without an error): 2^31 at most, in several launches if need be
       for (long long j = 0; j < N; j += rows << 22)
         hipLaunchKernelGGL(k_build_panel, dim3((unsigned)((std::min(N - j, rows << 22) + rows - 1) / rows)), dim3(512), smem_w, st, W, d_theta0,
-                           N, Npad, K, j, B, RB, dtype == ESPARSE_F16 ? 0x7c00u : 0x7f80u, d_P, d_count + 2);
+                           N, Npad, K, j, B, RB, dtype == ESPARSE_F16 ? 0x7c00u : 0x7f80u, d_sp, d_P, d_count + 2);
       ESP_HIP(ctx, hipGetLastError());
-      if (fast) {
-        hipLaunchKernelGGL(k_panel_columns, dim3((unsigned)(nblk * ((Npad + 63) / 64)), (unsigned)((B + 63) / 64)), dim3(256), 0, st,
-                           d_P, Npad, (int)nblk, B, d_PT);
-        ESP_HIP(ctx, hipGetLastError());
-      }
     }
+    auto panel_columns = [&]() -> int {
+      hipLaunchKernelGGL(k_panel_columns, dim3((unsigned)(nblk * ((Npad + 63) / 64)), (unsigned)((B + 63) / 64)), dim3(256), 0, st,
+                         d_P, Npad, (int)nblk, B, d_PT);
+      ESP_HIP(ctx, hipGetLastError());
+      return ESPARSE_OK;
+    };
+    int rc = fast ? panel_columns() : ESPARSE_OK;
+    if (rc) return rc;
     // LDS of the exact evaluation: a chunk of a multiple of 16 rows, about 4096 metric values (at most 16 per thread)
     const int rows_chunk = std::max(16, (4096 / B) / 16 * 16);
     const size_t smem = (size_t)rows_chunk * (B + 1) * 8;
     count[0] = fast ? (int)nblk : 0;
     count[1] = fast ? 0 : (int)nblk;
-    for (int mode : {LBS_FAST, LBS_EXACT}) {
-      int& active = count[mode == LBS_FAST ? 0 : 1];
-      bool first = true;
-      long long iter = 0;
-      while (active > 0) {
-        // rounds are queued several at a time: a round after the last exchange of every block only finds that (about
-        // 5 us), a look at the count from the host costs about 25
-        // With teams the first round is followed by all others in one launch.
-        const bool all_rounds = mode == LBS_FAST && first && d_meet;
-        for (int r = 0; r < (all_rounds ? 1 : LBS_ROUNDS_QUEUED); r++) {
-          if (mode == LBS_FAST) {
-#define LAUNCH_EVAL2(DTv, NK, MGv, NGv, FIRSTv, QCv)                                                                       \
-  hipLaunchKernelGGL((k_lbs_eval<DTv, NK, MGv, NGv, FIRSTv, QCv>),                                                         \
-                     dim3((unsigned)nblk, (unsigned)nsplit, (unsigned)(slices * (FIRSTv ? (B / MGv + NGv - 1) / NGv : 1))), \
+    // one round of all blocks in the given mode; first: all groups are evaluated
+    auto launch_round = [&](int mode, bool first) -> int {
+      if (mode == LBS_FAST) {
+#define LAUNCH_EVAL2(DTv, NK, MGv, FIRSTv, QCv)                                                                       \
+  hipLaunchKernelGGL((k_lbs_eval<DTv, NK, MGv, 2, FIRSTv, QCv>),                                                      \
+                     dim3((unsigned)nblk, (unsigned)nsplit, (unsigned)(slices * (FIRSTv ? (B / MGv + 1) / 2 : 1))),   \
                      dim3(64 * LBS_WAVES), 0, st, d_P, d_PT, d_sp, d_rec, N, Npad, B, slices, d_S)
-#define LAUNCH_EVAL(DTv, NK, MGv, ...)                                                      \
-  do {                                                                                      \
-    constexpr int NGv = 2;                                                   \
-    if (first && qc == 4) LAUNCH_EVAL2(DTv, NK, MGv, NGv, true, 4);                         \
-    else if (first) LAUNCH_EVAL2(DTv, NK, MGv, NGv, true, 2);                               \
-    else if (qc == 4) LAUNCH_EVAL2(DTv, NK, MGv, 2, false, 4);                              \
-    else LAUNCH_EVAL2(DTv, NK, MGv, 2, false, 2);                                           \
+#define LAUNCH_EVAL(DTv, NK, MGv, ...)                                   \
+  do {                                                                   \
+    if (first && qc == 4) LAUNCH_EVAL2(DTv, NK, MGv, true, 4);           \
+    else if (first) LAUNCH_EVAL2(DTv, NK, MGv, true, 2);                 \
+    else if (qc == 4) LAUNCH_EVAL2(DTv, NK, MGv, false, 4);              \
+    else LAUNCH_EVAL2(DTv, NK, MGv, false, 2);                           \
   } while (0)
-            DISPATCH_DT_NM(dtype, n, LAUNCH_EVAL, 0);
+        DISPATCH_DT_NM(dtype, n, LAUNCH_EVAL, 0);
 #undef LAUNCH_EVAL
 #undef LAUNCH_EVAL2
-          } else {
-            const int* rec = first ? nullptr : d_rec;
-            if (m == 4 && (B % 64 == 0 || B < 64)) {
-              // 2:4: 8 units per workgroup while every group is evaluated, 2 in the refresh rounds (more workgroups)
-              const int units = (first ? B / m : 2) * m * (B < 64 ? 1 : B / 64);
-              const int nc = first ? 8 : 2;
-              dim3 grid((unsigned)((units + nc - 1) / nc), (unsigned)nblk);
-              const size_t smem2 = smem + (size_t)rows_chunk * nc * 16;
+      } else {
+        const int* rec = first ? nullptr : d_rec;
+        if (m == 4 && (B % 64 == 0 || B < 64)) {
+          // 2:4: 8 units per workgroup while every group is evaluated, 2 in the refresh rounds (more workgroups)
+          const int units = (first ? B / m : 2) * m * (B < 64 ? 1 : B / 64);
+          const int nc = first ? 8 : 2;
+          dim3 grid((unsigned)((units + nc - 1) / nc), (unsigned)nblk);
+          const size_t smem2 = smem + (size_t)rows_chunk * nc * 16;
 #define LAUNCH_EXACT24(DTv, NCv)                                                                                             \
   hipLaunchKernelGGL((k_lbs_exact_2_4<DTv, NCv>), grid, dim3(1024), smem2, st, d_P, d_sp, d_lp, \
                      rec, d_state, N, Npad, B, rows_chunk, d_V)
-              if (dtype == ESPARSE_F16) {
-                if (first) LAUNCH_EXACT24(ESPARSE_F16, 8);
-                else LAUNCH_EXACT24(ESPARSE_F16, 2);
-              } else {
-                if (first) LAUNCH_EXACT24(ESPARSE_BF16, 8);
-                else LAUNCH_EXACT24(ESPARSE_BF16, 2);
-              }
+          if (dtype == ESPARSE_F16) {
+            if (first) LAUNCH_EXACT24(ESPARSE_F16, 8);
+            else LAUNCH_EXACT24(ESPARSE_F16, 2);
+          } else {
+            if (first) LAUNCH_EXACT24(ESPARSE_BF16, 8);
+            else LAUNCH_EXACT24(ESPARSE_BF16, 2);
+          }
 #undef LAUNCH_EXACT24
-            } else {
-              dim3 grid((unsigned)(((first ? B / m : 2) * m * B + 63) / 64), (unsigned)nblk);
+        } else {
+          dim3 grid((unsigned)(((first ? B / m : 2) * m * B + 63) / 64), (unsigned)nblk);
 #define LAUNCH_EXACT(DT, NK, MGv, ...)                                                                                        \
   hipLaunchKernelGGL((k_lbs_exact<DT, NK, MGv>), grid, dim3(1024), smem, st, d_P, d_sp, d_lp, \
                      rec, d_state, N, Npad, B, rows_chunk, d_V)
-              DISPATCH_DT_NM(dtype, n, LAUNCH_EXACT, 0);
+          DISPATCH_DT_NM(dtype, n, LAUNCH_EXACT, 0);
 #undef LAUNCH_EXACT
-            }
-          }
-          ESP_HIP(ctx, hipGetLastError());
+        }
+      }
+      ESP_HIP(ctx, hipGetLastError());
 #define LAUNCH_SELECT(MGv)                                                                                                     \
   hipLaunchKernelGGL(k_lbs_select<MGv>, dim3((unsigned)nblk), dim3(1024), 0, st, d_S, nsplit, d_V, d_lp, \
-                     d_rec, d_state, d_swaps, o->max_swaps, N, B, first ? 1 : 0, (int)mode,  \
+                     d_rec, d_state, d_swaps, o->max_swaps, N, B, first ? 1 : 0, mode,  \
                      d_count + 2, d_count)
-          if (m == 4) LAUNCH_SELECT(4);
-          else LAUNCH_SELECT(8);
+      if (m == 4) LAUNCH_SELECT(4);
+      else LAUNCH_SELECT(8);
 #undef LAUNCH_SELECT
-          ESP_HIP(ctx, hipGetLastError());
-          first = false;
-        }
-        if (all_rounds) {
-#define LAUNCH_ROUNDS2(DTv, NK, MGv, QCv)                                                                                             \
-  hipLaunchKernelGGL((k_lbs_rounds<DTv, NK, MGv, QCv>), dim3((unsigned)((nblk + 7) / 8 * 8 * team)), dim3(64 * LBS_WAVES), 0, st, d_P, d_PT, d_sp, \
-                     d_V, d_lp, d_rec, d_state, d_swaps, o->max_swaps, N, Npad, (int)nblk, B, team, d_meet, d_count + 3, d_count + 2, d_count)
-#define LAUNCH_ROUNDS(DTv, NK, MGv, ...)               \
-  do {                                                 \
-    if (qc == 4) LAUNCH_ROUNDS2(DTv, NK, MGv, 4);      \
-    else LAUNCH_ROUNDS2(DTv, NK, MGv, 2);              \
-  } while (0)
-          DISPATCH_DT_NM(dtype, n, LAUNCH_ROUNDS, 0);
-#undef LAUNCH_ROUNDS
-#undef LAUNCH_ROUNDS2
-          ESP_HIP(ctx, hipGetLastError());
-        }
-        iter += LBS_ROUNDS_QUEUED;
-        ESP_HIP(ctx, hipMemcpyAsync(count, d_count, 8, hipMemcpyDeviceToHost, st));
-        ESP_HIP(ctx, hipStreamSynchronize(st));
-        if (active > 0 && iter > (long long)B * B * LBS_ROUNDS_MAX)
-          return esp_fail(ctx, ESPARSE_EHIP, "block shuffle did not terminate after %lld rounds", iter);
-      }
-    }
-    hipLaunchKernelGGL(k_lbs_final_theta, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, d_theta0, d_lp, B,
-                       K, perm_out);
-    ESP_HIP(ctx, hipGetLastError());
-    if (swaps_out) {
-      ESP_HIP(ctx, hipMemcpyAsync(h_swaps, d_swaps, nblk * 8, hipMemcpyDeviceToHost, st));
-    }
-    // mask and retained metric under the final order, from the panel
-    {
-      const int row_blocks = (int)((N + 63) / 64);
-      const long long ng = K / m;
-      double* d_gv = retained_out ? scratch.get<double>(ng) : nullptr;
-      if (retained_out && !d_gv) return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation failed");
-      // the workgroups' sums (8 / m bytes per column and 64 rows) take the place of the panel by columns, which nothing reads any more
-      double* d_part = nullptr;
-      if (retained_out) d_part = d_PT ? reinterpret_cast<double*>(d_PT) : scratch.get<double>((size_t)row_blocks * ng);
+      ESP_HIP(ctx, hipGetLastError());
+      return ESPARSE_OK;
+    };
+    // order, mask and retained metric under the order as it is, the counts of blocks that are not done: queued, then waited for
+    const long long ng = K / m;
+    const int row_blocks = (int)((N + 63) / 64);
+    double* d_gv = retained_out ? scratch.get<double>(ng) : nullptr;
+    if (retained_out && !d_gv) return esp_fail(ctx, ESPARSE_ENOMEM, "scratch allocation failed");
+    // the workgroups' sums (8 / m bytes per column and 64 rows) take the place of the panel by columns, which nothing reads any more
+    double* d_part = nullptr;
+    if (retained_out) d_part = d_PT ? reinterpret_cast<double*>(d_PT) : scratch.get<double>((size_t)row_blocks * ng);
+    auto finish = [&]() -> int {
+      ESP_HIP(ctx, hipMemcpyAsync(count, d_count, 8, hipMemcpyDeviceToHost, st));
+      hipLaunchKernelGGL(k_lbs_final_theta, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, d_theta0, d_lp, B,
+                         K, perm_out);
+      ESP_HIP(ctx, hipGetLastError());
+      if (swaps_out) ESP_HIP(ctx, hipMemcpyAsync(h_swaps, d_swaps, nblk * 8, hipMemcpyDeviceToHost, st));
       const size_t smem_m = 256 * 8 + (size_t)64 * (B + 2) * 2;
       dim3 grid((unsigned)(nblk * row_blocks));
 #define LAUNCH_MASK(DT, NK, MGv, ...)                                                                                        \
@@ -1978,14 +2113,60 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
         ESP_HIP(ctx, hipGetLastError());
         ESP_HIP(ctx, hipMemcpyAsync(h_gv, d_gv, ng * 8, hipMemcpyDeviceToHost, st));
       }
+      int rc = fetch_scores();
+      if (rc) return rc;
       ESP_HIP(ctx, hipStreamSynchronize(st));
-      scratch.idle();
-      if (swaps_out) memcpy(swaps_out, h_swaps, nblk * 8);
-      if (retained_out) {
-        double tot = 0.0;
-        for (long long g = 0; g < ng; g++) tot = tot + h_gv[g];
-        *retained_out = tot;
+      return ESPARSE_OK;
+    };
+    bool first_fast = true;
+    if (d_meet) {
+      // the first round, all others in one launch, and the results behind them, which stand unless a block is left to the exact table
+      // or a team gave up waiting
+      if ((rc = launch_round(LBS_FAST, true))) return rc;
+      first_fast = false;
+#define LAUNCH_ROUNDS2(DTv, NK, MGv, QCv)                                                                                             \
+  hipLaunchKernelGGL((k_lbs_rounds<DTv, NK, MGv, QCv>), dim3((unsigned)((nblk + 7) / 8 * 8 * team)), dim3(64 * LBS_WAVES), 0, st, d_P, d_PT, d_sp, \
+                     d_V, d_lp, d_rec, d_state, d_swaps, o->max_swaps, N, Npad, (int)nblk, B, team, d_meet, d_count + 3, d_count + 2, d_count)
+#define LAUNCH_ROUNDS(DTv, NK, MGv, ...)               \
+  do {                                                 \
+    if (qc == 4) LAUNCH_ROUNDS2(DTv, NK, MGv, 4);      \
+    else LAUNCH_ROUNDS2(DTv, NK, MGv, 2);              \
+  } while (0)
+      DISPATCH_DT_NM(dtype, n, LAUNCH_ROUNDS, 0);
+#undef LAUNCH_ROUNDS
+#undef LAUNCH_ROUNDS2
+      ESP_HIP(ctx, hipGetLastError());
+      if ((rc = finish())) return rc;
+      if (count[0] > 0 && (rc = panel_columns())) return rc;  // the results' sums are where it was
+    }
+    if (!d_meet || count[0] > 0 || count[1] > 0) {
+      for (int mode : {LBS_FAST, LBS_EXACT}) {
+        int& active = count[mode == LBS_FAST ? 0 : 1];
+        bool first = mode == LBS_FAST ? first_fast : true;
+        long long iter = 0;
+        while (active > 0) {
+          // rounds are queued several at a time: a round after the last exchange of every block only finds that (about
+          // 5 us), a look at the count from the host costs about 25
+          for (int r = 0; r < LBS_ROUNDS_QUEUED; r++) {
+            if ((rc = launch_round(mode, first))) return rc;
+            first = false;
+          }
+          iter += LBS_ROUNDS_QUEUED;
+          ESP_HIP(ctx, hipMemcpyAsync(count, d_count, 8, hipMemcpyDeviceToHost, st));
+          ESP_HIP(ctx, hipStreamSynchronize(st));
+          if (active > 0 && iter > (long long)B * B * LBS_ROUNDS_MAX)
+            return esp_fail(ctx, ESPARSE_EHIP, "block shuffle did not terminate after %lld rounds", iter);
+        }
       }
+      if ((rc = finish())) return rc;
+    }
+    scratch.idle();
+    leave_scores();
+    if (swaps_out) memcpy(swaps_out, h_swaps, nblk * 8);
+    if (retained_out) {
+      double tot = 0.0;
+      for (long long g = 0; g < ng; g++) tot = tot + h_gv[g];
+      *retained_out = tot;
     }
     return ESPARSE_OK;
   }
@@ -2017,7 +2198,10 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const void* Wv, long
     for (long long g = 0; g < ng; g++) tot = tot + gv[g];
     *retained_out = tot;
   }
+  const int rc = fetch_scores();
+  if (rc) return rc;
   ESP_HIP(ctx, hipStreamSynchronize(st));
   scratch.idle();
+  leave_scores();
   return ESPARSE_OK;
 }
