@@ -70,6 +70,14 @@ __device__ double exact_bins_to_double(const unsigned long long* __restrict__ bi
   return ldexp((double)mant, 16 * top + 15 - lz - 52 - off);
 }
 
+// the same value, but nothing that is formed from it is moved ahead of this place (kept in registers through a loop whose body needs them all)
+__device__ __forceinline__ int opaque(int v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(v));
+#endif
+  return v;
+}
+
 __device__ __forceinline__ unsigned int ordered_bits(float f) {
   unsigned int u = __float_as_uint(f);
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
@@ -84,10 +92,11 @@ __device__ __forceinline__ unsigned int ordered_bits(float f) {
 // at most 11 bits, so its square is the integer m * m at binary position 2 E: bin and quotient of the exponent-
 // binned accumulation come from integer shifts (no float64 arithmetic, no ilogb / ldexp).
 // Scan B: the histogram over [min, max].  The bin of x is floor(((x - lo) * bins) / (hi - lo)) evaluated in
-// float64, clamped to bins - 1 (the definition).  A float32 estimate q of that quotient is at most 5e-5 off for
-// bins <= 256 (three roundings of 2^-24 relative), the float64 quotient at most 2^-44: whenever q is farther
-// than 1e-4 from the nearest integer both have the same floor, so only the lanes near a bin edge (and the lanes
-// where the estimate overflowed) evaluate the definition itself.
+// float64, clamped to bins - 1 (the definition).  A float32 estimate q of that quotient is at most 1.8e-7 bins off
+// (three roundings of 2^-24 relative), the float64 quotient at most 2^-44: whenever q is farther
+// than 2.1e-7 bins + 1e-6 from the nearest integer both have the same floor, so only the lanes near a bin edge (and the lanes
+// where the estimate overflowed) evaluate the definition itself.  (Some lane of a wave is that near in one trip of 256 rows in twelve
+// for 100 bins; with 1e-4 for any number of bins it was one in three.)
 // ------------------------------------------------------------------------------------------------
 // bin and quotient of the square of a 16-bit value for the exponent-binned exact accumulation, from the bits of the
 // (exact) floating-point square: fp16 squares have at most 22 significant bits and fit float32, bf16 squares have 16
@@ -133,9 +142,34 @@ __device__ __forceinline__ void load_rows(const uint16_t* __restrict__ p, long l
   }
 }
 
+// Exact sum of squares of one channel in a lane, fp16: a square is a multiple of 2^-48 below 2^32 and fits float32.  It is split in
+// float64 at 2^-12 (adding and subtracting 1.5 2^40 rounds to a multiple of that), both parts are added up exactly: up to SQ_ROWS = 256 of
+// them are below 2^52 and 2^43 units.  Eight instructions per value and none of them to the LDS; by exponent into LDS bins, as
+// bf16 squares go, it takes about 14 and an LDS atomic.
+#define SQ_ROWS 256
+struct SquareSum {
+  double hi, lo;
+};
+__device__ __forceinline__ void square_add(SquareSum& a, float x) {
+  const double s = (double)(x * x), c = 0x1.8p40;
+  const double h = (s + c) - c;
+  a.hi = a.hi + h;
+  a.lo = a.lo + (s - h);
+}
+// into the channel's bins: units of 2^-48 are bit 245 = 16 15 + 5, units of 2^-12 bit 281 = 16 17 + 9
+__device__ __forceinline__ void square_flush(SquareSum& a, unsigned long long* bins) {
+  static_assert(SQ_EOFF + SQ_SIG == 293, "the places of the two units");
+  const long long l = (long long)(a.lo * 0x1p48);
+  const unsigned long long h = (unsigned long long)((long long)(a.hi * 0x1p12) + (l >> 36));  // the parts below 2^-12 may add up to less than zero
+  atomicAdd(bins + 15, (unsigned long long)(l & 0xfffffffffll) << 5);
+  atomicAdd(bins + 17, (h & 0xffffffffull) << 9);
+  if (h >> 32) atomicAdd(bins + 19, (h >> 32) << 9);
+  a = SquareSum{0.0, 0.0};
+}
+
 template <int DT, int CPL, int ROWS, bool FULL>
 __device__ __forceinline__ void minmax_sumsq_trip(const uint16_t* __restrict__ p, long long stride32, long long rb, long long r1,
-                                                  float (&lo)[CPL], float (&hi)[CPL], unsigned long long* s_sq_lane, int want_sq) {
+                                                  float (&lo)[CPL], float (&hi)[CPL], SquareSum (&sum)[CPL], unsigned long long* s_sq_lane, int want_sq) {
   uint32_t w[ROWS][CPL / 2];
   load_rows<CPL, ROWS, FULL>(p, stride32, rb, r1, w);
 #pragma unroll
@@ -147,7 +181,9 @@ __device__ __forceinline__ void minmax_sumsq_trip(const uint16_t* __restrict__ p
       const float x = esp_to_float<DT>((uint16_t)(w[u][j / 2] >> (16 * (j & 1))));
       lo[j] = fminf(lo[j], x);
       hi[j] = fmaxf(hi[j], x);
-      if (want_sq) {
+      if (want_sq && DT == ESPARSE_F16) {
+        square_add(sum[j], live ? x : 0.0f);
+      } else if (want_sq) {
         unsigned int bi;
         unsigned long long q;
         square_bin<DT>(live ? x : 0.0f, &bi, &q);
@@ -158,7 +194,7 @@ __device__ __forceinline__ void minmax_sumsq_trip(const uint16_t* __restrict__ p
 }
 
 template <int DT, int CPL>
-__global__ void __launch_bounds__(1024) k_minmax_sumsq(const uint16_t* __restrict__ X, long long T, long long K,
+__global__ void __launch_bounds__(1024, 8) k_minmax_sumsq(const uint16_t* __restrict__ X, long long T, long long K,
                                                         long long rows_per_block, unsigned int* __restrict__ onmin /*~minimum*/,
                                                         unsigned int* __restrict__ omax,
                                                         unsigned long long* __restrict__ sq /*[K][SQ_NB]*/, int want_sq) {
@@ -187,10 +223,22 @@ __global__ void __launch_bounds__(1024) k_minmax_sumsq(const uint16_t* __restric
     const long long stride32 = 32 * K;
     const uint16_t* p = X + (r0 + rl) * K + c;
     unsigned long long* s_sq_lane = s_sq + cl * SQ_NB;
+    SquareSum sum[CPL];
+#pragma unroll
+    for (int j = 0; j < CPL; j++) sum[j] = SquareSum{0.0, 0.0};
+    auto flush = [&]() {
+      if (want_sq && DT == ESPARSE_F16)
+#pragma unroll
+        for (int j = 0; j < CPL; j++) square_flush(sum[j], s_sq_lane + j * (32 * SQ_NB));
+    };
     long long rb = r0 + rl;
-    for (; rb + 32 * (ROWS - 1) < r1; rb += 32 * ROWS, p += ROWS * stride32)
-      minmax_sumsq_trip<DT, CPL, ROWS, true>(p, stride32, rb, r1, lo, hi, s_sq_lane, want_sq);
-    if (rb < r1) minmax_sumsq_trip<DT, CPL, ROWS, false>(p, stride32, rb, r1, lo, hi, s_sq_lane, want_sq);
+    for (int trips = 0; rb + 32 * (ROWS - 1) < r1; rb += 32 * ROWS, p += ROWS * stride32) {
+      minmax_sumsq_trip<DT, CPL, ROWS, true>(p, stride32, rb, r1, lo, hi, sum, s_sq_lane, want_sq);
+      if (++trips % (SQ_ROWS / ROWS) == 0) flush();
+    }
+    flush();
+    if (rb < r1) minmax_sumsq_trip<DT, CPL, ROWS, false>(p, stride32, rb, r1, lo, hi, sum, s_sq_lane, want_sq);
+    flush();
 #pragma unroll
     for (int j = 0; j < CPL; j++) {
       atomicMin(&s_lo[j * 32 + cl], ordered_bits(lo[j]));
@@ -227,67 +275,62 @@ __device__ __forceinline__ float fraction_of(float q) {
 #endif
 }
 
-// the float32 estimate of a value's bin and whether it can be trusted: farther than 1e-4 from both neighbouring
-// integers and inside [0, bins)
-__device__ __forceinline__ bool bin_estimate(float x, float lo32, float c32, int bins, int* bi) {
-  const float q = (x - lo32) * c32;
-  *bi = (int)q;
-  return fabsf(fraction_of(q) - 0.5f) < 0.4999f && (unsigned int)*bi < (unsigned int)bins;
+// x - lo of a 16-bit value (one v_fma_mix_f32 for fp16: `one` is 1.0 in a register the compiler cannot see into)
+template <int DT>
+__device__ __forceinline__ float offset_of(uint16_t raw, float lo32, float one) {
+  if (DT == ESPARSE_F16) return __builtin_fmaf(esp_to_float<DT>(raw), one, -lo32);
+  return esp_to_float<DT>(raw) - lo32;
 }
 
+// An estimate q can be trusted if it is farther than `edge` from both neighbouring integers and, where it may overflow (bf16), below
+// `bins`.  Else the value is looked at in float64.  These are not as rare as `edge` makes them: 16-bit values stand on bin edges
+// (one in a thousand on a few of them per channel), so a wave meets some in most trips, and they are settled on the spot, between the
+// others; done after all others, with the estimates of the trip formed again, they cost 470 - 397 us.
 template <int DT, int CPL, int ROWS, bool FULL>
 __device__ __forceinline__ void hist_trip(const uint16_t* __restrict__ p, long long stride32, long long rb, long long r1,
                                           const float (&lo32)[CPL], const float (&c32)[CPL], const double (&lo)[CPL],
-                                          const double (&wd)[CPL], int bins, unsigned int* s_hist_lane, int row_stride) {
+                                          const double (&wd)[CPL], int bins, float one, float edge, unsigned int* s_hist_lane) {
   uint32_t w[ROWS][CPL / 2];
   load_rows<CPL, ROWS, FULL>(p, stride32, rb, r1, w);
-  // all estimates first, without branches (whether all can be trusted is kept in a lane mask, not in registers);
-  // the rare values near a bin edge are redone afterwards from the definition
-  int bsel[ROWS][CPL];
-  bool all_ok = true;
-#pragma unroll
-  for (int u = 0; u < ROWS; u++)
-#pragma unroll
-    for (int j = 0; j < CPL; j++)
-      all_ok &= bin_estimate(esp_to_float<DT>((uint16_t)(w[u][j / 2] >> (16 * (j & 1)))), lo32[j], c32[j], bins, &bsel[u][j]);
-  if (!all_ok) {
-    const double nb = (double)bins;
-#pragma unroll
-    for (int u = 0; u < ROWS; u++)
-#pragma unroll
-      for (int j = 0; j < CPL; j++) {
-        const float x = esp_to_float<DT>((uint16_t)(w[u][j / 2] >> (16 * (j & 1))));
-        int b;
-        if (!bin_estimate(x, lo32[j], c32[j], bins, &b)) {
-          b = 0;
-          if (wd[j] > 0.0) {
-            const double d = ((double)x - lo[j]) * nb / wd[j];  // the definition
-            b = (int)floor(d);
-            if (b > bins - 1) b = bins - 1;
-          }
-          bsel[u][j] = b;
-        }
-      }
-  }
+  const float safe = 0.5f - edge, nb32 = (float)bins;
+  const double nb = (double)bins;
 #pragma unroll
   for (int u = 0; u < ROWS; u++) {
-    const unsigned int one = (FULL || rb + 32 * u < r1) ? 1u : 0u;  // a repeated row counts nothing
+    const unsigned int add = (FULL || rb + 32 * u < r1) ? 1u : 0u;  // a repeated row counts nothing
 #pragma unroll
-    for (int j = 0; j < CPL; j++) atomicAdd(s_hist_lane + j * (32 * row_stride) + bsel[u][j], one);
+    for (int j = 0; j < CPL; j++) {
+      const uint16_t raw = (uint16_t)(w[u][j / 2] >> (16 * (j & 1)));
+      const float q = offset_of<DT>(raw, lo32[j], one) * c32[j];
+      unsigned int b = (unsigned int)(int)q;
+      if (!(fabsf(fraction_of(q) - 0.5f) <= safe) || (DT != ESPARSE_F16 && !(q < nb32))) {
+        const double t = ((double)esp_to_float<DT>(raw) - lo[j]) * nb;
+        if (DT == ESPARSE_F16) {
+          // t and multiples of the width are exact (at most 49 bits), and a quotient that is not an integer is at least 2^-41 away from
+          // one: floor(t / wd) is the nearest integer e to q, or e - 1 where t < e wd
+          const float e = rintf(q);
+          b = (unsigned int)((int)e - (__builtin_fma(-(double)e, wd[j], t) < 0.0 ? 1 : 0));
+        } else {
+          b = wd[j] > 0.0 ? (unsigned int)(int)floor(t / wd[j]) : 0u;  // the definition
+        }
+      }
+      atomicAdd(s_hist_lane + 32u * (j * (unsigned int)bins + min(b, (unsigned int)bins - 1u)), add);
+    }
   }
 }
 
 template <int DT, int CPL>
-__global__ void __launch_bounds__(1024) k_hist(const uint16_t* __restrict__ X, long long T, long long K,
+__global__ void __launch_bounds__(1024, 8) k_hist(const uint16_t* __restrict__ X, long long T, long long K,
                                                 long long rows_per_block, int bins, const unsigned int* __restrict__ onmin,
                                                 const unsigned int* __restrict__ omax, unsigned int* __restrict__ hist /*[K][bins]*/,
                                                 unsigned int* __restrict__ most /*[gridDim.x] no count of these channels is larger*/) {
   constexpr int CH = 32 * CPL;
   __shared__ unsigned int s_most;
-  extern __shared__ unsigned int s_hist[];  // [CH rows][stride]: the row of a channel is j * 32 + cl, the stride odd, so
-  const int stride = bins | 1;              // that the column lanes of one instruction start in 32 different banks
+  // [j][bins][cl] (cl: column lane, j: which of the lane's CPL channels): a column lane always adds in its own bank.  With the bins of
+  // a channel side by side the lanes of an instruction meet in banks by chance (16 clocks per atomic of a wave) and
+  // the atomics are what the scan waits for: T = 262144, K = 4096 465 us
+  extern __shared__ unsigned int s_hist[];
   const int tid = threadIdx.x, cl = tid & 31, rl = tid >> 5;
-  for (int i = tid; i < CH * stride; i += 1024) s_hist[i] = 0u;
+  for (int i = tid; i < CH * bins; i += 1024) s_hist[i] = 0u;
   if (tid == 0) s_most = 0u;
   __syncthreads();
   const long long c = ((long long)blockIdx.x * 32 + cl) * CPL;
@@ -302,27 +345,31 @@ __global__ void __launch_bounds__(1024) k_hist(const uint16_t* __restrict__ X, l
       lo32[j] = float_from_ordered_bits(~onmin[c + j]);
       lo[j] = (double)lo32[j];
       wd[j] = (double)float_from_ordered_bits(omax[c + j]) - lo[j];
-      // the estimate's factor; a constant channel (width 0) gets NaN, which sends every value to the definition
-      c32[j] = wd[j] > 0.0 ? (float)(nb / wd[j]) : __uint_as_float(0x7fc00000u);
+      // the estimate's factor; a constant channel (width 0) gets 0: every value in bin 0
+      c32[j] = wd[j] > 0.0 ? (float)(nb / wd[j]) : 0.0f;
     }
+    const float one = __int_as_float(opaque(0x3f800000)), edge = (float)bins * 2.1e-7f + 1e-6f;
     constexpr int ROWS = 8;
     const long long stride32 = 32 * K;
     const uint16_t* p = X + (r0 + rl) * K + c;
-    unsigned int* s_hist_lane = s_hist + cl * stride;
+    unsigned int* s_hist_lane = s_hist + cl;
     long long rb = r0 + rl;
     for (; rb + 32 * (ROWS - 1) < r1; rb += 32 * ROWS, p += ROWS * stride32)
-      hist_trip<DT, CPL, ROWS, true>(p, stride32, rb, r1, lo32, c32, lo, wd, bins, s_hist_lane, stride);
-    if (rb < r1) hist_trip<DT, CPL, ROWS, false>(p, stride32, rb, r1, lo32, c32, lo, wd, bins, s_hist_lane, stride);
+      hist_trip<DT, CPL, ROWS, true>(p, stride32, rb, r1, lo32, c32, lo, wd, bins, one, edge, s_hist_lane);
+    if (rb < r1) hist_trip<DT, CPL, ROWS, false>(p, stride32, rb, r1, lo32, c32, lo, wd, bins, one, edge, s_hist_lane);
   }
   __syncthreads();
   const long long cbase = (long long)blockIdx.x * CH;
+  // a wave takes 8 column lanes x 8 bins at a time: short runs in both layouts
   unsigned int mine = 0u;
-  for (int i = tid; i < CH * bins; i += 1024) {
-    const int row = i / bins, b = i - row * bins;
-    const long long ch = cbase + (long long)(row & 31) * CPL + (row >> 5);
-    const unsigned int v = s_hist[row * stride + b];
-    if (ch < K && v) atomicAdd(&hist[ch * bins + b], v);
-    if (ch < K) mine = v > mine ? v : mine;
+  const int octets = (bins + 7) / 8, lane = tid & 63;
+  for (int t = tid >> 6; t < 4 * CPL * octets; t += 16) {
+    const int b = t % octets * 8 + (lane >> 3), c8 = t / octets, col = c8 % 4 * 8 + (lane & 7), j = c8 / 4;
+    const long long ch = cbase + (long long)col * CPL + j;
+    if (b >= bins || ch >= K) continue;
+    const unsigned int v = s_hist[32 * (j * bins + b) + col];
+    if (v) atomicAdd(&hist[ch * bins + b], v);
+    mine = v > mine ? v : mine;
   }
   atomicMax(&s_most, mine);
   __syncthreads();
@@ -552,15 +599,15 @@ static int launch_scans(esparse_ctx* ctx, Scratch& scratch, const void* calib, l
   *out = Scans{d_sq, d_nmin, d_max, d_most, d_sums, d_hist, nmost};
   ESP_HIP(ctx, hipMemsetAsync(d_all, 0, all, st));
   const uint16_t* X = reinterpret_cast<const uint16_t*>(calib);
-  // about 1024 workgroups (four per CU over the two that fit at once), whole trips of 256 rows
-  const long long nchunk = std::max<long long>(1, std::min<long long>((T + 255) / 256, 1024 / gx + 1));
+  // 1024 workgroups, two rounds of the two per CU that fit at once (one more chunk would be a third round), whole trips of 256 rows
+  const long long nchunk = std::max<long long>(1, std::min<long long>((T + 255) / 256, 1024 / gx));
   long long rpb = (T + nchunk - 1) / nchunk;
   rpb = (rpb + 255) / 256 * 256;
   dim3 grid((unsigned)gx, (unsigned)((T + rpb - 1) / rpb));
 #define ESP_SCAN_A(DTv, CPLv)                                                                                        \
   hipLaunchKernelGGL((k_minmax_sumsq<DTv, CPLv>), grid, dim3(1024), 0, st, X, T, K, rpb, d_nmin, d_max, d_sq, want_sq ? 1 : 0)
 #define ESP_SCAN_B(DTv, CPLv)                                                                                        \
-  hipLaunchKernelGGL((k_hist<DTv, CPLv>), grid, dim3(1024), (size_t)32 * CPLv * (bins | 1) * 4, st, X, T, K, rpb, bins, d_nmin, d_max, d_hist, d_most)
+  hipLaunchKernelGGL((k_hist<DTv, CPLv>), grid, dim3(1024), (size_t)32 * CPLv * bins * 4, st, X, T, K, rpb, bins, d_nmin, d_max, d_hist, d_most)
   if (dtype == ESPARSE_F16) {
     if (cpl == 4) ESP_SCAN_A(ESPARSE_F16, 4);
     else ESP_SCAN_A(ESPARSE_F16, 2);
@@ -571,7 +618,7 @@ static int launch_scans(esparse_ctx* ctx, Scratch& scratch, const void* calib, l
   ESP_HIP(ctx, hipGetLastError());
   if (want_hist) {
     // 32 * 4 channels x 256 bins x 4 bytes = 128 KiB of LDS at most
-    const size_t smem = (size_t)32 * cpl * (bins | 1) * 4;
+    const size_t smem = (size_t)32 * cpl * bins * 4;
     if (smem > 48 * 1024) {
       ESP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hist<ESPARSE_F16, 4>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
       ESP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hist<ESPARSE_BF16, 4>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
@@ -1058,14 +1105,6 @@ __device__ __forceinline__ int lane_of(int v, int at) {
 __device__ __forceinline__ double lane_of(double v, int at) {
   const long long b = __double_as_longlong(v);
   return __longlong_as_double(((long long)lane_of((int)(b >> 32), at) << 32) | (unsigned int)lane_of((int)b, at));
-}
-
-// the same value, but nothing that is formed from it is moved ahead of this place (kept in registers through a loop whose body needs them all)
-__device__ __forceinline__ int opaque(int v) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  asm volatile("" : "+v"(v));
-#endif
-  return v;
 }
 
 // orders the LDS accesses of one wave as they are written (its lanes exchange data through LDS)

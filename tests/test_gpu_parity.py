@@ -76,6 +76,33 @@ def test_channel_stats_other_bin_counts(ctx):
         assert (ir == orc.channel_entropy(_np(Xc), bins)).all()
 
 
+# every value on the edge of a bin, and one unit beside it
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+@pytest.mark.parametrize("bins", [1, 64, 100, 256])
+def test_channel_entropy_values_on_bin_edges(ctx, dtype, bins):
+    g = torch.Generator().manual_seed(bins)
+    x = torch.randint(0, bins + 1, (700, 24), generator=g).float()
+    x[:, 8:16] += 1.0 / 64 * torch.randint(-1, 2, (700, 8), generator=g)
+    x[:, 16:] = x[:, 16:] * 0.37 - 11.0
+    Xc = x.to(dtype)
+    ir, _ = ctx.channel_stats(Xc.cuda(), bins)
+    assert (ir == orc.channel_entropy(_np(Xc), bins)).all()
+
+
+# so many channels that a lane adds up more than 256 rows: the largest and the smallest squares, alone and together
+def test_channel_amplitude_many_rows_per_lane(ctx):
+    T, K = 9000, 131072
+    Xc = torch.empty(T, K, dtype=torch.float16, device="cuda").normal_(generator=torch.Generator(device="cuda").manual_seed(1))
+    tiny = 2.0 ** -24
+    cols = {0: torch.full((T,), 65504.0), 5: torch.full((T,), tiny), 130: torch.where(torch.arange(T) % 3 == 0, 65504.0, tiny),
+            131071: torch.where(torch.arange(T) % 2 == 0, -0.015625, 3 * tiny)}
+    for c, v in cols.items():
+        Xc[:, c] = v.to(torch.float16).cuda()
+    _, am = ctx.channel_stats(Xc, 10)
+    pick = list(cols) + [1, 2, 77777]
+    assert (am[pick] == orc.channel_amplitude(_np(Xc[:, pick].cpu()))).all()
+
+
 # ---------------------------------------------------------------- prune
 def _prune_case(esp, ctx, N, K, T, B, n, m, dtype, flags, seed, max_swaps=0):
     scales = wl.channel_scales("lognormal", K, wl.stream_id("ps", seed))
