@@ -107,25 +107,64 @@ def _dtype_code(t: torch.Tensor) -> int:
 
 
 def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_PTRS = [None] + [C.c_void_p * n for n in range(1, 5)]  # arrays of a group call's pointers
+
+
+def _ptrs(ts):
+    n = len(ts)
+    return (_PTRS[n] if 0 < n < 5 else C.c_void_p * n)(*[_ptr(t) for t in ts])
+
+
+# sizes asked for before, a function of their arguments alone
+_sizes = {}
+
+
+def _remember(key, value):
+    if len(_sizes) >= 4096:
+        _sizes.clear()
+    _sizes[key] = value
+    return value
 
 
 def compressed_size(N: int, K: int, n: int, m: int, dtype: int = F16):
+    key = ("compressed", N, K, n, m, dtype)
+    known = _sizes.get(key)
+    if known is not None:
+        return known
     lib = load_library()
     a, b, c = C.c_size_t(), C.c_size_t(), C.c_size_t()
     rc = lib.esparse_compressed_size(N, K, n, m, dtype, C.byref(a), C.byref(b), C.byref(c))
     if rc:
         raise EsparseError(rc, "esparse_compressed_size")
-    return a.value, b.value, c.value
+    return _remember(key, (a.value, b.value, c.value))
 
 
 def spmm_workspace(M: int, N: int, K: int, variant: int = -1) -> int:
+    key = (M, N, K, variant)
+    known = _sizes.get(key)
+    if known is not None:
+        return known
     lib = load_library()
     a = C.c_size_t()
     rc = lib.esparse_spmm_workspace(M, N, K, variant, C.byref(a))
     if rc:
         raise EsparseError(rc, "esparse_spmm_workspace")
-    return a.value
+    return _remember(key, a.value)
+
+
+def _group_workspace(count: int, M: int, N: int, K: int) -> int:
+    key = ("group", count, M, N, K)
+    known = _sizes.get(key)
+    if known is not None:
+        return known
+    a = C.c_size_t(0)
+    rc = load_library().esparse_spmm_group_workspace(count, M, N, K, C.byref(a))
+    if rc:
+        raise EsparseError(rc, "esparse_spmm_group_workspace: bad arguments")
+    return _remember(key, a.value)
 
 
 def dense_packed_size(N: int, K: int) -> int:
@@ -181,6 +220,13 @@ class Compressed:
     dtype: int
 
 
+def _raw_stream(device: int) -> int:
+    return torch.cuda.current_stream(device).cuda_stream
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", _raw_stream)  # without the Stream object
+
+
 class Context:
     """One library context bound to a device and (per call) to torch's current stream."""
 
@@ -192,6 +238,8 @@ class Context:
             raise EsparseError(rc, "esparse_create")
         self.device = device
         self._ws = None
+        self._ws_at = self._ws_room = 0  # the workspace's first aligned address and the bytes from there
+        self._stream = None              # the stream the library knows
 
     def close(self):
         if self._h:
@@ -210,14 +258,27 @@ class Context:
             raise EsparseError(rc, self._lib.esparse_last_error(self._h).decode())
 
     def _sync_stream(self):
-        if torch.cuda.is_available():
+        if torch.cuda.is_initialized():
+            s = _raw_stream(self.device)
+        elif torch.cuda.is_available():
             s = torch.cuda.current_stream(self.device).cuda_stream
-            self._lib.esparse_set_stream(self._h, C.c_void_p(s))
+        else:
+            return
+        if s != self._stream:
+            self._lib.esparse_set_stream(self._h, s)
+            self._stream = s
+
+    def _scratch(self, nbytes: int) -> int:
+        """Address of the context's workspace, of at least nbytes, 256-byte aligned."""
+        if self._ws_room < nbytes:
+            self._ws = torch.empty(nbytes + 256, dtype=torch.uint8, device=f"cuda:{self.device}")
+            at = self._ws.data_ptr()
+            self._ws_at = at + -at % 256
+            self._ws_room = self._ws.numel() - -at % 256
+        return self._ws_at
 
     def workspace(self, nbytes: int) -> torch.Tensor:
-        if self._ws is None or self._ws.numel() < nbytes:
-            self._ws = torch.empty(nbytes + 256, dtype=torch.uint8, device=f"cuda:{self.device}")
-        off = (-self._ws.data_ptr()) % 256
+        off = self._scratch(nbytes) - self._ws.data_ptr()
         return self._ws[off:off + nbytes]
 
     # -- Section 3.2 --------------------------------------------------------------------------
@@ -278,12 +339,15 @@ class Context:
              out: Optional[torch.Tensor] = None) -> torch.Tensor:
         M, K = X.shape
         assert K == comp.K and _dtype_code(X) == comp.dtype
-        Y = out if out is not None else torch.empty((M, comp.N), dtype=X.dtype, device=X.device)
-        nbytes = spmm_workspace(M, comp.N, K)
-        ws = self.workspace(nbytes)
+        N = comp.N
+        Y = out if out is not None else X.new_empty((M, N))
+        nbytes = spmm_workspace(M, N, K)
+        ws = self._scratch(nbytes)
         self._sync_stream()
-        self._check(self._lib.esparse_spmm(self._h, _ptr(X), M, _ptr(comp.native), _ptr(perm), comp.N, K, comp.dtype,
-                                           comp.n_keep, comp.m_group, _ptr(Y), _ptr(ws), nbytes, variant))
+        rc = self._lib.esparse_spmm(self._h, X.data_ptr(), M, _ptr(comp.native), _ptr(perm), N, K, comp.dtype,
+                                    comp.n_keep, comp.m_group, Y.data_ptr(), ws, nbytes, variant)
+        if rc:
+            self._check(rc)
         return Y
 
     def spmm_static(self, X: torch.Tensor, comp: Compressed, perm: Optional[torch.Tensor], *, variant: int = -1,
@@ -304,42 +368,38 @@ class Context:
         assert len(Xs) == count and (perms is None or len(perms) == count)
         M, K = Xs[0].shape
         c0 = comps[0]
+        N, X0, seen = c0.N, Xs[0], None
         for X, c in zip(Xs, comps):
-            assert tuple(X.shape) == (M, K) and (c.N, c.K, c.dtype, c.n_keep, c.m_group) == (c0.N, K, c0.dtype, c0.n_keep, c0.m_group)
-            assert _dtype_code(X) == c0.dtype
+            assert (c.N, c.K, c.dtype, c.n_keep, c.m_group) == (N, K, c0.dtype, c0.n_keep, c0.m_group)
+            if X is not seen:
+                assert tuple(X.shape) == (M, K) and _dtype_code(X) == c0.dtype
+                seen = X
         if outs is None:
-            outs = [torch.empty((M, c0.N), dtype=Xs[0].dtype, device=Xs[0].device) for _ in range(count)]
-        nbytes = C.c_size_t(0)
-        rc = self._lib.esparse_spmm_group_workspace(count, M, c0.N, K, C.byref(nbytes))
-        if rc:
-            raise EsparseError(rc, "esparse_spmm_group_workspace: bad arguments")
-        ws = self.workspace(nbytes.value)
-        arr = C.c_void_p * count
-        xs = arr(*[_ptr(x) for x in Xs])
-        wsn = arr(*[_ptr(c.native) for c in comps])
-        ps = arr(*[_ptr(p) for p in perms]) if perms is not None else None
-        ys = arr(*[_ptr(y) for y in outs])
+            outs = [X0.new_empty((M, N)) for _ in range(count)]
+        nbytes = _group_workspace(count, M, N, K)
+        ws = self._scratch(nbytes)
         self._sync_stream()
-        self._check(self._lib.esparse_spmm_group(self._h, count, xs, M, wsn, ps, c0.N, K, c0.dtype, c0.n_keep, c0.m_group, ys,
-                                                 _ptr(ws), nbytes.value, variant))
+        rc = self._lib.esparse_spmm_group(self._h, count, _ptrs(Xs), M, _ptrs([c.native for c in comps]),
+                                          _ptrs(perms) if perms is not None else None, N, K, c0.dtype, c0.n_keep, c0.m_group,
+                                          _ptrs(outs), ws, nbytes, variant)
+        if rc:
+            self._check(rc)
         return outs
 
     def stage_activations_group(self, Xs, perms, comp0: Compressed, ws: torch.Tensor, *, variant: int = -1):
         count = len(Xs)
         M, K = Xs[0].shape
-        arr = C.c_void_p * count
-        ps = arr(*[_ptr(p) for p in perms]) if perms is not None else None
+        ps = _ptrs(perms) if perms is not None else None
         self._sync_stream()
-        self._check(self._lib.esparse_stage_activations_group(self._h, count, arr(*[_ptr(x) for x in Xs]), M, ps, comp0.N, K,
+        self._check(self._lib.esparse_stage_activations_group(self._h, count, _ptrs(Xs), M, ps, comp0.N, K,
                                                               comp0.dtype, comp0.n_keep, comp0.m_group, _ptr(ws), ws.numel(), variant))
 
     def spmm_group_staged(self, M: int, comps, ws: torch.Tensor, outs, *, variant: int = -1):
         count = len(comps)
         c0 = comps[0]
-        arr = C.c_void_p * count
         self._sync_stream()
-        self._check(self._lib.esparse_spmm_group_staged(self._h, count, M, arr(*[_ptr(c.native) for c in comps]), c0.N, c0.K,
-                                                        c0.dtype, c0.n_keep, c0.m_group, arr(*[_ptr(y) for y in outs]), _ptr(ws),
+        self._check(self._lib.esparse_spmm_group_staged(self._h, count, M, _ptrs([c.native for c in comps]), c0.N, c0.K,
+                                                        c0.dtype, c0.n_keep, c0.m_group, _ptrs(outs), _ptr(ws),
                                                         ws.numel(), variant))
         return outs
 
@@ -348,16 +408,11 @@ class Context:
         M, K = Xs[0].shape
         if outs is None:
             outs = [torch.empty((M, N), dtype=Xs[0].dtype, device=Xs[0].device) for _ in range(count)]
-        nbytes = C.c_size_t(0)
-        rc = self._lib.esparse_spmm_group_workspace(count, M, N, K, C.byref(nbytes))
-        if rc:
-            raise EsparseError(rc, "esparse_spmm_group_workspace: bad arguments")
-        ws = self.workspace(nbytes.value)
-        arr = C.c_void_p * count
+        nbytes = _group_workspace(count, M, N, K)
+        ws = self._scratch(nbytes)
         self._sync_stream()
-        self._check(self._lib.esparse_dense_gemm_group(self._h, count, arr(*[_ptr(x) for x in Xs]), M, arr(*[_ptr(w) for w in packed]),
-                                                       N, K, _dtype_code(Xs[0]), arr(*[_ptr(y) for y in outs]), _ptr(ws), nbytes.value,
-                                                       variant))
+        self._check(self._lib.esparse_dense_gemm_group(self._h, count, _ptrs(Xs), M, _ptrs(packed), N, K, _dtype_code(Xs[0]),
+                                                       _ptrs(outs), ws, nbytes, variant))
         return outs
 
     def stage_activations(self, X: torch.Tensor, perm: Optional[torch.Tensor], N: int,
@@ -394,12 +449,12 @@ class Context:
     def dense_gemm(self, X: torch.Tensor, packed: torch.Tensor, N: int, *, variant: int = -1,
                    out: Optional[torch.Tensor] = None) -> torch.Tensor:
         M, K = X.shape
-        Y = out if out is not None else torch.empty((M, N), dtype=X.dtype, device=X.device)
+        Y = out if out is not None else X.new_empty((M, N))
         nbytes = spmm_workspace(M, N, K)
-        ws = self.workspace(nbytes)
+        ws = self._scratch(nbytes)
         self._sync_stream()
-        self._check(self._lib.esparse_dense_gemm(self._h, _ptr(X), M, _ptr(packed), N, K, _dtype_code(X), _ptr(Y),
-                                                 _ptr(ws), nbytes, variant))
+        self._check(self._lib.esparse_dense_gemm(self._h, X.data_ptr(), M, _ptr(packed), N, K, _dtype_code(X), Y.data_ptr(),
+                                                 ws, nbytes, variant))
         return Y
 
     # -- Section 4, step 2 --------------------------------------------------------------------
