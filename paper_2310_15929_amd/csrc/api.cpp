@@ -290,15 +290,16 @@ static int tuned_variant(const esparse_ctx* ctx, int sparse, int dtype, long lon
   return -1;
 }
 
-static int pick_variant(esparse_ctx* ctx, int sparse, int dtype, long long M, long long N, long long K, int variant, int count = 1, bool grouped = false) {
+static int pick_variant(esparse_ctx* ctx, int sparse, int dtype, long long M, long long N, long long K, int variant, int phases, int count = 1, bool grouped = false) {
   if (variant >= 0) return variant;
   const int v = tuned_variant(ctx, sparse, dtype, M, N, K, count);
   if (v >= 0) return v;
   // the built-in choice is a function of the shape alone (made in 0.3 us, on a first call in 2)
-  const auto key = std::make_tuple(grouped ? -count : count, sparse, M, N, K);
+  const bool whole = phases == (ESP_PHASE_STAGE | ESP_PHASE_MULTIPLY);
+  const auto key = std::make_tuple((grouped ? -count : count) + (whole ? 0 : 16), sparse, M, N, K);
   auto it = ctx->defaults.find(key);
   if (it != ctx->defaults.end()) return it->second;
-  const int made = esp_default_variant(M, N, K, sparse, count, grouped);
+  const int made = (whole ? esp_default_variant : esp_default_variant_staged)(M, N, K, sparse, count, grouped);
   try {
     if (ctx->defaults.size() >= 4096) ctx->defaults.clear();
     ctx->defaults[key] = made;
@@ -330,7 +331,7 @@ static int spmm_phases(esparse_ctx* ctx, const void* X, long long M, const void*
   if (M == 0) return ESPARSE_OK;
   ESP_HIP(ctx, hipSetDevice(ctx->device));
   return esp_matmul_device(ctx, mode, X, M, native_w, perm, N, K, dtype, Y, workspace,
-                           pick_variant(ctx, mode, dtype, M, N, K, variant), phases);
+                           pick_variant(ctx, mode, dtype, M, N, K, variant, phases), phases);
 }
 
 int esparse_spmm(esparse_ctx* ctx, const void* X, long long M, const void* native_w, const int32_t* perm,
@@ -350,7 +351,7 @@ int esparse_spmm_static(esparse_ctx* ctx, const void* X, long long M, const void
   ESP_REQUIRE(ctx, K % m == 0, ESPARSE_EINVAL, "K = %lld is not a multiple of %d", K, m);
   ESP_REQUIRE(ctx, esp_aligned16(perm), ESPARSE_EINVAL, "perm is not 16-byte aligned");
   if (M == 0) return ESPARSE_OK;
-  int v = pick_variant(ctx, mode, dtype, M, N, K, variant);
+  int v = pick_variant(ctx, mode, dtype, M, N, K, variant, ESP_PHASE_STAGE | ESP_PHASE_MULTIPLY);
   size_t need = esp_variant_workspace_bytes(v, M, N, K);
   if (variant < 0 && need > (size_t)ESPARSE_STATIC_SCRATCH_BYTES) {
     // the tuned or built-in choice keeps partial tiles that do not fit the array: the built-in choice among the
@@ -406,7 +407,7 @@ static int spmm_group_phases(esparse_ctx* ctx, int count, const void* const* X, 
   if (M == 0) return ESPARSE_OK;
   ESP_REQUIRE(ctx, workspace_bytes >= esp_group_workspace_bytes(count, M, N, K), ESPARSE_EWORKSPACE,
               "workspace has %zu bytes, %zu needed", workspace_bytes, esp_group_workspace_bytes(count, M, N, K));
-  const int v = pick_variant(ctx, mode, dtype, M, N, K, variant, count, true);
+  const int v = pick_variant(ctx, mode, dtype, M, N, K, variant, phases, count, true);
   // (beyond 32 tokens the built-in choice may be a kernel without a grouped form: the halves need a named or tuned one)
   const bool chosen = variant >= 0 || M <= 32 || tuned_variant(ctx, mode, dtype, M, N, K, count) >= 0;
   ESP_REQUIRE(ctx, phases == (ESP_PHASE_STAGE | ESP_PHASE_MULTIPLY) || (chosen && esp_variant_is_decode_kernel(v)), ESPARSE_EUNSUPPORTED,
@@ -451,7 +452,7 @@ int esparse_dense_gemm_group(esparse_ctx* ctx, int count, const void* const* X, 
               "workspace has %zu bytes, %zu needed", workspace_bytes, esp_group_workspace_bytes(count, M, N, K));
   ESP_HIP(ctx, hipSetDevice(ctx->device));
   return esp_matmul_group_device(ctx, 0, count, X, M, packed_w, nullptr, N, K, dtype, Y, workspace,
-                                 pick_variant(ctx, 0, dtype, M, N, K, variant, count, count > 1),
+                                 pick_variant(ctx, 0, dtype, M, N, K, variant, ESP_PHASE_STAGE | ESP_PHASE_MULTIPLY, count, count > 1),
                                  ESP_PHASE_STAGE | ESP_PHASE_MULTIPLY);
 }
 
@@ -483,7 +484,7 @@ static int dense_phases(esparse_ctx* ctx, const void* X, long long M, const void
   if (M == 0) return ESPARSE_OK;
   ESP_HIP(ctx, hipSetDevice(ctx->device));
   return esp_matmul_device(ctx, 0, X, M, packed_w, nullptr, N, K, dtype, Y, workspace,
-                           pick_variant(ctx, 0, dtype, M, N, K, variant), phases);
+                           pick_variant(ctx, 0, dtype, M, N, K, variant, phases), phases);
 }
 
 int esparse_dense_gemm(esparse_ctx* ctx, const void* X, long long M, const void* packed_w, long long N,

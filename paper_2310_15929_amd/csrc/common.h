@@ -16,7 +16,7 @@ struct esparse_ctx {
   std::string err;
   // (sparse, dtype, M, N, K) -> variant chosen by esparse_tune
   std::map<std::tuple<int, int, int, long long, long long, long long>, int> tuned;  // (products per launch, mode, dtype, M, N, K) -> variant
-  std::map<std::tuple<int, int, long long, long long, long long>, int> defaults;  // built-in choices looked up before (count, negative for a group call, mode, M, N, K)
+  std::map<std::tuple<int, int, long long, long long, long long>, int> defaults;  // built-in choices looked up before (count, negative for a group call, + 16 for a half; mode, M, N, K)
   // device blocks that the offline stages have used and will use again (class Scratch), oldest first, and a pinned host
   // block for what they send and receive; given back by esparse_destroy
   struct Block {
@@ -160,8 +160,9 @@ int esp_read_rate_device(esparse_ctx* ctx, size_t bytes, double* gbs);
 int esp_num_variants();
 const char* esp_variant_name(int v);
 bool esp_variant_applicable(int v, long long M, long long N, long long K, int sparse);
-// count: products of one call; grouped: a group call (a decode kernel up to 32 tokens)
+// count: products of one call; grouped: a group call (a decode kernel up to 32 tokens); staged: for one of the halves of a product
 int esp_default_variant(long long M, long long N, long long K, int sparse, int count, bool grouped);
+int esp_default_variant_staged(long long M, long long N, long long K, int sparse, int count, bool grouped);
 int esp_default_variant_without_partials(long long M, long long N, long long K, int sparse);
 size_t esp_workspace_bytes(long long M, long long N, long long K);
 size_t esp_variant_workspace_bytes(int variant, long long M, long long N, long long K);

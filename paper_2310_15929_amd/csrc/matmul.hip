@@ -47,6 +47,7 @@ static hipError_t raise_dynamic_lds(std::atomic<unsigned long long>& done, int d
 // fp32 partial tiles the workspace has room for: 16 K splits up to 128 tokens, 4 up to 512, none beyond
 static inline int esp_split_capacity(long long M) { return M <= 128 ? MAX_SPLIT : (M <= 512 ? 4 : 1); }
 #define ESP_MAX_GROUP 4  // products of one shape that may share a launch
+#define FOLD_ROWS_LDS (158 * 1024)     // of the decode kernels that keep the tokens' rows
 
 // ------------------------------------------------------------------------------------------------
 // device-only intrinsics (hipcc also parses kernels in its host pass, where these do not exist)
@@ -523,19 +524,66 @@ __global__ void __launch_bounds__(256) k_mm_wave_tile(const uint4* __restrict__ 
 // the result does not depend on timing and no global synchronisation is needed.
 // grid = ceil(row tiles / RT), block = 64 * NW.
 // ------------------------------------------------------------------------------------------------
-// FOLD (few tokens and channels, MT = 1): there is no staged copy and no staging launch; the workgroup applies the channel
+// lanes 8 i .. 8 i + 7 of a wave hold one channel each, d its 8 tokens; afterwards one token each, its 8 channels in the lanes' order.
+// Pairs of 16-bit values across neighbouring lanes, then two steps of an exchange of 32-bit values.
+__device__ __forceinline__ uint4 transpose_8_lanes(uint4 d, unsigned lane) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const uint32_t sel = (lane & 1u) ? 0x07060302u : 0x01000504u;
+  auto pair = [&](uint32_t v) { return byte_perm(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xb1, 0xf, 0xf, true), sel); };
+  const uint32_t f0 = pair(d.x), f1 = pair(d.y), f2 = pair(d.z), f3 = pair(d.w);
+  const bool odd = (lane & 2u) != 0;
+  const uint32_t r0 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(odd ? f0 : f1), 0x4e, 0xf, 0xf, true);
+  const uint32_t r1 = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(odd ? f2 : f3), 0x4e, 0xf, 0xf, true);
+  const int g0 = (int)(odd ? r0 : f0), g1 = (int)(odd ? f1 : r0), g2 = (int)(odd ? r1 : f2), g3 = (int)(odd ? f3 : r1);
+  uint4 e;  // lanes 4 .. 7 and 12 .. 15 take from four lanes below, the others from four above
+  e.x = (uint32_t)__builtin_amdgcn_update_dpp(g0, g2, 0x114, 0xf, 0xa, false);
+  e.y = (uint32_t)__builtin_amdgcn_update_dpp(g1, g3, 0x114, 0xf, 0xa, false);
+  e.z = (uint32_t)__builtin_amdgcn_update_dpp(g2, g0, 0x104, 0xf, 0x5, false);
+  e.w = (uint32_t)__builtin_amdgcn_update_dpp(g3, g1, 0x104, 0xf, 0x5, false);
+  return e;
+#else
+  (void)lane;
+  return d;
+#endif
+}
+// in lanes 0 .. 7 of each 16 the value of the lane eight above
+__device__ __forceinline__ uint4 upper_8_lanes(uint4 d) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  auto up = [](uint32_t v) { return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x108, 0xf, 0xf, true); };
+  return uint4{up(d.x), up(d.y), up(d.z), up(d.w)};
+#else
+  return d;
+#endif
+}
+
+// place of a channel among the rows of the activations in LDS (FOLD_ROWS): a bijection within every 8 channels, so that the 16-byte rows that one
+// lane writes for 8 channels and its neighbours for the next 8 do not all start in the same bank
+__device__ __forceinline__ unsigned fold_place(unsigned channel) { return channel ^ ((channel >> 3) & 7u); }
+
+// How a decode kernel gets its activations: from the staged copy; from a gathered copy in LDS (one or two tokens, few channels); from the
+// rows of up to 8 (16) tokens in LDS, transposed, gathered as they are used
+enum { FOLD_NONE = 0, FOLD_GATHER = 1, FOLD_ROWS8 = 2, FOLD_ROWS16 = 3 };
+
+// FOLD_GATHER (few tokens and channels, MT = 1): there is no staged copy and no staging launch; the workgroup applies the channel
 // re-ordering of Section 3.3 itself: it gathers X[t, theta[p]] for all p into LDS (2 Kp bytes per token, the layout of the
 // compact copy), and the waves read their activation operands from there.
-template <int DT, int SPARSE, int MT, int RT, int NW, int IDXM, bool FOLD = false>
+// FOLD_ROWS8 / 16 (3 to 16 tokens, MT = 1): the workgroup copies the tokens' rows into LDS, coalesced, as 16 bytes of 8 tokens per channel, and the
+// positions' places beside them (18 or 34 bytes per channel); a wave reads the channels of its step through theta, one per lane, and
+// turns them into operands of one token per lane with 22 instructions (transpose_8_lanes), while its weights are on their way.  What is
+// left in the padding lanes only reaches outputs that are not stored.
+template <int DT, int SPARSE, int MT, int RT, int NW, int IDXM, int FOLD = FOLD_NONE>
 __global__ void __launch_bounds__(NW * 64) k_mm_ksplit(KsplitArgs args, long long M, long long N, long long Mp, long long Np,
                                                         long long Kp, int mc) {
-  static_assert(!FOLD || MT == 1, "the fold exists for the compact activation layout only");
+  static_assert(FOLD == FOLD_NONE || MT == 1, "the fold exists for one token tile only");
+  constexpr bool ROWS = FOLD >= FOLD_ROWS8;
   const uint4* __restrict__ A = args.A[blockIdx.y];
   const uint16_t* __restrict__ meta16 = args.meta16[blockIdx.y];
   const uint4* __restrict__ Xf = args.Xf[blockIdx.y];
   uint16_t* __restrict__ Y = args.Y[blockIdx.y];
   extern __shared__ floatx4_t s_red[];  // [NW][RT * MT][64]; FOLD: followed by the gathered activations [Kp / 8][mc]
-  uint4* s_x = reinterpret_cast<uint4*>(s_red + NW * RT * MT * 64);
+  uint4* s_x = reinterpret_cast<uint4*>(s_red + (ROWS ? 0 : NW * RT * MT * 64));  // ROWS: the partial tiles take their place at the end
+  const unsigned s_rows = (unsigned)args.K + 8u;                                  // ROWS: 16-byte rows of 8 tokens
+  uint16_t* s_pos = reinterpret_cast<uint16_t*>(s_x + (FOLD == FOLD_ROWS16 ? 2u : 1u) * s_rows);
   __shared__ uint4 s_lut[SPARSE == 2 ? LUT48_CODES : 1];  // 4:8: the byte-permute selectors of every pattern code
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const long long nrt = Np / 16, ntt = Mp / 16, nks = Kp / 64;
@@ -543,7 +591,68 @@ __global__ void __launch_bounds__(NW * 64) k_mm_ksplit(KsplitArgs args, long lon
   long long rts[RT];
 #pragma unroll
   for (int i = 0; i < RT; i++) rts[i] = (rt0 + i < nrt) ? rt0 + i : nrt - 1;
-  if (FOLD) {
+  if constexpr (ROWS) {
+    const uint16_t* __restrict__ X = args.X[blockIdx.y];
+    const int32_t* __restrict__ perm = args.perm[blockIdx.y];
+    const unsigned K = (unsigned)args.K;
+    constexpr unsigned PLANES = FOLD == FOLD_ROWS16 ? 2 : 1;
+    if (tid < (int)PLANES) s_x[tid * s_rows + fold_place(K)] = uint4{0u, 0u, 0u, 0u};  // for positions past K
+    auto copy = [&](auto eights) {
+      constexpr bool E8 = decltype(eights)::value;  // 8 channels at a time; else 4 (rows of a multiple of 8 bytes)
+      constexpr unsigned CH = E8 ? 8 : 4;
+      const unsigned units = K / CH;
+      uint32_t r[8][CH / 2];
+      auto load = [&](unsigned e) {
+        const unsigned pl = PLANES == 2 && e >= units ? 1u : 0u, u = e - pl * units;
+#pragma unroll
+        for (int t = 0; t < 8; t++) {
+          const uint16_t* src = X + (long long)(8 * pl + t < M ? 8 * pl + t : 0) * K + u * CH;  // (a token too many: the first one again, not used)
+          if constexpr (E8) {
+            const uint4 v = *reinterpret_cast<const uint4*>(src);
+            r[t][0] = v.x, r[t][1] = v.y, r[t][2] = v.z, r[t][3] = v.w;
+          } else {
+            const uint2 v = *reinterpret_cast<const uint2*>(src);
+            r[t][0] = v.x, r[t][1] = v.y;
+          }
+        }
+      };
+      // the first rows and all positions on their way together: one trip to memory, not one after the other
+      unsigned e = tid;
+      if (e < units * PLANES) load(e);
+      constexpr unsigned POS = 2;  // times 4 positions per thread and pass
+      for (unsigned p = tid * 4; p < (unsigned)Kp; p += NW * 64 * 4 * POS) {
+        int4 c[POS];
+#pragma unroll
+        for (unsigned q = 0; q < POS; q++) {
+          const unsigned at = p + q * NW * 64 * 4;  // four positions are all below K or none
+          c[q] = int4{(int)at, (int)at + 1, (int)at + 2, (int)at + 3};
+          if (at >= K) c[q] = int4{(int)K, (int)K, (int)K, (int)K};
+          else if (perm) c[q] = *reinterpret_cast<const int4*>(perm + at);
+        }
+#pragma unroll
+        for (unsigned q = 0; q < POS; q++) {
+          const unsigned at = p + q * NW * 64 * 4;
+          if (at < (unsigned)Kp)
+            *reinterpret_cast<uint2*>(s_pos + at) = uint2{fold_place((unsigned)c[q].x) | (fold_place((unsigned)c[q].y) << 16),
+                                                          fold_place((unsigned)c[q].z) | (fold_place((unsigned)c[q].w) << 16)};
+        }
+      }
+      while (e < units * PLANES) {
+        const unsigned pl = PLANES == 2 && e >= units ? 1u : 0u, u = e - pl * units;
+#pragma unroll
+        for (unsigned ch = 0; ch < CH; ch++) {
+          const uint32_t sel = (ch & 1) ? 0x07060302u : 0x05040100u;
+          s_x[pl * s_rows + fold_place(u * CH + ch)] = uint4{byte_perm(r[1][ch / 2], r[0][ch / 2], sel), byte_perm(r[3][ch / 2], r[2][ch / 2], sel),
+                                                             byte_perm(r[5][ch / 2], r[4][ch / 2], sel), byte_perm(r[7][ch / 2], r[6][ch / 2], sel)};
+        }
+        e += NW * 64;
+        if (e < units * PLANES) load(e);
+      }
+    };
+    if ((K & 7u) == 0) copy(std::true_type{});
+    else copy(std::false_type{});
+    __syncthreads();
+  } else if (FOLD == FOLD_GATHER) {
     const uint16_t* __restrict__ X = args.X[blockIdx.y];
     const int32_t* __restrict__ perm = args.perm[blockIdx.y];
     const long long K = args.K;
@@ -576,6 +685,20 @@ __global__ void __launch_bounds__(NW * 64) k_mm_ksplit(KsplitArgs args, long lon
     fill_expand_lut<1>(s_lut, tid);
     __syncthreads();
   }
+
+  // the operands of the two halves of step k, from the rows
+  auto rows_operands = [&](long long k, uint4& b0, uint4& b1) {
+    const unsigned c = lane & 15u, g = lane >> 4, at = 64u * (unsigned)k + 8u * g + (c & 7u);
+    if constexpr (FOLD == FOLD_ROWS8) {  // lanes 8 .. 15 read the second half and hand it down
+      const uint4 v = transpose_8_lanes(s_x[s_pos[at + 32u * (c >> 3)]], (unsigned)lane);
+      b0 = v;
+      b1 = upper_8_lanes(v);
+    } else {
+      const uint4* plane = s_x + (c >> 3) * s_rows;
+      b0 = transpose_8_lanes(plane[s_pos[at]], (unsigned)lane);
+      b1 = transpose_8_lanes(plane[s_pos[at + 32u]], (unsigned)lane);
+    }
+  };
 
   floatx4_t acc[RT][MT];
 #pragma unroll
@@ -610,7 +733,7 @@ __global__ void __launch_bounds__(NW * 64) k_mm_ksplit(KsplitArgs args, long lon
         iw[1][i] = w.y;
       }
       uint4 a[4][RT], b0[4][MT], b1[4][MT];
-      if (MT == 1 && mc) {
+      if (MT == 1 && mc && !ROWS) {
         // the padding lanes hold zeros; set before the loads (and opaque to the compiler), so that the loads of the
         // live lanes land on top of them: a zero moved in after the load would have to wait for the load
 #pragma unroll
@@ -627,14 +750,17 @@ __global__ void __launch_bounds__(NW * 64) k_mm_ksplit(KsplitArgs args, long lon
 #pragma unroll
         for (int i = 0; i < RT; i++) a[u][i] = load_stream_16(A + (rts[i] * nks + k) * 64 + lane);
       }
-      if (MT == 1 && mc) {
+      if constexpr (ROWS) {
+#pragma unroll
+        for (int u = 0; u < 4; u++) rows_operands(ks + u, b0[u][0], b1[u][0]);
+      } else if (MT == 1 && mc) {
         const int c = lane & 15, g = lane >> 4;
         const uint4* Xc = Xf + Kp * 2;  // the compact copy behind the 16 x Kp fragment-major one
         if (c < mc) {
 #pragma unroll
           for (int u = 0; u < 4; u++) {
             const long long k = ks + u;
-            if (FOLD) {
+            if (FOLD == FOLD_GATHER) {
               b0[u][0] = s_x[((2 * k) * 4 + g) * mc + c];
               b1[u][0] = s_x[((2 * k + 1) * 4 + g) * mc + c];
             } else {
@@ -700,13 +826,15 @@ __global__ void __launch_bounds__(NW * 64) k_mm_ksplit(KsplitArgs args, long lon
           a2[u][i] = load_stream_16(A + (rts[i] * (2 * nks) + 2 * kk[u] + 1) * 64 + lane);
         }
       }
-      if (MT == 1 && mc) {
+      if constexpr (ROWS) {
+        rows_operands(kk[u], b0[u][0], b1[u][0]);
+      } else if (MT == 1 && mc) {
         // compact activations (at most 16 tokens): lane (g, c) holds token c's channels 8 g .. 8 g + 7 of each half step
         const uint4 zero = {0u, 0u, 0u, 0u};
         const int c = lane & 15, g = lane >> 4;
         const bool live = c < mc;
         const uint4* Xc = Xf + Kp * 2;  // behind the 16 x Kp fragment-major copy
-        if (FOLD) {
+        if (FOLD == FOLD_GATHER) {
           b0[u][0] = live ? s_x[((2 * kk[u]) * 4 + g) * mc + c] : zero;
           b1[u][0] = live ? s_x[((2 * kk[u] + 1) * 4 + g) * mc + c] : zero;
         } else {
@@ -748,6 +876,7 @@ __global__ void __launch_bounds__(NW * 64) k_mm_ksplit(KsplitArgs args, long lon
     }
   }
 
+  if (ROWS) __syncthreads();  // every wave is done with the rows
 #pragma unroll
   for (int i = 0; i < RT; i++)
 #pragma unroll
@@ -1970,6 +2099,47 @@ static constexpr Cost kCost48[] = {
     {"tile48_w8_t128_splitk", 0.f, 0.929f, 7.99f, 1.69e-08f, 1.78e-07f, 4.34f, 0.0431f},
 };
 
+// Decode kernels that keep the tokens' rows (FOLD_ROWS8 / 16: 3 to 16 tokens, both phases in one call): `tokens` counts the bytes of rows and places that one CU
+// copies into LDS, over all its workgroups.  Fitted to the calls of 65 shapes from 512 x 512 to 22016 x 4096 with 4, 8 and 16 tokens
+// (mean error 5 %); a staged kernel takes STAGE_US more than its row above says.
+static constexpr Cost kFold24[] = {
+    {"ksplit_w16_r1", 2.94f, 2.25e-05f, 1.36e-05f, 3.8e-08f, 0.f, 0.f, 0.569f},
+    {"ksplit_w16_r1_q", 3.09f, 0.f, 2.23e-05f, 6.88e-08f, 0.f, 0.f, 0.668f},
+    {"ksplit_w16_r2", 3.59f, 1.26e-05f, 2.27e-05f, 5.5e-08f, 0.f, 0.f, 0.269f},
+    {"ksplit_w16_r3", 3.72f, 1.45e-05f, 2.45e-05f, 4.81e-08f, 0.f, 0.f, 0.481f},
+    {"ksplit_w8_r1", 3.55f, 4.35e-05f, 4.36e-06f, 0.f, 0.f, 0.f, 0.f},
+    {"ksplit_w8_r1_q", 3.56f, 5.28e-07f, 2.88e-05f, 4.84e-08f, 0.f, 0.f, 0.f},
+    {"ksplit_w8_r2", 3.55f, 2.9e-05f, 2.08e-05f, 0.f, 0.f, 0.f, 0.f},
+    {"ksplit_w8_r2_q", 4.2f, 2.11e-05f, 1.81e-06f, 6.04e-08f, 0.f, 0.f, 0.f},
+    {"ksplit_w8_r3", 4.24f, 2.28e-05f, 1.6e-05f, 1.7e-08f, 0.f, 0.f, 0.f},
+    {"ksplit_w8_r4", 4.22f, 2.76e-05f, 0.f, 1.97e-08f, 0.f, 0.f, 0.f},
+    {"ksplit_w8_r6", 3.84f, 2.26e-05f, 1.78e-05f, 4.13e-08f, 0.f, 0.f, 0.f},
+};
+static constexpr Cost kFoldDense[] = {
+    {"ksplit_w16_r1", 2.95f, 1.43e-05f, 1.73e-05f, 6.37e-08f, 0.f, 0.f, 0.486f},
+    {"ksplit_w16_r2", 3.5f, 1.87e-05f, 1.43e-05f, 5.66e-08f, 0.f, 0.f, 0.127f},
+    {"ksplit_w16_r3", 3.77f, 1.82e-05f, 1.26e-05f, 6.25e-08f, 0.f, 0.f, 0.f},
+    {"ksplit_w8_r1", 3.44f, 4.02e-05f, 4.04e-06f, 0.f, 0.f, 0.f, 0.f},
+    {"ksplit_w8_r2", 3.38f, 3.14e-05f, 7.34e-06f, 1.72e-08f, 0.f, 0.f, 0.f},
+    {"ksplit_w8_r3", 3.6f, 2.93e-05f, 8.77e-06f, 2.34e-08f, 0.f, 0.f, 0.f},
+    {"ksplit_w8_r4", 4.42f, 3.74e-05f, 0.f, 0.f, 0.f, 0.f, 0.f},
+    {"ksplit_w8_r6", 2.78f, 2.82e-05f, 2.8e-05f, 5.58e-08f, 0.f, 0.f, 0.f},
+};
+static constexpr Cost kFold48[] = {
+    {"ksplit_w16_r1", 3.92f, 1.83e-05f, 2.21e-05f, 1.94e-08f, 0.f, 0.f, 1.51f},
+    {"ksplit_w16_r1_q", 4.46f, 1.3e-05f, 1.07e-05f, 5.58e-08f, 0.f, 0.f, 1.63f},
+    {"ksplit_w16_r2", 3.29f, 1.87e-05f, 9.7e-06f, 5.53e-08f, 0.f, 0.f, 2.7f},
+    {"ksplit_w16_r3", 1.91f, 2.01e-05f, 1.19e-05f, 4.82e-08f, 0.f, 0.f, 4.12f},
+    {"ksplit_w8_r1", 5.35f, 4e-05f, 1.45e-05f, 0.f, 0.f, 0.f, 0.192f},
+    {"ksplit_w8_r1_q", 5.71f, 2.72e-05f, 1.19e-05f, 2.81e-08f, 0.f, 0.f, 0.219f},
+    {"ksplit_w8_r2", 5.66f, 2.84e-05f, 2.11e-05f, 0.f, 0.f, 0.f, 0.f},
+    {"ksplit_w8_r2_q", 5.73f, 2.24e-05f, 9.07e-06f, 3.84e-08f, 0.f, 0.f, 1.f},
+    {"ksplit_w8_r3", 5.92f, 2.59e-05f, 1.23e-05f, 2.23e-08f, 0.f, 0.f, 0.f},
+    {"ksplit_w8_r4", 5.91f, 2.54e-05f, 1.32e-05f, 2.2e-08f, 0.f, 0.f, 0.f},
+    {"ksplit_w8_r6", 6.06f, 2.33e-05f, 5.35e-06f, 3.8e-08f, 0.f, 0.f, 0.f},
+};
+#define STAGE_US 2.9  // a staging launch of up to 16 tokens and the gap behind it
+
 // number of K splits of a tile variant and their stages (32 channels each where v.half, else 64)
 static int tile_splits(const Variant& v, long long M, long long n_tiles, long long stages, long long* per_split) {
   int nsplit = 1;
@@ -2021,11 +2191,13 @@ static int aligned_stream(long long nrt, long long nks) {
 }
 
 static int compact_tokens(long long M);
+static size_t fold_rows_bytes(long long M, long long K, long long Kp);
+static int ksplit_fold(const Variant& v, long long M, long long Np, long long K, long long Kp, int sparse, int count);
 
 static bool is_decode_kernel(const Variant& v) { return v.kind == KIND_KSPLIT && v.split_mode == 0; }
 
-// estimated time (us) of `count` products of one shape in one launch (decode kernels) or of one product
-static double estimate(const Cost& c, const Variant& v, long long M, long long N, long long K, int sparse, int count) {
+// estimated time (us) of `count` products of one shape in one launch (decode kernels) or of one product; rows: of a kernel that keeps the tokens' rows
+static double estimate(const Cost& c, const Variant& v, long long M, long long N, long long K, int sparse, int count, bool rows_kept = false) {
   const long long nrt = (N + 15) / 16, nks = esp_round_up(K, 256) / 64, Mt = (M + 15) / 16;
   const double wb = sparse ? 1.125 : 2.0, step_row = 64.0 * 16 * wb;  // bytes of a row tile's step
   const double memory = (double)count * nrt * 16 * nks * 64 * wb, out = 8.0 * M * nrt * 16;  // out: one fp32 tile of Y, both ways
@@ -2036,7 +2208,7 @@ static double estimate(const Cost& c, const Variant& v, long long M, long long N
     const long long wgs = (nrt + v.rt - 1) / v.rt * ns * count;
     const double per = (double)((wgs + 255) / 256), steps = (double)nks / ns;
     weights = per * steps * step_row * v.rt;
-    tokens = per * steps * 64 * (M <= 16 ? 2 * compact_tokens(M) : 32 * mt);
+    tokens = rows_kept ? per * fold_rows_bytes(M, K, nks * 64) : per * steps * 64 * (M <= 16 ? 2 * compact_tokens(M) : 32 * mt);
     rounds = per;
     if (ns > 1) pieces = ns;
   } else if (v.kind == KIND_STREAM) {
@@ -2084,16 +2256,18 @@ static constexpr CostRows with_variants(const Cost (&table)[N]) {
   return out;
 }
 static constexpr CostRows kRows24 = with_variants(kCost24), kRowsDense = with_variants(kCostDense), kRows48 = with_variants(kCost48);
+static constexpr CostRows kFoldRows24 = with_variants(kFold24), kFoldRowsDense = with_variants(kFoldDense), kFoldRows48 = with_variants(kFold48);
 
 // grouped: for the group calls of the sparse product, whose two halves need a decode kernel; up to 32 tokens they get one whatever the
-// count
-static int pick_by_cost(long long M, long long N, long long K, int sparse, int count, bool grouped, bool partials) {
+// count.
+static const CostRow* pick_by_cost(long long M, long long N, long long K, int sparse, int count, bool grouped, bool partials, double* best_time) {
   constexpr int kDecode = variant_index("ksplit_w8_r1"), kTile = variant_index("tile_w8_r128_t128"), kTile48 = variant_index("tile48_w8_r128_t256");
   static_assert(kDecode >= 0 && kTile >= 0 && kTile48 >= 0, "kernels that take every shape of their token counts");
+  static constexpr CostRow kFallback[3] = {{{}, kVariants[kDecode], kDecode}, {{}, kVariants[kTile], kTile}, {{}, kVariants[kTile48], kTile48}};
   const CostRows& rows = sparse == 2 ? kRows48 : (sparse ? kRows24 : kRowsDense);
   const int stream_waves = M <= 128 ? aligned_stream((N + 15) / 16, esp_round_up(K, 256) / 64) : 0;
-  int best = M <= 64 ? kDecode : (sparse == 2 ? kTile48 : kTile);
-  double best_t = 1e30;
+  const CostRow* best = &kFallback[M <= 64 ? 0 : (sparse == 2 ? 2 : 1)];
+  *best_time = 1e30;
   for (int i = 0; i < rows.n; i++) {
     const CostRow& r = rows.row[i];
     if (!applicable(r.v, M, sparse)) continue;
@@ -2104,6 +2278,33 @@ static int pick_by_cost(long long M, long long N, long long K, int sparse, int c
     if (grouped && !shared && M <= 32) continue;  // up to 32 tokens a group is one launch, and its halves exist
     double t = estimate(r.cost, r.v, M, N, K, sparse, shared ? count : 1);
     if (count > 1 && !shared) t = t * count + 4.0 * (count - 1);  // one after the other, each with its staging launch
+    if (t < *best_time) {
+      *best_time = t;
+      best = &r;
+    }
+  }
+  return best;
+}
+
+// Both phases in one call, 3 to 16 tokens: where the choice for the staged product is a decode kernel, the fastest of the kernels that keep the
+// tokens' rows may take its place.  Only those that add in the same order (the same waves, the same index layout: a wave then takes
+// the same steps whatever its row tiles are), so that a call gives what its two halves give, bit by bit.  One that would leave a CU
+// more workgroups than a staged choice that gathers for itself as well is not taken (K = 256: estimates of 0.8 for what took 1.1 to 1.4).
+static int pick_whole(long long M, long long N, long long K, int sparse, int count, bool grouped, bool partials) {
+  double t;
+  const CostRow* staged = pick_by_cost(M, N, K, sparse, count, grouped, partials, &t);
+  if (M <= 2 || M > 16 || !is_decode_kernel(staged->v)) return staged->index;
+  const long long Np = esp_round_up(N, 16), Kp = esp_round_up(K, 256);
+  const CostRows& rows = sparse == 2 ? kFoldRows48 : (sparse ? kFoldRows24 : kFoldRowsDense);
+  const bool folds = ksplit_fold(staged->v, M, Np, K, Kp, sparse, count) != FOLD_NONE;
+  auto turns = [&](const Variant& v) { return ((N + 16LL * v.rt - 1) / (16 * v.rt) * count + 255) / 256; };  // workgroups of a CU
+  int best = staged->index;
+  double best_t = folds ? 1e30 : t + STAGE_US;
+  for (int i = 0; i < rows.n; i++) {
+    const CostRow& r = rows.row[i];
+    if (r.v.nw != staged->v.nw || r.v.quads != staged->v.quads || !applicable(r.v, M, sparse)) continue;
+    if (ksplit_fold(r.v, M, Np, K, Kp, sparse, count) < FOLD_ROWS8 || (folds && turns(r.v) > turns(staged->v))) continue;
+    t = estimate(r.cost, r.v, M, N, K, sparse, count, true);
     if (t < best_t) {
       best_t = t;
       best = r.index;
@@ -2113,13 +2314,18 @@ static int pick_by_cost(long long M, long long N, long long K, int sparse, int c
 }
 
 int esp_default_variant(long long M, long long N, long long K, int sparse, int count, bool grouped) {
-  return pick_by_cost(M, N, K, sparse, count, grouped, true);
+  return pick_whole(M, N, K, sparse, count, grouped, true);
+}
+
+int esp_default_variant_staged(long long M, long long N, long long K, int sparse, int count, bool grouped) {
+  double t;
+  return pick_by_cost(M, N, K, sparse, count, grouped, true, &t)->index;
 }
 
 // the built-in choice among the variants that keep no fp32 partial tiles in the workspace (for callers whose scratch
 // is too small for them)
 int esp_default_variant_without_partials(long long M, long long N, long long K, int sparse) {
-  return pick_by_cost(M, N, K, sparse, 1, false, false);
+  return pick_whole(M, N, K, sparse, 1, false, false);
 }
 
 // tokens of the compact copy of the staged activations (0: none), written when there are at most 16 tokens
@@ -2186,20 +2392,46 @@ static void launch_wave_tile(const Variant& v, dim3 grid, hipStream_t st, const 
 #undef LAUNCH
 }
 
-// Whether the decode kernel gathers the activations through theta itself (no staged copy, no staging launch): at most 16
-// tokens, a variant that keeps K inside the workgroup, the gathered copy (2 Kp bytes per token) fits beside the reduction
-// buffer in the 64 KiB of LDS a launch may ask for without further ado - and the gather is cheap enough: every workgroup
+// How the decode kernel gets its activations (FOLD_*; phases in one call).
+// One or two tokens: each workgroup gathers them through theta (no staged copy, no staging launch) if the gathered copy (2 Kp bytes per token)
+// fits beside the reduction buffer in the 64 KiB of LDS a launch may ask for without further ado - and the gather is cheap enough: every workgroup
 // repeats it, so it pays while workgroups x channels x tokens stays small (4096 x 4096, one token: 7.0 us against 6.5 + 2.1
-// for the staging launch; 36864 x 9216, 2304 workgroups: 77 us against 58 + 2.3, hence the limits; 16 tokens x 512
-// channels, 32 workgroups: a call 14.6 -> 11.5 us, one launch of 6 us instead of two of 3.5 and 3.9 and the gap).  Beyond two
-// tokens at most 9216 channels x tokens: over 11 decode kernels and 512 to 16384 rows the launches take 0.69 to 1.02 times those of
-// the staged form there, and up to 1.07 times at 10240 (8 tokens, 4096 x 1280, ksplit_w8_r1: 6.5 -> 6.9 us).
-static bool ksplit_folds(const Variant& v, long long M, long long Np, long long Kp) {
-  if (v.kind != KIND_KSPLIT || v.split_mode != 0 || M > 16) return false;
+// for the staging launch; 36864 x 9216, 2304 workgroups: 77 us against 58 + 2.3, hence the limits).
+//
+// 3 to 16 tokens: the workgroup keeps the tokens' rows (FOLD_ROWS8 / 16) where they fit the LDS and the copy, which every workgroup repeats, is
+// cheaper than the staging launch.  Call times with the rows in the kernel over those with the staging launch, 24 shapes from 512 x 512 to
+// 22016 x 4096 with 4, 8 and 16 tokens, 2:4, 4:8 and dense (KB: of rows in LDS; per: workgroups of a CU, one after the other):
+//   16 waves, per 1: 0.58 - 0.97 at any size; 72 KB, per 2 / 3 / 4 / 6: 0.94, 0.92, 0.86, 0.93; 144 KB, per 2: 1.05 and more
+//   8 waves copy half as fast.  18 and 36 KB, per up to 4: 0.74 - 0.96 (at 3 and more row tiles some 1.1, but 1.3 with the staging launch)
+//   72 KB, per 1: 0.77 - 0.96 with one, two and six row tiles, but 1.04 - 1.24 with three and four (of 13824 x 4096, 9216 x 4096); per 2: 0.80 -
+//   0.90 with two row tiles and more, 1.1 with one; per 3: 1.04 and more.  144 KB, per 1: 0.9 for one row tile with quads, 0.96 for six, about
+//   1.05 for the others, which end near 100 KB.  Dense weights, 63 and 72 KB: 1.02 - 1.15.
+// Up to 4096 channels x tokens the gathered copy is no slower from two row tiles on (dense: from three, up to 3072), by up to 0.9 us of 7.
+// Over 936 shapes from 256 x 256 to 32000 x 4096 with 3 to 16 tokens the call takes 0.89 of its time with the staging launch and the gather of
+// up to 9216 channels x tokens; the slowest 1.03.
+// 16 x 512 x 512: 11.5 -> 3.9 us of launches, 8 x 4096 x 4096: 9.4 -> 7.3, 8 x 11008 x 4096: 13.3 -> 12.1.
+static size_t fold_rows_bytes(long long M, long long K, long long Kp) { return (size_t)(M > 8 ? 2 : 1) * (K + 8) * 16 + (size_t)Kp * 2; }
+
+static int ksplit_fold(const Variant& v, long long M, long long Np, long long K, long long Kp, int sparse, int count) {
+  if (v.kind != KIND_KSPLIT || v.split_mode != 0 || M > 16) return FOLD_NONE;
   const long long mc = compact_tokens(M), groups = (Np / 16 + v.rt - 1) / v.rt;
-  if (Kp * mc > (M > 2 ? 9216 : 10240) || groups * Kp * mc > 3000000) return false;
-  const size_t red = (size_t)v.nw * v.rt * 64 * 16, gathered = (size_t)2 * Kp * mc;
-  return red + gathered <= 64 * 1024;
+  const size_t red = (size_t)v.nw * v.rt * 64 * 16;
+  if (M > 2) {
+    const long long bytes = (long long)fold_rows_bytes(M, K, Kp), per = (groups * count + 255) / 256;
+    if (v.rt >= (sparse ? 2 : 3) && Kp * mc <= (sparse ? 4096 : 3072) && groups * Kp * mc <= 3000000 && red + (size_t)2 * Kp * mc <= 64 * 1024) return FOLD_GATHER;
+    if (std::max((long long)red, bytes) > FOLD_ROWS_LDS) return FOLD_NONE;
+    const long long kb = bytes / 1024;
+    bool pays;
+    if (v.nw == 16) pays = per == 1 || (kb <= 76 && per <= 6);
+    else if (kb <= 40) pays = per <= 4;
+    else if (!sparse) pays = false;
+    else if (kb <= 76) pays = per == 1 ? v.rt <= 2 || v.rt == 6 : per == 2 && v.rt >= 2;
+    else pays = per == 1 && (v.rt == 6 || (v.rt == 1 && (v.quads || kb <= 112)) || (v.rt == 2 && kb <= (v.quads ? 112 : 92)));
+    if (!pays) return FOLD_NONE;
+    return M > 8 ? FOLD_ROWS16 : FOLD_ROWS8;
+  }
+  if (Kp * mc > 10240 || groups * Kp * mc > 3000000) return FOLD_NONE;
+  return red + (size_t)2 * Kp * mc <= 64 * 1024 ? FOLD_GATHER : FOLD_NONE;
 }
 
 // A kernel that gathers for itself reads X while others of its workgroups write Y: outputs that overlap an input (a layer
@@ -2209,26 +2441,63 @@ static bool overlap(const void* X, const void* Y, long long M, long long N, long
   return x < y + (uintptr_t)M * N * 2 && y < x + (uintptr_t)M * K * 2;
 }
 
+// launches with up to 160 KiB of dynamic LDS
+template <int DT, int SPARSE, int RT, int NW, int IDXM, int FOLD>
+static hipError_t launch_ksplit_rows(int device, dim3 grid, hipStream_t st, size_t smem, const KsplitArgs& args, long long M, long long N, long long Mp, long long Np,
+                                     long long Kp, int mc) {
+  static std::atomic<unsigned long long> raised{0};
+  if (smem > 64 * 1024) {
+    const hipError_t e = raise_dynamic_lds(raised, device, &k_mm_ksplit<DT, SPARSE, 1, RT, NW, IDXM, FOLD>, FOLD_ROWS_LDS);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL((k_mm_ksplit<DT, SPARSE, 1, RT, NW, IDXM, FOLD>), grid, dim3(NW * 64), smem, st, args, M, N, Mp, Np, Kp, mc);
+  return hipGetLastError();
+}
+
 template <int DT, int SPARSE, int MT>
-static void launch_ksplit(const Variant& v, hipStream_t st, KsplitArgs args, int count, long long M, long long N, long long Mp,
-                          long long Np, long long Kp, int mc, int nsplit, bool fold) {
+static hipError_t launch_ksplit(int device, const Variant& v, hipStream_t st, KsplitArgs args, int count, long long M, long long N, long long Mp,
+                          long long Np, long long Kp, int mc, int nsplit, int fold) {
   const long long nrt = Np / 16, nks = Kp / 64;
   // K split over workgroups: single products only; splits of a multiple of four steps
   const long long sps = nsplit > 1 ? ((nks + nsplit - 1) / nsplit + 3) / 4 * 4 : nks;
   nsplit = (int)((nks + sps - 1) / sps);
   args.sps = (int)sps;
   dim3 grid((unsigned)((nrt + v.rt - 1) / v.rt), (unsigned)count, (unsigned)nsplit);
-  fold = fold && MT == 1 && mc > 0 && nsplit == 1;
-  const size_t smem = (size_t)v.nw * v.rt * MT * 64 * 16 + (fold ? (size_t)2 * Kp * mc : 0);
+  if (!(MT == 1 && mc > 0 && nsplit == 1)) fold = FOLD_NONE;
+  const size_t red = (size_t)v.nw * v.rt * MT * 64 * 16;
+  const size_t smem = fold == FOLD_NONE ? red : (fold == FOLD_GATHER ? red + (size_t)2 * Kp * mc : std::max(red, fold_rows_bytes(M, args.K, Kp)));
+  if constexpr (MT == 1)
+    if (fold >= FOLD_ROWS8) {
+      hipError_t e = hipErrorInvalidValue;
+#define ROWS(R, W)                                                                                                                  \
+  do {                                                                                                                              \
+    constexpr int Q = SPARSE != 0 && ((R == 1) || (W == 8 && (R == 2 || R == 4))) ? 2 : 0;                                          \
+    if (v.quads && fold == FOLD_ROWS8) e = launch_ksplit_rows<DT, SPARSE, R, W, Q, FOLD_ROWS8>(device, grid, st, smem, args, M, N, Mp, Np, Kp, mc);  \
+    else if (v.quads) e = launch_ksplit_rows<DT, SPARSE, R, W, Q, FOLD_ROWS16>(device, grid, st, smem, args, M, N, Mp, Np, Kp, mc); \
+    else if (fold == FOLD_ROWS8) e = launch_ksplit_rows<DT, SPARSE, R, W, 0, FOLD_ROWS8>(device, grid, st, smem, args, M, N, Mp, Np, Kp, mc);        \
+    else e = launch_ksplit_rows<DT, SPARSE, R, W, 0, FOLD_ROWS16>(device, grid, st, smem, args, M, N, Mp, Np, Kp, mc);              \
+  } while (0)
+      if (v.nw == 16 && v.rt == 1) ROWS(1, 16);
+      else if (v.nw == 16 && v.rt == 2) ROWS(2, 16);
+      else if (v.nw == 16 && v.rt == 3) ROWS(3, 16);
+      else if (v.nw == 8 && v.rt == 1) ROWS(1, 8);
+      else if (v.nw == 8 && v.rt == 2) ROWS(2, 8);
+      else if (v.nw == 8 && v.rt == 6) ROWS(6, 8);
+      else if (v.nw == 8 && v.rt == 3) ROWS(3, 8);
+      else if (v.nw == 16 && v.rt == 4) ROWS(4, 16);
+      else ROWS(4, 8);
+#undef ROWS
+      return e;
+    }
   const bool pairs = SPARSE != 0 && MT >= 2 && ((sps / 2) % v.nw) == 0 && nks % sps == 0;
   const bool quads = v.quads != 0;
 #define LAUNCH(R, W)                                                                                                          \
   do {                                                                                                                        \
-    if (MT == 1 && fold && SPARSE != 0 && quads && ((R == 1) || (W == 8 && (R == 2 || R == 4))))                              \
-      hipLaunchKernelGGL((k_mm_ksplit<DT, SPARSE, MT, R, W, (SPARSE != 0 && MT == 1 && ((R == 1) || (W == 8 && (R == 2 || R == 4))) ? 2 : 0), MT == 1>), \
+    if (MT == 1 && fold == FOLD_GATHER && SPARSE != 0 && quads && ((R == 1) || (W == 8 && (R == 2 || R == 4))))                              \
+      hipLaunchKernelGGL((k_mm_ksplit<DT, SPARSE, MT, R, W, (SPARSE != 0 && MT == 1 && ((R == 1) || (W == 8 && (R == 2 || R == 4))) ? 2 : 0), MT == 1 ? FOLD_GATHER : FOLD_NONE>), \
                          grid, dim3(W * 64), smem, st, args, M, N, Mp, Np, Kp, mc);                                           \
-    else if (MT == 1 && fold)                                                                                                 \
-      hipLaunchKernelGGL((k_mm_ksplit<DT, SPARSE, MT, R, W, 0, MT == 1>), grid, dim3(W * 64), smem, st, args, M, N, Mp, Np, Kp, mc); \
+    else if (MT == 1 && fold == FOLD_GATHER)                                                                                                 \
+      hipLaunchKernelGGL((k_mm_ksplit<DT, SPARSE, MT, R, W, 0, MT == 1 ? FOLD_GATHER : FOLD_NONE>), grid, dim3(W * 64), smem, st, args, M, N, Mp, Np, Kp, mc); \
     else if (SPARSE != 0 && MT == 1 && quads && ((R == 1) || (W == 8 && (R == 2 || R == 4))))                                 \
       hipLaunchKernelGGL((k_mm_ksplit<DT, SPARSE, MT, R, W, (SPARSE != 0 && MT == 1 && ((R == 1) || (W == 8 && (R == 2 || R == 4))) ? 2 : 0)>), \
                          grid, dim3(W * 64), smem, st, args, M, N, Mp, Np, Kp, mc);                                           \
@@ -2252,6 +2521,7 @@ static void launch_ksplit(const Variant& v, hipStream_t st, KsplitArgs args, int
     const long long e = M * (Np / 4);
     hipLaunchKernelGGL(k_reduce_splits<DT>, dim3((unsigned)((e + 255) / 256)), dim3(256), 0, st, args.partial, nsplit, M, N, Mp, Np, args.Y[0]);
   }
+  return hipGetLastError();
 }
 
 template <int DT, int SPARSE>
@@ -2438,7 +2708,7 @@ static int stage_activations(esparse_ctx* ctx, const void* X, const int32_t* per
 
 // the decode kernels on `count` products of one shape: members share M, N, K; ka holds their operands
 static int launch_ksplit_any(esparse_ctx* ctx, const Variant& v, int sparse, int dtype, KsplitArgs ka, int count, long long M,
-                             long long N, long long Np, long long Kp, bool fold = false) {
+                             long long N, long long Np, long long Kp, int fold = FOLD_NONE) {
   const int mc = compact_tokens(M);
   // variants with K split over workgroups (tt = splits): single products of at most 64 tokens with room for the partial tiles
   const int nsplit = (v.split_mode == 1 && count == 1 && M <= 64 && ka.partial) ? v.tt : 1;
@@ -2451,11 +2721,12 @@ static int launch_ksplit_any(esparse_ctx* ctx, const Variant& v, int sparse, int
       kc.Xf[i] = ka.Xf[i] + (t0 / 16) * (2 * nks) * 64;
       kc.Y[i] = ka.Y[i] + t0 * N;
     }
+    hipError_t e = hipSuccess;
 #define ESP_KSPLIT(DTv, SPv)                                                          \
   do {                                                                                \
-    if (mcp == 16) launch_ksplit<DTv, SPv, 1>(v, st, kc, count, mcur, N, mcp, Np, Kp, mc, nsplit, fold);  \
-    else if (mcp == 32) launch_ksplit<DTv, SPv, 2>(v, st, kc, count, mcur, N, mcp, Np, Kp, 0, nsplit, false); \
-    else launch_ksplit<DTv, SPv, 4>(v, st, kc, count, mcur, N, mcp, Np, Kp, 0, nsplit, false);            \
+    if (mcp == 16) e = launch_ksplit<DTv, SPv, 1>(ctx->device, v, st, kc, count, mcur, N, mcp, Np, Kp, mc, nsplit, fold);  \
+    else if (mcp == 32) e = launch_ksplit<DTv, SPv, 2>(ctx->device, v, st, kc, count, mcur, N, mcp, Np, Kp, 0, nsplit, FOLD_NONE); \
+    else e = launch_ksplit<DTv, SPv, 4>(ctx->device, v, st, kc, count, mcur, N, mcp, Np, Kp, 0, nsplit, FOLD_NONE);            \
   } while (0)
     if (dtype == ESPARSE_F16) {
       if (sparse == 2) ESP_KSPLIT(ESPARSE_F16, 2);
@@ -2467,7 +2738,7 @@ static int launch_ksplit_any(esparse_ctx* ctx, const Variant& v, int sparse, int
       else ESP_KSPLIT(ESPARSE_BF16, 0);
     }
 #undef ESP_KSPLIT
-    ESP_HIP(ctx, hipGetLastError());
+    ESP_HIP(ctx, e);
   }
   return ESPARSE_OK;
 }
@@ -2487,8 +2758,8 @@ int esp_matmul_device(esparse_ctx* ctx, int sparse, const void* X, long long M, 
   const long long nrt = Np / 16, ntt = Mp / 16, nks = Kp / 64;
   int rc;
   // few tokens through a decode kernel, both halves in one call: the kernel gathers through theta itself
-  const bool fold = phases == (ESP_PHASE_STAGE | ESP_PHASE_MULTIPLY) && ksplit_folds(v, M, Np, Kp) && !overlap(X, Yv, M, N, K);
-  if ((phases & ESP_PHASE_STAGE) && !fold && (rc = stage_activations(ctx, X, perm, M, K, Mp, Kp, Xf, compact_tokens(M)))) return rc;
+  const int fold = phases == (ESP_PHASE_STAGE | ESP_PHASE_MULTIPLY) && !overlap(X, Yv, M, N, K) ? ksplit_fold(v, M, Np, K, Kp, sparse, 1) : FOLD_NONE;
+  if ((phases & ESP_PHASE_STAGE) && fold == FOLD_NONE && (rc = stage_activations(ctx, X, perm, M, K, Mp, Kp, Xf, compact_tokens(M)))) return rc;
   if (!(phases & ESP_PHASE_MULTIPLY)) return ESPARSE_OK;
 
   if (v.kind == KIND_KSPLIT) {
@@ -2589,8 +2860,9 @@ int esp_matmul_group_device(esparse_ctx* ctx, int sparse, int count, const void*
   const size_t xbytes = staged_bytes(M, K);
   GatherArgs ga = {};
   KsplitArgs ka = {};
-  bool fold = phases == (ESP_PHASE_STAGE | ESP_PHASE_MULTIPLY) && ksplit_folds(v, M, Np, Kp);
-  for (int i = 0; i < count * count && fold; i++) fold = !overlap(X[i / count], Y[i % count], M, N, K);
+  int fold = phases == (ESP_PHASE_STAGE | ESP_PHASE_MULTIPLY) ? ksplit_fold(v, M, Np, K, Kp, sparse, count) : FOLD_NONE;
+  for (int i = 0; i < count * count && fold; i++)
+    if (overlap(X[i / count], Y[i % count], M, N, K)) fold = FOLD_NONE;
   ka.K = K;
   for (int i = 0; i < count; i++) {
     uint4* Xf = reinterpret_cast<uint4*>(ws + WS_HEADER_BYTES + (size_t)i * xbytes);
@@ -2610,7 +2882,7 @@ int esp_matmul_group_device(esparse_ctx* ctx, int sparse, int count, const void*
       ka.Y[i] = reinterpret_cast<uint16_t*>(Y[i]);
     }
   }
-  if ((phases & ESP_PHASE_STAGE) && !fold) {
+  if ((phases & ESP_PHASE_STAGE) && fold == FOLD_NONE) {
     const int mc = compact_tokens(M);
     const long long units = Mp * Kp / 8, all = units + (long long)mc * (Kp / 8);
     hipLaunchKernelGGL(k_gather_x, dim3((unsigned)((all + 255) / 256), (unsigned)count), dim3(256), 0, ctx->stream, ga, M, K, Kp, units,

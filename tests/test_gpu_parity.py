@@ -583,6 +583,11 @@ def _spmm_case(esp, ctx, M, N, K, dtype, seed, use_perm=True):
     assert orc.rowwise_rel_error(_np(Y), Yref).max() <= TOL[dtype]
 
 
+def _aligned(nbytes):
+    ws = torch.zeros(nbytes + 256, dtype=torch.uint8, device="cuda")
+    return ws[(-ws.data_ptr()) % 256:]
+
+
 def _device_case(ctx, M, N, K, n, m, seed, dtype=torch.float16):
     """A case made on the device (sizes the CPU oracle would take seconds for): X, theta, compressed weights, float64 reference."""
     g = torch.Generator(device="cuda")
@@ -784,6 +789,39 @@ def test_few_tokens_gathered_in_the_kernel_equal_staged(esp, ctx, M, K, n, m):
     for v in decode:
         for Y, comp, perm in zip(ctx.spmm_group([X] * count, comps, perms, variant=v), comps, perms):
             assert torch.equal(Y, ctx.spmm(X, comp, perm, variant=v))
+
+
+# Tokens' rows kept by the decode kernels, at the edges: the first token of the second tile, K that ends within a unit of 8 channels, the
+# longest rows that the LDS holds and the first that it does not, no re-ordering, dense weights.  The sums are the staged product's in
+# the same order: equal bit by bit, for each kernel and for the built-in choice, alone and in a group
+@pytest.mark.parametrize("M,K,n,m", [(3, 4, 2, 4), (9, 1036, 2, 4), (5, 264, 4, 8), (8, 8960, 2, 4), (8, 8964, 2, 4), (3, 8960, 4, 8), (16, 4744, 2, 4),
+                                     (16, 4748, 2, 4), (9, 4744, 4, 8), (8, 8960, 0, 0), (16, 4744, 0, 0), (4, 1036, 0, 0)])
+def test_tokens_rows_kept_by_the_decode_kernels(esp, ctx, M, K, n, m):
+    N = 40
+    decode = [v for v in range(esp.num_variants()) if esp.variant_name(v).startswith("ksplit") and "_k" not in esp.variant_name(v)]
+    if m:
+        X, perm, comp, ref = _device_case(ctx, M, N, K, n, m, 71, torch.bfloat16)
+        ordered = X[:, perm.long()].contiguous()
+        calls = [(lambda v: ctx.spmm(X, comp, perm, variant=v)), (lambda v: ctx.spmm(ordered, comp, None, variant=v)),
+                 (lambda v: ctx.spmm_group([X, ordered], [comp] * 2, [perm, None], variant=v)[1])]
+        ws = _aligned(esp.spmm_workspace(M, N, K))
+        ctx.stage_activations(X, perm, N, ws=ws)
+        staged = lambda v: ctx.spmm_staged(M, comp, ws, torch.empty(M, N, dtype=X.dtype, device="cuda"), variant=v)
+    else:
+        g = torch.Generator(device="cuda").manual_seed(71)
+        X = torch.randn(M, K, device="cuda", generator=g).bfloat16()
+        W = (torch.randn(N, K, device="cuda", generator=g) * K ** -0.5).bfloat16()
+        packed, ref = ctx.dense_pack(W), (X.double() @ W.double().t().contiguous()).cpu().numpy()
+        calls = [(lambda v: ctx.dense_gemm(X, packed, N, variant=v)), (lambda v: ctx.dense_gemm_group([X, X], [packed] * 2, N, variant=v)[1])]
+        ws = _aligned(esp.spmm_workspace(M, N, K))
+        ctx.stage_activations(X, None, N, ws=ws)
+        staged = lambda v: ctx.dense_gemm_staged(M, packed, N, K, ws, torch.empty(M, N, dtype=X.dtype, device="cuda"), variant=v)
+        decode = [v for v in decode if "_q" not in esp.variant_name(v)]
+    for v in [-1] + decode:
+        want = staged(v)
+        assert orc.rowwise_rel_error(_np(want).astype(np.float64), ref).max() <= TOL[torch.bfloat16], v
+        for i, call in enumerate(calls):
+            assert (_bits(call(v)) == _bits(want)).all(), (v, i)
 
 
 # a square layer applied in place, whole and overlapping by some rows, alone and in a group whose members share an input
