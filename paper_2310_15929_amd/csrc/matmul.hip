@@ -1654,6 +1654,170 @@ __global__ void __launch_bounds__(512) k_mm_tile32(const uint4* __restrict__ A, 
 }
 
 // ------------------------------------------------------------------------------------------------
+// variant "pairs" (2:4, prompts of a few hundred tokens: macro tiles of 128 rows x 64 tokens, at most about one per CU).  Such a tile has only 128 clocks of
+// multiplies per stage; with the schedule above it takes as long as the waves' reads of LDS (2 x 4 waves: each weight operand is read
+// by four of them, each activation operand by two) and half the way of a copy from memory.  Here
+//   - the 8 waves are 2 (rows) x 2 (tokens) x 2 (stages of 64 channels): a wave takes every second stage for 64 rows x 32 tokens, which is 0.65
+//     of the LDS reads per multiply; the two sums of an output are added at the end, through LDS;
+//   - the copies run a ring of four pairs of stages ahead (136 of the 160 KiB), a wave reads its operands of the next pair while it
+//     multiplies, and there is one barrier per pair.
+// One pair takes 1100 clocks of a CU, about 840 of them LDS traffic.  Weights cold: 333 tokens x 5003 x 3020 22.3 -> 16.9 us (240 macro tiles, ragged
+// rows of Y stored one value per lane), 512 x 2048 x 2048 14.8 -> 10.0, 333 x 4096 x 4096 25.0 -> 19.0.  From more than 256 macro tiles on the larger ones are faster, and where K is long and the
+// tiles few the kernels that split K are.  Dense weights (twice the bytes) and 128 tokens per tile gained nothing in this form (0.93 - 2.5 of the time).
+// ------------------------------------------------------------------------------------------------
+#define PAIRS_TR 4   // row tiles of a wave
+#define PAIRS_TC 2   // token tiles of a wave
+#define PAIRS_RTM 8  // row tiles of the macro tile
+#define PAIRS_NTT 4  // token tiles of the macro tile
+#define PAIRS_NB 4   // pairs of stages in the ring
+#define PAIRS_A (2 * PAIRS_RTM * 64)                       // 16-byte units of a pair: weights,
+#define PAIRS_B (2 * PAIRS_NTT * 128)                      // activations
+#define PAIRS_SLOT (PAIRS_A + PAIRS_B + PAIRS_RTM * 16)    // and index words
+#define PAIRS_ROW (PAIRS_RTM * 16 + 4)                     // floats of a token in the sums at the end
+#define PAIRS_LDS (PAIRS_NB * PAIRS_SLOT * 16)
+static_assert(2 * PAIRS_NTT * 16 * PAIRS_ROW * 4 <= PAIRS_LDS && PAIRS_LDS <= 160 * 1024, "the sums take the ring's place");
+
+struct PairsRegs {  // a wave's operands of a pair
+  uint4 a[PAIRS_TR], b[PAIRS_TC][2];
+  int idx[PAIRS_TR];
+};
+
+template <int DT>
+__device__ __attribute__((always_inline)) void pairs_pipeline(uint4* __restrict__ ring, const uint4* __restrict__ A, const uint16_t* __restrict__ meta16,
+                                                              const uint4* __restrict__ Xf, uint16_t* __restrict__ Y, long long M, long long N, long long Mp,
+                                                              long long Np, long long Kp, long long n_tiles, long long ntb, int band) {
+  constexpr int NB = PAIRS_NB, AC = PAIRS_A / 512, BC = PAIRS_B / 512, OPS = AC + BC + 1;  // copies per wave and pair
+  const unsigned tid = threadIdx.x, lane = tid & 63, wave = (unsigned)wave_uniform((int)(tid >> 6));
+  const unsigned kk = wave >> 2, wr = (wave >> 1) & 1, wc = wave & 1;
+  const long long nrt = Np / 16, ntt = Mp / 16, nks = Kp / 64;
+  const unsigned np = (unsigned)(nks / 2);  // (Kp is a multiple of 256)
+  const long long per = (n_tiles + 7) / 8, tile = (long long)(blockIdx.x & 7) * per + (blockIdx.x >> 3);  // an XCD's tiles are neighbours
+  if ((long long)(blockIdx.x >> 3) >= per || tile >= n_tiles) return;
+  long long rb, tb;
+  tile_coords(tile, n_tiles, ntb, band, rb, tb);
+  const uint4* a_src[AC];
+  const uint4* x_src[BC];
+#pragma unroll
+  for (int c = 0; c < AC; c++) {  // chunk q = [stage of the pair][row tile] of 64 units
+    const unsigned q = 8 * c + wave;
+    long long rt = rb * PAIRS_RTM + q % PAIRS_RTM;
+    rt = rt < nrt ? rt : nrt - 1;  // past the end: duplicate work, not stored
+    a_src[c] = A + (rt * nks + q / PAIRS_RTM) * 64;
+  }
+#pragma unroll
+  for (int c = 0; c < BC; c++) {  // chunk q = [stage][token tile][half]
+    const unsigned q = 8 * c + wave;
+    long long tt = tb * PAIRS_NTT + q % (2 * PAIRS_NTT) / 2;
+    tt = tt < ntt ? tt : ntt - 1;
+    x_src[c] = Xf + ((tt * nks + q / (2 * PAIRS_NTT)) * 2 + (q & 1)) * 64;
+  }
+  long long mrt = rb * PAIRS_RTM + wave;
+  mrt = mrt < nrt ? mrt : nrt - 1;
+  const uint32_t* m_src = reinterpret_cast<const uint32_t*>(meta16) + mrt * (nks / 4) * 128;
+  // past the end the last pair is copied again (never used), so that the counted waits hold
+  auto issue = [&](uint4* slot, unsigned p) {
+    p = p < np ? p : np - 1;
+#pragma unroll
+    for (int c = 0; c < AC; c++) global_to_lds_16(a_src[c] + (p * 128u + lane), slot + (8 * c + wave) * 64);
+#pragma unroll
+    for (int c = 0; c < BC; c++) global_to_lds_16(x_src[c] + (p * 256u + lane), slot + PAIRS_A + (8 * c + wave) * 64);
+    // the lane's index word holds both stages of the pair
+    global_to_lds_4(m_src + ((p >> 1) * 128u + lane * 2u + (p & 1u)), reinterpret_cast<uint32_t*>(slot + PAIRS_A + PAIRS_B) + wave * 64);
+    sched_fence();
+  };
+  auto read = [&](const uint4* slot, PairsRegs& r) {
+    const uint4* sa = slot + (kk * PAIRS_RTM + wr * PAIRS_TR) * 64 + lane;
+    const uint4* sb = slot + PAIRS_A + (kk * PAIRS_NTT + wc * PAIRS_TC) * 128 + lane;
+    const uint32_t* sm = reinterpret_cast<const uint32_t*>(slot + PAIRS_A + PAIRS_B) + wr * PAIRS_TR * 64 + lane;
+#pragma unroll
+    for (int i = 0; i < PAIRS_TR; i++) {
+      r.a[i] = sa[i * 64];
+      r.idx[i] = (int)sm[i * 64];
+    }
+#pragma unroll
+    for (int j = 0; j < PAIRS_TC; j++)
+#pragma unroll
+      for (int h = 0; h < 2; h++) r.b[j][h] = sb[j * 128 + h * 64];
+    sched_fence();
+  };
+  // wait until this wave's copies but the newest n have landed and its LDS reads are back; meet the other waves
+  auto arrive = [&](auto outstanding) {
+    sched_fence();
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int n = decltype(outstanding)::value;
+    __builtin_amdgcn_s_waitcnt((n & 15) | ((n >> 4) << 14) | 0x0070);
+    __builtin_amdgcn_s_barrier();
+#endif
+    sched_fence();
+  };
+  floatx4_t acc[PAIRS_TR][PAIRS_TC];
+#pragma unroll
+  for (int i = 0; i < PAIRS_TR; i++)
+#pragma unroll
+    for (int j = 0; j < PAIRS_TC; j++) acc[i][j] = floatx4_t{0.f, 0.f, 0.f, 0.f};
+  // Pair p, its operands in `cur`: when pair p + 1 has landed everywhere and everyone holds the operands of pair p, copy pair p + NB to where p was
+  // and read the operands of p + 1 while p is multiplied.
+  auto step = [&](uint4* slot, const uint4* next_slot, const PairsRegs& cur, PairsRegs& next, unsigned p) {
+    arrive(std::integral_constant<int, (NB - 2) * OPS>{});
+    issue(slot, p + NB);
+    read(next_slot, next);
+#pragma unroll
+    for (int j = 0; j < PAIRS_TC; j++)
+#pragma unroll
+      for (int i = 0; i < PAIRS_TR; i++) acc[i][j] = smfmac16<DT, 0>(cur.a[i], cur.b[j][0], cur.b[j][1], acc[i][j], cur.idx[i] >> (16 * kk));
+  };
+#pragma unroll
+  for (int q = 0; q < NB; q++) issue(ring + q * PAIRS_SLOT, q);
+  arrive(std::integral_constant<int, (NB - 1) * OPS>{});
+  PairsRegs r[2];
+  read(ring, r[0]);
+  unsigned p = 0;
+  for (; p + NB <= np; p += NB)
+#pragma unroll
+    for (int q = 0; q < NB; q++) step(ring + q * PAIRS_SLOT, ring + (q + 1) % NB * PAIRS_SLOT, r[q & 1], r[(q + 1) & 1], p + q);
+#pragma unroll
+  for (int q = 0; q < NB - 1; q++)
+    if (p + q < np) step(ring + q * PAIRS_SLOT, ring + (q + 1) % NB * PAIRS_SLOT, r[q & 1], r[(q + 1) & 1], p + q);
+  arrive(std::integral_constant<int, 0>{});  // nothing is on its way to or from the ring
+  // the two sums of an output, [stage of the pair][token][row], then rows of Y
+  float* sums = reinterpret_cast<float*>(ring);
+#pragma unroll
+  for (int j = 0; j < PAIRS_TC; j++)
+#pragma unroll
+    for (int i = 0; i < PAIRS_TR; i++)
+      *reinterpret_cast<floatx4_t*>(sums + ((kk * PAIRS_NTT + wc * PAIRS_TC + j) * 16 + (lane & 15)) * PAIRS_ROW + (wr * PAIRS_TR + i) * 16 + (lane >> 4) * 4) = acc[i][j];
+  __syncthreads();
+  constexpr int OTHER = PAIRS_NTT * 16 * PAIRS_ROW;  // floats between the two sums
+  const long long t0 = tb * (PAIRS_NTT * 16), n0 = rb * (PAIRS_RTM * 16);
+  if ((N & 7) == 0) {
+#pragma unroll
+    for (int e = 0; e < PAIRS_NTT * 16 * PAIRS_RTM * 2 / 512; e++) {
+      const int at = e * 512 + (int)tid, t = at / (PAIRS_RTM * 2), n = at % (PAIRS_RTM * 2) * 8;
+      const float* f = sums + t * PAIRS_ROW + n;
+      uint32_t o[4];
+#pragma unroll
+      for (int w = 0; w < 4; w++) o[w] = esp_from_float<DT>(f[2 * w] + f[OTHER + 2 * w]) | ((uint32_t)esp_from_float<DT>(f[2 * w + 1] + f[OTHER + 2 * w + 1]) << 16);
+      if (t0 + t < M && n0 + n < N) *reinterpret_cast<uint4*>(Y + (t0 + t) * N + n0 + n) = uint4{o[0], o[1], o[2], o[3]};
+    }
+  } else {
+#pragma unroll
+    for (int e = 0; e < PAIRS_NTT * 16 * PAIRS_RTM * 16 / 512; e++) {
+      const int at = e * 512 + (int)tid, t = at / (PAIRS_RTM * 16), n = at % (PAIRS_RTM * 16);
+      const float* f = sums + t * PAIRS_ROW + n;
+      if (t0 + t < M && n0 + n < N) Y[(t0 + t) * N + n0 + n] = (uint16_t)esp_from_float<DT>(f[0] + f[OTHER]);
+    }
+  }
+}
+
+template <int DT>
+__global__ void __launch_bounds__(512) k_mm_pairs(const uint4* __restrict__ A, const uint16_t* __restrict__ meta16, const uint4* __restrict__ Xf,
+                                                  uint16_t* __restrict__ Y, long long M, long long N, long long Mp, long long Np, long long Kp,
+                                                  long long n_tiles, long long ntb, int band) {
+  extern __shared__ uint4 s_ring[];
+  pairs_pipeline<DT>(s_ring, A, meta16, Xf, Y, M, N, Mp, Np, Kp, n_tiles, ntb, band);
+}
+
+// ------------------------------------------------------------------------------------------------
 // variant "stream" (M <= 128, bound by reading the weights): a workgroup of NW waves owns NW RT row
 // tiles and all MT token tiles over a range of K; wave w owns row tiles (NW rb + w) RT .. + RT.
 // Weights go HBM -> registers, one 64-channel step at a time, NB - 1 steps ahead (registers, not LDS,
@@ -1903,6 +2067,7 @@ struct Variant {
   int depth;       // tile kind: token tiles the activation operands are read ahead (0 = 1)
   int half;        // tile kind: 1 = dense only, stages of 32 channels and the macro tile of the sparse form
   int four8;       // tile kind: 1 = 4:8 only, bitmaps expanded to dense operands in registers, dense instruction
+  int pairs;       // tile kind: 1 = k_mm_pairs (2:4 only)
 };
 static constexpr Variant kVariants[] = {
     {"wave_r2_t1_splitk", KIND_WAVE, 2, 1, 1, 0},
@@ -1970,6 +2135,8 @@ static constexpr Variant kVariants[] = {
     {"tile48_w8_r128_t256", KIND_TILE, 4, 4, 0, 4, 0, 0, 0, 0, 1},
     {"tile48_w8_t128", KIND_TILE, 8, 2, 0, 4, 0, 0, 0, 0, 1},
     {"tile48_w8_t128_splitk", KIND_TILE, 8, 2, 1, 4, 0, 0, 0, 0, 1},  // ... with K split over workgroups (M <= 512)
+    // 2:4 only: 128 rows x 64 tokens per workgroup, two stages at a time on two halves of the waves
+    {"pairs_w8_r128_t64", KIND_TILE, 4, 1, 0, 4, 0, 0, 0, 0, 0, 1},
 };
 static constexpr int kNumVariants = (int)(sizeof(kVariants) / sizeof(kVariants[0]));
 
@@ -1996,6 +2163,7 @@ static bool applicable(const Variant& var, long long M, int sparse) {
   if (var.kind == KIND_TILE && M < 64) return false;
   if (var.x32 && sparse != 1) return false;
   if (var.half && sparse != 0) return false;
+  if (var.pairs && sparse != 1) return false;
   if (var.kind == KIND_STREAM && M > 128) return false;
   return true;
 }
@@ -2033,7 +2201,9 @@ static constexpr int variant_index(const char* name) {
 // profiles/kernel_choice_times.csv and kernel_choice_fit.py beside it hold the times and make the constants again.
 // Picked by them, products take 1.012 / 1.016 / 1.008 times the time of the fastest of all kernels in the geometric mean (2:4 /
 // dense / 4:8) and 1.25 / 1.22 / 1.17 times it at worst; the rules on row and token counts they replace took 1.19 / 1.17 / 1.11 times
-// it, 2.9 / 2.8 / 2.0 at worst.  That is on the products of the fit, except that 240 of the 2:4 ones were kept out of a first fit and
+// it, 2.9 / 2.8 / 2.0 at worst.  (The pairs kernel came later: fitted to 561 products of up to 256 of its tiles, mean error 7 %, and its row stands 1.2 times
+// higher, so that it is chosen only where the others' estimates leave no doubt: for 140 of them, 0.94 of the time in the geometric mean over all 561 and
+// 1.01 times at worst; without the factor 0.93, but 42 of them above 1.06, up to 1.2.)  That is on the products of the fit, except that 240 of the 2:4 ones were kept out of a first fit and
 // came out at 1.02.  The estimate loses to the old rule by more than 3 % on 16, 3 and 12 of them: up to 12 % (512 x 2048 x 2048), 6 to
 // 10 % on matrices of a few MB at 20 to 32 tokens; the 4:8 ones are the same kernel timed twice.
 // ------------------------------------------------------------------------------------------------
@@ -2051,6 +2221,7 @@ static constexpr Cost kCost24[] = {
     {"ksplit_w8_r3", 2.66f, 2.23e-05f, 1.15e-05f, 5.63e-08f, 0.f, 0.f, 0.594f},
     {"ksplit_w8_r4", 3.26f, 2.04e-05f, 1.21e-05f, 6.8e-08f, 0.f, 0.f, 0.15f},
     {"ksplit_w8_r6", 2.66f, 2.07e-05f, 1.3e-05f, 6.06e-08f, 0.f, 0.f, 0.904f},
+    {"pairs_w8_r128_t64", 4.75f, 0.217f, 0.f, 1.76e-07f, 0.f, 0.f, 0.f},  // 1.2 times the fit, see above
     {"stream_w11_r1_d3", 3.2f, 2.66e-05f, 1.14e-05f, 4.57e-08f, 3.14e-07f, 4.27f, 0.f},
     {"stream_w8_r1_d3", 3.2f, 2.66e-05f, 1.14e-05f, 4.57e-08f, 3.14e-07f, 4.27f, 0.f},
     {"stream_w9_r1_d3", 3.2f, 2.66e-05f, 1.14e-05f, 4.57e-08f, 3.14e-07f, 4.27f, 0.f},
@@ -2273,6 +2444,7 @@ static const CostRow* pick_by_cost(long long M, long long N, long long K, int sp
     if (!applicable(r.v, M, sparse)) continue;
     if (!partials && (r.v.split_mode == 1 || r.v.kind == KIND_STREAM)) continue;
     if (r.v.kind == KIND_STREAM && r.v.nw != stream_waves) continue;
+    if (r.v.pairs && ((N + 127) / 128) * ((M + 63) / 64) > 256) continue;  // one macro tile per CU: beyond, larger ones are faster (3 of 259 shapes)
     if (r.v.kind == KIND_KSPLIT && M > 64) continue;  // 4:8 beyond 64 tokens: 64 at a time, slower than the tiles throughout
     const bool shared = is_decode_kernel(r.v);  // the products of a group share the launch
     if (grouped && !shared && M <= 32) continue;  // up to 32 tokens a group is one launch, and its halves exist
@@ -2563,6 +2735,12 @@ static int launch_tile(esparse_ctx* ctx, const Variant& v, hipStream_t st, const
       hipLaunchKernelGGL((k_mm_tile32<DT, 2>), grid, dim3(512), 0, st, A, meta16, Xf, Y, partial, M, N, Mp, Np, Kp, n_tiles, ntb, nsplit, (int)sps, band);
     else
       hipLaunchKernelGGL((k_mm_tile32<DT, 1>), grid, dim3(512), 0, st, A, meta16, Xf, Y, partial, M, N, Mp, Np, Kp, n_tiles, ntb, nsplit, (int)sps, band);
+    ESP_HIP(ctx, hipGetLastError());
+  } else if (v.pairs) {
+    if (SPARSE != 1) return esp_fail(ctx, ESPARSE_EINVAL, "the pairs kernel multiplies 2:4 weights only");
+    static std::atomic<unsigned long long> raised{0};
+    ESP_HIP(ctx, raise_dynamic_lds(raised, ctx->device, &k_mm_pairs<DT>, PAIRS_LDS));
+    hipLaunchKernelGGL((k_mm_pairs<DT>), grid, dim3(512), PAIRS_LDS, st, A, meta16, Xf, Y, M, N, Mp, Np, Kp, n_tiles, ntb, band);
     ESP_HIP(ctx, hipGetLastError());
   } else
   {

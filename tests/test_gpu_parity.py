@@ -824,6 +824,21 @@ def test_tokens_rows_kept_by_the_decode_kernels(esp, ctx, M, K, n, m):
             assert (_bits(call(v)) == _bits(want)).all(), (v, i)
 
 
+# the pairs kernel: fewer pairs of stages than its ring holds, one more, two more and a multiple; one row tile, a macro tile and one row more; the last
+# token tile and token of a macro tile; rows of Y that are no multiple of 8 values; some rows and all tokens beyond one XCD's share
+@pytest.mark.parametrize("M,N,K", [(64, 16, 64), (65, 129, 512), (100, 128, 772), (79, 8, 1024), (512, 1031, 1280), (333, 1000, 2304), (1024, 2048, 256), (96, 4099, 516)])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+def test_pairs_of_stages(esp, ctx, M, N, K, dtype):
+    X, perm, comp, ref = _device_case(ctx, M, N, K, 2, 4, 81, dtype)
+    v = [esp.variant_name(i) for i in range(esp.num_variants())].index("pairs_w8_r128_t64")
+    guard = 4096
+    buf = torch.full((M * N + 2 * guard,), 7.0, dtype=dtype, device="cuda")
+    Y = ctx.spmm(X, comp, perm, variant=v, out=buf[guard:guard + M * N].view(M, N))
+    assert orc.rowwise_rel_error(_np(Y).astype(np.float64), ref).max() <= TOL[dtype]
+    assert (buf[:guard] == 7.0).all() and (buf[guard + M * N:] == 7.0).all()
+    assert torch.equal(ctx.spmm(X, comp, perm, variant=v), Y)
+
+
 # a square layer applied in place, whole and overlapping by some rows, alone and in a group whose members share an input
 @pytest.mark.parametrize("M", [2, 4, 8])
 def test_outputs_that_overlap_the_input(esp, ctx, M):
