@@ -28,6 +28,8 @@ struct esparse_ctx {
   size_t kept_bytes = 0;
   void* h_stage = nullptr;
   size_t h_stage_bytes = 0;
+  unsigned long long team_wait = 5000000;  // block shuffle: ticks of 10 ns that a team of workgroups waits for a member (50 ms)
+  int teams_left = 0;                      // ... and calls in which one gave up
 };
 
 int esp_fail(esparse_ctx* ctx, int code, const char* fmt, ...);
@@ -139,6 +141,7 @@ struct EspCalib {
   double alpha;
   bool entropy, norm;
 };
+int esp_team_wait(esparse_ctx* ctx, unsigned long long ticks);
 // score_host, or the scores of `calib` (then score_out receives them, if given)
 int esp_prune_device(esparse_ctx* ctx, const double* score_host, const EspCalib* calib, const void* W, long long N,
                      long long K, int dtype, const esparse_prune_opts* o, int32_t* perm_out,

@@ -1552,10 +1552,9 @@ __global__ void __launch_bounds__(1024) k_lbs_select(const double* __restrict__ 
 // Waiting: workgroups are dispatched in the order of their numbers, in turn to the 8 XCDs (b mod 8); a team is consecutive
 // numbers of one XCD, at most 32 of the 64 workgroups that an XCD holds at a time.  So at most the last team of an XCD is there
 // in part, all others finish without anyone's help and make room, also beside another launch of this kernel.  Only progress hangs
-// on that: a wait ends after LBS_WAIT_TICKS or once another one has ended that way, the block then stays in LBS_FAST as it was before
-// the launch and the caller goes on with a launch per round.
+// on that: a wait ends after `wait` ticks of 10 ns (the context's team_wait) or once another one has ended that way, the block then stays in
+// LBS_FAST as it was before the launch and the caller goes on with a launch per round.
 #define LBS_EMPTY 0xffffffffffffffffull
-#define LBS_WAIT_TICKS 5000000ull  // of 10 ns
 #define LBS_TEAM_MAX 32
 #define LBS_XCD_GROUPS 64          // workgroups of an XCD at a time, two per CU
 #define LBS_TEAM_BLOCK 64          // largest block: V in LDS
@@ -1564,7 +1563,7 @@ template <int DT, int NKEEP, int MG, int QC>
 __global__ void __launch_bounds__(64 * LBS_WAVES, 4) k_lbs_rounds(const uint16_t* __restrict__ P, const uint16_t* __restrict__ PT, const double* __restrict__ sp,
                                                                 const double* __restrict__ V, int* __restrict__ lp, int* __restrict__ rec, int* __restrict__ state,
                                                                 long long* __restrict__ swaps, long long max_swaps, long long N, long long Npad, int nblk, int B,
-                                                                int T, unsigned long long* __restrict__ S /*[3][nblk][T][2 MG][B]*/, int* __restrict__ gave_up,
+                                                                int T, unsigned long long* __restrict__ S /*[3][nblk][T][2 MG][B]*/, int* __restrict__ gave_up, unsigned long long wait,
                                                                 const int* __restrict__ not_finite, int* __restrict__ count) {
   using Sh = LbsShape<MG, 2, QC>;
   constexpr int NC = Sh::NC, XC = Sh::XC, NT = 64 * LBS_WAVES;
@@ -1647,7 +1646,7 @@ __global__ void __launch_bounds__(64 * LBS_WAVES, 4) k_lbs_rounds(const uint16_t
         if (!look()) {
           const unsigned long long t0 = wall_clock64();
           while (!look()) {
-            if (__hip_atomic_load(gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 || wall_clock64() - t0 > LBS_WAIT_TICKS) {
+            if (__hip_atomic_load(gave_up, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0 || wall_clock64() - t0 > wait) {
               __hip_atomic_store(gave_up, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
               s_go = 0;
               break;
@@ -1899,6 +1898,13 @@ __global__ void __launch_bounds__(64) k_group_values(const uint16_t* __restrict_
     else if ((n) == 2) KERNEL(ESPARSE_BF16, 2, 4, __VA_ARGS__);                     \
     else KERNEL(ESPARSE_BF16, 4, 8, __VA_ARGS__);                                   \
   } while (0)
+
+// How long the block shuffles of a context wait for a team of workgroups; returns how many of them have given up so far.  (The launches that take over
+// then give the same result, which only a wait that is too short shows.)
+int esp_team_wait(esparse_ctx* ctx, unsigned long long ticks) {
+  ctx->team_wait = ticks;
+  return ctx->teams_left;
+}
 
 int esp_prune_device(esparse_ctx* ctx, const double* score, const EspCalib* calib, const void* Wv, long long N, long long K, int dtype,
                      const esparse_prune_opts* o, int32_t* perm_out, uint8_t* mask_out, double* score_out, int64_t* swaps_out,
@@ -2165,7 +2171,7 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const EspCalib* cali
       first_fast = false;
 #define LAUNCH_ROUNDS2(DTv, NK, MGv, QCv)                                                                                             \
   hipLaunchKernelGGL((k_lbs_rounds<DTv, NK, MGv, QCv>), dim3((unsigned)((nblk + 7) / 8 * 8 * team)), dim3(64 * LBS_WAVES), 0, st, d_P, d_PT, d_sp, \
-                     d_V, d_lp, d_rec, d_state, d_swaps, o->max_swaps, N, Npad, (int)nblk, B, team, d_meet, d_count + 3, d_count + 2, d_count)
+                     d_V, d_lp, d_rec, d_state, d_swaps, o->max_swaps, N, Npad, (int)nblk, B, team, d_meet, d_count + 3, ctx->team_wait, d_count + 2, d_count)
 #define LAUNCH_ROUNDS(DTv, NK, MGv, ...)               \
   do {                                                 \
     if (qc == 4) LAUNCH_ROUNDS2(DTv, NK, MGv, 4);      \
@@ -2176,7 +2182,10 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const EspCalib* cali
 #undef LAUNCH_ROUNDS2
       ESP_HIP(ctx, hipGetLastError());
       if ((rc = finish())) return rc;
-      if (count[0] > 0 && (rc = panel_columns())) return rc;  // the results' sums are where it was
+      if (count[0] > 0) {
+        ctx->teams_left++;
+        if ((rc = panel_columns())) return rc;  // the results' sums are where it was
+      }
     }
     if (!d_meet || count[0] > 0 || count[1] > 0) {
       for (int mode : {LBS_FAST, LBS_EXACT}) {

@@ -3,6 +3,7 @@
 Bar: permutation, mask, statistics, compressed values and metadata bit-exact; products within a
 normwise relative error per output row of 2e-3 (fp16) / 1e-2 (bf16).
 """
+import ctypes as C
 import hashlib
 import json
 import math
@@ -206,6 +207,40 @@ def test_block_shuffle_teams(esp, ctx, n, m, B, nblk, N):
     W = _rand((N, K), torch.bfloat16 if N % 2 else torch.float16, 5 + N, scale=K ** -0.5)
     s = np.random.default_rng(N + B).lognormal(size=K)
     assert _check_block_shuffle(esp, ctx, W, s, n, m, B, max_swaps=3 if N * B * nblk > 100000 else 0).max() > 1
+
+
+# Teams that stop waiting: at once, or sooner or later for some of the blocks.  The launches that take over go on from the first
+# table and lead to the same exchanges, mask and retained metric (whose sums have taken the place of the panel by columns by then);
+# with equal columns in every second block (no global shuffle then) some blocks are left to the exact table meanwhile
+@pytest.mark.parametrize("n,m,B,nblk,N", [(2, 4, 64, 2, 520), (2, 4, 32, 12, 300), (4, 8, 64, 2, 270), (4, 8, 32, 5, 520)])
+@pytest.mark.parametrize("ties", [False, True])
+def test_block_shuffle_teams_that_give_up(esp, n, m, B, nblk, N, ties):
+    K = B * nblk
+    W = _rand((N, K), torch.float16, 41 + N, scale=K ** -0.5)
+    s = np.random.default_rng(N + B).lognormal(size=K)
+    if ties:
+        tied = np.arange(K) // B % 2 == 0
+        s[tied] = 1.0
+        W[:, torch.tensor(tied)] = W[:, :1]
+    opts = esp.PruneOpts(n_keep=n, m_group=m, block=B, max_swaps=6, flags=esp.USE_NORM | esp.USE_LBS | (0 if ties else esp.USE_GNS))
+    Wn = _np(W)
+    theta0 = np.arange(K) if ties else orc.global_naive_shuffle(Wn, s, m)
+    theta, swaps = orc.local_block_shuffle_vectorised(Wn, s, theta0, n, m, B, 6, order=("lanes", 16))
+    mask, retained = orc.nm_mask_vectorised(Wn, s, theta, n, m), orc.retained_metric(Wn, s, theta, n, m)
+    c = esp.Context(0)
+    team_wait = c._lib._Z13esp_team_waitP11esparse_ctxy
+    team_wait.argtypes, team_wait.restype = [C.c_void_p, C.c_ulonglong], C.c_int
+    left = 0
+    for wait in (0, 30, 100, 300, 1000, 0):
+        before = team_wait(c._h, wait)
+        print(f"teams that give up: {n}:{m} B={B} nblk={nblk} N={N} ties={ties} wait={wait}", flush=True)
+        res = c.prune(None, W.cuda(), opts, score=s, want_retained=True)
+        assert (res.swaps == swaps).all() and (res.perm.cpu().numpy() == theta).all()
+        assert (res.mask.cpu().numpy() == mask).all() and res.retained == pytest.approx(retained, rel=1e-12)
+        left = team_wait(c._h, wait)
+        assert left == before + 1 or wait > 0
+    print("given up", left)
+    c.close()
 
 
 # exchanges that the cheaper table cannot decide: equal columns (ties), columns without weights and channels kept in every
