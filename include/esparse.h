@@ -93,7 +93,7 @@ int esparse_channel_stats(esparse_ctx* ctx, const void* calib, long long T, long
  * pinned host memory at most; larger blocks are allocated and freed within the call.  The block shuffle takes 4 bytes of
  * device memory per weight while it runs (two panels; 2 bytes, and more time, where the device has no room for the second)
  * and 8 block^2 bytes for each of its tables: one per block, and as many again or 512 in all, whichever is more; blocks of up
- * to 64 columns 48 m_group bytes per channel and workgroup of a team (at most 32) as well. */
+ * to 64 columns 48 m_group bytes per channel and workgroup of a team (at most 16) as well. */
 int esparse_prune(esparse_ctx* ctx, const void* calib, long long T, const void* W, long long N,
                   long long K, esparse_dtype dtype, const esparse_prune_opts* opts,
                   int32_t* perm_out, uint8_t* mask_out, double* score_out, int64_t* swaps_out,

@@ -1550,12 +1550,16 @@ __global__ void __launch_bounds__(1024) k_lbs_select(const double* __restrict__ 
 // member's sums of round r - 1, which come after that member's last read of that buffer (round r - 2).  Buffer 0 is empty at the start.
 //
 // Waiting: workgroups are dispatched in the order of their numbers, in turn to the 8 XCDs (b mod 8); a team is consecutive
-// numbers of one XCD, at most 32 of the 64 workgroups that an XCD holds at a time.  So at most the last team of an XCD is there
-// in part, all others finish without anyone's help and make room, also beside another launch of this kernel.  Only progress hangs
+// numbers of one XCD, at most 16 of the 64 workgroups that an XCD holds at a time.  So of one launch at most the last team of an XCD is there
+// in part, and parts of four launches at a time (as many as the hardware queues of a process) leave four places of the 64, enough to complete one
+// of them: all others finish without anyone's help and make room.  Only progress hangs
 // on that: a wait ends after `wait` ticks of 10 ns (the context's team_wait) or once another one has ended that way, the block then stays in
 // LBS_FAST as it was before the launch and the caller goes on with a launch per round.
+// (Teams of up to 32: 512 channels, 16384 rows 841 instead of 1003 us for 2:4, 1170 instead of 1397 for 4:8; 1024 channels 1133 instead of 1085 and
+// 1541 instead of 1650; 1536 channels 1696 instead of 1512 and 2320 both; the same up to 4096 rows.  But parts of three launches then fill an XCD.)
 #define LBS_EMPTY 0xffffffffffffffffull
-#define LBS_TEAM_MAX 32
+#define LBS_TEAM_MAX 16
+#define LBS_XCDS 8
 #define LBS_XCD_GROUPS 64          // workgroups of an XCD at a time, two per CU
 #define LBS_TEAM_BLOCK 64          // largest block: V in LDS
 
@@ -1899,6 +1903,15 @@ __global__ void __launch_bounds__(64) k_group_values(const uint16_t* __restrict_
     else KERNEL(ESPARSE_BF16, 4, 8, __VA_ARGS__);                                   \
   } while (0)
 
+// Workgroups of a block's team in k_lbs_rounds, 0: a launch per round.  As many as fill the places of an XCD, which takes every eighth block, and
+// have a batch of rows for each wave.  A device with fewer compute units is a part of the chip, with fewer XCDs: numbers eight apart are then not on one XCD, and
+// its places hold parts of many teams of which none can end.
+int esp_lbs_team(long long N, long long nblk, int B, int compute_units) {
+  if (B > LBS_TEAM_BLOCK || 2 * compute_units < LBS_XCDS * LBS_XCD_GROUPS) return 0;
+  const long long places = LBS_XCD_GROUPS / ((nblk + LBS_XCDS - 1) / LBS_XCDS), rows = (N + LBS_WAVES * LBS_ROWS - 1) / (LBS_WAVES * LBS_ROWS);
+  return (int)std::max<long long>(1, std::min(std::min<long long>(places, LBS_TEAM_MAX), rows));
+}
+
 // How long the block shuffles of a context wait for a team of workgroups; returns how many of them have given up so far.  (The launches that take over
 // then give the same result, which only a wait that is too short shows.)
 int esp_team_wait(esparse_ctx* ctx, unsigned long long ticks) {
@@ -2006,10 +2019,9 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const EspCalib* cali
     const int qc = B <= 32 ? 2 : 4;
     const int slices = (B + 16 * qc - 1) / (16 * qc);
     const int nsplit = (int)std::max<long long>(1, std::min<long long>(512 / (nblk * slices), (N + LBS_WAVES * LBS_ROWS - 1) / (LBS_WAVES * LBS_ROWS)));
-    // teams of k_lbs_rounds: as many workgroups as fill the places of an XCD, which takes every eighth block
-    const bool teams = B <= LBS_TEAM_BLOCK;
-    const int team = (int)std::max<long long>(1, std::min<long long>(std::min<long long>(LBS_XCD_GROUPS / ((nblk + 7) / 8), LBS_TEAM_MAX),
-                                                                     (N + LBS_WAVES * LBS_ROWS - 1) / (LBS_WAVES * LBS_ROWS)));
+    int cus = 0;
+    ESP_HIP(ctx, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device));
+    const int team = esp_lbs_team(N, nblk, B, cus);
     const long long batch = (long long)std::max(nsplit, team) * LBS_WAVES * LBS_ROWS;  // rows that are read past the panel's end, at most
     const long long Npad = (N + LBS_ROWS - 1) / LBS_ROWS * LBS_ROWS;
     bool finite = true, fast = true;  // of the scores: all finite (on the device: k_build_panel looks); and none negative
@@ -2038,7 +2050,7 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const EspCalib* cali
     uint16_t* d_PT = d_S ? scratch.get<uint16_t>((size_t)(Npad * K)) : nullptr;
     fast = d_PT != nullptr;
     const long long meet = 2ll * K * m * team;  // places of the teams' sums, one of three buffers
-    unsigned long long* d_meet = fast && teams ? scratch.get<unsigned long long>((size_t)(3 * meet)) : nullptr;
+    unsigned long long* d_meet = fast && team ? scratch.get<unsigned long long>((size_t)(3 * meet)) : nullptr;
     int* count = reinterpret_cast<int*>(h_stage + K);
     long long* h_swaps = reinterpret_cast<long long*>(h_stage + K + 8);
     double* h_gv = h_stage + K + 8 + nblk;

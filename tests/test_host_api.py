@@ -163,6 +163,26 @@ def test_built_in_choices_can_run():
             assert fits(v, M, N, K, sparse) and not any(p in names[v] for p in ("splitk", "stream", "_k")), (M, N, K, sparse, names[v])
 
 
+def test_block_shuffle_teams_can_end():
+    """Teams only where the device has 8 XCDs of 64 places; no more workgroups than an XCD has places for its share of the blocks, and so
+    few per team that parts of the teams of four launches never fill the places of an XCD."""
+    team = esp.load_library()._Z12esp_lbs_teamxxii
+    team.argtypes = [C.c_longlong, C.c_longlong, C.c_int, C.c_int]
+    rng, largest = random.Random(7), 0
+    for _ in range(5000):
+        N, nblk, B = int(2 ** rng.uniform(0, 24)), int(2 ** rng.uniform(0, 16)), 4 * rng.randint(2, 64)
+        for cus in (32, 64, 128, 255):
+            assert team(N, nblk, B, cus) == 0
+        t = team(N, nblk, B, 256)
+        if B > 64:
+            assert t == 0
+            continue
+        assert t >= 1 and 4 * (t - 1) < 64
+        assert t == 1 or (t * -(-nblk // 8) <= 64 and (t - 1) * 256 < N)
+        largest = max(largest, t)
+    assert largest == 16
+
+
 @pytest.mark.parametrize("room_mib", [64, 1])
 def test_entropies_without_threads_or_memory(room_mib):
     """The host part of the channel statistics on 8 threads, and where the address space has no room for another thread's
