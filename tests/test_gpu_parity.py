@@ -206,7 +206,16 @@ def test_block_shuffle_teams(esp, ctx, n, m, B, nblk, N):
     K = B * nblk
     W = _rand((N, K), torch.bfloat16 if N % 2 else torch.float16, 5 + N, scale=K ** -0.5)
     s = np.random.default_rng(N + B).lognormal(size=K)
-    assert _check_block_shuffle(esp, ctx, W, s, n, m, B, max_swaps=3 if N * B * nblk > 100000 else 0).max() > 1
+    assert _check_block_shuffle(esp, ctx, W, s, n, m, B, max_swaps=3).max() > 1
+
+
+# teams to the last exchange, so that each of the three buffers of their sums comes round many times: 2 to 16 workgroups per team
+@pytest.mark.parametrize("n,m,B,nblk,N", [(2, 4, 16, 40, 700), (2, 4, 32, 6, 1030), (2, 4, 64, 1, 700), (4, 8, 16, 30, 520), (4, 8, 32, 10, 600),
+                                          (4, 8, 32, 2, 4000), (4, 8, 64, 1, 520)])
+def test_block_shuffle_teams_to_the_end(esp, ctx, n, m, B, nblk, N):
+    W = _rand((N, B * nblk), torch.float16 if N % 8 else torch.bfloat16, 6 + N, scale=(B * nblk) ** -0.5)
+    s = np.random.default_rng(N + B + 1).lognormal(size=B * nblk)
+    assert _check_block_shuffle(esp, ctx, W, s, n, m, B).max() > 4
 
 
 # Teams that stop waiting: at once, or sooner or later for some of the blocks.  The launches that take over go on from the first
