@@ -1903,6 +1903,15 @@ __global__ void __launch_bounds__(64) k_group_values(const uint16_t* __restrict_
     else KERNEL(ESPARSE_BF16, 4, 8, __VA_ARGS__);                                   \
   } while (0)
 
+// Whether the scores of calibration features stay on the device, so that nothing comes back to the host before the end: where a score below zero can be
+// ruled out (the cheaper table of exchanges needs that), the channels are ranked on the device, and the host has the T terms of eq. 1 about as soon as the scans
+// are done.  Both times grow with T (a term takes one of eight threads 8 ns, the scans 0.9 ps per token and channel), so that is a matter of K: calls of
+// 256 rows with 768 channels take 0.70 - 1.01 of the time with scores from the host at 8192 to 2097152 tokens, with 1024 and more 0.4 - 0.88, with 512 0.8 - 1.4, with
+// 256 0.8 - 1.5.  Up to 4096 tokens one thread makes the terms while the first scan runs (256 channels 0.96, 512 0.71 of the time).
+bool esp_scores_on_device(long long T, long long K, bool entropy, bool norm, double alpha) {
+  return K <= RANK_ON_DEVICE && (!norm || alpha >= 0.0) && (!entropy || K >= 768 || T <= 4096);
+}
+
 // Workgroups of a block's team in k_lbs_rounds, 0: a launch per round.  As many as fill the places of an XCD, which takes every eighth block, and
 // have a batch of rows for each wave.  A device with fewer compute units is a part of the chip, with fewer XCDs: numbers eight apart are then not on one XCD, and
 // its places hold parts of many teams of which none can end.
@@ -1930,14 +1939,10 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const EspCalib* cali
   const long long nblk = use_lbs ? K / B : 0;
   if (swaps_out && !use_lbs && o->block > 0 && K % o->block == 0) memset(swaps_out, 0, sizeof(int64_t) * (K / o->block));
 
-  // Scores from calibration features: on the device, so that nothing comes back to the host before the end, where the host has the terms
-  // of eq. 1 in time (a term takes a thread 8 ns and the scans 0.9 ps per token and channel: T <= 64 K), a score below zero can be
-  // ruled out (the cheaper table of exchanges needs that) and the channels are ranked on the device.
-  // 4096 channels, 262144 tokens: 350 us between the scans and the shuffle, 20 now.
   std::vector<double> host_score;
   size_t terms = calib && calib->entropy ? (size_t)calib->T : 0;
   const size_t results = (size_t)(K + 8 + nblk + K / m);
-  bool on_device = calib && K <= RANK_ON_DEVICE && (!calib->entropy || calib->T <= 64 * K) && (!calib->norm || calib->alpha >= 0.0);
+  bool on_device = calib && esp_scores_on_device(calib->T, K, calib->entropy, calib->norm, calib->alpha);
   on_device = on_device && esp_host_stage(ctx, (results + terms) * 8);
   if (!on_device) terms = 0;
   if (calib && !on_device) {

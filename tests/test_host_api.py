@@ -163,6 +163,17 @@ def test_built_in_choices_can_run():
             assert fits(v, M, N, K, sparse) and not any(p in names[v] for p in ("splitk", "stream", "_k")), (M, N, K, sparse, names[v])
 
 
+def test_scores_stay_on_the_device_by_channels():
+    """Terms and scans both grow with the tokens: from some number of channels on any number of tokens stays on the device; negative
+    scores and more channels than are ranked there never do."""
+    on = esp.load_library()._Z20esp_scores_on_devicexxbbd
+    on.argtypes, on.restype = [C.c_longlong, C.c_longlong, C.c_bool, C.c_bool, C.c_double], C.c_bool
+    for T in (1, 4096, 4097, 32768, 262144, 1 << 22):
+        for K in (768, 1024, 2048, 3072, 4096, 196608):
+            assert on(T, K, True, True, 0.5) and on(T, K, True, False, -1.0) and not on(T, K, True, True, -1e-9)
+        assert on(T, 512, True, True, 0.0) == (T <= 4096) and on(T, 8, False, True, 1.0) and not on(T, 196612, True, True, 1.0)
+
+
 def test_block_shuffle_teams_can_end():
     """Teams only where the device has 8 XCDs of 64 places; no more workgroups than an XCD has places for its share of the blocks, and so
     few per team that parts of the teams of four launches never fill the places of an XCD."""
