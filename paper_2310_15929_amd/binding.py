@@ -7,6 +7,7 @@ Names follow include/esparse.h.
 from __future__ import annotations
 
 import ctypes as C
+import functools
 import os
 from dataclasses import dataclass
 from typing import Optional
@@ -118,53 +119,36 @@ def _ptrs(ts):
     return (_PTRS[n] if 0 < n < 5 else C.c_void_p * n)(*[_ptr(t) for t in ts])
 
 
-# sizes asked for before, a function of their arguments alone
-_sizes = {}
-
-
-def _remember(key, value):
-    if len(_sizes) >= 4096:
-        _sizes.clear()
-    _sizes[key] = value
-    return value
-
-
 def compressed_size(N: int, K: int, n: int, m: int, dtype: int = F16):
-    key = ("compressed", N, K, n, m, dtype)
-    known = _sizes.get(key)
-    if known is not None:
-        return known
     lib = load_library()
     a, b, c = C.c_size_t(), C.c_size_t(), C.c_size_t()
     rc = lib.esparse_compressed_size(N, K, n, m, dtype, C.byref(a), C.byref(b), C.byref(c))
     if rc:
         raise EsparseError(rc, "esparse_compressed_size")
-    return _remember(key, (a.value, b.value, c.value))
+    return a.value, b.value, c.value
 
 
 def spmm_workspace(M: int, N: int, K: int, variant: int = -1) -> int:
-    key = (M, N, K, variant)
-    known = _sizes.get(key)
-    if known is not None:
-        return known
     lib = load_library()
     a = C.c_size_t()
     rc = lib.esparse_spmm_workspace(M, N, K, variant, C.byref(a))
     if rc:
         raise EsparseError(rc, "esparse_spmm_workspace")
-    return _remember(key, a.value)
+    return a.value
 
 
 def _group_workspace(count: int, M: int, N: int, K: int) -> int:
-    key = ("group", count, M, N, K)
-    known = _sizes.get(key)
-    if known is not None:
-        return known
     a = C.c_size_t(0)
     rc = load_library().esparse_spmm_group_workspace(count, M, N, K, C.byref(a))
     if rc:
         raise EsparseError(rc, "esparse_spmm_group_workspace: bad arguments")
-    return _remember(key, a.value)
+    return a.value
+
+
+# for the calls: sizes asked for before, a function of their arguments alone (typed: 16.0 is not the 16 that was asked for)
+_known_size = functools.lru_cache(4096, typed=True)(compressed_size)
+_known_workspace = functools.lru_cache(4096, typed=True)(spmm_workspace)
+_known_group_workspace = functools.lru_cache(4096, typed=True)(_group_workspace)
 
 
 def dense_packed_size(N: int, K: int) -> int:
@@ -324,7 +308,7 @@ class Context:
                  n_keep: int = 2, m_group: int = 4, *, canonical: bool = True, native: bool = True) -> Compressed:
         N, K = W.shape
         dt = _dtype_code(W)
-        vb, mb, nb = compressed_size(N, K, n_keep, m_group, dt)
+        vb, mb, nb = _known_size(N, K, n_keep, m_group, dt)
         dev = W.device
         values = torch.empty((N, K * n_keep // m_group), dtype=W.dtype, device=dev) if canonical else None
         meta = torch.empty(mb, dtype=torch.uint8, device=dev) if canonical else None
@@ -341,7 +325,7 @@ class Context:
         assert K == comp.K and _dtype_code(X) == comp.dtype
         N = comp.N
         Y = out if out is not None else X.new_empty((M, N))
-        nbytes = spmm_workspace(M, N, K)
+        nbytes = _known_workspace(M, N, K)
         ws = self._scratch(nbytes)
         self._sync_stream()
         rc = self._lib.esparse_spmm(self._h, X.data_ptr(), M, _ptr(comp.native), _ptr(perm), N, K, comp.dtype,
@@ -376,7 +360,7 @@ class Context:
                 seen = X
         if outs is None:
             outs = [X0.new_empty((M, N)) for _ in range(count)]
-        nbytes = _group_workspace(count, M, N, K)
+        nbytes = _known_group_workspace(count, M, N, K)
         ws = self._scratch(nbytes)
         self._sync_stream()
         rc = self._lib.esparse_spmm_group(self._h, count, _ptrs(Xs), M, _ptrs([c.native for c in comps]),
@@ -408,7 +392,7 @@ class Context:
         M, K = Xs[0].shape
         if outs is None:
             outs = [torch.empty((M, N), dtype=Xs[0].dtype, device=Xs[0].device) for _ in range(count)]
-        nbytes = _group_workspace(count, M, N, K)
+        nbytes = _known_group_workspace(count, M, N, K)
         ws = self._scratch(nbytes)
         self._sync_stream()
         self._check(self._lib.esparse_dense_gemm_group(self._h, count, _ptrs(Xs), M, _ptrs(packed), N, K, _dtype_code(Xs[0]),
@@ -418,7 +402,7 @@ class Context:
     def stage_activations(self, X: torch.Tensor, perm: Optional[torch.Tensor], N: int,
                           ws: Optional[torch.Tensor] = None) -> torch.Tensor:
         M, K = X.shape
-        nbytes = spmm_workspace(M, N, K)
+        nbytes = _known_workspace(M, N, K)
         if ws is None:
             ws = self.workspace(nbytes)
         self._sync_stream()
@@ -450,7 +434,7 @@ class Context:
                    out: Optional[torch.Tensor] = None) -> torch.Tensor:
         M, K = X.shape
         Y = out if out is not None else X.new_empty((M, N))
-        nbytes = spmm_workspace(M, N, K)
+        nbytes = _known_workspace(M, N, K)
         ws = self._scratch(nbytes)
         self._sync_stream()
         self._check(self._lib.esparse_dense_gemm(self._h, X.data_ptr(), M, _ptr(packed), N, K, _dtype_code(X), Y.data_ptr(),

@@ -141,6 +141,19 @@ def test_halves_of_a_group_up_to_32_tokens_have_a_decode_kernel():
     assert lib.esparse_stage_activations_group(ctx._h, 1, a, 33, None, 4096, 4096, 0, 2, 4, fake, 1 << 40, -1) == -2
 
 
+def test_sizes_refuse_the_same_arguments_again():
+    """Arguments that the library's size queries refuse stay refused after a call with equal ones of the right type, also where a call
+    looks a size up again."""
+    known = [(esp.spmm_workspace, (16, 512, 512)), (binding._known_workspace, (16, 512, 512)), (esp.compressed_size, (8, 512, 2, 4)),
+             (binding._known_size, (8, 512, 2, 4)), (binding._known_group_workspace, (2, 16, 512, 512))]
+    for f, args in known:
+        assert f(*args) == f(*args)
+        for i in range(len(args)):
+            with pytest.raises(C.ArgumentError):
+                f(*args[:i], float(args[i]), *args[i + 1:])
+    assert binding._known_workspace(16, 512, 512) == esp.spmm_workspace(16, 512, 512)
+
+
 def test_built_in_choices_can_run():
     """Over all sizes: the built-in choice is a kernel that takes the shape; a group of at most 32 tokens gets one with a grouped
     form; where no partial tiles fit, it is one that keeps none."""
