@@ -222,7 +222,7 @@ class Context:
             raise EsparseError(rc, "esparse_create")
         self.device = device
         self._ws = None
-        self._ws_at = self._ws_room = 0  # the workspace's first aligned address and the bytes from there
+        self._ws_at, self._ws_room = 0, -1  # the workspace's first aligned address and the bytes from there (-1: no workspace yet)
         self._stream = None              # the stream the library knows
 
     def close(self):

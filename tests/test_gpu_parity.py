@@ -628,6 +628,12 @@ def _spmm_case(esp, ctx, M, N, K, dtype, seed, use_perm=True):
     assert orc.rowwise_rel_error(_np(Y), Yref).max() <= TOL[dtype]
 
 
+def test_workspace_of_no_bytes(esp):
+    c = esp.Context(0)
+    assert c.workspace(0).numel() == 0 and c.workspace(0).data_ptr() % 256 == 0 and c.workspace(300).numel() == 300
+    c.close()
+
+
 def _aligned(nbytes):
     ws = torch.zeros(nbytes + 256, dtype=torch.uint8, device="cuda")
     return ws[(-ws.data_ptr()) % 256:]
