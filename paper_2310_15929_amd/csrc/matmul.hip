@@ -2613,12 +2613,12 @@ static bool overlap(const void* X, const void* Y, long long M, long long N, long
   return x < y + (uintptr_t)M * N * 2 && y < x + (uintptr_t)M * K * 2;
 }
 
-// launches with up to 160 KiB of dynamic LDS
+// launches with up to 160 KiB of LDS, the table of the 4:8 selectors included
 template <int DT, int SPARSE, int RT, int NW, int IDXM, int FOLD>
 static hipError_t launch_ksplit_rows(int device, dim3 grid, hipStream_t st, size_t smem, const KsplitArgs& args, long long M, long long N, long long Mp, long long Np,
                                      long long Kp, int mc) {
   static std::atomic<unsigned long long> raised{0};
-  if (smem > 64 * 1024) {
+  if (smem + (SPARSE == 2 ? LUT48_CODES * 16 : 0) > 64 * 1024) {
     const hipError_t e = raise_dynamic_lds(raised, device, &k_mm_ksplit<DT, SPARSE, 1, RT, NW, IDXM, FOLD>, FOLD_ROWS_LDS);
     if (e != hipSuccess) return e;
   }

@@ -843,10 +843,12 @@ def test_few_tokens_gathered_in_the_kernel_equal_staged(esp, ctx, M, K, n, m):
 
 
 # Tokens' rows kept by the decode kernels, at the edges: the first token of the second tile, K that ends within a unit of 8 channels, the
-# longest rows that the LDS holds and the first that it does not, no re-ordering, dense weights.  The sums are the staged product's in
+# longest rows that the LDS holds and the first that it does not, no re-ordering, dense weights; 4:8 rows that stay below 64 KiB of dynamic LDS
+# only without the table of selectors beside them.  The sums are the staged product's in
 # the same order: equal bit by bit, for each kernel and for the built-in choice, alone and in a group
 @pytest.mark.parametrize("M,K,n,m", [(3, 4, 2, 4), (9, 1036, 2, 4), (5, 264, 4, 8), (8, 8960, 2, 4), (8, 8964, 2, 4), (3, 8960, 4, 8), (16, 4744, 2, 4),
-                                     (16, 4748, 2, 4), (9, 4744, 4, 8), (8, 8960, 0, 0), (16, 4744, 0, 0), (4, 1036, 0, 0)])
+                                     (16, 4748, 2, 4), (9, 4744, 4, 8), (8, 8960, 0, 0), (16, 4744, 0, 0), (4, 1036, 0, 0),
+                                     (8, 3600, 4, 8), (16, 1904, 4, 8)])
 def test_tokens_rows_kept_by_the_decode_kernels(esp, ctx, M, K, n, m):
     N = 40
     decode = [v for v in range(esp.num_variants()) if esp.variant_name(v).startswith("ksplit") and "_k" not in esp.variant_name(v)]
