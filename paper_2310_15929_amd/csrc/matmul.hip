@@ -2656,8 +2656,7 @@ static hipError_t launch_ksplit(int device, const Variant& v, hipStream_t st, Ks
       else if (v.nw == 8 && v.rt == 2) ROWS(2, 8);
       else if (v.nw == 8 && v.rt == 6) ROWS(6, 8);
       else if (v.nw == 8 && v.rt == 3) ROWS(3, 8);
-      else if (v.nw == 16 && v.rt == 4) ROWS(4, 16);
-      else ROWS(4, 8);
+      else if (v.nw == 8 && v.rt == 4) ROWS(4, 8);
 #undef ROWS
       return e;
     }
