@@ -848,8 +848,8 @@ __device__ __forceinline__ double lanes_total(double part) {
 // Replacing the member that the last exchange brought into a group leaves the same other members as before it, so those
 // entries stay valid and are not written again.
 //
-// A workgroup (8 waves) takes NG groups and 16 QC columns, a wave an equal share of the rows.  A lane owns QC columns and
-// every fourth row of its wave, so the panel value and its product with the score are formed once for NG groups.  A wave forms the
+// A workgroup (8 waves) takes two groups and 16 QC columns, a wave an equal share of the rows.  A lane owns QC columns and
+// every fourth row of its wave, so the panel value and its product with the score are formed once for both groups.  A wave forms the
 // operands of its next 32 rows itself (one lane per row and group, members read from PT - gathered
 // from P they cost the vector-memory path a third of the kernel's time) and needs no barrier.
 //
@@ -1170,15 +1170,15 @@ __device__ __forceinline__ double mfma_rows(double a, double b, double c) {
 #endif
 }
 
-// what a wave of k_lbs_eval or k_lbs_rounds takes: all members of NG groups, 16 QC columns
-template <int MG, int NG, int QC>
+// what a wave of k_lbs_eval or k_lbs_rounds takes: all members of two groups, 16 QC columns
+template <int MG, int QC>
 struct LbsShape {
-  static_assert((NG == 2 || NG == 4) && (MG == 4 || MG == 8) && (QC == 2 || QC == 4), "");
+  static_assert((MG == 4 || MG == 8) && (QC == 2 || QC == 4), "");
+  static constexpr int NG = 2;              // groups: one per half of the operand lanes
   static constexpr int RLW = 4;             // rows of a wave at a time, 16 lanes each
   static constexpr int U = LBS_ROWS / RLW;  // ... per batch
   static constexpr int NC = NG * MG;        // combinations of group and member
   static constexpr int NS = MG / 4;         // matrix instructions per group and column
-  static constexpr int GL = NG / 2;         // groups of an operand lane
   static constexpr int XC = 16 * QC;        // columns
   static constexpr int SUMS = NC * (XC + 1);                       // doubles: a wave's sums, the last of a row its base
   static constexpr int OPS = LBS_ROWS * (2 * NG + NG * MG / 2);    // doubles: a wave's operands
@@ -1198,24 +1198,22 @@ __host__ __device__ __forceinline__ long long lbs_wave_rows(long long N, long lo
 // A workgroup's sums over its waves' rows [r0, r0 + nrows).  prow: the lane's place in the wave's first rows; next: its values
 // there, loaded.  smc, sms: the wave's columns and scores of the members, [NG][MG].  At the end s_o holds, complete after the barrier the function ends with, LBS_WAVES / 2
 // partial sums [NC][XC + 1] (lbs_sum adds them).
-template <int DT, int NKEEP, int MG, int NG, int QC>
+template <int DT, int NKEEP, int MG, int QC>
 __device__ __forceinline__ void lbs_sums(const uint16_t* __restrict__ prow, uint2& next, const double (&s)[QC],
                                          const uint16_t* __restrict__ PTb, const int* smc, const double* sms, long long r0, long long nrows, long long N,
                                          long long Npad, int B, double* s_o, int wave, int lane) {
-  using Sh = LbsShape<MG, NG, QC>;
-  constexpr int RLW = Sh::RLW, XC = Sh::XC, NS = Sh::NS, GL = Sh::GL;
+  using Sh = LbsShape<MG, QC>;
+  constexpr int NG = Sh::NG, RLW = Sh::RLW, XC = Sh::XC, NS = Sh::NS;
   const int rlw = lane / 16, xl = lane % 16;
-  const int ir = lane % LBS_ROWS, ih = lane / LBS_ROWS;  // operand lane: row ir of the batch, groups ih, ih + 2
+  const int ir = lane % LBS_ROWS, ih = lane / LBS_ROWS;  // operand lane: row ir of the batch, group ih
   double* sw = s_o + wave * Sh::OPS;                                            // [row][NG][2]: the NKEEP-th and the next largest member
   uint32_t* sm = reinterpret_cast<uint32_t*>(sw + LBS_ROWS * 2 * NG);           // [row][NG][MG]: upper half of 0.0 or 1.0
   const long long r1 = r0 + nrows < N ? r0 + nrows : N;
-  uint16_t mraw[GL][MG];
+  uint16_t mraw[MG];
   auto load_members = [&](long long rb) {
     const long long r = rb + ir < N ? rb + ir : N - 1;
 #pragma unroll
-    for (int h = 0; h < GL; h++)
-#pragma unroll
-      for (int k = 0; k < MG; k++) mraw[h][k] = PTb[smc[(ih + 2 * h) * MG + k] * Npad + r];
+    for (int k = 0; k < MG; k++) mraw[k] = PTb[smc[ih * MG + k] * Npad + r];
   };
   if (r0 < r1) load_members(r0);
   double acc[NG][NS][QC], low[NG][QC];  // sum of D for the members that are not among the NKEEP largest; sum of max(o', x)
@@ -1227,22 +1225,19 @@ __device__ __forceinline__ void lbs_sums(const uint16_t* __restrict__ prow, uint
 #pragma unroll
       for (int t = 0; t < NS; t++) acc[g][t][q] = 0.0;
     }
-  double base[GL][MG];  // operand lanes: what the other members keep besides the candidate's place
+  double base[MG];  // operand lanes: what the other members keep besides the candidate's place
 #pragma unroll
-  for (int h = 0; h < GL; h++)
-#pragma unroll
-    for (int k = 0; k < MG; k++) base[h][k] = 0.0;
+  for (int k = 0; k < MG; k++) base[k] = 0.0;
 
   for (long long rb = r0; rb < r1; rb += LBS_ROWS) {
     const bool live = rb + ir < r1;
     wave_lds_fence();
-#pragma unroll
-    for (int h = 0; h < GL; h++) {
-      const double* sc = sms + (ih + 2 * h) * MG;
+    {
+      const double* sc = sms + ih * MG;
       double w[NKEEP + 1];  // the largest members in order
       int raw[MG];
 #pragma unroll
-      for (int k = 0; k < MG; k++) raw[k] = live ? mraw[h][k] : 0;
+      for (int k = 0; k < MG; k++) raw[k] = live ? mraw[k] : 0;
       auto member = [&](int k) { return (double)esp_to_float<DT>((uint16_t)raw[k]) * sc[k]; };
       w[0] = member(0);
 #pragma unroll
@@ -1266,10 +1261,10 @@ __device__ __forceinline__ void lbs_sums(const uint16_t* __restrict__ prow, uint
         raw[k] = opaque(raw[k]);  // formed a second time: kept, the values would push sums out of the registers
         const double v = member(k);
         const bool top = v >= w[NKEEP - 1];
-        base[h][k] = base[h][k] + (top ? all - v : most);
+        base[k] = base[k] + (top ? all - v : most);
         out[k] = top ? 0u : 0x3ff00000u;
       }
-      const int at = ir * NG + ih + 2 * h;
+      const int at = ir * NG + ih;
       *reinterpret_cast<double2*>(sw + at * 2) = double2{w[NKEEP - 1], w[NKEEP]};
 #pragma unroll
       for (int k = 0; k < MG; k += 4) *reinterpret_cast<uint4*>(sm + at * MG + k) = uint4{out[k], out[k + 1], out[k + 2], out[k + 3]};
@@ -1327,11 +1322,9 @@ __device__ __forceinline__ void lbs_sums(const uint16_t* __restrict__ prow, uint
 #pragma unroll
       for (int q = 0; q < QC; q++) acc[g][t][q] = mfma_rows(1.0, low[g][q], acc[g][t][q]);
 #pragma unroll
-  for (int h = 0; h < GL; h++)
+  for (int k = 0; k < MG; k++)
 #pragma unroll
-    for (int k = 0; k < MG; k++)
-#pragma unroll
-      for (int d = 1; d < LBS_ROWS; d <<= 1) base[h][k] = base[h][k] + __shfl_xor(base[h][k], d);
+    for (int d = 1; d < LBS_ROWS; d <<= 1) base[k] = base[k] + __shfl_xor(base[k], d);
   // the upper half of the waves leaves its sums in LDS, the lower half adds its own
   double* red = s_o + (wave % (LBS_WAVES / 2)) * Sh::SUMS;
 #pragma unroll
@@ -1347,18 +1340,16 @@ __device__ __forceinline__ void lbs_sums(const uint16_t* __restrict__ prow, uint
           for (int q = 0; q < QC; q++) leave(red + (g * MG + 4 * t + rlw) * (XC + 1) + QC * xl + q, acc[g][t][q]);
       if (ir == 0)
 #pragma unroll
-        for (int h = 0; h < GL; h++)
-#pragma unroll
-          for (int k = 0; k < MG; k++) leave(red + ((ih + 2 * h) * MG + k) * (XC + 1) + XC, base[h][k]);
+        for (int k = 0; k < MG; k++) leave(red + (ih * MG + k) * (XC + 1) + XC, base[k]);
     }
   }
   __syncthreads();
 }
 
 // the sum of combination c and column x
-template <int MG, int NG, int QC>
+template <int MG, int QC>
 __device__ __forceinline__ double lbs_sum(const double* s_o, int c, int x) {
-  using Sh = LbsShape<MG, NG, QC>;
+  using Sh = LbsShape<MG, QC>;
   const double* sums = s_o + c * (Sh::XC + 1);
   double t = sums[x], tb = sums[Sh::XC];
 #pragma unroll
@@ -1369,14 +1360,13 @@ __device__ __forceinline__ double lbs_sum(const double* s_o, int c, int x) {
   return t + tb;
 }
 
-// FIRST: groups gset NG .. of every block; else the two groups of the last exchange
-template <int DT, int NKEEP, int MG, int NG, bool FIRST, int QC>
+// FIRST: two groups of every block, from 2 gset on; else those of the last exchange
+template <int DT, int NKEEP, int MG, bool FIRST, int QC>
 __global__ void __launch_bounds__(64 * LBS_WAVES, 4) k_lbs_eval(const uint16_t* __restrict__ P, const uint16_t* __restrict__ PT, const double* __restrict__ sp /*[K] score in panel order*/,
                                                               const int* __restrict__ rec /*[nblk][2][LBS_REC] exchanged positions and their groups*/,
                                                               long long N, long long Npad, int B, int slices, double* __restrict__ S /*[nsplit][nblk][B][B]*/) {
-  static_assert(FIRST || NG == 2, "");
-  using Sh = LbsShape<MG, NG, QC>;
-  constexpr int NC = Sh::NC, XC = Sh::XC;
+  using Sh = LbsShape<MG, QC>;
+  constexpr int NG = Sh::NG, NC = Sh::NC, XC = Sh::XC;
   __shared__ __align__(16) double s_o[Sh::LDS];
   __shared__ double s_ms[LBS_WAVES * NC];
   __shared__ int s_mc[LBS_WAVES * NC];
@@ -1401,12 +1391,12 @@ __global__ void __launch_bounds__(64 * LBS_WAVES, 4) k_lbs_eval(const uint16_t* 
   double s[QC];
 #pragma unroll
   for (int q = 0; q < QC; q++) s[q] = sp[(long long)blk * B + colc + q];
-  lbs_sums<DT, NKEEP, MG, NG, QC>(prow, next, s, PT + (long long)blk * B * Npad, smc, sms, r0, nrows, N, Npad, B, s_o, wave, lane);
+  lbs_sums<DT, NKEEP, MG, QC>(prow, next, s, PT + (long long)blk * B * Npad, smc, sms, r0, nrows, N, Npad, B, s_o, wave, lane);
   double* Sb = S + ((long long)split * nblk + blk) * B * B;
   for (int e = tid; e < NC * XC; e += 64 * LBS_WAVES) {
     const int c = e / XC, x = slice * XC + e % XC, k = c / MG, i = c % MG;
     const int p = FIRST ? 0 : rec[(blk * 2 + k) * LBS_REC], g = FIRST ? gset * NG + k : p / MG;
-    if (x < B && g < B / MG && (FIRST || i != p % MG)) Sb[(long long)(g * MG + i) * B + x] = lbs_sum<MG, NG, QC>(s_o, c, e % XC);
+    if (x < B && g < B / MG && (FIRST || i != p % MG)) Sb[(long long)(g * MG + i) * B + x] = lbs_sum<MG, QC>(s_o, c, e % XC);
   }
 }
 
@@ -1569,7 +1559,7 @@ __global__ void __launch_bounds__(64 * LBS_WAVES, 4) k_lbs_rounds(const uint16_t
                                                                 long long* __restrict__ swaps, long long max_swaps, long long N, long long Npad, int nblk, int B,
                                                                 int T, unsigned long long* __restrict__ S /*[3][nblk][T][2 MG][B]*/, int* __restrict__ gave_up, unsigned long long wait,
                                                                 const int* __restrict__ not_finite, int* __restrict__ count) {
-  using Sh = LbsShape<MG, 2, QC>;
+  using Sh = LbsShape<MG, QC>;
   constexpr int NC = Sh::NC, XC = Sh::XC, NT = 64 * LBS_WAVES;
   constexpr int VS = XC + 1;  // a row of V in LDS: a column's entries stand in different banks
   __shared__ __align__(16) double s_o[Sh::LDS];
@@ -1619,7 +1609,7 @@ __global__ void __launch_bounds__(64 * LBS_WAVES, 4) k_lbs_rounds(const uint16_t
 #pragma unroll
       for (int q = 0; q < QC; q++) s[q] = s_sp[colc + q];
       wave_lds_fence();
-      lbs_sums<DT, NKEEP, MG, 2, QC>(first_row + (lane / 16 * B + colc), next, s, PTb, smc, sms, r0, nrows, N, Npad, B, s_o, wave, lane);
+      lbs_sums<DT, NKEEP, MG, QC>(first_row + (lane / 16 * B + colc), next, s, PTb, smc, sms, r0, nrows, N, Npad, B, s_o, wave, lane);
     }
     // ---- the team's sums, the touched entries of the table
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -1629,7 +1619,7 @@ __global__ void __launch_bounds__(64 * LBS_WAVES, 4) k_lbs_rounds(const uint16_t
     unsigned long long* Sb = S + ((long long)(round % 3) * nblk + blk) * T * per;
     for (int e = opaque(tid); e < NC * XC; e += NT) {
       const int c = e / XC, x = e % XC;
-      unsigned long long bits = (unsigned long long)__double_as_longlong(lbs_sum<MG, 2, QC>(s_o, c, x));
+      unsigned long long bits = (unsigned long long)__double_as_longlong(lbs_sum<MG, QC>(s_o, c, x));
       if (bits == LBS_EMPTY) bits = 0x7ff8000000000000ull;  // another NaN
       if (x < B) __hip_atomic_store(Sb + (long long)member * per + c * B + x, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -2092,7 +2082,7 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const EspCalib* cali
     auto launch_round = [&](int mode, bool first) -> int {
       if (mode == LBS_FAST) {
 #define LAUNCH_EVAL2(DTv, NK, MGv, FIRSTv, QCv)                                                                       \
-  hipLaunchKernelGGL((k_lbs_eval<DTv, NK, MGv, 2, FIRSTv, QCv>),                                                      \
+  hipLaunchKernelGGL((k_lbs_eval<DTv, NK, MGv, FIRSTv, QCv>),                                                         \
                      dim3((unsigned)nblk, (unsigned)nsplit, (unsigned)(slices * (FIRSTv ? (B / MGv + 1) / 2 : 1))),   \
                      dim3(64 * LBS_WAVES), 0, st, d_P, d_PT, d_sp, d_rec, N, Npad, B, slices, d_S)
 #define LAUNCH_EVAL(DTv, NK, MGv, ...)                                   \
