@@ -2199,11 +2199,11 @@ static constexpr int variant_index(const char* name) {
 // The constants are least-squares fits to the times of every kernel, weights cold, on 35 (2:4), 18 (dense) and 17 (4:8) weight
 // shapes from 512 x 512 to 36864 x 9216 with 1 .. 4096 tokens (670, 191 and 189 products; mean error of an estimate 5 %);
 // profiles/kernel_choice_times.csv and kernel_choice_fit.py beside it hold the times and make the constants again.
-// Picked by them, products take 1.012 / 1.016 / 1.008 times the time of the fastest of all kernels in the geometric mean (2:4 /
-// dense / 4:8) and 1.25 / 1.22 / 1.17 times it at worst; the rules on row and token counts they replace took 1.19 / 1.17 / 1.11 times
+// Picked by them, products take 1.008 / 1.014 / 1.012 times the time of the fastest of all kernels in the geometric mean (2:4 /
+// dense / 4:8) and 1.21 / 1.22 / 1.17 times it at worst; the rules on row and token counts they replace took 1.19 / 1.17 / 1.11 times
 // it, 2.9 / 2.8 / 2.0 at worst.  (The pairs kernel came later: fitted to 561 products of up to 256 of its tiles, mean error 7 %, and its row stands 1.2 times
-// higher, so that it is chosen only where the others' estimates leave no doubt: for 140 of them, 0.94 of the time in the geometric mean over all 561 and
-// 1.01 times at worst; without the factor 0.93, but 42 of them above 1.06, up to 1.2.)  That is on the products of the fit, except that 240 of the 2:4 ones were kept out of a first fit and
+// higher, so that it is chosen only where the others' estimates leave no doubt: for 141 of them, 0.94 of the time in the geometric mean over all 561 and
+// 1.01 times at worst; without the factor 0.93, but 42 of them above 1.06, up to 1.2: kernel_choice_pairs_times.csv.)  That is on the products of the fit, except that 240 of the 2:4 ones were kept out of a first fit and
 // came out at 1.02.  The estimate loses to the old rule by more than 3 % on 16, 3 and 12 of them: up to 12 % (512 x 2048 x 2048), 6 to
 // 10 % on matrices of a few MB at 20 to 32 tokens; the 4:8 ones are the same kernel timed twice.
 // ------------------------------------------------------------------------------------------------
@@ -2271,8 +2271,8 @@ static constexpr Cost kCost48[] = {
 };
 
 // Decode kernels that keep the tokens' rows (FOLD_ROWS8 / 16: 3 to 16 tokens, both phases in one call): `tokens` counts the bytes of rows and places that one CU
-// copies into LDS, over all its workgroups.  Fitted to the calls of 65 shapes from 512 x 512 to 22016 x 4096 with 4, 8 and 16 tokens
-// (mean error 5 %); a staged kernel takes STAGE_US more than its row above says.
+// copies into LDS, over all its workgroups.  Fitted to the calls of 68 (4:8: 59) weight shapes from 512 x 512 to 22016 x 4096 with 4, 8 and
+// 16 tokens (mean error 5 %; profiles/kernel_choice_rows_times.csv, made again by the same script); a staged kernel takes STAGE_US more than its row above says.
 static constexpr Cost kFold24[] = {
     {"ksplit_w16_r1", 2.94f, 2.25e-05f, 1.36e-05f, 3.8e-08f, 0.f, 0.f, 0.569f},
     {"ksplit_w16_r1_q", 3.09f, 0.f, 2.23e-05f, 6.88e-08f, 0.f, 0.f, 0.668f},
@@ -2444,7 +2444,7 @@ static const CostRow* pick_by_cost(long long M, long long N, long long K, int sp
     if (!applicable(r.v, M, sparse)) continue;
     if (!partials && (r.v.split_mode == 1 || r.v.kind == KIND_STREAM)) continue;
     if (r.v.kind == KIND_STREAM && r.v.nw != stream_waves) continue;
-    if (r.v.pairs && ((N + 127) / 128) * ((M + 63) / 64) > 256) continue;  // one macro tile per CU: beyond, larger ones are faster (3 of 259 shapes)
+    if (r.v.pairs && ((N + 127) / 128) * ((M + 63) / 64) > 256) continue;  // one macro tile per CU: beyond, larger ones are faster (but for 4 of 259 shapes)
     if (r.v.kind == KIND_KSPLIT && M > 64) continue;  // 4:8 beyond 64 tokens: 64 at a time, slower than the tiles throughout
     const bool shared = is_decode_kernel(r.v);  // the products of a group share the launch
     if (grouped && !shared && M <= 32) continue;  // up to 32 tokens a group is one launch, and its halves exist
@@ -2580,7 +2580,7 @@ static void launch_wave_tile(const Variant& v, dim3 grid, hipStream_t st, const 
 //   1.05 for the others, which end near 100 KB.  Dense weights, 63 and 72 KB: 1.02 - 1.15.
 // Up to 4096 channels x tokens the gathered copy is no slower from two row tiles on (dense: from three, up to 3072), by up to 0.9 us of 7.
 // Over 936 shapes from 256 x 256 to 32000 x 4096 with 3 to 16 tokens the call takes 0.89 of its time with the staging launch and the gather of
-// up to 9216 channels x tokens; the slowest 1.03.
+// up to 9216 channels x tokens; the slowest 1.03 (profiles/kernel_choice_rows_calls.csv).
 // 16 x 512 x 512: 11.5 -> 3.9 us of launches, 8 x 4096 x 4096: 9.4 -> 7.3, 8 x 11008 x 4096: 13.3 -> 12.1.
 static size_t fold_rows_bytes(long long M, long long K, long long Kp) { return (size_t)(M > 8 ? 2 : 1) * (K + 8) * 16 + (size_t)Kp * 2; }
 

@@ -270,3 +270,11 @@ def test_traffic_profile_rows_parse_and_name_existing_variants():
         seen.add(key)
         moved = int(f["fetch_bytes"]) + int(f["write_bytes"])
         assert moved >= 0.98 * int(f["algorithmic_bytes"])
+
+
+def test_constants_of_the_kernel_choice_come_from_their_times():
+    """The fits that profiles/kernel_choice_fit.py makes of the times beside it are the constants in the source, to their printed digits."""
+    run = subprocess.run([sys.executable, os.path.join(ROOT, "profiles", "kernel_choice_fit.py")], capture_output=True, text=True, timeout=100)
+    assert run.returncode == 0, run.stderr
+    off = [float(x) for x in re.findall(r"refit within ([0-9.]+) % of a time", run.stdout)]
+    assert len(off) == 3 + 2 + 3 and max(off) < 0.3, run.stdout
