@@ -2460,8 +2460,11 @@ static const CostRow* pick_by_cost(long long M, long long N, long long K, int sp
 
 // Both phases in one call, 3 to 16 tokens: where the choice for the staged product is a decode kernel, the fastest of the kernels that keep the
 // tokens' rows may take its place.  Only those that add in the same order (the same waves, the same index layout: a wave then takes
-// the same steps whatever its row tiles are), so that a call gives what its two halves give, bit by bit.  One that would leave a CU
-// more workgroups than a staged choice that gathers for itself as well is not taken (K = 256: estimates of 0.8 for what took 1.1 to 1.4).
+// the same steps whatever its row tiles are), so that a call gives what its two halves give, bit by bit.  Where the staged choice needs no staging launch in a
+// whole call either, one that would leave a CU more workgroups is not taken (K = 256: estimates of 0.8 for what took 1.1 to 1.4).  If that choice keeps rows
+// it is among the compared; if it gathers it has no estimate and gives way to any other that is left, which are few: over 400000 shapes
+// of up to 1024 channels only 9 to 16 tokens x 35000 to 37000 rows x at most 256 channels, ksplit_w8_r4 to ksplit_w8_r3 (10 x 36750 x 200 9.1 -> 6.4 us,
+// 14 x 36111 x 256 9.3 -> 6.5).
 static int pick_whole(long long M, long long N, long long K, int sparse, int count, bool grouped, bool partials) {
   double t;
   const CostRow* staged = pick_by_cost(M, N, K, sparse, count, grouped, partials, &t);
