@@ -289,7 +289,7 @@ __device__ __forceinline__ float offset_of(uint16_t raw, float lo32, float one) 
 template <int DT, int CPL, int ROWS, bool FULL>
 __device__ __forceinline__ void hist_trip(const uint16_t* __restrict__ p, long long stride32, long long rb, long long r1,
                                           const float (&lo32)[CPL], const float (&c32)[CPL], const double (&lo)[CPL],
-                                          const double (&wd)[CPL], int bins, float one, float edge, unsigned int* s_hist_lane) {
+                                          const double (&wd)[CPL], int bins, float one, float edge, unsigned int* s_hist_lane, int stride) {
   uint32_t w[ROWS][CPL / 2];
   load_rows<CPL, ROWS, FULL>(p, stride32, rb, r1, w);
   const float safe = 0.5f - edge, nb32 = (float)bins;
@@ -313,7 +313,7 @@ __device__ __forceinline__ void hist_trip(const uint16_t* __restrict__ p, long l
           b = wd[j] > 0.0 ? (unsigned int)(int)floor(t / wd[j]) : 0u;  // the definition
         }
       }
-      atomicAdd(s_hist_lane + 32u * (j * (unsigned int)bins + min(b, (unsigned int)bins - 1u)), add);
+      atomicAdd(s_hist_lane + j * (32 * stride) + min(b, (unsigned int)bins - 1u), add);
     }
   }
 }
@@ -325,12 +325,13 @@ __global__ void __launch_bounds__(1024, 8) k_hist(const uint16_t* __restrict__ X
                                                 unsigned int* __restrict__ most /*[gridDim.x] no count of these channels is larger*/) {
   constexpr int CH = 32 * CPL;
   __shared__ unsigned int s_most;
-  // [j][bins][cl] (cl: column lane, j: which of the lane's CPL channels): a column lane always adds in its own bank.  With the bins of
-  // a channel side by side the lanes of an instruction meet in banks by chance (16 clocks per atomic of a wave) and
-  // the atomics are what the scan waits for: T = 262144, K = 4096 465 us
+  // [CH rows][stride]: the row of a channel is j * 32 + cl (cl: column lane, j: which of the lane's CPL channels), the stride odd, so that the column
+  // lanes of one instruction start in 32 different banks.  A column lane always in its own bank ([j][bins][cl]) is no faster in the loop (T = 262144,
+  // K = 4096 408 us, 100 bins; 500 us, 256 bins; this 394 and 430), and its bins go out in short pieces: T = 131072, K = 232 97 and 186 us, this 52 and 91
   extern __shared__ unsigned int s_hist[];
+  const int stride = bins | 1;
   const int tid = threadIdx.x, cl = tid & 31, rl = tid >> 5;
-  for (int i = tid; i < CH * bins; i += 1024) s_hist[i] = 0u;
+  for (int i = tid; i < CH * stride; i += 1024) s_hist[i] = 0u;
   if (tid == 0) s_most = 0u;
   __syncthreads();
   const long long c = ((long long)blockIdx.x * 32 + cl) * CPL;
@@ -352,26 +353,31 @@ __global__ void __launch_bounds__(1024, 8) k_hist(const uint16_t* __restrict__ X
     constexpr int ROWS = 8;
     const long long stride32 = 32 * K;
     const uint16_t* p = X + (r0 + rl) * K + c;
-    unsigned int* s_hist_lane = s_hist + cl;
+    unsigned int* s_hist_lane = s_hist + cl * stride;
     long long rb = r0 + rl;
     for (; rb + 32 * (ROWS - 1) < r1; rb += 32 * ROWS, p += ROWS * stride32)
-      hist_trip<DT, CPL, ROWS, true>(p, stride32, rb, r1, lo32, c32, lo, wd, bins, one, edge, s_hist_lane);
-    if (rb < r1) hist_trip<DT, CPL, ROWS, false>(p, stride32, rb, r1, lo32, c32, lo, wd, bins, one, edge, s_hist_lane);
+      hist_trip<DT, CPL, ROWS, true>(p, stride32, rb, r1, lo32, c32, lo, wd, bins, one, edge, s_hist_lane, stride);
+    if (rb < r1) hist_trip<DT, CPL, ROWS, false>(p, stride32, rb, r1, lo32, c32, lo, wd, bins, one, edge, s_hist_lane, stride);
   }
   __syncthreads();
   const long long cbase = (long long)blockIdx.x * CH;
-  // a wave takes 8 column lanes x 8 bins at a time: short runs in both layouts
+  // a wave takes a channel's bins: runs of 256 bytes in both layouts
   unsigned int mine = 0u;
-  const int octets = (bins + 7) / 8, lane = tid & 63;
-  for (int t = tid >> 6; t < 4 * CPL * octets; t += 16) {
-    const int b = t % octets * 8 + (lane >> 3), c8 = t / octets, col = c8 % 4 * 8 + (lane & 7), j = c8 / 4;
-    const long long ch = cbase + (long long)col * CPL + j;
-    if (b >= bins || ch >= K) continue;
-    const unsigned int v = s_hist[32 * (j * bins + b) + col];
-    if (v) atomicAdd(&hist[ch * bins + b], v);
-    mine = v > mine ? v : mine;
+  for (int row = tid >> 6; row < CH; row += 16) {
+    const long long ch = cbase + (long long)(row & 31) * CPL + (row >> 5);
+    if (ch >= K) continue;
+    for (int b = tid & 63; b < bins; b += 64) {
+      const unsigned int v = s_hist[row * stride + b];
+      if (v) atomicAdd(&hist[ch * bins + b], v);
+      mine = v > mine ? v : mine;
+    }
   }
-  atomicMax(&s_most, mine);
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const unsigned int other = __shfl_xor(mine, d);
+    mine = other > mine ? other : mine;
+  }
+  if ((tid & 63) == 0) atomicMax(&s_most, mine);
   __syncthreads();
   if (tid == 0) atomicAdd(&most[blockIdx.x], s_most);  // the workgroups' largest counts, added up
 }
@@ -607,7 +613,7 @@ static int launch_scans(esparse_ctx* ctx, Scratch& scratch, const void* calib, l
 #define ESP_SCAN_A(DTv, CPLv)                                                                                        \
   hipLaunchKernelGGL((k_minmax_sumsq<DTv, CPLv>), grid, dim3(1024), 0, st, X, T, K, rpb, d_nmin, d_max, d_sq, want_sq ? 1 : 0)
 #define ESP_SCAN_B(DTv, CPLv)                                                                                        \
-  hipLaunchKernelGGL((k_hist<DTv, CPLv>), grid, dim3(1024), (size_t)32 * CPLv * bins * 4, st, X, T, K, rpb, bins, d_nmin, d_max, d_hist, d_most)
+  hipLaunchKernelGGL((k_hist<DTv, CPLv>), grid, dim3(1024), (size_t)32 * CPLv * (bins | 1) * 4, st, X, T, K, rpb, bins, d_nmin, d_max, d_hist, d_most)
   if (dtype == ESPARSE_F16) {
     if (cpl == 4) ESP_SCAN_A(ESPARSE_F16, 4);
     else ESP_SCAN_A(ESPARSE_F16, 2);
@@ -618,7 +624,7 @@ static int launch_scans(esparse_ctx* ctx, Scratch& scratch, const void* calib, l
   ESP_HIP(ctx, hipGetLastError());
   if (want_hist) {
     // 32 * 4 channels x 256 bins x 4 bytes = 128 KiB of LDS at most
-    const size_t smem = (size_t)32 * cpl * bins * 4;
+    const size_t smem = (size_t)32 * cpl * (bins | 1) * 4;
     if (smem > 48 * 1024) {
       ESP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hist<ESPARSE_F16, 4>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
       ESP_HIP(ctx, hipFuncSetAttribute(reinterpret_cast<const void*>(&k_hist<ESPARSE_BF16, 4>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem));
