@@ -143,10 +143,10 @@ __device__ __forceinline__ void load_rows(const uint16_t* __restrict__ p, long l
 }
 
 // Exact sum of squares of one channel in a lane, fp16: a square is a multiple of 2^-48 below 2^32 and fits float32.  It is split in
-// float64 at 2^-12 (adding and subtracting 1.5 2^40 rounds to a multiple of that), both parts are added up exactly: up to SQ_ROWS = 256 of
-// them are below 2^52 and 2^43 units.  Eight instructions per value and none of them to the LDS; by exponent into LDS bins, as
+// float64 at 2^-12 (adding and subtracting 1.5 2^40 rounds to a multiple of that), both parts are added up exactly: SQ_ROWS of
+// them are below 2^51 and 2^43 units.  Eight instructions per value and none of them to the LDS; by exponent into LDS bins, as
 // bf16 squares go, it takes about 14 and an LDS atomic.
-#define SQ_ROWS 256
+#define SQ_ROWS 128
 struct SquareSum {
   double hi, lo;
 };
@@ -159,8 +159,10 @@ __device__ __forceinline__ void square_add(SquareSum& a, float x) {
 // into the channel's bins: units of 2^-48 are bit 245 = 16 15 + 5, units of 2^-12 bit 281 = 16 17 + 9
 __device__ __forceinline__ void square_flush(SquareSum& a, unsigned long long* bins) {
   static_assert(SQ_EOFF + SQ_SIG == 293, "the places of the two units");
-  const long long l = (long long)(a.lo * 0x1p48);
-  const unsigned long long h = (unsigned long long)((long long)(a.hi * 0x1p12) + (l >> 36));  // the parts below 2^-12 may add up to less than zero
+  // whole numbers below 2^43 and 2^51, read out of the significand of a sum (conversions to 64-bit integers take ten times as long); the parts
+  // below 2^-12 may add up to less than zero
+  const long long l = __double_as_longlong(__builtin_fma(a.lo, 0x1p48, 0x1.8p52)) - __double_as_longlong(0x1.8p52);
+  const unsigned long long h = (unsigned long long)(__double_as_longlong(__builtin_fma(a.hi, 0x1p12, 0x1p52)) - __double_as_longlong(0x1p52) + (l >> 36));
   atomicAdd(bins + 15, (unsigned long long)(l & 0xfffffffffll) << 5);
   atomicAdd(bins + 17, (h & 0xffffffffull) << 9);
   if (h >> 32) atomicAdd(bins + 19, (h >> 32) << 9);
@@ -236,7 +238,6 @@ __global__ void __launch_bounds__(1024, 8) k_minmax_sumsq(const uint16_t* __rest
       minmax_sumsq_trip<DT, CPL, ROWS, true>(p, stride32, rb, r1, lo, hi, sum, s_sq_lane, want_sq);
       if (++trips % (SQ_ROWS / ROWS) == 0) flush();
     }
-    flush();
     if (rb < r1) minmax_sumsq_trip<DT, CPL, ROWS, false>(p, stride32, rb, r1, lo, hi, sum, s_sq_lane, want_sq);
     flush();
 #pragma unroll
