@@ -1977,6 +1977,13 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const EspCalib* cali
   auto leave_scores = [&]() {
     if (on_device && score_out) memcpy(score_out, h_stage, (size_t)K * 8);
   };
+  double* h_gv = h_stage + K + 8 + nblk;
+  auto leave_retained = [&]() {
+    if (!retained_out) return;
+    double tot = 0.0;
+    for (long long g = 0; g < K / m; g++) tot = tot + h_gv[g];
+    *retained_out = tot;
+  };
 
   // ---- global naive shuffle
   double* d_g = nullptr;
@@ -2055,7 +2062,6 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const EspCalib* cali
     unsigned long long* d_meet = fast && team ? scratch.get<unsigned long long>((size_t)(3 * meet)) : nullptr;
     int* count = reinterpret_cast<int*>(h_stage + K);
     long long* h_swaps = reinterpret_cast<long long*>(h_stage + K + 8);
-    double* h_gv = h_stage + K + 8 + nblk;
     hipLaunchKernelGGL(k_lbs_init, dim3((unsigned)std::max<long long>((K + 255) / 256, d_meet ? 512 : 0)), dim3(256), 0, st, d_lp, d_state,
                        fast ? LBS_FAST : LBS_EXACT, d_swaps, d_count, d_meet, d_meet ? meet : 0, (int)nblk, B);
     {
@@ -2225,11 +2231,7 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const EspCalib* cali
     scratch.idle();
     leave_scores();
     if (swaps_out) memcpy(swaps_out, h_swaps, nblk * 8);
-    if (retained_out) {
-      double tot = 0.0;
-      for (long long g = 0; g < ng; g++) tot = tot + h_gv[g];
-      *retained_out = tot;
-    }
+    leave_retained();
     return ESPARSE_OK;
   }
   ESP_HIP(ctx, hipMemcpyAsync(perm_out, d_theta0, K * 4, hipMemcpyDeviceToDevice, st));
@@ -2253,17 +2255,13 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const EspCalib* cali
     DISPATCH_DT_NM(dtype, n, LAUNCH_GV, 0);
 #undef LAUNCH_GV
     ESP_HIP(ctx, hipGetLastError());
-    std::vector<double> gv((size_t)ng);
-    ESP_HIP(ctx, hipMemcpyAsync(gv.data(), d_gv, ng * 8, hipMemcpyDeviceToHost, st));
-    ESP_HIP(ctx, hipStreamSynchronize(st));
-    double tot = 0.0;
-    for (long long g = 0; g < ng; g++) tot = tot + gv[g];
-    *retained_out = tot;
+    ESP_HIP(ctx, hipMemcpyAsync(h_gv, d_gv, ng * 8, hipMemcpyDeviceToHost, st));
   }
   const int rc = fetch_scores();
   if (rc) return rc;
-  ESP_HIP(ctx, hipStreamSynchronize(st));
+  ESP_HIP(ctx, hipStreamSynchronize(st));  // the one wait: for scores and group values
   scratch.idle();
   leave_scores();
+  leave_retained();
   return ESPARSE_OK;
 }
