@@ -141,7 +141,7 @@ struct EspCalib {
   double alpha;
   bool entropy, norm;
 };
-bool esp_scores_on_device(long long T, long long K, bool entropy, bool norm, double alpha);
+bool esp_scores_on_device(long long T, long long K, int bins, bool entropy, bool norm, double alpha);
 int esp_lbs_team(long long N, long long nblk, int B, int compute_units);
 int esp_team_wait(esparse_ctx* ctx, unsigned long long ticks);
 // score_host, or the scores of `calib` (then score_out receives them, if given)

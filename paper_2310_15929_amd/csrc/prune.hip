@@ -538,6 +538,13 @@ __global__ void __launch_bounds__(1024) k_naive_shuffle(const double* __restrict
   }
 }
 
+#define ENTROPY_COUNTS 65536  // of a thread of esp_entropies at least
+#define ENTROPY_TERMS 4096    // and of entropy_terms
+// Threads that share work of the host, which is worth starting one for every `share` of it, and about how long they take (us; starting them is most
+// of it).
+static inline int host_threads(long long work, long long share) { return (int)std::max<long long>(1, std::min<long long>(8, work / share)); }
+static inline double threads_us(double alone, int threads) { return alone / threads + (threads > 1 ? 14.0 * threads - 2.0 : 0.0); }
+
 // eq. 1: IR_c = - sum_k p_k ln p_k, ascending k, empty bins skipped.  K * bins logarithms on the host (the host's log is
 // the one the result is defined by); the counts of a channel set repeat, so each thread keeps the terms it has met (a
 // logarithm of a count below 16384 is taken about once in ten times at T = 262144).  Without memory for the terms or without
@@ -563,7 +570,7 @@ void esp_entropies(const unsigned int* hist, long long K, int bins, long long T,
       out[c] = -acc;
     }
   };
-  const int nthr = (int)std::max<long long>(1, std::min<long long>(8, K * bins / 65536));
+  const int nthr = host_threads(K * bins, ENTROPY_COUNTS);
   std::thread pool[8];
   int started = 1;
   try {
@@ -690,7 +697,7 @@ static void entropy_terms(long long T, double* terms) {
       terms[n] = n ? p * std::log(p) : 0.0;
     }
   };
-  const int nthr = (int)std::max<long long>(1, std::min<long long>(8, T / 4096));
+  const int nthr = host_threads(T, ENTROPY_TERMS);
   std::thread pool[8];
   int started = 1;
   try {
@@ -1901,12 +1908,16 @@ __global__ void __launch_bounds__(64) k_group_values(const uint16_t* __restrict_
   } while (0)
 
 // Whether the scores of calibration features stay on the device, so that nothing comes back to the host before the end: where a score below zero can be
-// ruled out (the cheaper table of exchanges needs that), the channels are ranked on the device, and the host has the T terms of eq. 1 about as soon as the scans
-// are done.  Both times grow with T (a term takes one of eight threads 8 ns, the scans 0.9 ps per token and channel), so that is a matter of K: calls of
-// 256 rows with 768 channels take 0.70 - 1.01 of the time with scores from the host at 8192 to 2097152 tokens, with 1024 and more 0.4 - 0.88, with 512 0.8 - 1.4, with
-// 256 0.8 - 1.5.  Up to 4096 tokens one thread makes the terms while the first scan runs (256 channels 0.96, 512 0.71 of the time).
-bool esp_scores_on_device(long long T, long long K, bool entropy, bool norm, double alpha) {
-  return K <= RANK_ON_DEVICE && (!norm || alpha >= 0.0) && (!entropy || K >= 768 || T <= 4096);
+// ruled out (the cheaper table of exchanges needs that), the channels are ranked on the device, and the host is done with the T terms of eq. 1, which it
+// makes while the scans run (0.9 ps per token and channel), sooner than it would have the scores from K x bins counts: a term takes it 3 ns, a count
+// 1.1 ns, a channel 16 ns on its way, and a look in between 8 us.  Over 512 to 524288 tokens, 64 to 2048 channels, 10 to 256 bins (534 calls, fp16) a call
+// takes 1.004 of the faster way's time in the geometric mean, 1.22 at worst (131072 tokens, 256 channels, 256 bins: 243 and 200 us); all scores from the
+// host: 1.34 and 4.3, all on the device: 1.10 and 2.9.  By channels alone (768 and more, fewer up to 4096 tokens) 6000 tokens of 640 channels and 256 bins took
+// 184 us, 86 on the device, and 32768 of 768 and 10 bins 194, 123 from the host.
+bool esp_scores_on_device(long long T, long long K, int bins, bool entropy, bool norm, double alpha) {
+  if (K > RANK_ON_DEVICE || (norm && !(alpha >= 0.0))) return false;
+  const double wait = threads_us(0.003 * (double)T, host_threads(T, ENTROPY_TERMS)) - 0.9e-6 * (double)T * (double)K;
+  return !entropy || wait <= 8.0 + 0.016 * (double)K + threads_us(1.1e-3 * (double)K * bins, host_threads(K * bins, ENTROPY_COUNTS));
 }
 
 // Workgroups of a block's team in k_lbs_rounds, 0: a launch per round.  As many as fill the places of an XCD, which takes every eighth block, and
@@ -1939,7 +1950,7 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const EspCalib* cali
   std::vector<double> host_score;
   size_t terms = calib && calib->entropy ? (size_t)calib->T : 0;
   const size_t results = (size_t)(K + 8 + nblk + K / m);
-  bool on_device = calib && esp_scores_on_device(calib->T, K, calib->entropy, calib->norm, calib->alpha);
+  bool on_device = calib && esp_scores_on_device(calib->T, K, calib->bins, calib->entropy, calib->norm, calib->alpha);
   on_device = on_device && esp_host_stage(ctx, (results + terms) * 8);
   if (!on_device) terms = 0;
   if (calib && !on_device) {

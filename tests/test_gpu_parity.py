@@ -134,8 +134,8 @@ def test_prune_bit_exact(esp, ctx, n, m, B, dtype):
     _prune_case(esp, ctx, 96, 128, 200, B, n, m, dtype, esp.USE_ALL, 21)
 
 
-# scores on the device and, beyond 4096 tokens of fewer than 768 channels or with a negative weight of the norm, on the host: constant channels
-# (all tokens in one bin), few and many bins, each term alone
+# scores on the device and, with many tokens of few channels (4096 of 24, 4097 of 24) or a negative weight of the norm, on the host: constant
+# channels (all tokens in one bin), few and many bins, each term alone
 @pytest.mark.parametrize("T,K,bins,alpha,which", [(512, 8, 100, 0.3, 3), (513, 8, 100, 0.3, 3), (300, 24, 1, 0.1, 3), (700, 40, 256, 0.0, 3),
                                                   (700, 40, 100, -0.2, 3), (1, 16, 7, 1.0, 3), (90, 36, 33, 1.0, 1), (90, 36, 33, 0.7, 2),
                                                   (4096, 24, 100, 0.1, 3), (4097, 24, 100, 0.1, 3), (4097, 760, 100, 0.1, 3), (50000, 768, 100, 0.1, 3)])

@@ -176,15 +176,17 @@ def test_built_in_choices_can_run():
             assert fits(v, M, N, K, sparse) and not any(p in names[v] for p in ("splitk", "stream", "_k")), (M, N, K, sparse, names[v])
 
 
-def test_scores_stay_on_the_device_by_channels():
-    """Terms and scans both grow with the tokens: from some number of channels on any number of tokens stays on the device; negative
-    scores and more channels than are ranked there never do."""
-    on = esp.load_library()._Z20esp_scores_on_devicexxbbd
-    on.argtypes, on.restype = [C.c_longlong, C.c_longlong, C.c_bool, C.c_bool, C.c_double], C.c_bool
-    for T in (1, 4096, 4097, 32768, 262144, 1 << 22):
-        for K in (768, 1024, 2048, 3072, 4096, 196608):
-            assert on(T, K, True, True, 0.5) and on(T, K, True, False, -1.0) and not on(T, K, True, True, -1e-9)
-        assert on(T, 512, True, True, 0.0) == (T <= 4096) and on(T, 8, False, True, 1.0) and not on(T, 196612, True, True, 1.0)
+def test_scores_stay_on_the_device_where_that_is_faster():
+    """Sizes at which one of the two ways was measured faster by a fifth and more; negative scores and more channels than are ranked
+    there never stay on the device, scores without a logarithm always do."""
+    on = esp.load_library()._Z20esp_scores_on_devicexxibbd
+    on.argtypes, on.restype = [C.c_longlong, C.c_longlong, C.c_int, C.c_bool, C.c_bool, C.c_double], C.c_bool
+    for T, K, bins in [(512, 256, 100), (2048, 64, 256), (4096, 384, 100), (6000, 640, 256), (6000, 256, 256), (16384, 640, 256), (32768, 1024, 100),
+                       (131072, 1024, 100), (131072, 1536, 256), (524288, 640, 100), (262144, 3072, 100), (262144, 4096, 100), (1 << 22, 4096, 100)]:
+        assert on(T, K, bins, True, True, 0.5) and on(T, K, bins, True, False, -1.0) and not on(T, K, bins, True, True, -1e-9), (T, K, bins)
+    for T, K, bins in [(8192, 128, 100), (16384, 256, 10), (16384, 256, 100), (32768, 768, 10), (131072, 512, 10), (524288, 64, 256)]:
+        assert not on(T, K, bins, True, True, 0.5) and on(T, K, bins, False, True, 0.5), (T, K, bins)
+    assert not on(512, 196612, 100, True, True, 1.0) and not on(512, 196612, 100, False, True, 1.0)
 
 
 def test_block_shuffle_teams_can_end():
