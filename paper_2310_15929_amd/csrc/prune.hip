@@ -1374,10 +1374,9 @@ __device__ __forceinline__ double lbs_sum(const double* s_o, int c, int x) {
   return t + tb;
 }
 
-// FIRST: two groups of every block, from 2 gset on; else those of the last exchange
-template <int DT, int NKEEP, int MG, bool FIRST, int QC>
+// the first table: groups 2 gset and 2 gset + 1 of every block
+template <int DT, int NKEEP, int MG, int QC>
 __global__ void __launch_bounds__(64 * LBS_WAVES, 4) k_lbs_eval(const uint16_t* __restrict__ P, const uint16_t* __restrict__ PT, const double* __restrict__ sp /*[K] score in panel order*/,
-                                                              const int* __restrict__ rec /*[nblk][2][LBS_REC] exchanged positions and their groups*/,
                                                               long long N, long long Npad, int B, int slices, double* __restrict__ S /*[nsplit][nblk][B][B]*/) {
   using Sh = LbsShape<MG, QC>;
   constexpr int NG = Sh::NG, NC = Sh::NC, XC = Sh::XC;
@@ -1389,15 +1388,14 @@ __global__ void __launch_bounds__(64 * LBS_WAVES, 4) k_lbs_eval(const uint16_t* 
   const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
   const int col0 = slice * XC + QC * (lane % 16);
   const int colc = col0 < B ? col0 : 0;  // columns past the block compute along and are dropped at the end
-  if (!FIRST && rec[blk * 2 * LBS_REC] < 0) return;  // the block is done
   const long long nrows = lbs_wave_rows(N, nsplit * LBS_WAVES), r0 = (split * LBS_WAVES + wave) * nrows;
   const uint16_t* prow = P + ((long long)blk * Npad + r0 + lane / 16) * B + colc;
   uint2 next = lbs_row<QC>(prow);
   int* smc = s_mc + wave * NC;
   double* sms = s_ms + wave * NC;
-  if (lane < NC) {  // first round: positions are columns; past the last group: its first one again, dropped at the end
+  if (lane < NC) {  // positions are columns; past the last group: the first one again, dropped at the end
     const int g = gset * NG + lane / MG;
-    const int c = FIRST ? (g < B / MG ? g : 0) * MG + lane % MG : rec[(blk * 2 + lane / MG) * LBS_REC + 1 + lane % MG];
+    const int c = (g < B / MG ? g : 0) * MG + lane % MG;
     smc[lane] = c;
     sms[lane] = sp[(long long)blk * B + c];
   }
@@ -1408,9 +1406,249 @@ __global__ void __launch_bounds__(64 * LBS_WAVES, 4) k_lbs_eval(const uint16_t* 
   lbs_sums<DT, NKEEP, MG, QC>(prow, next, s, PT + (long long)blk * B * Npad, smc, sms, r0, nrows, N, Npad, B, s_o, wave, lane);
   double* Sb = S + ((long long)split * nblk + blk) * B * B;
   for (int e = tid; e < NC * XC; e += 64 * LBS_WAVES) {
-    const int c = e / XC, x = slice * XC + e % XC, k = c / MG, i = c % MG;
-    const int p = FIRST ? 0 : rec[(blk * 2 + k) * LBS_REC], g = FIRST ? gset * NG + k : p / MG;
-    if (x < B && g < B / MG && (FIRST || i != p % MG)) Sb[(long long)(g * MG + i) * B + x] = lbs_sum<MG, QC>(s_o, c, e % XC);
+    const int c = e / XC, x = slice * XC + e % XC, g = gset * NG + c / MG, i = c % MG;
+    if (x < B && g < B / MG) Sb[(long long)(g * MG + i) * B + x] = lbs_sum<MG, QC>(s_o, c, e % XC);
+  }
+}
+
+// ---- rounds in a launch of their own (blocks of more than LBS_TEAM_BLOCK columns, teams that gave up)
+// Such a round is short and leaves many CUs idle, so the form above, which makes one wave do all members of both groups, loses to the one it is derived from:
+// without member i, with o the NKEEP largest of the other members, a candidate x adds o_0 + .. + o_(NKEEP-2) + max(o_(NKEEP-1), x) to a row, a number per
+// member and two operations per row, candidate and member.  2:4 takes both groups in a workgroup, 4:8 one; the member that the last exchange brought in is
+// left out.  The sums are as near to the real ones as those above.  A lane owns QC columns and every fourth row of its wave; the 16 lanes of a
+// row read its operands once and pass them around.
+// Calls with 40 exchanges, 4:8: 8 blocks of 512 x 72 880 -> 692 us with this form, 2 of 256 x 128 1209 -> 1006, 32 of 4096 x 256 5538 -> 5077; 2:4: 860 -> 816,
+// 973 -> 925, 64 of 4096 x 128 2661 -> 2484.  Of 81 sizes three are slower: 4:8, 72 columns, 64 blocks of 8192 and 36 of 9216 rows (5672 -> 6040, 4152 ->
+// 4365), 2:4, 256 columns, 16 blocks of 2048 rows (2338 -> 2449).
+// the value of lane LANE of each row of 16 lanes in all lanes of that row
+template <int LANE>
+__device__ __forceinline__ double row_bcast(double v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, 0x150 + LANE, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), 0x150 + LANE, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+#else
+  return v;
+#endif
+}
+
+// a + b with half of the lanes of each exchanged: lanes 0-31 get a[l] + a[l + 32], lanes 32-63 b[l - 32] + b[l]
+// (HALF), or the same within each pair of 16-lane rows
+template <bool HALF>
+__device__ __forceinline__ double swap_add(double a, double b) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+  unsigned int r[4];
+  if (HALF) {
+    const auto lo = __builtin_amdgcn_permlane32_swap((unsigned int)x, (unsigned int)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap((unsigned int)(x >> 32), (unsigned int)(y >> 32), false, false);
+    r[0] = lo[0]; r[1] = lo[1]; r[2] = hi[0]; r[3] = hi[1];
+  } else {
+    const auto lo = __builtin_amdgcn_permlane16_swap((unsigned int)x, (unsigned int)y, false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap((unsigned int)(x >> 32), (unsigned int)(y >> 32), false, false);
+    r[0] = lo[0]; r[1] = lo[1]; r[2] = hi[0]; r[3] = hi[1];
+  }
+  return __longlong_as_double(((long long)r[2] << 32) | r[0]) + __longlong_as_double(((long long)r[3] << 32) | r[1]);
+#else
+  return a + b;
+#endif
+}
+
+template <int DT, int NKEEP, int MG, int QC>
+__global__ void __launch_bounds__(64 * LBS_WAVES, 4) k_lbs_refresh(const uint16_t* __restrict__ P, const uint16_t* __restrict__ PT, const double* __restrict__ sp /*[K] score in panel order*/,
+                                                              const int* __restrict__ rec /*[nblk][2][LBS_REC] exchanged positions and their groups*/,
+                                                              long long N, long long Npad, int B, int slices, double* __restrict__ S /*[nsplit][nblk][B][B]*/) {
+  constexpr int RLW = 4;                 // rows of a wave at a time, 16 lanes each
+  constexpr int U = LBS_ROWS / RLW;      // rows of a lane per batch
+  constexpr int NG = MG == 4 ? 2 : 1;    // groups of a workgroup
+  constexpr int NM = MG - 1;             // members to evaluate
+  constexpr int NC = NG * NM;            // combinations of group and member
+  constexpr int XC = 16 * QC;            // columns of a workgroup
+  static_assert(NC <= 16 && (QC == 2 || QC == 4), "a row's operands fit its 16 lanes");
+  constexpr int NCP = NC | 1;            // operands of a row in LDS
+  constexpr int ROOM = LBS_ROWS * NCP > NC * (XC + 1) ? LBS_ROWS * NCP : NC * (XC + 1);
+  __shared__ __align__(16) double s_o[LBS_WAVES * ROOM];  // per wave: operands; at the end its sums
+  __shared__ double s_ms[LBS_WAVES * 2 * MG];
+  __shared__ int s_mc[LBS_WAVES * 2 * MG];
+  const int blk = blockIdx.x, nblk = gridDim.x, split = blockIdx.y, nsplit = gridDim.y;
+  const int slice = (int)blockIdx.z % slices, gset = (int)blockIdx.z / slices;
+  const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+  const int rlw = lane / 16, xl = lane % 16;
+  const int col0 = slice * XC + QC * xl;
+  const int colc = col0 < B ? col0 : 0;  // columns past the block compute along and are dropped at the end
+  // operand lane: row ir of the batch; NG = 2: group ih, all members; NG = 1: members ih, ih + 2, ...
+  const int ir = lane % LBS_ROWS, ih = lane / LBS_ROWS;
+  // batches of 32 rows: rows rb + u RLW + rlw of the panel, which is padded to whole batches; rows past N are replaced
+  // by zeros
+  const long long step = (long long)nsplit * LBS_WAVES * LBS_ROWS;
+  const long long rb0 = (long long)(split * LBS_WAVES + wave) * LBS_ROWS;
+  const uint16_t* Pb = P + (long long)blk * Npad * B;
+  const int xoff = rlw * B + colc;
+  // the values are loaded AHEAD rows ahead: a row takes about 1700 clocks with four waves per SIMD, a load from the
+  // last-level cache as long
+  constexpr int AHEAD = 3;
+  const uint16_t* prow = Pb + rb0 * B;
+  const long long jump = (step - LBS_ROWS) * B;  // from one batch of the wave to the next
+  uint2 next[AHEAD];
+  auto load_row = [&]() {
+    if (QC == 4) return *reinterpret_cast<const uint2*>(prow + xoff);
+    return uint2{*reinterpret_cast<const uint32_t*>(prow + xoff), 0u};
+  };
+#pragma unroll
+  for (int q = 0; q < AHEAD; q++, prow += RLW * B) next[q] = load_row();
+  // groups of this workgroup: their number, the member that needs no evaluation, the members' columns
+  int wg[NG], wskip[NG];
+  int* smc = s_mc + (wave * 2 + (NG == 2 ? ih : 0)) * MG;  // the lane's group: columns and scores of the members
+  double* sms = s_ms + (wave * 2 + (NG == 2 ? ih : 0)) * MG;
+#pragma unroll
+  for (int k = 0; k < NG; k++) {
+    const int* rg = rec + (blk * 2 + gset * NG + k) * LBS_REC;
+    if (rg[0] < 0) return;  // the block is done
+    wg[k] = rg[0] / MG;
+    wskip[k] = rg[0] % MG;
+    if (NG == 1 || ih == k)
+#pragma unroll
+      for (int i = 0; i < MG; i++) smc[i] = rg[1 + i];
+  }
+  const int iskip = NG == 2 && ih == 1 ? wskip[NG - 1] : wskip[0];
+  wave_lds_fence();
+  const uint16_t* PTb = PT + (long long)blk * B * Npad + ir;
+  uint16_t mraw[MG];
+  auto load_members = [&](long long rb) {
+#pragma unroll
+    for (int k = 0; k < MG; k++) mraw[k] = PTb[smc[k] * Npad + rb];
+  };
+  if (rb0 < N) load_members(rb0);
+  double s[QC];
+#pragma unroll
+  for (int q = 0; q < QC; q++) s[q] = sp[(long long)blk * B + colc + q];
+#pragma unroll
+  for (int k = 0; k < MG; k++) sms[k] = sp[(long long)blk * B + smc[k]];
+  double* so = s_o + wave * ROOM;
+  constexpr int NA = (NC * QC + 3) / 4 * 4;
+  double acc[NA];  // [NC][QC], a multiple of four
+#pragma unroll
+  for (int f = 0; f < NA; f++) acc[f] = 0.0;
+  constexpr int NB = NG == 2 ? NM : (NM + 1) / 2;  // members of an operand lane
+  double base[NB];  // operand lanes: what the other members keep besides the operand
+#pragma unroll
+  for (int c = 0; c < NB; c++) base[c] = 0.0;
+
+  for (long long rb = rb0; rb < N; rb += step) {
+    {
+      const bool live = rb + ir < N;
+      double w[NKEEP + 1];  // the largest members, in order
+      wave_lds_fence();
+      auto member = [&](int k) {
+        const double v = (double)esp_to_float<DT>(mraw[k]) * sms[k];
+        return live ? v : 0.0;
+      };
+      w[0] = member(0);
+#pragma unroll
+      for (int k = 1; k < MG; k++) {
+        double v = member(k);
+#pragma unroll
+        for (int q = 0; q <= NKEEP && q < k; q++) {
+          const double hi = max_f64(w[q], v);
+          v = min_f64(w[q], v);
+          w[q] = hi;
+        }
+        if (k <= NKEEP) w[k] = v;
+      }
+#pragma unroll
+      for (int q = 0; q < NB; q++) {  // without member i: the largest, with the next one in place of that member
+        const int c = NG == 2 ? q : 2 * q + ih;
+        double v;
+        if (NG == 2) v = member(q);
+        else v = ih ? member(2 * q + 1 < MG ? 2 * q + 1 : 2 * q) : member(2 * q);
+        double vn;
+        if (NG == 2) vn = member(q + 1);
+        else vn = ih ? member(2 * q + 2 < MG ? 2 * q + 2 : 2 * q) : member(2 * q + 1 < MG ? 2 * q + 1 : 2 * q);
+        v = c >= iskip ? vn : v;
+        double kept = v >= w[0] ? w[1] : w[0];
+#pragma unroll
+        for (int k = 1; k < NKEEP - 1; k++) kept = kept + (v >= w[k] ? w[k + 1] : w[k]);
+        base[q] = base[q] + kept;
+        if (c < NM) so[ir * NCP + (NG == 2 ? ih : 0) * NM + c] = v >= w[NKEEP - 1] ? w[NKEEP] : w[NKEEP - 1];
+      }
+      wave_lds_fence();
+    }
+    const long long rnext = rb + step;
+    const bool full = rb + LBS_ROWS <= N;
+    if (rnext < N) load_members(rnext);
+    // lane c of a row reads the operand of combination c and hands it to the other 15
+    const double* src = so + rlw * NCP + (xl < NC ? xl : NC - 1);
+    double o_next = *src;
+#pragma unroll 1
+    for (int u = 0; u < U; u++) {
+      const uint2 raw = next[0];
+#pragma unroll
+      for (int q = 1; q < AHEAD; q++) next[q - 1] = next[q];
+      if (u == U - AHEAD) prow += jump;
+      next[AHEAD - 1] = load_row();
+      prow += RLW * B;
+      const double o = o_next;
+      src += u < U - 1 ? RLW * NCP : 0;
+      o_next = *src;
+      double x[QC];
+#pragma unroll
+      for (int q = 0; q < QC; q++) {
+        const uint32_t two = q < 2 ? raw.x : raw.y;
+        x[q] = (double)esp_to_float<DT>((uint16_t)(q & 1 ? two >> 16 : two & 0xffffu)) * s[q];
+      }
+      if (!full) {  // no such row: adds exactly 0 whatever the scores are
+        const bool live = rb + u * RLW + rlw < N;
+#pragma unroll
+        for (int q = 0; q < QC; q++) x[q] = live ? x[q] : 0.0;
+      }
+#define LBS_ADD(c)                                                                                         \
+  if constexpr (c < NC) {                                                                                  \
+    const double oc = row_bcast<c>(o);                                                                     \
+    _Pragma("unroll") for (int q = 0; q < QC; q++) acc[c * QC + q] = acc[c * QC + q] + max_f64(oc, x[q]);  \
+  }
+      LBS_ADD(0) LBS_ADD(1) LBS_ADD(2) LBS_ADD(3) LBS_ADD(4) LBS_ADD(5) LBS_ADD(6) LBS_ADD(7)
+#undef LBS_ADD
+    }
+  }
+  // the four rows of the wave: row lane r ends up with the sums number 4 k + {0, 2, 1, 3}[r]
+#pragma unroll
+  for (int f = 0; f < NA; f += 4) acc[f / 4] = swap_add<false>(swap_add<true>(acc[f], acc[f + 1]), swap_add<true>(acc[f + 2], acc[f + 3]));
+  // operand lanes: over the 32 rows; NG = 1: the other half of the lanes holds the other members
+#pragma unroll
+  for (int q = 0; q < NB; q++)
+#pragma unroll
+    for (int d = 1; d < LBS_ROWS; d <<= 1) base[q] = base[q] + __shfl_xor(base[q], d);
+  wave_lds_fence();
+  double* red = so;  // [NC][XC + 1]: the wave's sums and, last in a row, its base
+#pragma unroll
+  for (int k = 0; k < NA / 4; k++) {
+    const int f = 4 * k + ((rlw & 1) << 1 | rlw >> 1), c = f / QC;
+    if (c < NC) red[c * (XC + 1) + QC * xl + f % QC] = acc[k];
+  }
+  if (ir == 0) {
+#pragma unroll
+    for (int q = 0; q < NB; q++) {
+      const int c = NG == 2 ? q : 2 * q + ih;
+      if (c < NM) red[((NG == 2 ? ih : 0) * NM + c) * (XC + 1) + XC] = base[q];
+    }
+  }
+  __syncthreads();
+  double* Sb = S + ((long long)split * nblk + blk) * B * B;
+  for (int e = tid; e < NC * XC; e += 64 * LBS_WAVES) {
+    const int c = e / XC, x = slice * XC + e % XC;
+    const double* sums = s_o + c * (XC + 1);
+    double t = sums[e % XC], tb = sums[XC];
+#pragma unroll
+    for (int wv = 1; wv < LBS_WAVES; wv++) {
+      t = t + sums[wv * ROOM + e % XC];
+      tb = tb + sums[wv * ROOM + XC];
+    }
+    t = t + tb;
+    const int k = c / NM, g = NG == 2 && k == 1 ? wg[NG - 1] : wg[0], skip = NG == 2 && k == 1 ? wskip[NG - 1] : wskip[0];
+    int i = c % NM;
+    if (i >= skip) i++;
+    if (x < B) Sb[(long long)(g * MG + i) * B + x] = t;
   }
 }
 
@@ -2038,7 +2276,10 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const EspCalib* cali
     // workgroups per CU share the two groups that an exchange touches (at least one batch of rows per wave)
     const int qc = B <= 32 ? 2 : 4;
     const int slices = (B + 16 * qc - 1) / (16 * qc);
-    const int nsplit = (int)std::max<long long>(1, std::min<long long>(512 / (nblk * slices), (N + LBS_WAVES * LBS_ROWS - 1) / (LBS_WAVES * LBS_ROWS)));
+    const long long most_splits = (N + LBS_WAVES * LBS_ROWS - 1) / (LBS_WAVES * LBS_ROWS);
+    const int nsplit = (int)std::max<long long>(1, std::min<long long>(512 / (nblk * slices), most_splits));
+    const int refresh_sets = m == 4 ? 1 : 2;  // k_lbs_refresh: workgroups for the two groups
+    const int nsplit_refresh = (int)std::max<long long>(1, std::min<long long>(512 / (nblk * slices * refresh_sets), most_splits));
     int cus = 0;
     ESP_HIP(ctx, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device));
     const int team = esp_lbs_team(N, nblk, B, cus);
@@ -2105,20 +2346,23 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const EspCalib* cali
     // one round of all blocks in the given mode; first: all groups are evaluated
     auto launch_round = [&](int mode, bool first) -> int {
       if (mode == LBS_FAST) {
-#define LAUNCH_EVAL2(DTv, NK, MGv, FIRSTv, QCv)                                                                       \
-  hipLaunchKernelGGL((k_lbs_eval<DTv, NK, MGv, FIRSTv, QCv>),                                                         \
-                     dim3((unsigned)nblk, (unsigned)nsplit, (unsigned)(slices * (FIRSTv ? (B / MGv + 1) / 2 : 1))),   \
-                     dim3(64 * LBS_WAVES), 0, st, d_P, d_PT, d_sp, d_rec, N, Npad, B, slices, d_S)
-#define LAUNCH_EVAL(DTv, NK, MGv, ...)                                   \
-  do {                                                                   \
-    if (first && qc == 4) LAUNCH_EVAL2(DTv, NK, MGv, true, 4);           \
-    else if (first) LAUNCH_EVAL2(DTv, NK, MGv, true, 2);                 \
-    else if (qc == 4) LAUNCH_EVAL2(DTv, NK, MGv, false, 4);              \
-    else LAUNCH_EVAL2(DTv, NK, MGv, false, 2);                           \
+#define LAUNCH_EVAL(DTv, NK, MGv, QCv)                                                                                              \
+  do {                                                                                                                              \
+    if (first)                                                                                                                      \
+      hipLaunchKernelGGL((k_lbs_eval<DTv, NK, MGv, QCv>), dim3((unsigned)nblk, (unsigned)nsplit, (unsigned)(slices * ((B / MGv + 1) / 2))), \
+                         dim3(64 * LBS_WAVES), 0, st, d_P, d_PT, d_sp, N, Npad, B, slices, d_S);                                    \
+    else                                                                                                                            \
+      hipLaunchKernelGGL((k_lbs_refresh<DTv, NK, MGv, QCv>), dim3((unsigned)nblk, (unsigned)nsplit_refresh, (unsigned)(slices * refresh_sets)), \
+                         dim3(64 * LBS_WAVES), 0, st, d_P, d_PT, d_sp, d_rec, N, Npad, B, slices, d_S);                             \
   } while (0)
-        DISPATCH_DT_NM(dtype, n, LAUNCH_EVAL, 0);
+#define LAUNCH_EVALS(DTv, NK, MGv, ...)           \
+  do {                                            \
+    if (qc == 4) LAUNCH_EVAL(DTv, NK, MGv, 4);    \
+    else LAUNCH_EVAL(DTv, NK, MGv, 2);            \
+  } while (0)
+        DISPATCH_DT_NM(dtype, n, LAUNCH_EVALS, 0);
+#undef LAUNCH_EVALS
 #undef LAUNCH_EVAL
-#undef LAUNCH_EVAL2
       } else {
         const int* rec = first ? nullptr : d_rec;
         if (m == 4 && (B % 64 == 0 || B < 64)) {
@@ -2149,7 +2393,7 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const EspCalib* cali
       }
       ESP_HIP(ctx, hipGetLastError());
 #define LAUNCH_SELECT(MGv)                                                                                                     \
-  hipLaunchKernelGGL(k_lbs_select<MGv>, dim3((unsigned)nblk), dim3(1024), 0, st, d_S, nsplit, d_V, d_lp, \
+  hipLaunchKernelGGL(k_lbs_select<MGv>, dim3((unsigned)nblk), dim3(1024), 0, st, d_S, first ? nsplit : nsplit_refresh, d_V, d_lp, \
                      d_rec, d_state, d_swaps, o->max_swaps, N, B, first ? 1 : 0, mode,  \
                      d_count + 2, d_count)
       if (m == 4) LAUNCH_SELECT(4);
