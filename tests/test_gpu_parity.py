@@ -77,6 +77,15 @@ def test_channel_stats_other_bin_counts(ctx):
         assert (ir == orc.channel_entropy(_np(Xc), bins)).all()
 
 
+# several channels' bins to a wave, with lanes left over, up to one channel to a wave; channels that end within a workgroup and within a wave's share
+@pytest.mark.parametrize("K", [300, 302])
+def test_channel_stats_few_bins_of_many_channels(ctx, K):
+    Xc = _rand((600, K), torch.float16, 13)
+    for bins in (2, 3, 10, 30, 32, 33, 63, 64, 65):
+        ir, _ = ctx.channel_stats(Xc.cuda(), bins)
+        assert (ir == orc.channel_entropy(_np(Xc), bins)).all(), bins
+
+
 # every value on the edge of a bin, and one unit beside it
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
 @pytest.mark.parametrize("bins", [1, 64, 100, 256])
