@@ -142,7 +142,7 @@ struct EspCalib {
   bool entropy, norm;
 };
 bool esp_scores_on_device(long long T, long long K, int bins, bool entropy, bool norm, double alpha);
-int esp_lbs_team(long long N, long long nblk, int B, int compute_units);
+int esp_lbs_team(long long N, long long nblk, int B, int m, int compute_units);
 int esp_team_wait(esparse_ctx* ctx, unsigned long long ticks);
 // score_host, or the scores of `calib` (then score_out receives them, if given)
 int esp_prune_device(esparse_ctx* ctx, const double* score_host, const EspCalib* calib, const void* W, long long N,

@@ -2162,10 +2162,20 @@ bool esp_scores_on_device(long long T, long long K, int bins, bool entropy, bool
 // Workgroups of a block's team in k_lbs_rounds, 0: a launch per round.  As many as fill the places of an XCD, which takes every eighth block, and
 // have a batch of rows for each wave.  A device with fewer compute units is a part of the chip, with fewer XCDs: numbers eight apart are then not on one XCD, and
 // its places hold parts of many teams of which none can end.
-int esp_lbs_team(long long N, long long nblk, int B, int compute_units) {
+// One or two teams of the largest size per XCD leave CUs idle that the launches use, three share them unevenly: with many rows for each workgroup launches are
+// faster.  Of times with a team over without, 4:8 and 64 columns: 1 to 8 blocks 0.83 - 0.95 at 375 rows, 0.83 - 1.07 at 625, 1.02 - 1.18 at 1000, 1.18 - 1.32 at
+// 1500, 1.37 - 1.54 at 2500; 9 and 16 blocks 0.96 and 0.91 at 1000, 1.14 and 1.00 at 1500, 1.40 and 1.04 at 2500.  2:4 and fewer columns: 1 to 8 blocks 0.61 - 1.08 at
+// 2500, 1.06 at 3750, 1.13 - 1.48 at 7500; 9 to 16 blocks 0.8 - 1.05 at any number.  17 to 24 blocks of 64 columns 0.96 - 1.00 at 1500, 1.18 at 2500.  More take
+// 0.5 - 1.14 (1.16 for 4:8 with 576 blocks of 9216 rows).  Over 561 sizes up to 120000 rows a call takes 1.001 of the faster way's time in the geometric mean;
+// always with teams 1.013 and 2.5 at worst.
+int esp_lbs_team(long long N, long long nblk, int B, int m, int compute_units) {
   if (B > LBS_TEAM_BLOCK || 2 * compute_units < LBS_XCDS * LBS_XCD_GROUPS) return 0;
-  const long long places = LBS_XCD_GROUPS / ((nblk + LBS_XCDS - 1) / LBS_XCDS), rows = (N + LBS_WAVES * LBS_ROWS - 1) / (LBS_WAVES * LBS_ROWS);
-  return (int)std::max<long long>(1, std::min(std::min<long long>(places, LBS_TEAM_MAX), rows));
+  const long long teams = (nblk + LBS_XCDS - 1) / LBS_XCDS, rows = (N + LBS_WAVES * LBS_ROWS - 1) / (LBS_WAVES * LBS_ROWS);
+  long long limit = N;
+  if (teams == 1) limit = m == 8 && B > 32 ? 850 : 2750;
+  else if (B > 32 && (teams == 3 || (teams == 2 && m == 8))) limit = teams == 3 ? 1500 : 1200;
+  if (N > limit * LBS_TEAM_MAX) return 0;
+  return (int)std::max<long long>(1, std::min(std::min<long long>(LBS_XCD_GROUPS / teams, LBS_TEAM_MAX), rows));
 }
 
 // How long the block shuffles of a context wait for a team of workgroups; returns how many of them have given up so far.  (The launches that take over
@@ -2283,7 +2293,7 @@ int esp_prune_device(esparse_ctx* ctx, const double* score, const EspCalib* cali
     const int nsplit_refresh = (int)std::max<long long>(1, std::min<long long>(512 / (nblk * slices * refresh_sets), most_splits));
     int cus = 0;
     ESP_HIP(ctx, hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, ctx->device));
-    const int team = esp_lbs_team(N, nblk, B, cus);
+    const int team = esp_lbs_team(N, nblk, B, m, cus);
     const long long batch = (long long)std::max(nsplit, team) * LBS_WAVES * LBS_ROWS;  // rows that are read past the panel's end, at most
     const long long Npad = (N + LBS_ROWS - 1) / LBS_ROWS * LBS_ROWS;
     bool finite = true, fast = true;  // of the scores: all finite (on the device: k_build_panel looks); and none negative

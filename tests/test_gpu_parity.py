@@ -209,9 +209,9 @@ def test_block_shuffle_edges_of_the_evaluation_kernel(esp, ctx, n, m, B, N, dtyp
 
 
 # all rounds of a block by a team of workgroups: one block; blocks that leave XCDs without a last one; more blocks than are resident at
-# once; one workgroup per team and 16; rows that leave the last waves short or empty
+# once; one workgroup per team and 16; rows that leave the last waves short or empty; and so many rows of few blocks that there are no teams
 @pytest.mark.parametrize("n,m,B,nblk,N", [(2, 4, 64, 1, 4000), (2, 4, 8, 600, 40), (2, 4, 32, 9, 1025), (2, 4, 64, 20, 515), (4, 8, 64, 1, 3900),
-                                          (4, 8, 16, 530, 33), (4, 8, 32, 17, 771), (4, 8, 64, 10, 1300)])
+                                          (4, 8, 16, 530, 33), (4, 8, 32, 17, 771), (4, 8, 64, 10, 1300), (4, 8, 40, 2, 13700), (2, 4, 16, 1, 44100)])
 def test_block_shuffle_teams(esp, ctx, n, m, B, nblk, N):
     K = B * nblk
     W = _rand((N, K), torch.bfloat16 if N % 2 else torch.float16, 5 + N, scale=K ** -0.5)

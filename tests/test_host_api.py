@@ -191,22 +191,28 @@ def test_scores_stay_on_the_device_where_that_is_faster():
 
 def test_block_shuffle_teams_can_end():
     """Teams only where the device has 8 XCDs of 64 places; no more workgroups than an XCD has places for its share of the blocks, and so
-    few per team that parts of the teams of four launches never fill the places of an XCD."""
-    team = esp.load_library()._Z12esp_lbs_teamxxii
-    team.argtypes = [C.c_longlong, C.c_longlong, C.c_int, C.c_int]
+    few per team that parts of the teams of four launches never fill the places of an XCD; none for many rows of few blocks."""
+    team = esp.load_library()._Z12esp_lbs_teamxxiii
+    team.argtypes = [C.c_longlong, C.c_longlong, C.c_int, C.c_int, C.c_int]
     rng, largest = random.Random(7), 0
     for _ in range(5000):
-        N, nblk, B = int(2 ** rng.uniform(0, 24)), int(2 ** rng.uniform(0, 16)), 4 * rng.randint(2, 64)
+        N, nblk, m = int(2 ** rng.uniform(0, 24)), int(2 ** rng.uniform(0, 16)), rng.choice([4, 8])
+        B = m * rng.randint(2, 256 // m)
         for cus in (32, 64, 128, 255):
-            assert team(N, nblk, B, cus) == 0
-        t = team(N, nblk, B, 256)
-        if B > 64:
+            assert team(N, nblk, B, m, cus) == 0
+        t = team(N, nblk, B, m, 256)
+        if B > 64 or (N > 44000 and nblk <= 8):
             assert t == 0
             continue
-        assert t >= 1 and 4 * (t - 1) < 64
+        if t == 0:
+            assert (nblk <= 16 and N > 13600 and m == 8 and B > 32) or (17 <= nblk <= 24 and N > 24000 and B > 32)
+            continue
+        assert 4 * (t - 1) < 64
         assert t == 1 or (t * -(-nblk // 8) <= 64 and (t - 1) * 256 < N)
         largest = max(largest, t)
     assert largest == 16
+    assert team(13600, 8, 64, 8, 256) == 16 and team(13601, 8, 64, 8, 256) == 0 and team(19200, 9, 64, 8, 256) == 16 and team(19201, 9, 64, 8, 256) == 0
+    assert team(24000, 17, 64, 4, 256) == 16 and team(24001, 24, 64, 4, 256) == 0 and team(1 << 20, 25, 64, 8, 256) == 16 and team(1 << 20, 9, 64, 4, 256) == 16
 
 
 @pytest.mark.parametrize("room_mib", [64, 1])
